@@ -627,18 +627,158 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 }
 
 // ---------------------------------------------------------------------------------
-// Merge the vocabulary ranges of each token (ascending) and form every output.  One thread per token.
+// Merge the vocabulary ranges of each token and form every output.  A workgroup takes 8 tokens with 32 threads each:
+// thread (t, g) reads the g-th 1/32 of token t's ranges (and, for the sampler's token, of its half tiles), so that
+// neighbouring lanes read neighbouring tokens of the [range][token] arrays and the loads of a token are spread over
+// 32 threads.  What bounds it is the latency of those loads: with one thread per token walking all of them, the merge
+// took 174 us of a call with 64 tokens (256 ranges) and 780 us with 4096 tokens and the sampler's token (16 ranges,
+// 1188 half tiles); now 15 and 34 us.
 // ---------------------------------------------------------------------------------
+constexpr int kFinTokens = 8, kFinGroups = kBlock / kFinTokens;
+
 __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, LmHeadWorkspace ws, int splits, int n_vt,
                                                                  GumbelOutputs og, IptOutputs oi)
 {
-    const int64_t n = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (n >= b.N) return;
+    __shared__ float lds_y[kWaves][kFinTokens], lds_m[kWaves][kFinTokens];
+    __shared__ int32_t lds_v[kWaves][kFinTokens], lds_a[kWaves][kFinTokens];
+    __shared__ double lds_Z[kWaves][kFinTokens], lds_P[kWaves][kFinTokens];
+    __shared__ double lds_mass[kFinGroups][kFinTokens];
+    __shared__ int32_t lds_half[kFinTokens];
+
+    const int tid = threadIdx.x, tk = tid % kFinTokens, g = tid / kFinTokens, wave = tid >> 6;
+    const int64_t n = (int64_t)blockIdx.x * kFinTokens + tk;
+    const bool live = n < b.N;
     const float nan = __builtin_nanf("");
     const float ninf = -__builtin_inff();
-    const TokInfo t = load_tok(b, n);
-    const int32_t tg_raw = b.claimed_gumbel ? b.claimed_gumbel[n] : -1;
-    (void)tg_raw;
+    const TokInfo t = load_tok(b, live ? n : b.N - 1);
+    const bool use = live && t.ok;  // (threads without a row, or with a rejected one, only keep the barriers company)
+    const float c = t.inv_T * kLog2e;
+
+    // ---- the ranges: this thread's share in ascending order, then the 8 groups of the wave, then the 4 waves ----
+    float best_y = ninf, m = ninf;
+    int32_t best_v = 0x7FFFFFFF;
+    double Z = 0.0, P = 0.0;
+    int32_t above = 0;
+    if (use) {
+        const int sp1 = (int)((int64_t)(g + 1) * splits / kFinGroups);
+#pragma unroll 4
+        for (int sp = (int)((int64_t)g * splits / kFinGroups); sp < sp1; ++sp) {
+            const int64_t o = (int64_t)sp * b.N + n;
+            argmax_combine(best_y, best_v, ws.best_y[o], ws.best_v[o]);
+            merge_softmax(m, Z, P, ws.m[o], ws.Z[o], ws.P[o], c);
+            if (og.logit_rank) above += ws.above[o];
+        }
+    }
+#pragma unroll
+    for (int off = kFinTokens; off < 64; off <<= 1) {  // (references are whole exponents: merging is order-free but for fp64 rounding)
+        const float oy = __shfl_xor(best_y, off, 64), om = __shfl_xor(m, off, 64);
+        const int32_t ov = __shfl_xor(best_v, off, 64);
+        const double oZ = __shfl_xor(Z, off, 64), oP = __shfl_xor(P, off, 64);
+        above += __shfl_xor(above, off, 64);
+        argmax_combine(best_y, best_v, oy, ov);
+        merge_softmax(m, Z, P, om, oZ, oP, c);
+    }
+    if ((tid & 63) < kFinTokens) {
+        lds_y[wave][tk] = best_y;
+        lds_v[wave][tk] = best_v;
+        lds_m[wave][tk] = m;
+        lds_Z[wave][tk] = Z;
+        lds_P[wave][tk] = P;
+        lds_a[wave][tk] = above;
+    }
+    if (tid < kFinTokens) lds_half[tid] = -1;
+    __syncthreads();
+    best_y = lds_y[0][tk];
+    best_v = lds_v[0][tk];
+    m = lds_m[0][tk];
+    Z = lds_Z[0][tk];
+    P = lds_P[0][tk];
+    above = lds_a[0][tk];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+        argmax_combine(best_y, best_v, lds_y[w][tk], lds_v[w][tk]);
+        merge_softmax(m, Z, P, lds_m[w][tk], lds_Z[w][tk], lds_P[w][tk], c);
+        above += lds_a[w][tk];
+    }
+    const bool ipt_bad = !(Z > 0.0) || !(Z < (double)__builtin_inff()) || !(m < __builtin_inff()) || !(m > ninf);
+    const bool nonfinite = !(Z == Z) || !(Z < (double)__builtin_inff()) || !(m < __builtin_inff());
+
+    // ---- Token-IPT-DiFR: the uniform and the claimed token's interval (in every thread of the token) ----
+    uint32_t r[4];
+    noise_block(t.key, t.pos, t.seq, kStreamIpt, 0u, r);
+    const float u = uniform_from_bits(r[0]);
+    float a = nan, bb = nan, dd = nan;
+    double ad = 0.0, bd = 0.0;
+    bool match = false;
+    if (use && t.ti >= 0 && !ipt_bad) {
+        const double et = (double)fast_exp2(__fmaf_rn(ws.x_claim_ipt[n], c, -ref_exp(m, c)));
+        const double ud = (double)u;
+        ad = P / Z;
+        bd = (P + et) / Z;
+        a = (float)ad;
+        bb = (float)bd;
+        dd = (float)fmax(fmax(ad - ud, ud - bd), 0.0);
+        match = (ad <= ud) && (ud < bd);
+    }
+
+    // ---- the half tile that holds the sampler's own token: the claim's if it matches, else the first at which the
+    // CDF passes u, from the masses the scoring pass left (vocabulary order, each brought to the row's final
+    // reference).  Every thread sums its 1/32 of them, the share in which the CDF passes is found from the 32 sums and
+    // its thread walks it; the entry inside the half tile is found by the kernel that follows. ----
+    if (oi.ipt_token) {
+        const bool search = use && !ipt_bad && !match;
+        const int h0 = (int)((int64_t)g * 2 * n_vt / kFinGroups), h1 = (int)((int64_t)(g + 1) * 2 * n_vt / kFinGroups);
+        const float rm = ref_exp(m, c);
+        // calls f(h, mass) for the thread's half tiles in order; eight loads in flight, f is a chain of additions
+        auto for_each_mass = [&](auto &&f) {
+            for (int h = h0; h < h1; h += 8) {
+                float2 p[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) p[k] = ws.half_sum[(int64_t)min(h + k, h1 - 1) * b.N + n];
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (h + k < h1) f(h + k, p[k].x > 0.0f ? (double)p[k].x * (double)fast_exp2(ref_exp(p[k].y, c) - rm) : 0.0);
+            }
+        };
+        double sum = 0.0;
+        if (search) for_each_mass([&](int, double w) { sum += w; });
+        lds_mass[g][tk] = sum;
+        __syncthreads();
+        if (search) {
+            const double target = (double)u * Z;
+            double cum = 0.0, before = 0.0;  // before: the mass below the share that is walked
+            int share = -1;                  // the first at which the CDF passes u, else the last with any mass
+            for (int k = 0; k < kFinGroups; ++k) {
+                const double w = lds_mass[k][tk];
+                if (w > 0.0) {
+                    share = k;
+                    before = cum;
+                }
+                cum += w;
+                if (cum > target) break;
+            }
+            if (share == g) {
+                double at = before, at_last = before;
+                int32_t half = -1, last = -1;  // last half tile with any mass: where rounding puts a u beyond the sum
+                for_each_mass([&](int h, double w) {
+                    if (half >= 0) return;
+                    if (w > 0.0) {
+                        last = h;
+                        at_last = at;
+                    }
+                    if (at + w > target) half = h;
+                    at += w;
+                });
+                if (half < 0) half = last;
+                lds_half[tk] = half;
+                ws.cross_rest[n] = target - at_last;
+                ws.final_m[n] = m;
+            }
+        }
+        __syncthreads();
+    }
+
+    if (g != 0 || !live) return;  // one thread per token writes the outputs
     if (!t.ok) {
         const uint8_t f = (uint8_t)(t.seq_ok ? kFlagNonfinite : kFlagInvalidClaim);
         og.margin[n] = nan;
@@ -659,20 +799,7 @@ __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, 
         oi.flags[n] = f;
         return;
     }
-    const float c = t.inv_T * kLog2e;
-    float best_y = ninf, m = ninf;
-    int32_t best_v = 0x7FFFFFFF;
-    double Z = 0.0, P = 0.0;
-    int32_t above = 0;
-    for (int sp = 0; sp < splits; ++sp) {
-        const int64_t o = (int64_t)sp * b.N + n;
-        argmax_combine(best_y, best_v, ws.best_y[o], ws.best_v[o]);
-        merge_softmax(m, Z, P, ws.m[o], ws.Z[o], ws.P[o], c);
-        if (og.logit_rank) above += ws.above[o];
-    }
     if (best_v == 0x7FFFFFFF) best_v = 0;
-    const bool ipt_bad = !(Z > 0.0) || !(Z < (double)__builtin_inff()) || !(m < __builtin_inff()) || !(m > ninf);
-    const bool nonfinite = !(Z == Z) || !(Z < (double)__builtin_inff()) || !(m < __builtin_inff());
 
     // Token-DiFR
     uint32_t fg = nonfinite ? kFlagNonfinite : 0u;
@@ -692,21 +819,6 @@ __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, 
     if (og.logit_rank) og.logit_rank[n] = t.tg >= 0 ? above : -1;
 
     // Token-IPT-DiFR
-    uint32_t r[4];
-    noise_block(t.key, t.pos, t.seq, kStreamIpt, 0u, r);
-    const float u = uniform_from_bits(r[0]);
-    float a = nan, bb = nan, dd = nan, lm = nan;
-    bool match = false;
-    if (t.ti >= 0 && !ipt_bad) {
-        const double et = (double)fast_exp2(__fmaf_rn(ws.x_claim_ipt[n], c, -ref_exp(m, c)));
-        const double ud = (double)u;
-        const double ad = P / Z, bd = (P + et) / Z;
-        a = (float)ad;
-        bb = (float)bd;
-        dd = (float)fmax(fmax(ad - ud, ud - bd), 0.0);
-        match = (ad <= ud) && (ud < bd);
-        if (oi.log_mass) lm = (float)gaussian_log_mass(ad, bd, ud, oi.sigma, oi.eps);
-    }
     uint32_t fi = 0;
     if (t.ti < 0) fi |= kFlagInvalidClaim;
     if (ipt_bad) fi |= kFlagNonfinite;
@@ -715,47 +827,13 @@ __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, 
     if (oi.cdf_lo) oi.cdf_lo[n] = a;
     if (oi.cdf_hi) oi.cdf_hi[n] = bb;
     if (oi.u) oi.u[n] = u;
-    if (oi.log_mass) oi.log_mass[n] = lm;
+    if (oi.log_mass)
+        oi.log_mass[n] = (t.ti >= 0 && !ipt_bad) ? (float)gaussian_log_mass(ad, bd, (double)u, oi.sigma, oi.eps) : nan;
     if (oi.ipt_token) {
-        // The sampler's own token: the claim if it matches; else the first entry at which the CDF passes u.  The
-        // half tile in which that happens is found from the masses the scoring pass left (vocabulary order, each
-        // brought to the row's final reference); the entry inside it by the kernel that follows.
-        int32_t tok = -1, half = -1;
-        double rest = 0.0;
-        if (ipt_bad) {
-            tok = -1;
-        } else if (match) {
-            tok = t.ti;
-        } else {
-            const double target = (double)u * Z;
-            double cum = 0.0;
-            int32_t last = -1;  // last half tile with any mass: where rounding puts a u beyond the summed total
-            double cum_last = 0.0;
-            for (int h = 0; h < 2 * n_vt; ++h) {
-                const float2 p = ws.half_sum[(int64_t)h * b.N + n];
-                if (!(p.x > 0.0f)) continue;
-                const double w = (double)p.x * (double)fast_exp2(ref_exp(p.y, c) - ref_exp(m, c));
-                if (cum + w > target) {
-                    half = h;
-                    rest = target - cum;
-                    break;
-                }
-                if (w > 0.0) {
-                    last = h;
-                    cum_last = cum;
-                }
-                cum += w;
-            }
-            if (half < 0) {
-                half = last;
-                rest = target - cum_last;
-            }
-            if (half >= 0) fi |= kFlagSlowPath;
-        }
-        oi.ipt_token[n] = tok;
+        const int32_t half = lds_half[tk];
+        if (half >= 0) fi |= kFlagSlowPath;
+        oi.ipt_token[n] = match ? t.ti : -1;
         ws.cross_half[n] = half;
-        ws.cross_rest[n] = rest;
-        ws.final_m[n] = m;
     }
     oi.flags[n] = (uint8_t)fi;
 }
@@ -846,8 +924,8 @@ int launch_lmhead_score(const LmHeadBatch &b, const LmHeadWorkspace &ws, const L
     else
         lmhead_score_kernel<false, false><<<grid, block, 0, stream>>>(b, ws, plan);
     if (hipGetLastError() != hipSuccess) return 1;
-    lmhead_finalize_kernel<<<dim3((unsigned)((b.N + kBlock - 1) / kBlock)), block, 0, stream>>>(b, ws, plan.splits, plan.n_vt,
-                                                                                            og, oi);
+    lmhead_finalize_kernel<<<dim3((unsigned)((b.N + kFinTokens - 1) / kFinTokens)), block, 0, stream>>>(b, ws, plan.splits,
+                                                                                                      plan.n_vt, og, oi);
     if (hipGetLastError() != hipSuccess) return 1;
     if (tok) {
         lmhead_ipt_token_kernel<<<dim3((unsigned)b.N), block, 0, stream>>>(b, ws, oi);
