@@ -189,9 +189,11 @@ __device__ __forceinline__ void refresh_gates(const Slot &s, BlockCtx &k)
 // logit must be known before the first tile, so the count is made against its plain fp32 dot product from the
 // preparation kernel; the claimed entry itself is left out by index (its matrix-core value may differ from that
 // reference in the last bits).
-template <bool RANK>
+//
+// TOK: `part` follows the mass of the half tile the block belongs to, relative to the slot's reference.
+template <bool RANK, bool TOK>
 __device__ __forceinline__ void score_block(const f32x16 acc, Slot &s, BlockCtx &k, int32_t vlane, int32_t V,
-                                            bool ragged, int64_t n, const LmHeadWorkspace &ws)
+                                            bool ragged, int64_t n, const LmHeadWorkspace &ws, double &part)
 {
     const float ninf = -__builtin_inff();
     // the accumulators live in the accumulation registers; fetch them one by one (left to itself the
@@ -219,6 +221,7 @@ __device__ __forceinline__ void score_block(const f32x16 acc, Slot &s, BlockCtx 
             const double f = (s.m > ninf) ? (double)fast_exp2(ref_exp(s.m, k.c) - ref_exp(bm, k.c)) : 0.0;
             s.Z *= f;
             s.P *= f;
+            if (TOK) part *= f;
             s.m = bm;
             k.neg_mc = -ref_exp(bm, k.c);
             refresh_gates(s, k);  // the logit cap of the noise gate has moved
@@ -253,6 +256,7 @@ __device__ __forceinline__ void score_block(const f32x16 acc, Slot &s, BlockCtx 
     }
     s.Z += (double)bs;
     s.P += (double)ps;
+    if (TOK) part += (double)bs;
 
     // ---- Token-DiFR: noise for all 16 entries, exact score only where the gates allow ----
     uint32_t rw[16];
@@ -542,21 +546,15 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
             k.neg_mc = (slot[jb].m > -__builtin_inff()) ? -ref_exp(slot[jb].m, k.c) : 0.0f;
             refresh_gates(slot[jb], k);
             const int32_t vl = (int32_t)v0 + wv * 128 + 4 * lh;
-            const double Z_before = slot[jb].Z;
-            const float m_before = slot[jb].m;
-            score_block<RANK>(acc[0][jb], slot[jb], k, vl, V, ragged, tok_row(jb), ws);
-            score_block<RANK>(acc[1][jb], slot[jb], k, vl + 32, V, ragged, tok_row(jb), ws);
-            score_block<RANK>(acc[2][jb], slot[jb], k, vl + 64, V, ragged, tok_row(jb), ws);
-            score_block<RANK>(acc[3][jb], slot[jb], k, vl + 96, V, ragged, tok_row(jb), ws);
+            double part = 0.0;  // TOK: what this lane's 64 entries of the half tile add to its sum
+            score_block<RANK, TOK>(acc[0][jb], slot[jb], k, vl, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK>(acc[1][jb], slot[jb], k, vl + 32, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK>(acc[2][jb], slot[jb], k, vl + 64, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK>(acc[3][jb], slot[jb], k, vl + 96, V, ragged, tok_row(jb), ws, part);
             if (TOK) {
-                // what this lane's 64 entries of the half tile added to its sum, relative to its reference now;
-                // then the two lanes that share the token (rows 0-3 and 4-7 mod 8) combined
+                // the two lanes that share the token (rows 0-3 and 4-7 mod 8) combined
                 const float ninf = -__builtin_inff();
-                const Slot &s = slot[jb];
-                double mine = s.Z;
-                if (m_before > ninf)
-                    mine -= Z_before * (s.m == m_before ? 1.0 : (double)fast_exp2(ref_exp(m_before, k.c) - ref_exp(s.m, k.c)));
-                const float ms = mine > 0.0 ? (float)mine : 0.0f, mm = s.m;
+                const float ms = (float)part, mm = slot[jb].m;
                 const float os = __shfl_xor(ms, 32, 64), om = __shfl_xor(mm, 32, 64);
                 const float M = fmaxf(mm, om);
                 const float both = (mm > ninf ? ms * fast_exp2(ref_exp(mm, k.c) - ref_exp(M, k.c)) : 0.0f) +
@@ -839,72 +837,80 @@ __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, 
 }
 
 // ---------------------------------------------------------------------------------
-// The sampler's own Token-IPT-DiFR token inside the half tile the merge kernel found: the 128 logits of that
-// half tile are formed again as plain fp32 dot products (one wave per 32 of them, a row of the LM-head matrix
-// read by the whole wave at a time), turned into softmax terms relative to the row's final reference and scanned
-// in vocabulary order for the first entry at which the running sum passes what was left to cover.  One workgroup
-// per token; tokens that are already known (matching or missing claims, rejected rows) leave at once.
+// The sampler's own Token-IPT-DiFR token inside the half tile the merge kernel found: its logits are formed again as
+// plain fp32 dot products, 32 at a time in vocabulary order (eight per wave, a row of the LM-head matrix read by the
+// whole wave), turned into softmax terms relative to the row's final reference and scanned for the first entry at which
+// the running sum passes what was left to cover; the 32 that hold it are the last that are read.  One workgroup per
+// token; tokens that are already known (matching or missing claims, rejected rows) leave at once.
+// Bound by reading those rows (2 d bytes each, 80 of the 128 on average): N = 4096 tokens, V = 151936, d = 4096, 55% of
+// them searched: 490 us when all 128 were formed before the scan, one row at a time; now 244.  Eight rows at a time keep
+// nine loads in flight per lane.
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void lmhead_ipt_token_kernel(LmHeadBatch b, LmHeadWorkspace ws, IptOutputs oi)
 {
-    __shared__ float lds_e[128];
+    constexpr int kRows = 8, kStep = kRows * kWaves;  // rows per wave and per workgroup at a time
+    __shared__ float lds_e[2][kStep];                 // (two, so that a step's terms outlive the barrier of the next)
     const int64_t n = blockIdx.x;
     const int32_t half = ws.cross_half[n];
     if (half < 0) return;  // uniform
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const TokInfo t = load_tok(b, n);
     const float c = t.inv_T * kLog2e, m = ws.final_m[n];
-    const int64_t v0 = (int64_t)half * 128;
+    const double rest = ws.cross_rest[n];
     const uint16_t *h = b.hidden + n * b.ldh;
-    for (int r = wave * 32; r < wave * 32 + 32; ++r) {
-        const int64_t v = v0 + r;
-        float e = 0.0f;
-        if (v < b.V) {  // uniform per wave
-            const uint16_t *w = b.weight + v * b.ldw;
-            float dot = 0.0f;
-            for (int64_t q = lane; q < b.d / 8; q += 64) {
-                const uint4 hv = *reinterpret_cast<const uint4 *>(h + 8 * q);
-                const uint4 wv = *reinterpret_cast<const uint4 *>(w + 8 * q);
-                const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w}, ww[4] = {wv.x, wv.y, wv.z, wv.w};
+    double before = 0.0;   // mass of the half tile's entries below this step
+    int32_t last = 0;      // last entry with any mass: rounding may leave the rest uncovered
+    for (int step = 0; step < 128 / kStep; ++step) {
+        const int64_t v0 = (int64_t)half * 128 + step * kStep;
+        float dot[kRows];
+        const uint16_t *w[kRows];  // (rows past the end of the vocabulary re-read the last one; their terms are dropped)
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            const int64_t v = v0 + wave * kRows + k;
+            dot[k] = 0.0f;
+            w[k] = b.weight + (v < b.V ? v : b.V - 1) * b.ldw;
+        }
+        for (int64_t q = lane; q < b.d / 8; q += 64) {
+            const uint4 hv = *reinterpret_cast<const uint4 *>(h + 8 * q);
+            uint4 wv[kRows];
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) wv[k] = *reinterpret_cast<const uint4 *>(w[k] + 8 * q);
+            const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w};
+#pragma unroll
+            for (int k = 0; k < kRows; ++k) {
+                const uint32_t ww[4] = {wv[k].x, wv[k].y, wv[k].z, wv[k].w};
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    dot = __fmaf_rn(__uint_as_float(hw[j] << 16), __uint_as_float(ww[j] << 16), dot);
-                    dot = __fmaf_rn(__uint_as_float(hw[j] & 0xFFFF0000u), __uint_as_float(ww[j] & 0xFFFF0000u), dot);
+                    dot[k] = __fmaf_rn(__uint_as_float(hw[j] << 16), __uint_as_float(ww[j] << 16), dot[k]);
+                    dot[k] = __fmaf_rn(__uint_as_float(hw[j] & 0xFFFF0000u), __uint_as_float(ww[j] & 0xFFFF0000u), dot[k]);
                 }
             }
-            dot = wave_sum(dot);
-            e = fast_exp2(__fmaf_rn(dot, c, -ref_exp(m, c)));
-            if (!(e == e)) e = 0.0f;
         }
-        if (lane == 0) lds_e[r] = e;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        // inclusive scan over the 128 terms in vocabulary order: lane l holds entries 2l and 2l + 1
-        const double e0 = (double)lds_e[2 * lane], e1 = (double)lds_e[2 * lane + 1];
-        double incl = e0 + e1;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
+        for (int k = 0; k < kRows; ++k) {
+            dot[k] = wave_sum(dot[k]);
+            const float e = fast_exp2(__fmaf_rn(dot[k], c, -ref_exp(m, c)));
+            if (lane == 0) lds_e[step & 1][wave * kRows + k] = (e == e) && v0 + wave * kRows + k < b.V ? e : 0.0f;
+        }
+        __syncthreads();
+        // every wave scans the step's terms by itself (lanes 32 and up hold zeros): no second barrier
+        const double e = lane < kStep ? (double)lds_e[step & 1][lane] : 0.0;
+        double incl = e;
+#pragma unroll
+        for (int off = 1; off < kStep; off <<= 1) {
             const double o = __shfl_up(incl, off, 64);
             if (lane >= off) incl += o;
         }
-        const double before = incl - (e0 + e1), rest = ws.cross_rest[n];
-        int32_t idx = 0x7FFFFFFF;
-        if (e0 > 0.0 && before + e0 > rest)
-            idx = 2 * lane;
-        else if (e1 > 0.0 && before + e0 + e1 > rest)
-            idx = 2 * lane + 1;
-        int32_t last = e1 > 0.0 ? 2 * lane + 1 : (e0 > 0.0 ? 2 * lane : -1);  // rounding may leave `rest` uncovered
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            idx = min(idx, __shfl_xor(idx, off, 64));
-            last = max(last, __shfl_xor(last, off, 64));
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(e > 0.0 && before + incl > rest);
+        const uint64_t mass = __builtin_amdgcn_ballot_w64(e > 0.0);
+        if (mass != 0ull) last = step * kStep + 63 - __builtin_clzll(mass);
+        if (hit != 0ull) {
+            last = step * kStep + __builtin_ctzll(hit);
+            break;  // uniform over the workgroup: every wave has scanned the same terms
         }
-        if (lane == 0) {
-            if (idx == 0x7FFFFFFF) idx = last >= 0 ? last : 0;
-            oi.ipt_token[n] = (int32_t)(v0 + idx);
-        }
+        before += __shfl(incl, kStep - 1, 64);
     }
+    if (tid == 0) oi.ipt_token[n] = (int32_t)((int64_t)half * 128 + last);
 }
 
 int launch_lmhead_score(const LmHeadBatch &b, const LmHeadWorkspace &ws, const LmHeadPlan &plan, const GumbelOutputs &og,
