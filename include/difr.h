@@ -100,8 +100,8 @@ typedef enum { DIFR_BF16 = 0, DIFR_F32 = 1 } difr_dtype;
  */
 typedef struct {
     const void *logits;        /* [N, ld] row-major, element type `dtype`; base aligned to */
-                               /* the element size.  Fast path: base and ld*sizeof(elt)    */
-                               /* multiples of 16 bytes; otherwise a slower generic path   */
+                               /* the element size (rows that start on 16 bytes are read a */
+                               /* little faster; some calls ask for them)                  */
     int32_t dtype;             /* difr_dtype                                               */
     int64_t N;                 /* token rows, 0 <= N < 2^31                                */
     int64_t V;                 /* vocabulary size, 0 < V < 2^31                            */
@@ -182,8 +182,8 @@ int difr_score_both(const difr_rows *in, const int32_t *claimed_ipt, float *marg
  * kernel tests each wave's 512 logits before it regenerates their noise and skips the noise where none of them can
  * reach the running maximum whatever its Gumbel variate [Sec. 6.3: the variates are bounded once the uniforms are
  * quantised]; on such rows the pass approaches the speed of reading them (a quarter to 40% faster when the logits fall
- * off as -3 ln rank or steeper), on flat rows (where the test never fires) it is 1-2% slower than difr_score_both.  With logit_rank != NULL, and for rows that are not 16-byte
- * aligned, it is difr_score_both.
+ * off as -3 ln rank or steeper), on flat rows (where the test never fires) it is 1-2% slower than difr_score_both.  With
+ * logit_rank != NULL it is difr_score_both.
  */
 int difr_score_both_peaked(const difr_rows *in, const int32_t *claimed_ipt, float *margin, int32_t *argmax,
                            float *max_score, float *claimed_score, uint8_t *flags_gumbel, int32_t *logit_rank, float *dist,
@@ -421,7 +421,7 @@ int difr_seq_reduce(const float *scores, const uint8_t *row_flags, const int64_t
  * Test and audit helper: difr_gumbel_score with the exact pre-filter switched off, so that
  * every vocabulary entry goes through both logarithms.  Same arguments, same outputs; the
  * two must agree bit for bit (the filter only skips entries that provably cannot reach the
- * row maximum).  Rows that are not 16-byte aligned always take this path.
+ * row maximum).
  */
 int difr_debug_gumbel_score_unfiltered(const difr_rows *in, float *margin, int32_t *argmax, float *max_score,
                                        float *claimed_score, uint8_t *flags, int32_t *logit_rank, void *hip_stream);

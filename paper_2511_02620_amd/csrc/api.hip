@@ -186,7 +186,7 @@ int difr_gumbel_score(const difr_rows *in, float *margin, int32_t *argmax, float
     if (b.N == 0) return DIFR_OK;
     if (!margin || !argmax || !flags) return DIFR_ERR_NULL;
     if ((rc = check_device()) != DIFR_OK) return rc;
-    return difr::launch_gumbel_score(b, aligned, true, margin, argmax, max_score, claimed_score, flags, logit_rank,
+    return difr::launch_gumbel_score(b, true, margin, argmax, max_score, claimed_score, flags, logit_rank,
                                      (hipStream_t)hip_stream)
                ? DIFR_ERR_LAUNCH
                : DIFR_OK;
@@ -202,7 +202,7 @@ int difr_debug_gumbel_score_unfiltered(const difr_rows *in, float *margin, int32
     if (b.N == 0) return DIFR_OK;
     if (!margin || !argmax || !flags) return DIFR_ERR_NULL;
     if ((rc = check_device()) != DIFR_OK) return rc;
-    return difr::launch_gumbel_score(b, aligned, false, margin, argmax, max_score, claimed_score, flags, logit_rank,
+    return difr::launch_gumbel_score(b, false, margin, argmax, max_score, claimed_score, flags, logit_rank,
                                      (hipStream_t)hip_stream)
                ? DIFR_ERR_LAUNCH
                : DIFR_OK;
@@ -219,7 +219,7 @@ int difr_ipt_score(const difr_rows *in, float *dist, float *cdf_lo, float *cdf_h
     if (b.N == 0) return DIFR_OK;
     if (!dist || !flags) return DIFR_ERR_NULL;
     if ((rc = check_device()) != DIFR_OK) return rc;
-    return difr::launch_ipt_score(b, aligned, dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags,
+    return difr::launch_ipt_score(b, dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags,
                                   logit_rank, (hipStream_t)hip_stream)
                ? DIFR_ERR_LAUNCH
                : DIFR_OK;
@@ -252,7 +252,7 @@ int difr_admissible_count(const difr_rows *in, const float *max_score, float del
     if (b.N == 0) return DIFR_OK;
     if (!max_score || !count) return DIFR_ERR_NULL;
     if ((rc = check_device()) != DIFR_OK) return rc;
-    return difr::launch_admissible_count(b, aligned, max_score, delta, count, log2_count, (hipStream_t)hip_stream)
+    return difr::launch_admissible_count(b, max_score, delta, count, log2_count, (hipStream_t)hip_stream)
                ? DIFR_ERR_LAUNCH
                : DIFR_OK;
 }
@@ -354,21 +354,9 @@ static int score_both_any(bool peaked, const difr_rows *in, const int32_t *claim
     if (b.N == 0) return DIFR_OK;
     if (!margin || !argmax || !flags_gumbel || !dist || !flags_ipt) return DIFR_ERR_NULL;
     if ((rc = check_device()) != DIFR_OK) return rc;
-    hipStream_t stream = (hipStream_t)hip_stream;
-    if (aligned) {
-        const difr::GumbelOutputs og{margin, argmax, max_score, claimed_score, flags_gumbel, logit_rank};
-        const difr::IptOutputs oi{dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags_ipt, nullptr};
-        return difr::launch_score_both(b, claimed_ipt, og, oi, peaked, stream) ? DIFR_ERR_LAUNCH : DIFR_OK;
-    }
-    // rows that are not 16-byte aligned: the two generic kernels, one after the other
-    if (difr::launch_gumbel_score(b, false, true, margin, argmax, max_score, claimed_score, flags_gumbel, logit_rank, stream))
-        return DIFR_ERR_LAUNCH;
-    difr::RowBatch bi = b;
-    bi.claimed = claimed_ipt;
-    return difr::launch_ipt_score(bi, false, dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags_ipt, nullptr,
-                                  stream)
-               ? DIFR_ERR_LAUNCH
-               : DIFR_OK;
+    const difr::GumbelOutputs og{margin, argmax, max_score, claimed_score, flags_gumbel, logit_rank};
+    const difr::IptOutputs oi{dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags_ipt, nullptr};
+    return difr::launch_score_both(b, claimed_ipt, og, oi, peaked, (hipStream_t)hip_stream) ? DIFR_ERR_LAUNCH : DIFR_OK;
 }
 
 int difr_score_both(const difr_rows *in, const int32_t *claimed_ipt, float *margin, int32_t *argmax, float *max_score,

@@ -9,22 +9,24 @@
 
 namespace difr {
 
-// filtered = false forces the unfiltered kernel (every entry evaluated exactly); unaligned rows always use it.
-int launch_gumbel_score(const RowBatch &b, bool aligned, bool filtered, float *margin, int32_t *argmax,
+// filtered = false forces the unfiltered kernel (every entry evaluated exactly).
+int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t *argmax,
                         float *max_score, float *claimed_score, uint8_t *flags, int32_t *logit_rank,
                         hipStream_t stream);
-int launch_ipt_score(const RowBatch &b, bool aligned, float *dist, float *cdf_lo, float *cdf_hi, float *u,
+int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_hi, float *u,
                      int32_t *ipt_token, double sigma, double eps, float *log_mass, uint8_t *flags,
                      int32_t *logit_rank, hipStream_t stream);
 // Size of each row's admissible set { v : max_score - y_v <= delta } (max_score from launch_gumbel_score).
-int launch_admissible_count(const RowBatch &b, bool aligned, const float *max_score, float delta, int32_t *count,
+int launch_admissible_count(const RowBatch &b, const float *max_score, float delta, int32_t *count,
                             float *log2_count, hipStream_t stream);
 struct GumbelOutputs;
 struct IptOutputs;
-// Both estimators in one pass (aligned rows only).
+// The bare nucleus (aligned rows only).
 int launch_ipt_nucleus(const RowBatch &b, float top_p, const IptOutputs &o, int32_t *kept, float *tau, hipStream_t stream);
+// Both estimators in one pass.
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                       bool peaked, hipStream_t stream);
+// (aligned rows only)
 int launch_score_both_admissible(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og,
                                  const IptOutputs &oi, float delta, int32_t *count, float *log2_count, hipStream_t stream);
 // Token-DiFR likelihood estimate (aligned rows only).

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
     // a round in which the IPT stream must look at indices (it holds the claimed token, or it is ragged)
     auto careful = [&](int r, bool prefix_open) {
         u32x4 q = u32x4{0u, 0u, 0u, 0u};
-        if (s.has_vector(r)) q = load_round(x_row, r);
+        if (s.has_vector(r)) q = load_vector<DT>(x_row, ((int64_t)r * kBlock + tid) * E, V);
         g.process_any(q, r, (int64_t)r * kBlock + tid < nvec);
         s.careful_round(q, r, prefix_open);
     };
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
             if (oa.log2_count) oa.log2_count[row] = c > 0 ? __log2f((float)c) : __builtin_nanf("");
         }
     }
-    ipt_finish<DT, true>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, &lds_tok);
+    ipt_finish<DT>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, &lds_tok);
 }
 
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,

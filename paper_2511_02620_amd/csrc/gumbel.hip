@@ -12,9 +12,8 @@
 
 namespace difr {
 
-// Unfiltered kernel: every entry goes through both logarithms.  Any alignment.  The reference
-// for the filtered kernel and the path for rows that are not 16-byte aligned.
-template <int DT, bool ALIGNED>
+// Unfiltered kernel: every entry goes through both logarithms.  The reference for the filtered kernel.
+template <int DT>
 __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float *__restrict__ margin,
                                                               int32_t *__restrict__ argmax,
                                                               float *__restrict__ max_score,
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float 
 
     for (int64_t base = (int64_t)tid * E; base < V; base += (int64_t)kBlock * E) {
         float x[E];
-        load_elems<DT, ALIGNED>(x_row, base, V, x);
+        unpack_vector<DT>(load_vector<DT>(x_row, base, V), x);
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
             uint32_t r[4];
@@ -105,7 +104,7 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float 
     }
 }
 
-// Filtered streaming kernel for 16-byte aligned rows (the filter is described in gumbel_stream.hpp).
+// Filtered streaming kernel (the filter is described in gumbel_stream.hpp).
 template <int DT, bool RANK>
 __global__ __launch_bounds__(kBlock) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o)
 {
@@ -172,8 +171,8 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_filtered_kernel(RowBatch 
 // Size of the admissible set of each row (Sec. 7: A_t(tau) = tokens whose score passes the threshold; here
 // the score is the margin, so A_t = { v : max_score - y_v <= delta }).  Second pass over the row with the
 // row maximum known: the same exact pre-filter with the fixed bound M - delta, and a count instead of an
-// argmax.  Any alignment is accepted; unaligned rows evaluate every entry.
-template <int DT, bool ALIGNED>
+// argmax.
+template <int DT>
 __global__ __launch_bounds__(kBlock) void admissible_count_kernel(RowBatch b, const float *__restrict__ max_score,
                                                                   float delta, int32_t *__restrict__ count,
                                                                   float *__restrict__ log2_count)
@@ -197,55 +196,39 @@ __global__ __launch_bounds__(kBlock) void admissible_count_kernel(RowBatch b, co
     }
     const elt_t *x_row = reinterpret_cast<const elt_t *>(b.logits) + row * b.ld;
     const int64_t V = b.V;
-    int32_t c = 0;
-    if (ALIGNED) {
-        GumbelStream<DT, false, true> g(ri, x_row, V, lds_L);
-        __syncthreads();
-        g.arm_count(M, delta);
-        __syncthreads();
-        const int64_t nvec = V / E;
-        const int n_main = (int)(nvec / kBlock);
-        int round = 0;
-        auto run_rounds = [&](auto mode_tag) {  // the bound never moves, so neither does the gate mode
-            constexpr int MODE = decltype(mode_tag)::value;
-            u32x4 q_next = load_round(x_row, round);
-            while (round < n_main) {
-                const u32x4 q = q_next;
-                if (round + 1 < n_main) q_next = load_round(x_row, round + 1);
-                g.template process<MODE>(q, round, true);
-                ++round;
-            }
-        };
-        if (n_main > 0) {
-            if (g.gate.mode == 0)
-                run_rounds(std::integral_constant<int, 0>());
-            else if (g.gate.mode == 1)
-                run_rounds(std::integral_constant<int, 1>());
-            else
-                run_rounds(std::integral_constant<int, 2>());
+    GumbelStream<DT, false, true> g(ri, x_row, V, lds_L);
+    __syncthreads();
+    g.arm_count(M, delta);
+    __syncthreads();
+    const int64_t nvec = V / E;
+    const int n_main = (int)(nvec / kBlock);
+    int round = 0;
+    auto run_rounds = [&](auto mode_tag) {  // the bound never moves, so neither does the gate mode
+        constexpr int MODE = decltype(mode_tag)::value;
+        u32x4 q_next = load_round(x_row, round);
+        while (round < n_main) {
+            const u32x4 q = q_next;
+            if (round + 1 < n_main) q_next = load_round(x_row, round + 1);
+            g.template process<MODE>(q, round, true);
+            ++round;
         }
-        if ((int64_t)n_main * kBlock < nvec) {
-            const bool active = (int64_t)n_main * kBlock + tid < nvec;
-            u32x4 q = u32x4{0u, 0u, 0u, 0u};
-            if (active) q = load_round(x_row, n_main);
-            g.process_any(q, n_main, active);
-        }
-        g.tail();
-        c = (int32_t)g.count;
-    } else {
-        const float inv_T = 1.0f / ri.T;
-        for (int64_t base = (int64_t)tid * E; base < V; base += (int64_t)kBlock * E) {
-            float x[E];
-            load_elems<DT, false>(x_row, base, V, x);
-#pragma unroll
-            for (int q = 0; q < E / 4; ++q) {
-                uint32_t r[4];
-                noise_block(ri.key, ri.pos, ri.seq, kStreamGumbel, (uint32_t)((base >> 2) + q), r);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) c += (int32_t)(M - perturbed_score(x[4 * q + j], inv_T, r[j]) <= delta);
-            }
-        }
+    };
+    if (n_main > 0) {
+        if (g.gate.mode == 0)
+            run_rounds(std::integral_constant<int, 0>());
+        else if (g.gate.mode == 1)
+            run_rounds(std::integral_constant<int, 1>());
+        else
+            run_rounds(std::integral_constant<int, 2>());
     }
+    if ((int64_t)n_main * kBlock < nvec) {
+        const bool active = (int64_t)n_main * kBlock + tid < nvec;
+        u32x4 q = u32x4{0u, 0u, 0u, 0u};
+        if (active) q = load_round(x_row, n_main);
+        g.process_any(q, n_main, active);
+    }
+    g.tail();
+    int32_t c = (int32_t)g.count;
     c = block_sum_i32(c, lds_c);
     if (tid == 0) {
         count[row] = c;
@@ -275,14 +258,13 @@ __global__ __launch_bounds__(kBlock) void debug_gumbel_map_kernel(const uint32_t
         g[i] = gumbel_from_bits(bits[i]);
 }
 
-int launch_gumbel_score(const RowBatch &b, bool aligned, bool filtered, float *margin, int32_t *argmax,
+int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t *argmax,
                         float *max_score, float *claimed_score, uint8_t *flags, int32_t *logit_rank,
                         hipStream_t stream)
 {
     const dim3 grid((unsigned)b.N), block(kBlock);
     const GumbelOutputs o{margin, argmax, max_score, claimed_score, flags, logit_rank};
-#define DIFR_ARGS b, margin, argmax, max_score, claimed_score, flags, logit_rank
-    if (aligned && filtered) {
+    if (filtered) {
         if (b.dtype == 0) {
             if (logit_rank)
                 gumbel_score_filtered_kernel<0, true><<<grid, block, 0, stream>>>(b, o);
@@ -295,35 +277,21 @@ int launch_gumbel_score(const RowBatch &b, bool aligned, bool filtered, float *m
                 gumbel_score_filtered_kernel<1, false><<<grid, block, 0, stream>>>(b, o);
         }
     } else if (b.dtype == 0) {
-        if (aligned)
-            gumbel_score_kernel<0, true><<<grid, block, 0, stream>>>(DIFR_ARGS);
-        else
-            gumbel_score_kernel<0, false><<<grid, block, 0, stream>>>(DIFR_ARGS);
+        gumbel_score_kernel<0><<<grid, block, 0, stream>>>(b, margin, argmax, max_score, claimed_score, flags, logit_rank);
     } else {
-        if (aligned)
-            gumbel_score_kernel<1, true><<<grid, block, 0, stream>>>(DIFR_ARGS);
-        else
-            gumbel_score_kernel<1, false><<<grid, block, 0, stream>>>(DIFR_ARGS);
+        gumbel_score_kernel<1><<<grid, block, 0, stream>>>(b, margin, argmax, max_score, claimed_score, flags, logit_rank);
     }
-#undef DIFR_ARGS
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
-int launch_admissible_count(const RowBatch &b, bool aligned, const float *max_score, float delta, int32_t *count,
+int launch_admissible_count(const RowBatch &b, const float *max_score, float delta, int32_t *count,
                             float *log2_count, hipStream_t stream)
 {
     const dim3 grid((unsigned)b.N), block(kBlock);
-    if (b.dtype == 0) {
-        if (aligned)
-            admissible_count_kernel<0, true><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
-        else
-            admissible_count_kernel<0, false><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
-    } else {
-        if (aligned)
-            admissible_count_kernel<1, true><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
-        else
-            admissible_count_kernel<1, false><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
-    }
+    if (b.dtype == 0)
+        admissible_count_kernel<0><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
+    else
+        admissible_count_kernel<1><<<grid, block, 0, stream>>>(b, max_score, delta, count, log2_count);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

@@ -11,7 +11,7 @@
 namespace difr {
 
 // ---------------------------------------------------------------------------------
-// Filtered streaming kernel (aligned rows only).
+// Filtered streaming kernel.
 //
 // The row maximum is bounded from below by L: the claimed token's own score at first
 // (for an honest claim that IS the maximum), then the best score seen so far.  An entry
@@ -42,7 +42,6 @@ constexpr float kGumbelMax = 16.6356f;
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ u16x2 as_u16x2(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
 __device__ __forceinline__ i16x2 as_i16x2(uint32_t w) { return __builtin_bit_cast(i16x2, w); }
@@ -669,12 +668,5 @@ struct GumbelStream {
         }
     }
 };
-
-// 16-byte non-temporal load of lane `tid`'s vector in vector round `round` of a row.
-__device__ __forceinline__ u32x4 load_round(const void *x_row, int round)
-{
-    const char *p = reinterpret_cast<const char *>(x_row) + (size_t)round * (kBlock * 16) + threadIdx.x * 16u;
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-}
 
 }  // namespace difr

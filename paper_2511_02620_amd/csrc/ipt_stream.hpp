@@ -7,8 +7,6 @@
 
 namespace difr {
 
-typedef uint32_t ipt_u32x4 __attribute__((ext_vector_type(4)));
-
 // Inclusive scan (fp64) over the 256 threads in thread order; returns the inclusive value and
 // the block total.  Fixed shape.
 __device__ __forceinline__ double block_inclusive_scan(double v, double *lds /* kWaves */, double &total)
@@ -99,7 +97,7 @@ struct IptOutputs {
     int32_t *logit_rank;
 };
 
-template <int DT, bool ALIGNED>
+template <int DT>
 __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
                                            const typename Elem<DT>::type *x_row, float c, float ref, double Z,
                                            double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
@@ -168,7 +166,7 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
             float e[E];
             if (base < V) {
                 float x[E];
-                load_elems<DT, ALIGNED>(x_row, base, V, x);
+                unpack_vector<DT>(load_vector<DT>(x_row, base, V), x);
 #pragma unroll
                 for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
             } else {
@@ -270,21 +268,6 @@ struct IptStream {
         lane_above = 0;
     }
 
-    static __device__ __forceinline__ void unpack(ipt_u32x4 q, float x[E])
-    {
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-        if (DT == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                x[2 * j] = __uint_as_float(w[j] << 16);
-                x[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[j] = __uint_as_float(w[j]);
-        }
-    }
-
     // Exponentials of one vector relative to the lane's reference point m.  The reference is the maximum of the
     // first vector the lane met and moves only when it has to: the sum of the eight terms is needed anyway,
     // and as long as it stays below 2^64 no term has overflowed (an entry more than 64 / c above m, or a lane
@@ -326,10 +309,10 @@ struct IptStream {
     }
 
     // a full round: every lane holds a complete vector, no index tests
-    __device__ __forceinline__ void fast_round(ipt_u32x4 q)
+    __device__ __forceinline__ void fast_round(u32x4 q)
     {
         float x[E], e[E];
-        unpack(q, x);
+        unpack_vector<DT>(q, x);
         if (want_rank) {  // logit rank: one compare per entry, counted with ballots
             uint32_t n = 0;
 #pragma unroll
@@ -352,12 +335,12 @@ struct IptStream {
 
     // a round that needs index tests: the one holding the claimed token and the last, ragged one.
     // `q` must have been loaded for every lane whose first entry v0 is below V.
-    __device__ __forceinline__ void careful_round(ipt_u32x4 q, int round, bool prefix_open)
+    __device__ __forceinline__ void careful_round(u32x4 q, int round, bool prefix_open)
     {
         const int64_t v0 = ((int64_t)round * kBlock + tid) * E;
         if (v0 < V) {
             float x[E], e[E];
-            unpack(q, x);
+            unpack_vector<DT>(q, x);
 #pragma unroll
             for (int j = 0; j < E; ++j)
                 if (v0 + j >= V) x[j] = -__builtin_inff();

@@ -103,9 +103,9 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // requested while the current one is worked on.  Entries past the end of the row read as -inf.
     const int32_t nvec = (int32_t)((V + E - 1) / E);  // V < 2^31
     const uint32_t V32 = (uint32_t)V;
-    auto fetch = [&](int32_t vec) { return *reinterpret_cast<const ipt_u32x4 *>(x_row + (size_t)vec * E); };
+    auto fetch = [&](int32_t vec) { return *reinterpret_cast<const u32x4 *>(x_row + (size_t)vec * E); };
     // the last vector of a ragged row: entries past the end become -inf
-    auto ragged_patched = [&](ipt_u32x4 q, uint32_t base) __attribute__((always_inline)) {
+    auto ragged_patched = [&](u32x4 q, uint32_t base) __attribute__((always_inline)) {
         if (base + E > V32) {
             uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -116,16 +116,16 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 else
                     w[j] = 0xFF800000u;
             }
-            q = ipt_u32x4{w[0], w[1], w[2], w[3]};
+            q = u32x4{w[0], w[1], w[2], w[3]};
         }
         return q;
     };
     auto for_each_vector = [&](auto &&f) __attribute__((always_inline)) {
         int32_t vec = tid;
-        ipt_u32x4 q_next = ipt_u32x4{0u, 0u, 0u, 0u};
+        u32x4 q_next = u32x4{0u, 0u, 0u, 0u};
         if (vec < nvec) q_next = fetch(vec);
         while (vec < nvec) {
-            ipt_u32x4 q = q_next;
+            u32x4 q = q_next;
             const int32_t next = vec + kBlock;
             if (next < nvec) q_next = fetch(next);
             const uint32_t base = (uint32_t)vec * E;
@@ -138,7 +138,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // a larger key.  -0 and +0 are the same logit (ties go by index, not by sign), so they share a key.
     // bf16: two 16-bit keys per dword, formed on the packed patterns: 0x8000 + magnitude for a clear sign bit,
     // 0x8000 - magnitude for a set one.  fp32: float_order_bits of the value with -0 read as +0.
-    auto keys_of = [&](const ipt_u32x4 &q, uint32_t (&kw)[4]) __attribute__((always_inline)) {
+    auto keys_of = [&](const u32x4 &q, uint32_t (&kw)[4]) __attribute__((always_inline)) {
         const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -158,7 +158,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         const uint32_t b = __float_as_uint(x) >> 16, m = b & 0x7FFFu;
         return (b & 0x8000u) ? 0x8000u - m : 0x8000u + m;
     };
-    auto value_of = [&](const ipt_u32x4 &q, int j) __attribute__((always_inline)) {
+    auto value_of = [&](const u32x4 &q, int j) __attribute__((always_inline)) {
         const uint32_t w[4] = {q.x, q.y, q.z, q.w};
         if (DT == 0) return __uint_as_float((j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16));
         return __uint_as_float(w[j]);
@@ -170,7 +170,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     //      R = M in the rare case that M lies so far above R that terms could overflow.  The two together tell the
     //      first search pass where to put its bins.  A first round without a usable value takes a pass of its own. ----
     float R = ninf, lo_s = __builtin_inff();
-    auto look = [&](const ipt_u32x4 &q) __attribute__((always_inline)) {
+    auto look = [&](const u32x4 &q) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < E; ++j) {
             const float v = value_of(q, j);
@@ -185,7 +185,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     if (!(R > ninf && R < __builtin_inff())) {  // uniform
         R = ninf;
         lo_s = __builtin_inff();
-        for_each_vector([&](const ipt_u32x4 &q, uint32_t) { look(q); });
+        for_each_vector([&](const u32x4 &q, uint32_t) { look(q); });
         R = block_max(R, lds_f);
         if (!(R > ninf && R < __builtin_inff())) {  // every entry masked, or a +inf
             give_up(kFlagNonfinite | (valid ? 0u : kFlagInvalidClaim), 0);
@@ -306,7 +306,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
         uint32_t kmax = 0u, kmin = 0xFFFFFFFFu;
         uint32_t smax = 0x80008000u, umax = 0u, umin = 0xFFFFFFFFu;
-        for_each_vector([&](const ipt_u32x4 &q, uint32_t) {
+        for_each_vector([&](const u32x4 &q, uint32_t) {
             if (DT == 0) {
                 const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
@@ -410,7 +410,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int k = 0; k < kNucBins; ++k) cnt[k * kBlock + tid] = 0u;
         double below_above = 0.0;
         int32_t n_above = 0;
-        for_each_vector([&](const ipt_u32x4 &q, uint32_t base) {
+        for_each_vector([&](const u32x4 &q, uint32_t base) {
             uint32_t kw[4];
             keys_of(q, kw);
             float below_vec = 0.0f;
@@ -528,7 +528,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         const uint32_t span = khi - klo;
         const int sh = max(0, 28 - (int)__builtin_clz(span));  // span >> sh <= 15
         clear_bins();
-        for_each_vector([&](const ipt_u32x4 &q, uint32_t) {
+        for_each_vector([&](const u32x4 &q, uint32_t) {
             uint32_t kw[4];
             keys_of(q, kw);
 #pragma unroll
@@ -557,7 +557,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     int32_t ties = 0;          // ... and all of them
     int32_t n_above = 0;       // entries above the bracket
     const uint32_t span_c = khi - klo;
-    for_each_vector([&](const ipt_u32x4 &q, uint32_t base) {
+    for_each_vector([&](const u32x4 &q, uint32_t base) {
         uint32_t kw[4];
         keys_of(q, kw);
         float below_vec = 0.0f;
@@ -730,7 +730,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int32_t vec0 = 0; vec0 < nvec; vec0 += kBlock) {
             const int32_t vec = vec0 + tid;
             const uint32_t base = (uint32_t)vec * E;
-            ipt_u32x4 q = ipt_u32x4{0u, 0u, 0u, 0u};
+            u32x4 q = u32x4{0u, 0u, 0u, 0u};
             uint32_t kw[4] = {0u, 0u, 0u, 0u};
             int32_t my_ties = 0;
             if (vec < nvec) {
