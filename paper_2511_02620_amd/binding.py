@@ -1,8 +1,10 @@
-"""ctypes binding of libdifr.so: argument marshalling only.
+"""Binding of libdifr.so: argument marshalling only.
 
 Every function takes torch tensors that already live on the GPU, hands their device
 pointers and the current HIP stream to the C entry point of the same name, and returns
-freshly allocated output tensors.  No arithmetic of the method happens here.
+freshly allocated output tensors.  No arithmetic of the method happens here.  The calls of
+the hot path are marshalled in native code (csrc/binding.cpp); the audit helpers, the
+allocation-free LM-head call and every check's error message are ctypes and Python.
 """
 from __future__ import annotations
 
@@ -14,6 +16,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libdifr.so")
 _lib = None
+_native = None
 
 FLAG_MATCH = 1
 FLAG_INVALID_CLAIM = 2
@@ -137,6 +140,19 @@ def load_library():
     return lib
 
 
+def _load_native():
+    """The native side of this binding (csrc/binding.cpp), with the addresses of the library's entry points."""
+    global _native
+    lib = load_library()
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise ImportError("_native.so is missing or does not load: build it with `python -m paper_2511_02620_amd.build`") from e
+    native.bind({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
+    _native = native
+    return native
+
+
 def version() -> int:
     return int(load_library().difr_version())
 
@@ -202,53 +218,42 @@ def _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatur
     return r, N, dev
 
 
+def _refused(name, rc, checks):
+    """The native call handed back no tensors: raise what is wrong (rc: the difr_status of the entry point, or None if an
+    argument is not what it has to be, which `checks` then names)."""
+    if rc is None:
+        checks()
+        raise ValueError("%s: an argument is not a tensor of the kind the call takes" % name)
+    raise DifrError(rc, name)
+
+
+def _check_z(z, dev):
+    if z.device != dev or z.dtype != torch.float32 or z.dim() != 1 or not z.is_contiguous():
+        raise ValueError("z must be a contiguous 1-D float32 tensor on the device of logits")
+
+
 def gumbel_score(logits, temperature, seeds, seq_ids, positions, claimed=None, temperatures=None, V=None,
                  want_scores=True, unfiltered=False, want_rank=False):
     """difr_gumbel_score (or, with unfiltered=True, difr_debug_gumbel_score_unfiltered).
     logits [N, >=V] bf16/fp32 on the GPU; seeds int64 [S] (uint64 bits); seq_ids, positions,
     claimed int32 [N].  Returns a dict of device tensors."""
-    lib = load_library()
-    entry = lib.difr_debug_gumbel_score_unfiltered if unfiltered else lib.difr_gumbel_score
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures)
-    out = dict(margin=torch.empty(N, dtype=torch.float32, device=dev),
-               argmax=torch.empty(N, dtype=torch.int32, device=dev),
-               flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_scores:
-        out["max_score"] = torch.empty(N, dtype=torch.float32, device=dev)
-        out["claimed_score"] = torch.empty(N, dtype=torch.float32, device=dev)
-    if want_rank:
-        out["logit_rank"] = torch.empty(N, dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        rc = entry(C.byref(r), _ptr(out["margin"]), _ptr(out["argmax"]), _ptr(out.get("max_score")),
-                                   _ptr(out.get("claimed_score")), _ptr(out["flags"]), _ptr(out.get("logit_rank")),
-                                   _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_gumbel_score")
+    out = (_native or _load_native()).gumbel_score(logits, V if V is None else int(V), float(temperature), seeds, seq_ids, positions,
+                                                   claimed, temperatures, want_scores, unfiltered, want_rank)
+    if out.__class__ is not dict:
+        _refused("difr_gumbel_score", out,
+                 lambda: _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures))
     return out
 
 
 def ipt_score(logits, temperature, seeds, seq_ids, positions, claimed=None, temperatures=None, V=None,
               want_token=False, want_log_mass=False, sigma=0.01, eps=1e-30, want_interval=True, want_rank=False):
     """difr_ipt_score.  Same inputs as :func:`gumbel_score`.  Returns a dict of device tensors."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures)
-    f32 = dict(dtype=torch.float32, device=dev)
-    out = dict(dist=torch.empty(N, **f32), flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_interval:
-        out.update(cdf_lo=torch.empty(N, **f32), cdf_hi=torch.empty(N, **f32), u=torch.empty(N, **f32))
-    if want_token:
-        out["ipt_token"] = torch.empty(N, dtype=torch.int32, device=dev)
-    if want_log_mass:
-        out["log_mass"] = torch.empty(N, **f32)
-    if want_rank:
-        out["logit_rank"] = torch.empty(N, dtype=torch.int32, device=dev)
-    with torch.cuda.device(dev):
-        rc = lib.difr_ipt_score(C.byref(r), _ptr(out["dist"]), _ptr(out.get("cdf_lo")), _ptr(out.get("cdf_hi")),
-                                _ptr(out.get("u")), _ptr(out.get("ipt_token")), float(sigma), float(eps),
-                                _ptr(out.get("log_mass")), _ptr(out["flags"]), _ptr(out.get("logit_rank")),
-                                _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_ipt_score")
+    out = (_native or _load_native()).ipt_score(logits, V if V is None else int(V), float(temperature), seeds, seq_ids, positions,
+                                                claimed, temperatures, want_token, want_log_mass, float(sigma), float(eps),
+                                                want_interval, want_rank)
+    if out.__class__ is not dict:
+        _refused("difr_ipt_score", out,
+                 lambda: _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures))
     return out
 
 
@@ -257,7 +262,7 @@ def score_both(logits, temperature, seeds, seq_ids, positions, claimed_gumbel=No
     """difr_score_both: both estimators in one pass.  Returns (gumbel dict, ipt dict) of device tensors;
     want_rank adds logit_rank (of the Token-DiFR claim) to the first, want_token / want_log_mass add ipt_token /
     log_mass to the second (as in :func:`ipt_score`)."""
-    return _score_both("difr_score_both", logits, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt,
+    return _score_both("difr_score_both", False, logits, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt,
                        temperatures, V, want_rank, want_token, want_log_mass, sigma, eps)
 
 
@@ -265,105 +270,60 @@ def score_both_peaked(logits, temperature, seeds, seq_ids, positions, claimed_gu
                       temperatures=None, V=None, want_rank=False, want_token=False, want_log_mass=False, sigma=0.01,
                       eps=1e-30):
     """difr_score_both_peaked: :func:`score_both` for rows known to be concentrated; same arguments, same results."""
-    return _score_both("difr_score_both_peaked", logits, temperature, seeds, seq_ids, positions, claimed_gumbel,
+    return _score_both("difr_score_both_peaked", True, logits, temperature, seeds, seq_ids, positions, claimed_gumbel,
                        claimed_ipt, temperatures, V, want_rank, want_token, want_log_mass, sigma, eps)
 
 
-def _score_both(entry_name, logits, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt, temperatures, V,
-                want_rank, want_token, want_log_mass, sigma, eps):
-    lib = load_library()
+def _check_pair(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt, temperatures):
     r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel, temperatures)
     _check(claimed_ipt, torch.int32, N, "claimed_ipt", dev)
-    f32 = dict(dtype=torch.float32, device=dev)
-    g = dict(margin=torch.empty(N, **f32), argmax=torch.empty(N, dtype=torch.int32, device=dev),
-             max_score=torch.empty(N, **f32), claimed_score=torch.empty(N, **f32),
-             flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    i = dict(dist=torch.empty(N, **f32), cdf_lo=torch.empty(N, **f32), cdf_hi=torch.empty(N, **f32),
-             u=torch.empty(N, **f32), flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_rank:
-        g["logit_rank"] = torch.empty(N, dtype=torch.int32, device=dev)
-    if want_token:
-        i["ipt_token"] = torch.empty(N, dtype=torch.int32, device=dev)
-    if want_log_mass:
-        i["log_mass"] = torch.empty(N, **f32)
-    with torch.cuda.device(dev):
-        rc = getattr(lib, entry_name)(C.byref(r), _ptr(claimed_ipt), _ptr(g["margin"]), _ptr(g["argmax"]),
-                                      _ptr(g["max_score"]), _ptr(g["claimed_score"]), _ptr(g["flags"]),
-                                      _ptr(g.get("logit_rank")), _ptr(i["dist"]), _ptr(i["cdf_lo"]), _ptr(i["cdf_hi"]),
-                                      _ptr(i["u"]), _ptr(i.get("ipt_token")), float(sigma), float(eps),
-                                      _ptr(i.get("log_mass")), _ptr(i["flags"]), _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, entry_name)
-    return g, i
+    return dev
+
+
+def _score_both(entry_name, peaked, logits, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt, temperatures, V,
+                want_rank, want_token, want_log_mass, sigma, eps):
+    out = (_native or _load_native()).score_both(logits, V if V is None else int(V), float(temperature), seeds, seq_ids, positions,
+                                                 claimed_gumbel, temperatures, claimed_ipt, peaked, want_rank, want_token,
+                                                 want_log_mass, float(sigma), float(eps))
+    if out.__class__ is not tuple:
+        _refused(entry_name, out, lambda: _check_pair(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel,
+                                                      claimed_ipt, temperatures))
+    return out
 
 
 def score_both_admissible(logits, temperature, seeds, seq_ids, positions, delta, claimed_gumbel=None, claimed_ipt=None,
                           temperatures=None, V=None):
     """difr_score_both_admissible: both estimators and the admissible-set size in one pass.
     Returns (gumbel dict, ipt dict, admissible dict with count [-1 = undetermined] and log2_count)."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel, temperatures)
-    _check(claimed_ipt, torch.int32, N, "claimed_ipt", dev)
-    f32 = dict(dtype=torch.float32, device=dev)
-    g = dict(margin=torch.empty(N, **f32), argmax=torch.empty(N, dtype=torch.int32, device=dev),
-             max_score=torch.empty(N, **f32), claimed_score=torch.empty(N, **f32),
-             flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    i = dict(dist=torch.empty(N, **f32), cdf_lo=torch.empty(N, **f32), cdf_hi=torch.empty(N, **f32),
-             u=torch.empty(N, **f32), flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    a = dict(count=torch.empty(N, dtype=torch.int32, device=dev), log2_count=torch.empty(N, **f32))
-    with torch.cuda.device(dev):
-        rc = lib.difr_score_both_admissible(C.byref(r), _ptr(claimed_ipt), float(delta), _ptr(g["margin"]),
-                                            _ptr(g["argmax"]), _ptr(g["max_score"]), _ptr(g["claimed_score"]),
-                                            _ptr(g["flags"]), _ptr(i["dist"]), _ptr(i["cdf_lo"]), _ptr(i["cdf_hi"]),
-                                            _ptr(i["u"]), _ptr(i["flags"]), _ptr(a["count"]), _ptr(a["log2_count"]),
-                                            _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_score_both_admissible")
-    return g, i, a
+    out = (_native or _load_native()).score_both_admissible(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
+                                                            positions, claimed_gumbel, temperatures, claimed_ipt, float(delta))
+    if out.__class__ is not tuple:
+        _refused("difr_score_both_admissible", out, lambda: _check_pair(logits, V, temperature, seeds, seq_ids, positions,
+                                                                        claimed_gumbel, claimed_ipt, temperatures))
+    return out
 
 
 def ipt_score_filtered(logits, temperature, seeds, seq_ids, positions, claimed=None, top_k=50, top_p=1.0,
                        temperatures=None, V=None, want_token=False, want_log_mass=False, sigma=0.01, eps=1e-30):
     """difr_ipt_score_filtered.  Returns a dict of device tensors (dist, cdf_lo, cdf_hi, u, kept, flags, ...)."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures)
-    f32 = dict(dtype=torch.float32, device=dev)
-    out = dict(dist=torch.empty(N, **f32), cdf_lo=torch.empty(N, **f32), cdf_hi=torch.empty(N, **f32),
-               u=torch.empty(N, **f32), kept=torch.empty(N, dtype=torch.int32, device=dev),
-               flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_token:
-        out["ipt_token"] = torch.empty(N, dtype=torch.int32, device=dev)
-    if want_log_mass:
-        out["log_mass"] = torch.empty(N, **f32)
-    with torch.cuda.device(dev):
-        rc = lib.difr_ipt_score_filtered(C.byref(r), int(top_k), float(top_p), _ptr(out["dist"]), _ptr(out["cdf_lo"]),
-                                         _ptr(out["cdf_hi"]), _ptr(out["u"]), _ptr(out.get("ipt_token")), float(sigma),
-                                         float(eps), _ptr(out.get("log_mass")), _ptr(out["kept"]), _ptr(out["flags"]),
-                                         _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_ipt_score_filtered")
+    out = (_native or _load_native()).ipt_score_filtered(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
+                                                         positions, claimed, temperatures, int(top_k), float(top_p), want_token,
+                                                         want_log_mass, float(sigma), float(eps))
+    if out.__class__ is not dict:
+        _refused("difr_ipt_score_filtered", out,
+                 lambda: _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures))
     return out
 
 
 def gumbel_likelihood(logits, temperature, seeds, seq_ids, positions, claimed, z, top_k=0, top_p=1.0, s=16, sigma=1.0,
                       temperatures=None, V=None, want_active=False):
     """difr_gumbel_likelihood.  z: fp32 [M] standard normal draws on the GPU.  Returns a dict of device tensors."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures)
-    if z.device != dev or z.dtype != torch.float32 or z.dim() != 1 or not z.is_contiguous():
-        raise ValueError("z must be a contiguous 1-D float32 tensor on the device of logits")
-    p = _LikelihoodParams(int(top_k), float(top_p), int(s), float(sigma), z.shape[0], z.data_ptr())
-    f32 = dict(dtype=torch.float32, device=dev)
-    out = dict(pi=torch.empty(N, **f32), log_pi=torch.empty(N, **f32), tau=torch.empty(N, **f32),
-               flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_active:
-        out["active"] = torch.empty(N, max(int(s), 1), dtype=torch.int32, device=dev)[:, :int(s)].contiguous()
-    with torch.cuda.device(dev):
-        rc = lib.difr_gumbel_likelihood(C.byref(r), C.byref(p), _ptr(out["pi"]), _ptr(out["log_pi"]), _ptr(out["tau"]),
-                                        _ptr(out.get("active")) if int(s) > 0 else None, _ptr(out["flags"]),
-                                        _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_gumbel_likelihood")
+    out = (_native or _load_native()).gumbel_likelihood(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
+                                                        positions, claimed, temperatures, z, int(top_k), float(top_p), int(s),
+                                                        float(sigma), want_active)
+    if out.__class__ is not dict:
+        _refused("difr_gumbel_likelihood", out,
+                 lambda: _check_z(z, _rows(logits, V, temperature, seeds, seq_ids, positions, claimed, temperatures)[2]))
     return out
 
 
@@ -372,50 +332,27 @@ def score_both_filtered(logits, temperature, seeds, seq_ids, positions, claimed_
                         want_log_mass=False, sigma_ipt=0.01, eps=1e-30):
     """difr_score_both_filtered: gumbel_likelihood and ipt_score_filtered in one pass over the logits.
     Returns (likelihood dict, filtered-IPT dict), each as the single call returns it."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel, temperatures)
-    _check(claimed_ipt, torch.int32, N, "claimed_ipt", dev)
-    if z.device != dev or z.dtype != torch.float32 or z.dim() != 1 or not z.is_contiguous():
-        raise ValueError("z must be a contiguous 1-D float32 tensor on the device of logits")
-    p = _LikelihoodParams(int(top_k), float(top_p), int(s), float(sigma), z.shape[0], z.data_ptr())
-    f32 = dict(dtype=torch.float32, device=dev)
-    lik = dict(pi=torch.empty(N, **f32), log_pi=torch.empty(N, **f32), tau=torch.empty(N, **f32),
-               flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_active:
-        lik["active"] = torch.empty(N, max(int(s), 1), dtype=torch.int32, device=dev)[:, :int(s)].contiguous()
-    ipt = dict(dist=torch.empty(N, **f32), cdf_lo=torch.empty(N, **f32), cdf_hi=torch.empty(N, **f32),
-               u=torch.empty(N, **f32), kept=torch.empty(N, dtype=torch.int32, device=dev),
-               flags=torch.empty(N, dtype=torch.uint8, device=dev))
-    if want_token:
-        ipt["ipt_token"] = torch.empty(N, dtype=torch.int32, device=dev)
-    if want_log_mass:
-        ipt["log_mass"] = torch.empty(N, **f32)
-    with torch.cuda.device(dev):
-        rc = lib.difr_score_both_filtered(C.byref(r), _ptr(claimed_ipt), C.byref(p), _ptr(lik["pi"]), _ptr(lik["log_pi"]),
-                                          _ptr(lik["tau"]), _ptr(lik.get("active")) if int(s) > 0 else None,
-                                          _ptr(lik["flags"]), _ptr(ipt["dist"]), _ptr(ipt["cdf_lo"]), _ptr(ipt["cdf_hi"]),
-                                          _ptr(ipt["u"]), _ptr(ipt.get("ipt_token")), float(sigma_ipt), float(eps),
-                                          _ptr(ipt.get("log_mass")), _ptr(ipt["kept"]), _ptr(ipt["flags"]),
-                                          _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_score_both_filtered")
-    return lik, ipt
+    out = (_native or _load_native()).score_both_filtered(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
+                                                          positions, claimed_gumbel, temperatures, z, int(top_k), float(top_p),
+                                                          int(s), float(sigma), want_active, claimed_ipt, want_token,
+                                                          want_log_mass, float(sigma_ipt), float(eps))
+    if out.__class__ is not tuple:
+        _refused("difr_score_both_filtered", out,
+                 lambda: _check_z(z, _check_pair(logits, V, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt,
+                                                 temperatures)))
+    return out
 
 
 def admissible_count(logits, temperature, seeds, seq_ids, positions, max_score, delta, temperatures=None, V=None,
                      want_log2=True):
     """difr_admissible_count: size of { v : max_score - y_v <= delta } per row (max_score from gumbel_score)."""
-    lib = load_library()
-    r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, None, temperatures)
-    _check(max_score, torch.float32, N, "max_score", dev)
-    out = dict(count=torch.empty(N, dtype=torch.int32, device=dev))
-    if want_log2:
-        out["log2_count"] = torch.empty(N, dtype=torch.float32, device=dev)
-    with torch.cuda.device(dev):
-        rc = lib.difr_admissible_count(C.byref(r), _ptr(max_score), float(delta), _ptr(out["count"]),
-                                       _ptr(out.get("log2_count")), _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_admissible_count")
+    out = (_native or _load_native()).admissible_count(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
+                                                       positions, None, temperatures, max_score, float(delta), want_log2)
+    if out.__class__ is not dict:
+        def checks():
+            r, N, dev = _rows(logits, V, temperature, seeds, seq_ids, positions, None, temperatures)
+            _check(max_score, torch.float32, N, "max_score", dev)
+        _refused("difr_admissible_count", out, checks)
     return out
 
 
@@ -506,6 +443,14 @@ def lmhead_score(hidden, weight, temperature, seeds, seq_ids, positions, claimed
     ipt_token (the sampler's own token; it needs a larger workspace: lmhead_workspace_bytes(..., want_token=True)) to the second;
     `out` = a pair from lmhead_outputs() to write into instead of new tensors (it decides which optional outputs
     are produced)."""
+    if out is None:
+        got = (_native or _load_native()).lmhead_score(hidden, weight, float(temperature), seeds, seq_ids, positions, claimed_gumbel,
+                                                       claimed_ipt, temperatures, workspace, want_rank, want_log_mass, want_token,
+                                                       float(sigma), float(eps))
+        if got.__class__ is tuple:
+            return got
+        if got is not None:
+            raise DifrError(got, "difr_lmhead_score")
     r, dev, N, V, d = _lmhead_args(hidden, weight, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt,
                                    temperatures)
     g, i = _lmhead_out(out, N, dev, want_rank, want_log_mass, want_token)
@@ -535,43 +480,31 @@ def lmhead_score_static(hidden, weight, temperature, seeds, seq_ids, positions, 
 
 def seq_reduce(scores, row_flags, seq_offsets, threshold):
     """difr_seq_reduce.  scores fp32 [N], row_flags uint8 [N] or None, seq_offsets int64 [S+1]."""
-    lib = load_library()
+    out = (_native or _load_native()).seq_reduce(scores, row_flags, seq_offsets, float(threshold))
+    if out.__class__ is not dict:
+        def checks():
+            dev = _check_scores(scores)
+            _check(row_flags, torch.uint8, scores.shape[0], "row_flags", dev)
+            raise ValueError("seq_offsets must be a contiguous 1-D int64 GPU tensor of S+1 elements")
+        _refused("difr_seq_reduce", out, checks)
+    return out
+
+
+def _check_scores(scores):
     if not scores.is_cuda or scores.dtype != torch.float32 or scores.dim() != 1 or not scores.is_contiguous():
         raise ValueError("scores must be a contiguous 1-D float32 GPU tensor")
-    dev = scores.device
-    N = scores.shape[0]
-    _check(row_flags, torch.uint8, N, "row_flags", dev)
-    if (seq_offsets.device != dev or seq_offsets.dtype != torch.int64 or seq_offsets.dim() != 1
-            or seq_offsets.shape[0] < 1 or not seq_offsets.is_contiguous()):
-        raise ValueError("seq_offsets must be a contiguous 1-D int64 GPU tensor of S+1 elements")
-    S = seq_offsets.shape[0] - 1
-    out = dict(seq_mean=torch.empty(S, dtype=torch.float32, device=dev),
-               seq_max=torch.empty(S, dtype=torch.float32, device=dev),
-               seq_mismatch=torch.empty(S, dtype=torch.int32, device=dev),
-               seq_flag=torch.empty(S, dtype=torch.uint8, device=dev))
-    with torch.cuda.device(dev):
-        rc = lib.difr_seq_reduce(_ptr(scores), _ptr(row_flags), _ptr(seq_offsets), N, S, float(threshold),
-                                 _ptr(out["seq_mean"]), _ptr(out["seq_max"]), _ptr(out["seq_mismatch"]),
-                                 _ptr(out["seq_flag"]), _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_seq_reduce")
-    return out
+    return scores.device
 
 
 def classify(scores, ranks, tau, rank_cutoff, V, log2_admissible=None):
     """difr_classify.  scores fp32 [N], ranks int32 [N] on the GPU.  Returns dict(cls uint8, bits fp32)."""
-    lib = load_library()
-    if not scores.is_cuda or scores.dtype != torch.float32 or scores.dim() != 1 or not scores.is_contiguous():
-        raise ValueError("scores must be a contiguous 1-D float32 GPU tensor")
-    dev, N = scores.device, scores.shape[0]
-    _check(ranks, torch.int32, N, "ranks", dev)
-    _check(log2_admissible, torch.float32, N, "log2_admissible", dev)
-    out = dict(cls=torch.empty(N, dtype=torch.uint8, device=dev), bits=torch.empty(N, dtype=torch.float32, device=dev))
-    with torch.cuda.device(dev):
-        rc = lib.difr_classify(_ptr(scores), _ptr(ranks), N, float(tau), int(rank_cutoff), int(V),
-                               _ptr(log2_admissible), _ptr(out["cls"]), _ptr(out["bits"]), _stream_ptr(dev))
-    if rc:
-        raise DifrError(rc, "difr_classify")
+    out = (_native or _load_native()).classify(scores, ranks, float(tau), int(rank_cutoff), int(V), log2_admissible)
+    if out.__class__ is not dict:
+        def checks():
+            dev, N = _check_scores(scores), scores.shape[0]
+            _check(ranks, torch.int32, N, "ranks", dev)
+            _check(log2_admissible, torch.float32, N, "log2_admissible", dev)
+        _refused("difr_classify", out, checks)
     return out
 
 
