@@ -22,8 +22,10 @@ struct AdmissibleOutputs {
 
 // With the rank count the body needs 97 registers, one too many for five waves per SIMD; asked for five it fits in 96
 // without spills and runs 5% faster.  The other variants ask for one wave, which is no constraint.
-template <int DT, bool ADM, bool RANK, bool PEAKED = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5 : 1))) void score_both_kernel(
+//
+// TOK: with the honest sampler's Token-IPT-DiFR token (ipt_stream.hpp).
+template <int DT, bool ADM, bool RANK, bool TOK, bool PEAKED = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || TOK ? 5 : 1))) void score_both_kernel(
     RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa)
 {
     typedef typename Elem<DT>::type elt_t;
@@ -34,7 +36,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
     __shared__ int32_t lds_rank[kWaves];
     __shared__ float lds_f[kWaves];
     __shared__ double lds_d[kWaves];
-    __shared__ int32_t lds_tok;
+    __shared__ double mark_Z[TOK ? kMarks : 1][kBlock];
+    __shared__ float mark_ref[TOK ? kMarks : 1][kBlock];
+    __shared__ WalkScratch walk;
     __shared__ float adm_lists[ADM ? kWaves * kAdmCap : 1];
     __shared__ int32_t adm_fills[kWaves];
     __shared__ int32_t lds_c[kWaves];
@@ -69,6 +73,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
     const int full_rounds = (int)(nvec / kBlock);                    // rounds of 256 complete vectors
     const int n_rounds = (int)((nvec_total + kBlock - 1) / kBlock);  // full_rounds or full_rounds + 1
     const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;    // round holding the IPT claim
+    IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
     // Full rounds [round, r_end): Gumbel gates + IPT accumulation on the same vector.  The loop body is
     // instantiated once per Gumbel gate mode; a change of mode leaves the inner loop.
@@ -95,12 +100,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
     };
     auto run_to = [&](int r_end) {
         while (round < r_end) {
+            const int stop = marks.stop(r_end);
             if (g.gate.mode == 0)
-                run_rounds(std::integral_constant<int, 0>(), r_end);
+                run_rounds(std::integral_constant<int, 0>(), stop);
             else if (g.gate.mode == 1)
-                run_rounds(std::integral_constant<int, 1>(), r_end);
+                run_rounds(std::integral_constant<int, 1>(), stop);
             else
-                run_rounds(std::integral_constant<int, 2>(), r_end);
+                run_rounds(std::integral_constant<int, 2>(), stop);
+            marks.at(round, s);
         }
     };
     // a round in which the IPT stream must look at indices (it holds the claimed token, or it is ragged)
@@ -115,6 +122,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
         run_to(round_t);
         careful(round_t, true);
         round = round_t + 1;
+        marks.at(round, s);
         run_to(full_rounds);
         if (n_rounds > full_rounds) careful(full_rounds, false);
     } else {
@@ -133,32 +141,36 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK ? 5
             if (oa.log2_count) oa.log2_count[row] = c > 0 ? __log2f((float)c) : __builtin_nanf("");
         }
     }
-    ipt_finish<DT>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, &lds_tok);
+    ipt_finish<DT, TOK>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, marks, &walk);
+}
+
+template <int DT, bool TOK>
+static void launch_score_both_of(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
+                                 bool peaked, hipStream_t stream)
+{
+    const dim3 grid((unsigned)b.N), block(kBlock);
+    const AdmissibleOutputs none{0.0f, nullptr, nullptr};
+    if (og.logit_rank)  // counted in the same stream, only when asked for; every round is then looked at: no early test
+        score_both_kernel<DT, false, true, TOK><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+    else if (peaked)
+        score_both_kernel<DT, false, false, TOK, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+    else
+        score_both_kernel<DT, false, false, TOK><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
 }
 
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                       bool peaked, hipStream_t stream)
 {
-    const dim3 grid((unsigned)b.N), block(kBlock);
-    const AdmissibleOutputs none{0.0f, nullptr, nullptr};
-    const bool rank = og.logit_rank != nullptr;  // counted in the same stream, only when asked for
-    if (peaked && !rank) {  // (with the rank count every round is looked at anyway: the ordinary kernel)
-        if (b.dtype == 0)
-            score_both_kernel<0, false, false, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
-        else
-            score_both_kernel<1, false, false, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
-        return hipGetLastError() == hipSuccess ? 0 : 1;
-    }
     if (b.dtype == 0) {
-        if (rank)
-            score_both_kernel<0, false, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+        if (oi.ipt_token)
+            launch_score_both_of<0, true>(b, claimed_ipt, og, oi, peaked, stream);
         else
-            score_both_kernel<0, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+            launch_score_both_of<0, false>(b, claimed_ipt, og, oi, peaked, stream);
     } else {
-        if (rank)
-            score_both_kernel<1, false, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+        if (oi.ipt_token)
+            launch_score_both_of<1, true>(b, claimed_ipt, og, oi, peaked, stream);
         else
-            score_both_kernel<1, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+            launch_score_both_of<1, false>(b, claimed_ipt, og, oi, peaked, stream);
     }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
@@ -169,9 +181,9 @@ int launch_score_both_admissible(const RowBatch &b, const int32_t *claimed_ipt, 
     const dim3 grid((unsigned)b.N), block(kBlock);
     const AdmissibleOutputs oa{delta, count, log2_count};
     if (b.dtype == 0)
-        score_both_kernel<0, true, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        score_both_kernel<0, true, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
     else
-        score_both_kernel<1, true, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        score_both_kernel<1, true, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

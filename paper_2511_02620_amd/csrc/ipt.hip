@@ -13,15 +13,17 @@
 
 namespace difr {
 
-// Streaming kernel (the streaming state is described in ipt_stream.hpp).
-template <int DT>
+// Streaming kernel (the streaming state is described in ipt_stream.hpp).  TOK: with the honest sampler's token.
+template <int DT, bool TOK>
 __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutputs o)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
     __shared__ float lds_f[kWaves];
     __shared__ double lds_d[kWaves];
-    __shared__ int32_t lds_tok;
+    __shared__ double mark_Z[TOK ? kMarks : 1][kBlock];
+    __shared__ float mark_ref[TOK ? kMarks : 1][kBlock];
+    __shared__ WalkScratch walk;
     __shared__ int32_t lds_rank[kWaves];
 
     const int64_t row = blockIdx.x;
@@ -32,13 +34,22 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
 
     IptStream<DT> s(ri, x_row, V, o.logit_rank != nullptr);
 
+    const int64_t nvec_total = (V + E - 1) / E;                      // the last vector may be partial
+    const int full_rounds = (int)((V / E) / kBlock);                 // rounds of 256 complete vectors
+    const int n_rounds = (int)((nvec_total + kBlock - 1) / kBlock);  // full_rounds or full_rounds + 1
+    const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;
+    IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
+
     auto stream = [&](int r0, int r1) {  // full rounds [r0, r1) with one vector kept in flight
         if (r0 >= r1) return;
         u32x4 q_next = load_round(x_row, r0);
-        for (int round = r0; round < r1; ++round) {
-            const u32x4 q = q_next;
-            if (round + 1 < r1) q_next = load_round(x_row, round + 1);
-            s.fast_round(q);
+        for (int round = r0; round < r1;) {
+            for (const int end = marks.stop(r1); round < end; ++round) {
+                const u32x4 q = q_next;
+                if (round + 1 < r1) q_next = load_round(x_row, round + 1);
+                s.fast_round(q);
+            }
+            marks.at(round, s);
         }
     };
     auto careful = [&](int round, bool prefix_open) {
@@ -47,14 +58,10 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
         s.careful_round(q, round, prefix_open);
     };
 
-    const int64_t nvec_total = (V + E - 1) / E;                      // the last vector may be partial
-    const int full_rounds = (int)((V / E) / kBlock);                 // rounds of 256 complete vectors
-    const int n_rounds = (int)((nvec_total + kBlock - 1) / kBlock);  // full_rounds or full_rounds + 1
-    const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;
-
     if (s.valid && round_t < full_rounds) {
         stream(0, round_t);
         careful(round_t, true);
+        marks.at(round_t + 1, s);
         stream(round_t + 1, full_rounds);
         if (n_rounds > full_rounds) careful(full_rounds, false);
     } else {
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
         if (n_rounds > full_rounds) careful(full_rounds, s.valid);
     }
     const int32_t above = s.total_above(lds_rank);
-    ipt_finish<DT>(b, ri, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), above, o, lds_f, lds_d, &lds_tok);
+    ipt_finish<DT, TOK>(b, ri, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), above, o, lds_f, lds_d, marks, &walk);
 }
 
 int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_hi, float *u,
@@ -72,10 +79,17 @@ int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_h
 {
     const dim3 grid((unsigned)b.N), block(kBlock);
     const IptOutputs o{dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags, logit_rank};
-    if (b.dtype == 0)
-        ipt_score_kernel<0><<<grid, block, 0, stream>>>(b, o);
-    else
-        ipt_score_kernel<1><<<grid, block, 0, stream>>>(b, o);
+    if (b.dtype == 0) {
+        if (ipt_token)
+            ipt_score_kernel<0, true><<<grid, block, 0, stream>>>(b, o);
+        else
+            ipt_score_kernel<0, false><<<grid, block, 0, stream>>>(b, o);
+    } else {
+        if (ipt_token)
+            ipt_score_kernel<1, true><<<grid, block, 0, stream>>>(b, o);
+        else
+            ipt_score_kernel<1, false><<<grid, block, 0, stream>>>(b, o);
+    }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

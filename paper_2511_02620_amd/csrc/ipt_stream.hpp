@@ -86,6 +86,146 @@ __device__ double gaussian_log_mass(double a, double b, double u, double sigma, 
     return log(mass + eps);
 }
 
+// Search for the honest sampler's token, min { v : C_v > u }, after the streaming pass.
+//
+// Marks.  While the row is streamed every thread leaves its running sum Z, with the exponent it is taken against, in LDS
+// after each 1/kMarks of the full rounds (its own slots: no barrier).  Once the total is known, the sums at the marks say in
+// which stretch the CDF passes u Z, and only that stretch is read again.  What bounds the search is that second read and the
+// latency of its dependent steps: walking the CDF from the row's start, one round and two barriers at a time, made a call on
+// 2048 rows of 151,936 bf16 logits without claims take 227 us; with the marks, and up to 16 rounds (four loads in flight)
+// between two barriers, it takes 136.  Six marks: 19 KB of LDS, eight workgroups to a compute unit; four (longer stretches)
+// 142 us, eight (six workgroups) 139.
+constexpr int kMarks = 6;
+constexpr int kWalkRounds = 16;  // rounds summed between two barriers of the walk: 16 x 4 wave sums, one per lane
+static_assert(kWalkRounds * kWaves == 64, "the walk scans one wave sum per lane");
+
+template <bool TOK>
+struct IptMarks {
+    double (*Z)[kBlock];   // [kMarks][kBlock]
+    float (*ref)[kBlock];  // [kMarks][kBlock]
+    int len, next, n;      // rounds between marks, round of the next one, marks left so far (uniform over the workgroup)
+
+    __device__ __forceinline__ IptMarks(double (*Z_)[kBlock], float (*ref_)[kBlock], int full_rounds)
+        : Z(Z_), ref(ref_), len((full_rounds + kMarks - 1) / kMarks), next(len), n(0)
+    {
+        if (len == 0) next = 0x7FFFFFFF;
+    }
+    __device__ __forceinline__ int stop(int r_end) const { return TOK ? min(r_end, next) : r_end; }
+    // `round` rounds of the row have been summed
+    template <class Stream>
+    __device__ __forceinline__ void at(int round, const Stream &s)
+    {
+        if (TOK && round == next) {  // (n < kMarks: kMarks * len >= full_rounds, and no full round follows the last mark)
+            Z[n][threadIdx.x] = s.Z;
+            ref[n][threadIdx.x] = s.ref();
+            ++n;
+            next = n < kMarks ? next + len : 0x7FFFFFFF;
+        }
+    }
+};
+
+// LDS of the search (of one workgroup).
+struct WalkScratch {
+    double mark_sum[kMarks][kWaves];
+    double round_sum[kWalkRounds * kWaves];
+    int32_t tok;
+};
+
+// All 256 threads: the token at which the CDF of the entries of rounds r0, r0 + 1, ... passes `target`; `before` is the mass of
+// the rounds below r0, terms are 2^(x c + neg_Mc).  -1 if it is not passed before the end of the row.  The wave sums of up to
+// kWalkRounds rounds are formed between two barriers, one scan over them finds the 512 entries that hold the token, and their
+// wave finds it.
+template <int DT>
+__device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row, int64_t V, float c, float neg_Mc, int r0,
+                                            double before, double target, WalkScratch &w)
+{
+    constexpr int E = Elem<DT>::kPerVec;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_rounds = (int)(((V + E - 1) / E + kBlock - 1) / kBlock);
+    if (tid == 0) w.tok = -1;
+    const int full_rounds = (int)((V / E) / kBlock);
+    const uint32_t ninf = DT == 0 ? 0xFF80FF80u : 0xFF800000u;
+    const u32x4 masked = u32x4{ninf, ninf, ninf, ninf};  // no mass
+    auto terms = [&](u32x4 q, float (&e)[E]) {
+        float x[E];
+        unpack_vector<DT>(q, x);
+#pragma unroll
+        for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
+        return (double)tree_sum<E>(e);
+    };
+    for (; r0 < n_rounds; r0 += kWalkRounds) {
+        const int nr = min(kWalkRounds, n_rounds - r0);
+        __syncthreads();  // (the scan of the batch before has been read; w.tok is set)
+        for (int k0 = 0; k0 < nr; k0 += 4) {
+            u32x4 q[4];
+            if (k0 + 4 <= nr && r0 + k0 + 4 <= full_rounds) {  // uniform: four loads in flight
+#pragma unroll
+                for (int i = 0; i < 4; ++i) q[i] = load_round(x_row, r0 + k0 + i);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t base = ((int64_t)(r0 + k0 + i) * kBlock + tid) * E;
+                    q[i] = k0 + i < nr && base < V ? load_vector<DT>(x_row, base, V) : masked;
+                }
+            }
+            double ls[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float e[E];
+                ls[i] = terms(q[i], e);
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) ls[i] += __shfl_xor(ls[i], off, 64);
+            if (lane < 4) w.round_sum[(k0 + lane) * kWaves + wave] = lane == 0 ? ls[0] : (lane == 1 ? ls[1] : (lane == 2 ? ls[2] : ls[3]));
+        }
+        __syncthreads();
+        const double mine = lane < nr * kWaves ? w.round_sum[lane] : 0.0;
+        double incl = mine;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double o = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += o;
+        }
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(before + incl > target);  // the same in every wave
+        if (hit != 0ull) {
+            const int f = __builtin_ctzll(hit);
+            if (wave == f % kWaves) {
+                const double start = before + __shfl(incl - mine, f, 64);  // mass below the wave's 64 vectors
+                const int64_t base = ((int64_t)(r0 + f / kWaves) * kBlock + tid) * E;
+                float e[E];
+                const double ls = terms(base < V ? load_vector<DT>(x_row, base, V) : masked, e);
+                double in = ls;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const double o = __shfl_up(in, off, 64);
+                    if (lane >= off) in += o;
+                }
+                const uint64_t over = __builtin_amdgcn_ballot_w64(ls > 0.0 && start + in > target);
+                const uint64_t mass = __builtin_amdgcn_ballot_w64(ls > 0.0);
+                // (the two sums of the same terms may round apart: then the last vector with any mass)
+                const int l = over != 0ull ? __builtin_ctzll(over) : (mass != 0ull ? 63 - __builtin_clzll(mass) : 0);
+                if (lane == l) {
+                    double cacc = start + (in - ls);
+                    int32_t found = -1;
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        cacc += (double)e[j];
+                        if (found < 0 && cacc > target) found = (int32_t)(base + j);
+                    }
+                    if (found < 0) found = (int32_t)((base + E - 1 < V) ? base + E - 1 : V - 1);
+                    w.tok = found;
+                }
+            }
+            __syncthreads();
+            return w.tok;
+        }
+        before += __shfl(incl, 63, 64);
+    }
+    return -1;
+}
+
 // Everything after the streaming pass: combine the 256 partial (max, sum) pairs, regenerate u,
 // form the interval and the distance, optionally search the honest sampler's token, write outputs.
 struct IptOutputs {
@@ -97,13 +237,12 @@ struct IptOutputs {
     int32_t *logit_rank;
 };
 
-template <int DT>
+template <int DT, bool TOK>
 __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
                                            const typename Elem<DT>::type *x_row, float c, float ref, double Z,
                                            double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
-                                           double *lds_d, int32_t *lds_tok)
+                                           double *lds_d, const IptMarks<TOK> &marks, WalkScratch *walk)
 {
-    constexpr int E = Elem<DT>::kPerVec;
     const int tid = threadIdx.x;
     const float nan = __builtin_nanf("");
     const float ninf = -__builtin_inff();
@@ -154,47 +293,26 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
     if (match) f |= kFlagMatch;
 
     int32_t tok = match ? (int32_t)t : -1;
-    if (o.ipt_token != nullptr && !match && !bad) {
-        // Second pass: walk the CDF in token order until it exceeds u * Z.
+    if (TOK && !match && !bad) {  // uniform
         f |= kFlagSlowPath;
         const double target = (double)u * Ztot;
-        double before = 0.0;  // mass of all entries before the current step
-        if (tid == 0) *lds_tok = -1;
-        __syncthreads();
-        for (int64_t step0 = 0; step0 < V; step0 += (int64_t)kBlock * E) {
-            const int64_t base = step0 + (int64_t)tid * E;
-            float e[E];
-            if (base < V) {
-                float x[E];
-                unpack_vector<DT>(load_vector<DT>(x_row, base, V), x);
+        for (int k = 0; k < marks.n; ++k) {
+            double v = marks.Z[k][tid] * (double)fast_exp2(marks.ref[k][tid] - M);
 #pragma unroll
-                for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
-            } else {
-#pragma unroll
-                for (int j = 0; j < E; ++j) e[j] = 0.0f;
-            }
-            const double ls = (double)tree_sum<E>(e);
-            double total;
-            const double incl = block_inclusive_scan(ls, lds_d, total);
-            if (before + total > target) {  // uniform: the token is inside this step
-                const double excl = before + (incl - ls);
-                if (excl <= target && before + incl > target) {  // exactly one thread
-                    double cacc = excl;
-                    int32_t found = -1;
-#pragma unroll
-                    for (int j = 0; j < E; ++j) {
-                        cacc += (double)e[j];
-                        if (found < 0 && cacc > target) found = (int32_t)(base + j);
-                    }
-                    if (found < 0) found = (int32_t)((base + E - 1 < V) ? base + E - 1 : V - 1);
-                    *lds_tok = found;
-                }
-                break;
-            }
-            before += total;
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            if ((tid & 63) == 0) walk->mark_sum[k][tid >> 6] = v;
         }
         __syncthreads();
-        tok = *lds_tok;
+        // the last mark at which the CDF has not passed u yet
+        double before = 0.0;
+        int r0 = 0;
+        for (int k = 0; k < marks.n; ++k) {
+            const double v = walk->mark_sum[k][0] + walk->mark_sum[k][1] + walk->mark_sum[k][2] + walk->mark_sum[k][3];
+            if (v > target) break;
+            before = v;
+            r0 = (k + 1) * marks.len;
+        }
+        tok = ipt_walk<DT>(x_row, V, c, neg_Mc, r0, before, target, *walk);
         if (tok < 0) tok = (int32_t)(V - 1);  // u * Z at or beyond the accumulated total
     }
 
@@ -203,7 +321,7 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
         if (o.cdf_lo) o.cdf_lo[row] = a;
         if (o.cdf_hi) o.cdf_hi[row] = bb;
         if (o.u) o.u[row] = u;
-        if (o.ipt_token) o.ipt_token[row] = bad ? -1 : tok;
+        if (TOK) o.ipt_token[row] = bad ? -1 : tok;
         if (o.log_mass)
             o.log_mass[row] =
                 (valid && !bad) ? (float)gaussian_log_mass(ad, bd, (double)u, o.sigma, o.eps) : nan;
