@@ -191,6 +191,41 @@ int difr_score_both_peaked(const difr_rows *in, const int32_t *claimed_ipt, floa
                            float *log_mass, uint8_t *flags_ipt, void *hip_stream);
 
 /*
+ * Small batches.  The calls above give every row one workgroup, which leaves most of the device idle when there are few rows.
+ * difr_score_split shares each row among several workgroups and merges their partial results, which live in a workspace of the
+ * caller; difr_split_workspace_bytes (host only, no device needed) says how large it has to be, or 0 if the batch fills the
+ * device by its rows (or is not valid): use the call above that has the outputs then.  want_admissible != 0: with room for
+ * what `count` needs.
+ *
+ * Outputs, by pointer: the Token-DiFR side if margin is not NULL (argmax and flags_gumbel then required), the Token-IPT-DiFR
+ * side if dist is not NULL (flags_ipt then required), the admissible set's size if count is not NULL (both sides then
+ * required, no optional output but log2_count, rows aligned to 16 bytes); meaning, layout and optionality as in
+ * difr_gumbel_score, difr_ipt_score and difr_score_both_admissible.  The Token-DiFR outputs and the counts equal those
+ * calls' bit for bit (and a count is never -1); the Token-IPT-DiFR sums are formed in another order, equal to fp32 rounding.
+ * in->claimed are the Token-DiFR claims, claimed_ipt the Token-IPT-DiFR ones.  The workspace is 8-byte aligned, needs no
+ * initial contents and may be reused once the call's work is done.
+ */
+typedef struct difr_scores {
+    float *margin;
+    int32_t *argmax;
+    float *max_score, *claimed_score;
+    uint8_t *flags_gumbel;
+    int32_t *rank_gumbel;
+    float *dist, *cdf_lo, *cdf_hi, *u;
+    int32_t *ipt_token;
+    double sigma, eps;
+    float *log_mass;
+    uint8_t *flags_ipt;
+    int32_t *rank_ipt;
+    float delta;
+    int32_t *count;
+    float *log2_count;
+} difr_scores;
+size_t difr_split_workspace_bytes(int64_t N, int64_t V, int32_t dtype, int32_t want_admissible);
+int difr_score_split(const difr_rows *in, const int32_t *claimed_ipt, const difr_scores *out, void *workspace,
+                     size_t workspace_bytes, void *hip_stream);
+
+/*
  * Token-IPT-DiFR on the distribution a filtering sampler used.  [Sec. 3.2: the IPT sampler applied under the
  * generation policy's top-k / top-p filter; Sec. 6.2 and the appendix "convolved Gaussian score", whose input p is
  * the probabilities the sampler actually used.]  The kept set K is a prefix of the tokens ranked by logit (ties to

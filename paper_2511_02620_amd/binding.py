@@ -71,12 +71,20 @@ class _LmHead(C.Structure):
     ]
 
 
+class _Scores(C.Structure):
+    _fields_ = [("margin", C.c_void_p), ("argmax", C.c_void_p), ("max_score", C.c_void_p), ("claimed_score", C.c_void_p),
+                ("flags_gumbel", C.c_void_p), ("rank_gumbel", C.c_void_p), ("dist", C.c_void_p), ("cdf_lo", C.c_void_p),
+                ("cdf_hi", C.c_void_p), ("u", C.c_void_p), ("ipt_token", C.c_void_p), ("sigma", C.c_double),
+                ("eps", C.c_double), ("log_mass", C.c_void_p), ("flags_ipt", C.c_void_p), ("rank_ipt", C.c_void_p),
+                ("delta", C.c_float), ("count", C.c_void_p), ("log2_count", C.c_void_p)]
+
+
 class _LikelihoodParams(C.Structure):
     _fields_ = [("top_k", C.c_int32), ("top_p", C.c_float), ("s", C.c_int32), ("sigma", C.c_float),
                 ("M", C.c_int32), ("z", C.c_void_p)]
 
 
-EXPORTS = ("difr_gumbel_score", "difr_debug_gumbel_score_unfiltered", "difr_ipt_score", "difr_score_both", "difr_score_both_peaked", "difr_score_both_admissible", "difr_admissible_count", "difr_gumbel_likelihood", "difr_ipt_score_filtered", "difr_score_both_filtered", "difr_lmhead_score", "difr_lmhead_score_static", "difr_lmhead_workspace_bytes", "difr_classify", "difr_seq_reduce", "difr_debug_noise", "difr_debug_gumbel_map",
+EXPORTS = ("difr_gumbel_score", "difr_debug_gumbel_score_unfiltered", "difr_ipt_score", "difr_score_both", "difr_score_both_peaked", "difr_score_both_admissible", "difr_admissible_count", "difr_gumbel_likelihood", "difr_ipt_score_filtered", "difr_score_both_filtered", "difr_lmhead_score", "difr_lmhead_score_static", "difr_lmhead_workspace_bytes", "difr_split_workspace_bytes", "difr_score_split", "difr_classify", "difr_seq_reduce", "difr_debug_noise", "difr_debug_gumbel_map",
            "difr_philox4x32_10", "difr_status_string", "difr_version")
 
 
@@ -121,6 +129,10 @@ def load_library():
     lib.difr_lmhead_score.restype = C.c_int
     lib.difr_lmhead_score_static.argtypes = [C.POINTER(_LmHead)] + [vp] * 10 + [C.c_double, C.c_double, vp, vp, vp]
     lib.difr_lmhead_score_static.restype = C.c_int
+    lib.difr_split_workspace_bytes.argtypes = [C.c_int64, C.c_int64, C.c_int32, C.c_int32]
+    lib.difr_split_workspace_bytes.restype = C.c_size_t
+    lib.difr_score_split.argtypes = [C.POINTER(_Rows), vp, C.POINTER(_Scores), vp, C.c_size_t, vp]
+    lib.difr_score_split.restype = C.c_int
     lib.difr_classify.argtypes = [vp, vp, C.c_int64, C.c_float, C.c_int64, C.c_int64, vp, vp, vp, vp]
     lib.difr_classify.restype = C.c_int
     lib.difr_ipt_score.restype = C.c_int

@@ -398,6 +398,45 @@ int difr_score_both_admissible(const difr_rows *in, const int32_t *claimed_ipt, 
                : DIFR_OK;
 }
 
+size_t difr_split_workspace_bytes(int64_t N, int64_t V, int32_t dtype, int32_t want_admissible)
+{
+    const int parts = difr::split_parts(N, V, dtype);
+    return parts < 2 ? 0 : difr::split_workspace_bytes(N, parts, want_admissible != 0);
+}
+
+int difr_score_split(const difr_rows *in, const int32_t *claimed_ipt, const difr_scores *out, void *workspace,
+                     size_t workspace_bytes, void *hip_stream)
+{
+    difr::RowBatch b;
+    bool aligned = false;
+    int rc = validate_rows(in, &b, &aligned);
+    if (rc != DIFR_OK) return rc;
+    if (!out) return DIFR_ERR_NULL;
+    if (out->log_mass && (!(out->sigma > 0.0) || !isfinite(out->sigma) || !(out->eps >= 0.0) || !isfinite(out->eps)))
+        return DIFR_ERR_ARGUMENT;
+    if (out->count && (!(out->delta >= 0.0f) || !isfinite(out->delta))) return DIFR_ERR_ARGUMENT;
+    if (b.N == 0) return DIFR_OK;
+    if (!out->margin && !out->dist) return DIFR_ERR_NULL;
+    if (out->margin && (!out->argmax || !out->flags_gumbel)) return DIFR_ERR_NULL;
+    if (out->dist && !out->flags_ipt) return DIFR_ERR_NULL;
+    if (out->count) {
+        if (!out->margin || !out->dist) return DIFR_ERR_NULL;
+        if (out->rank_gumbel || out->rank_ipt || out->ipt_token || out->log_mass) return DIFR_ERR_ARGUMENT;
+        if (!aligned) return DIFR_ERR_ALIGN;
+    }
+    if (out->margin && out->dist && out->rank_ipt) return DIFR_ERR_ARGUMENT;  // the pair has the Token-DiFR claim's rank only
+    const int parts = difr::split_parts(b.N, b.V, b.dtype);
+    if (parts < 2 || workspace_bytes < difr::split_workspace_bytes(b.N, parts, out->count != nullptr)) return DIFR_ERR_SHAPE;
+    if (!workspace) return DIFR_ERR_NULL;
+    if ((uintptr_t)workspace % 8u) return DIFR_ERR_ALIGN;
+    if ((rc = check_device()) != DIFR_OK) return rc;
+    const difr::GumbelOutputs og{out->margin, out->argmax, out->max_score, out->claimed_score, out->flags_gumbel, out->rank_gumbel};
+    const difr::IptOutputs oi{out->dist, out->cdf_lo, out->cdf_hi, out->u, out->ipt_token, out->sigma, out->eps, out->log_mass,
+                              out->flags_ipt, out->rank_ipt};
+    const difr::AdmissibleOutputs oa{out->delta, out->count, out->log2_count};
+    return difr::launch_score_split(b, claimed_ipt, og, oi, oa, workspace, parts, (hipStream_t)hip_stream) ? DIFR_ERR_LAUNCH : DIFR_OK;
+}
+
 int difr_classify(const float *scores, const int32_t *ranks, int64_t N, float tau, int64_t rank_cutoff, int64_t V,
                   const float *log2_admissible, uint8_t *cls, float *bits, void *hip_stream)
 {

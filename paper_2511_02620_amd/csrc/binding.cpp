@@ -34,6 +34,8 @@ namespace {
     X(difr_gumbel_likelihood)                                                                                           \
     X(difr_score_both_filtered)                                                                                         \
     X(difr_admissible_count)                                                                                            \
+    X(difr_split_workspace_bytes)                                                                                       \
+    X(difr_score_split)                                                                                                 \
     X(difr_lmhead_workspace_bytes)                                                                                      \
     X(difr_lmhead_score)                                                                                                \
     X(difr_seq_reduce)                                                                                                  \
@@ -174,6 +176,18 @@ PyObject *three(int rc, Outputs &a, Outputs &b, Outputs &c)
     return rc ? PyLong_FromLong(rc) : PyTuple_Pack(3, a.dict.get(), b.dict.get(), c.dict.get());
 }
 
+// A small batch goes through difr_score_split, with a workspace from torch's allocator that belongs to the call's stream.
+// Returns whether it did; the outputs are those of the call in `o`.
+bool split(const Rows &r, const int32_t *claimed_ipt, const difr_scores &o, int *rc)
+{
+    const size_t need = lib.difr_split_workspace_bytes(r.in.N, r.in.V, r.in.dtype, o.count != nullptr);
+    if (need == 0) return false;
+    const at::Tensor ws = at::empty({(int64_t)need}, at::TensorOptions().dtype(at::kByte).device(r.dev));
+    void *p = ws.data_ptr();
+    *rc = enter(r.dev, [&](void *s) { return lib.difr_score_split(&r.in, claimed_ipt, &o, p, need, s); });
+    return true;
+}
+
 // ---- one function per entry point; arguments beyond the row arguments in the comment ----
 
 // claimed_gumbel side of a call that scores both estimators
@@ -208,6 +222,16 @@ struct IptSide {
     }
 };
 
+difr_scores both_sides(const GumbelSide &g, const IptSide &i, double sigma, double eps)
+{
+    difr_scores sc = {};
+    sc.margin = g.margin, sc.argmax = g.argmax, sc.max_score = g.max_score, sc.claimed_score = g.claimed_score;
+    sc.flags_gumbel = g.flags, sc.rank_gumbel = g.rank;
+    sc.dist = i.dist, sc.cdf_lo = i.cdf_lo, sc.cdf_hi = i.cdf_hi, sc.u = i.u, sc.ipt_token = i.token, sc.sigma = sigma, sc.eps = eps;
+    sc.log_mass = i.log_mass, sc.flags_ipt = i.flags;
+    return sc;
+}
+
 // rows, want_scores, unfiltered, want_rank
 PyObject *gumbel_score(PyObject *const *a)
 {
@@ -224,6 +248,11 @@ PyObject *gumbel_score(PyObject *const *a)
     }
     const auto entry = truth(a[1]) ? lib.difr_debug_gumbel_score_unfiltered : lib.difr_gumbel_score;
     int32_t *rank = truth(a[2]) ? o.i32(key::logit_rank, r.N) : nullptr;
+    int rc;
+    difr_scores sc = {};
+    sc.margin = margin, sc.argmax = argmax, sc.max_score = max_score, sc.claimed_score = claimed_score, sc.flags_gumbel = flags;
+    sc.rank_gumbel = rank;
+    if (entry == lib.difr_gumbel_score && split(r, nullptr, sc, &rc)) return one(rc, o);
     return one(enter(r.dev, [&](void *s) { return entry(&r.in, margin, argmax, max_score, claimed_score, flags, rank, s); }), o);
 }
 
@@ -245,6 +274,11 @@ PyObject *ipt_score(PyObject *const *a)
     int32_t *token = truth(a[0]) ? o.i32(key::ipt_token, r.N) : nullptr;
     float *log_mass = truth(a[1]) ? o.f32(key::log_mass, r.N) : nullptr;
     int32_t *rank = truth(a[5]) ? o.i32(key::logit_rank, r.N) : nullptr;
+    int rc;
+    difr_scores sc = {};
+    sc.dist = dist, sc.cdf_lo = cdf_lo, sc.cdf_hi = cdf_hi, sc.u = u, sc.ipt_token = token, sc.sigma = sigma, sc.eps = eps;
+    sc.log_mass = log_mass, sc.flags_ipt = flags, sc.rank_ipt = rank;
+    if (split(r, r.in.claimed, sc, &rc)) return one(rc, o);
     return one(enter(r.dev, [&](void *s) {
                    return lib.difr_ipt_score(&r.in, dist, cdf_lo, cdf_hi, u, token, sigma, eps, log_mass, flags, rank, s);
                }), o);
@@ -262,6 +296,8 @@ PyObject *score_both(PyObject *const *a)
     IptSide i(r.dev, r.N, false);
     if (truth(a[3])) i.token = i.out.i32(key::ipt_token, r.N);
     if (truth(a[4])) i.log_mass = i.out.f32(key::log_mass, r.N);
+    int rc;
+    if (split(r, ci, both_sides(g, i, sigma, eps), &rc)) return two(rc, g.out, i.out);
     return two(enter(r.dev, [&](void *s) {
                    return entry(&r.in, ci, g.margin, g.argmax, g.max_score, g.claimed_score, g.flags, g.rank, i.dist, i.cdf_lo,
                                 i.cdf_hi, i.u, i.token, sigma, eps, i.log_mass, i.flags, s);
@@ -280,6 +316,10 @@ PyObject *score_both_admissible(PyObject *const *a)
     Outputs o(r.dev);
     int32_t *count = o.i32(key::count, r.N);
     float *log2_count = o.f32(key::log2_count, r.N);
+    int rc;
+    difr_scores sc = both_sides(g, i, 0.0, 0.0);
+    sc.delta = delta, sc.count = count, sc.log2_count = log2_count;
+    if (split(r, ci, sc, &rc)) return three(rc, g.out, i.out, o);
     return three(enter(r.dev, [&](void *s) {
                      return lib.difr_score_both_admissible(&r.in, ci, delta, g.margin, g.argmax, g.max_score, g.claimed_score,
                                                            g.flags, i.dist, i.cdf_lo, i.cdf_hi, i.u, i.flags, count, log2_count, s);

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "difr_device.hpp"
@@ -23,6 +24,18 @@ struct GumbelOutputs;
 struct IptOutputs;
 // The bare nucleus (aligned rows only).
 int launch_ipt_nucleus(const RowBatch &b, float top_p, const IptOutputs &o, int32_t *kept, float *tau, hipStream_t stream);
+struct AdmissibleOutputs {
+    float delta;
+    int32_t *count;     // [N]; -1: not determined in one pass
+    float *log2_count;  // [N] or null
+};
+// How many workgroups share a row of a small batch (1: none, the batch fills the chip by its rows), the workspace that takes,
+// and the launch: the Token-DiFR side if og.margin, the Token-IPT-DiFR side if oi.dist, the admissible set (with both) if
+// oa.count.
+int split_parts(int64_t N, int64_t V, int dtype);
+size_t split_workspace_bytes(int64_t N, int parts, bool admissible);
+int launch_score_split(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
+                       const AdmissibleOutputs &oa, void *workspace, int parts, hipStream_t stream);
 // Both estimators in one pass.
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                       bool peaked, hipStream_t stream);

@@ -11,14 +11,9 @@
 #include "difr_host.hpp"
 #include "gumbel_stream.hpp"
 #include "ipt_stream.hpp"
+#include "row_stream.hpp"
 
 namespace difr {
-
-struct AdmissibleOutputs {
-    float delta;
-    int32_t *count;     // [N]; -1: not determined in one pass
-    float *log2_count;  // [N] or null
-};
 
 // With the rank count the body needs 97 registers, one too many for five waves per SIMD; asked for five it fits in 96
 // without spills and runs 5% faster.  The other variants ask for one wave, which is no constraint.
@@ -68,69 +63,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || 
         __syncthreads();
     }
 
-    const int64_t nvec = V / E;                                      // complete vectors
-    const int64_t nvec_total = (V + E - 1) / E;                      // the last vector may be partial
-    const int full_rounds = (int)(nvec / kBlock);                    // rounds of 256 complete vectors
-    const int n_rounds = (int)((nvec_total + kBlock - 1) / kBlock);  // full_rounds or full_rounds + 1
-    const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;    // round holding the IPT claim
+    const int full_rounds = (int)((V / E) / kBlock);  // rounds of 256 complete vectors
     IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
-    // Full rounds [round, r_end): Gumbel gates + IPT accumulation on the same vector.  The loop body is
-    // instantiated once per Gumbel gate mode; a change of mode leaves the inner loop.
-    int round = 0;
-    auto run_rounds = [&](auto mode_tag, int r_end) {
-        constexpr int MODE = decltype(mode_tag)::value;
-        // one round; returns false when the loop must be left (end reached, or the gate changed mode)
-        auto body = [&](const u32x4 &q) {
-            g.template process<MODE>(q, round, true);
-            s.fast_round(q);
-            ++round;
-            if ((round & 15) == 0) g.pickup();
-            return round < r_end && g.gate.mode == MODE;
-        };
-        // one vector is kept in flight; two copies of the body, so that the vector being loaded and the one
-        // being used simply swap roles instead of being copied from register to register every round
-        u32x4 qa = load_round(x_row, round), qb = qa;
-        while (true) {
-            if (round + 1 < r_end) qb = load_round(x_row, round + 1);
-            if (!body(qa)) break;
-            if (round + 1 < r_end) qa = load_round(x_row, round + 1);
-            if (!body(qb)) break;
-        }
-    };
-    auto run_to = [&](int r_end) {
-        while (round < r_end) {
-            const int stop = marks.stop(r_end);
-            if (g.gate.mode == 0)
-                run_rounds(std::integral_constant<int, 0>(), stop);
-            else if (g.gate.mode == 1)
-                run_rounds(std::integral_constant<int, 1>(), stop);
-            else
-                run_rounds(std::integral_constant<int, 2>(), stop);
-            marks.at(round, s);
-        }
-    };
-    // a round in which the IPT stream must look at indices (it holds the claimed token, or it is ragged)
-    auto careful = [&](int r, bool prefix_open) {
-        u32x4 q = u32x4{0u, 0u, 0u, 0u};
-        if (s.has_vector(r)) q = load_vector<DT>(x_row, ((int64_t)r * kBlock + tid) * E, V);
-        g.process_any(q, r, (int64_t)r * kBlock + tid < nvec);
-        s.careful_round(q, r, prefix_open);
-    };
-
-    if (s.valid && round_t < full_rounds) {
-        run_to(round_t);
-        careful(round_t, true);
-        round = round_t + 1;
-        marks.at(round, s);
-        run_to(full_rounds);
-        if (n_rounds > full_rounds) careful(full_rounds, false);
-    } else {
-        run_to(full_rounds);
-        if (s.valid) s.snapshot();  // everything so far lies below the IPT claim
-        if (n_rounds > full_rounds) careful(full_rounds, s.valid);
-    }
-    g.tail();
+    stream_rounds<DT, TOK>(g, s, marks, x_row, V, 0, full_rounds, true);
     g.finish(row, og, lds_y, lds_i, lds_rank);
     if (ADM) {
         const float M = g.best_y;  // the row maximum, in every thread

@@ -170,67 +170,30 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_filtered_kernel(RowBatch 
 
 // Size of the admissible set of each row (Sec. 7: A_t(tau) = tokens whose score passes the threshold; here
 // the score is the margin, so A_t = { v : max_score - y_v <= delta }).  Second pass over the row with the
-// row maximum known: the same exact pre-filter with the fixed bound M - delta, and a count instead of an
-// argmax.
+// row maximum known.
 template <int DT>
 __global__ __launch_bounds__(kBlock) void admissible_count_kernel(RowBatch b, const float *__restrict__ max_score,
                                                                   float delta, int32_t *__restrict__ count,
                                                                   float *__restrict__ log2_count)
 {
     typedef typename Elem<DT>::type elt_t;
-    constexpr int E = Elem<DT>::kPerVec;
     __shared__ float lds_L[kWaves];
     __shared__ int32_t lds_c[kWaves];
     const int64_t row = blockIdx.x;
     RowInfo ri = load_row_info(b, row);
     ri.claimed = -1;
-    const int tid = threadIdx.x;
     const float M = max_score[row];
     const float nan = __builtin_nanf("");
     if (!ri.seq_ok || !ri.temp_ok || !(M == M) || !(fabsf(M) < __builtin_inff())) {  // uniform over the workgroup
-        if (tid == 0) {
+        if (threadIdx.x == 0) {
             count[row] = 0;
             if (log2_count) log2_count[row] = nan;
         }
         return;
     }
     const elt_t *x_row = reinterpret_cast<const elt_t *>(b.logits) + row * b.ld;
-    const int64_t V = b.V;
-    GumbelStream<DT, false, true> g(ri, x_row, V, lds_L);
-    __syncthreads();
-    g.arm_count(M, delta);
-    __syncthreads();
-    const int64_t nvec = V / E;
-    const int n_main = (int)(nvec / kBlock);
-    int round = 0;
-    auto run_rounds = [&](auto mode_tag) {  // the bound never moves, so neither does the gate mode
-        constexpr int MODE = decltype(mode_tag)::value;
-        u32x4 q_next = load_round(x_row, round);
-        while (round < n_main) {
-            const u32x4 q = q_next;
-            if (round + 1 < n_main) q_next = load_round(x_row, round + 1);
-            g.template process<MODE>(q, round, true);
-            ++round;
-        }
-    };
-    if (n_main > 0) {
-        if (g.gate.mode == 0)
-            run_rounds(std::integral_constant<int, 0>());
-        else if (g.gate.mode == 1)
-            run_rounds(std::integral_constant<int, 1>());
-        else
-            run_rounds(std::integral_constant<int, 2>());
-    }
-    if ((int64_t)n_main * kBlock < nvec) {
-        const bool active = (int64_t)n_main * kBlock + tid < nvec;
-        u32x4 q = u32x4{0u, 0u, 0u, 0u};
-        if (active) q = load_round(x_row, n_main);
-        g.process_any(q, n_main, active);
-    }
-    g.tail();
-    int32_t c = (int32_t)g.count;
-    c = block_sum_i32(c, lds_c);
-    if (tid == 0) {
+    const int32_t c = admissible_count_row<DT>(ri, x_row, b.V, M, delta, lds_L, lds_c);
+    if (threadIdx.x == 0) {
         count[row] = c;
         if (log2_count) log2_count[row] = c > 0 ? __log2f((float)c) : nan;
     }

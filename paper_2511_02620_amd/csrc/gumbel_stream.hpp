@@ -124,6 +124,27 @@ __device__ __forceinline__ bool gumbel_row_rejected(const RowInfo &ri, int64_t r
     return true;
 }
 
+// Outputs of a row from its best score; one thread.
+__device__ __forceinline__ void gumbel_write(int64_t row, const GumbelOutputs &o, int32_t t, bool valid, float yt, float best_y,
+                                             int32_t best_v, bool any_bad, bool rank, int32_t above)
+{
+    if (rank) o.logit_rank[row] = valid ? above : -1;
+    if (best_v == 0x7FFFFFFF) best_v = 0;  // every entry masked: all scores are -inf
+    uint32_t f = any_bad ? kFlagNonfinite : 0u;
+    float mg = __builtin_nanf("");
+    if (valid) {
+        mg = best_y - yt;
+        if (best_v == t) f |= kFlagMatch;
+    } else {
+        f |= kFlagInvalidClaim;
+    }
+    o.margin[row] = mg;
+    o.argmax[row] = best_v;
+    if (o.max_score) o.max_score[row] = best_y;
+    if (o.claimed_score) o.claimed_score[row] = yt;
+    o.flags[row] = (uint8_t)f;
+}
+
 // RANK: also count the entries whose raw logit exceeds the claimed token's (logit rank, Sec. 7.1).
 // For bf16 the count works on the raw bit patterns, two per dword, without unpacking: for a claimed
 // logit >= +0 "x > x_t" is "bits > bits(x_t)" as signed 16-bit, for a negative one it is
@@ -641,32 +662,72 @@ struct GumbelStream {
                 __builtin_amdgcn_ballot_w64(v < V && Elem<DT>::to_float(x_row[v < V ? v : 0]) > xt));
     }
 
+    // block reduction: afterwards best_y / best_v are the row's in every thread, and in thread 0 the result holds
+    // whether a NaN or +inf was seen and (RANK) the number of entries above the claim
+    struct Reduced {
+        int any_bad;
+        int32_t above;
+    };
+    __device__ __forceinline__ Reduced reduce(float *lds_y, int32_t *lds_i, int32_t *lds_rank)
+    {
+        block_argmax(best_y, best_v, lds_y, lds_i);
+        if (RANK && (tid & 63) == 0) lds_rank[wave] = (int32_t)above;
+        Reduced r;
+        r.any_bad = __syncthreads_or((int)bad);
+        r.above = RANK && tid == 0 ? lds_rank[0] + lds_rank[1] + lds_rank[2] + lds_rank[3] : 0;
+        return r;
+    }
+
     // block reduction and outputs
     __device__ __forceinline__ void finish(int64_t row, const GumbelOutputs &o, float *lds_y, int32_t *lds_i,
                                            int32_t *lds_rank)
     {
-        block_argmax(best_y, best_v, lds_y, lds_i);
-        if (RANK && (tid & 63) == 0) lds_rank[wave] = (int32_t)above;
-        const int any_bad = __syncthreads_or((int)bad);
-        if (tid == 0) {
-            const float nan = __builtin_nanf("");
-            if (RANK) o.logit_rank[row] = valid ? lds_rank[0] + lds_rank[1] + lds_rank[2] + lds_rank[3] : -1;
-            if (best_v == 0x7FFFFFFF) best_v = 0;  // every entry masked: all scores are -inf
-            uint32_t f = any_bad ? kFlagNonfinite : 0u;
-            float mg = nan;
-            if (valid) {
-                mg = best_y - yt;
-                if (best_v == t) f |= kFlagMatch;
-            } else {
-                f |= kFlagInvalidClaim;
-            }
-            o.margin[row] = mg;
-            o.argmax[row] = best_v;
-            if (o.max_score) o.max_score[row] = best_y;
-            if (o.claimed_score) o.claimed_score[row] = yt;
-            o.flags[row] = (uint8_t)f;
-        }
+        const Reduced r = reduce(lds_y, lds_i, lds_rank);
+        if (tid == 0) gumbel_write(row, o, t, valid, yt, best_y, best_v, r.any_bad != 0, RANK, r.above);
     }
 };
+
+// Size of the admissible set of a row whose maximum M is known (all 256 threads): the same exact pre-filter with the
+// fixed bound M - delta, and a count instead of an argmax.  ri.claimed must be -1.
+template <int DT>
+__device__ __forceinline__ int32_t admissible_count_row(const RowInfo &ri, const typename Elem<DT>::type *x_row, int64_t V, float M,
+                                                        float delta, float *lds_L, int32_t *lds_c)
+{
+    constexpr int E = Elem<DT>::kPerVec;
+    const int tid = threadIdx.x;
+    GumbelStream<DT, false, true> g(ri, x_row, V, lds_L);
+    __syncthreads();
+    g.arm_count(M, delta);
+    __syncthreads();
+    const int64_t nvec = V / E;
+    const int n_main = (int)(nvec / kBlock);
+    int round = 0;
+    auto run_rounds = [&](auto mode_tag) {  // the bound never moves, so neither does the gate mode
+        constexpr int MODE = decltype(mode_tag)::value;
+        u32x4 q_next = load_round(x_row, round);
+        while (round < n_main) {
+            const u32x4 q = q_next;
+            if (round + 1 < n_main) q_next = load_round(x_row, round + 1);
+            g.template process<MODE>(q, round, true);
+            ++round;
+        }
+    };
+    if (n_main > 0) {
+        if (g.gate.mode == 0)
+            run_rounds(std::integral_constant<int, 0>());
+        else if (g.gate.mode == 1)
+            run_rounds(std::integral_constant<int, 1>());
+        else
+            run_rounds(std::integral_constant<int, 2>());
+    }
+    if ((int64_t)n_main * kBlock < nvec) {
+        const bool active = (int64_t)n_main * kBlock + tid < nvec;
+        u32x4 q = u32x4{0u, 0u, 0u, 0u};
+        if (active) q = load_round(x_row, n_main);
+        g.process_any(q, n_main, active);
+    }
+    g.tail();
+    return block_sum_i32((int32_t)g.count, lds_c);
+}
 
 }  // namespace difr

@@ -115,11 +115,13 @@ struct IptMarks {
     template <class Stream>
     __device__ __forceinline__ void at(int round, const Stream &s)
     {
-        if (TOK && round == next) {  // (n < kMarks: kMarks * len >= full_rounds, and no full round follows the last mark)
-            Z[n][threadIdx.x] = s.Z;
-            ref[n][threadIdx.x] = s.ref();
-            ++n;
-            next = n < kMarks ? next + len : 0x7FFFFFFF;
+        if constexpr (TOK) {
+            if (round == next) {  // (n < kMarks: kMarks * len >= full_rounds, and no full round follows the last mark)
+                Z[n][threadIdx.x] = s.Z;
+                ref[n][threadIdx.x] = s.ref();
+                ++n;
+                next = n < kMarks ? next + len : 0x7FFFFFFF;
+            }
         }
     }
 };
@@ -226,7 +228,7 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
     return -1;
 }
 
-// Everything after the streaming pass: combine the 256 partial (max, sum) pairs, regenerate u,
+// Everything after the streaming pass: combine the partial (reference, sum) pairs, regenerate u,
 // form the interval and the distance, optionally search the honest sampler's token, write outputs.
 struct IptOutputs {
     float *dist, *cdf_lo, *cdf_hi, *u;
@@ -237,32 +239,18 @@ struct IptOutputs {
     int32_t *logit_rank;
 };
 
-template <int DT, bool TOK>
-__device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
-                                           const typename Elem<DT>::type *x_row, float c, float ref, double Z,
-                                           double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
-                                           double *lds_d, const IptMarks<TOK> &marks, WalkScratch *walk)
+// Outputs of a row from its total mass Z and the mass P below the claim, both relative to the exponent M.  All 256 threads;
+// search(u Z): the token at which the CDF passes u, called (by all of them) only if it is asked for and the claim is not it.
+template <int DT, bool TOK, class Search>
+__device__ __forceinline__ void ipt_write(const RowBatch &b, const RowInfo &ri, int64_t row, const typename Elem<DT>::type *x_row,
+                                          float c, float M, double Ztot, double Ptot, int32_t above, const IptOutputs &o,
+                                          Search &&search)
 {
-    const int tid = threadIdx.x;
     const float nan = __builtin_nanf("");
     const float ninf = -__builtin_inff();
     const int64_t V = b.V;
     const int64_t t = ri.claimed;
     const bool valid = (t >= 0 && t < V);
-
-    // Combine the 256 partial (reference, sum) pairs in a fixed order.  `ref` is the exponent a thread's terms were
-    // taken against: they are 2^(x c - ref), with ref the ROUNDED product of the thread's reference logit and c.  The
-    // common reference is the largest of them, and a thread's scale is 2^(ref - M) from the difference of the two
-    // rounded numbers: forming it from the reference logits instead, as 2^((m - M) c), would be off by the rounding
-    // of m c - half a unit in its last place, 1e-5 when |m| / T runs into the hundreds, a different amount in every
-    // thread.
-    const float M = block_max(ref, lds_f);  // (-inf: every entry masked; +inf or NaN: a +inf or NaN logit)
-    const float neg_Mc = -M;
-    // a thread that saw only masked entries has ref = -inf and Z = 0: its scale is 2^-inf = 0
-    const double Zs = Z * (double)fast_exp2(ref - M);
-    const double Ps = (refP > ninf) ? P * (double)fast_exp2(refP - M) : 0.0;
-    const double Ztot = block_sum_f64(Zs, lds_d);
-    const double Ptot = block_sum_f64(Ps, lds_d);
 
     // Regenerated uniform: stream 1, vocabulary index 0.
     uint32_t r[4];
@@ -277,7 +265,7 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
     double ad = 0.0, bd = 0.0;
     bool match = false;
     if (valid && !bad) {
-        const double et = (double)fast_exp2(__fmaf_rn(Elem<DT>::to_float(x_row[t]), c, neg_Mc));
+        const double et = (double)fast_exp2(__fmaf_rn(Elem<DT>::to_float(x_row[t]), c, -M));
         const double ud = (double)u;
         ad = Ptot / Ztot;
         bd = (Ptot + et) / Ztot;
@@ -295,9 +283,59 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
     int32_t tok = match ? (int32_t)t : -1;
     if (TOK && !match && !bad) {  // uniform
         f |= kFlagSlowPath;
-        const double target = (double)u * Ztot;
+        tok = search((double)u * Ztot);
+        if (tok < 0) tok = (int32_t)(V - 1);  // u * Z at or beyond the accumulated total
+    }
+
+    if (threadIdx.x == 0) {
+        o.dist[row] = d;
+        if (o.cdf_lo) o.cdf_lo[row] = a;
+        if (o.cdf_hi) o.cdf_hi[row] = bb;
+        if (o.u) o.u[row] = u;
+        if (TOK) o.ipt_token[row] = bad ? -1 : tok;
+        if (o.log_mass)
+            o.log_mass[row] =
+                (valid && !bad) ? (float)gaussian_log_mass(ad, bd, (double)u, o.sigma, o.eps) : nan;
+        if (o.logit_rank) o.logit_rank[row] = valid ? above : -1;
+        o.flags[row] = (uint8_t)f;
+    }
+}
+
+// The sums of the 256 threads on a common reference.
+struct IptTotals {
+    float M;
+    double Z, P;
+};
+
+__device__ __forceinline__ IptTotals ipt_combine(float ref, double Z, double P, float refP, float *lds_f, double *lds_d)
+{
+    // Combine the 256 partial (reference, sum) pairs in a fixed order.  `ref` is the exponent a thread's terms were
+    // taken against, a whole number: they are 2^(x c - ref).  The common reference is the largest of them, and a thread's
+    // scale is the exact 2^(ref - M): forming it from the reference logits instead, as 2^((m - M) c), would be off by the
+    // rounding of m c - half a unit in its last place, 1e-5 when |m| / T runs into the hundreds, a different amount in
+    // every thread.
+    const float ninf = -__builtin_inff();
+    IptTotals t;
+    t.M = block_max(ref, lds_f);  // (-inf: every entry masked; +inf or NaN: a +inf or NaN logit)
+    // a thread that saw only masked entries has ref = -inf and Z = 0 (NaN: it saw a NaN), so does a part of a row
+    const double Zs = Z * (ref > ninf ? (double)fast_exp2(ref - t.M) : 0.0);
+    const double Ps = (refP > ninf) ? P * (double)fast_exp2(refP - t.M) : 0.0;
+    t.Z = block_sum_f64(Zs, lds_d);
+    t.P = block_sum_f64(Ps, lds_d);
+    return t;
+}
+
+template <int DT, bool TOK>
+__device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
+                                           const typename Elem<DT>::type *x_row, float c, float ref, double Z,
+                                           double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
+                                           double *lds_d, const IptMarks<TOK> &marks, WalkScratch *walk)
+{
+    const IptTotals t = ipt_combine(ref, Z, P, refP, lds_f, lds_d);
+    ipt_write<DT, TOK>(b, ri, row, x_row, c, t.M, t.Z, t.P, above, o, [&](double target) {
+        const int tid = threadIdx.x;
         for (int k = 0; k < marks.n; ++k) {
-            double v = marks.Z[k][tid] * (double)fast_exp2(marks.ref[k][tid] - M);
+            double v = marks.Z[k][tid] * (double)fast_exp2(marks.ref[k][tid] - t.M);
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
             if ((tid & 63) == 0) walk->mark_sum[k][tid >> 6] = v;
@@ -312,22 +350,8 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
             before = v;
             r0 = (k + 1) * marks.len;
         }
-        tok = ipt_walk<DT>(x_row, V, c, neg_Mc, r0, before, target, *walk);
-        if (tok < 0) tok = (int32_t)(V - 1);  // u * Z at or beyond the accumulated total
-    }
-
-    if (tid == 0) {
-        o.dist[row] = d;
-        if (o.cdf_lo) o.cdf_lo[row] = a;
-        if (o.cdf_hi) o.cdf_hi[row] = bb;
-        if (o.u) o.u[row] = u;
-        if (TOK) o.ipt_token[row] = bad ? -1 : tok;
-        if (o.log_mass)
-            o.log_mass[row] =
-                (valid && !bad) ? (float)gaussian_log_mass(ad, bd, (double)u, o.sigma, o.eps) : nan;
-        if (o.logit_rank) o.logit_rank[row] = valid ? above : -1;
-        o.flags[row] = (uint8_t)f;
-    }
+        return ipt_walk<DT>(x_row, b.V, c, -t.M, r0, before, target, *walk);
+    });
 }
 
 __device__ __forceinline__ bool ipt_row_rejected(const RowInfo &ri, int64_t row, const IptOutputs &o)
@@ -411,7 +435,9 @@ struct IptStream {
                     // half a unit in its last place, 1e-6 at 16 and beyond, and the entries that lie far above a
                     // lane's first vector - the few tokens that carry the mass of a peaked row - are the ones whose
                     // terms have to be exact; the many small ones below average their roundings out.
-                    const float moved = -(m8 * c + kRefLift);
+                    // A whole number, so that bringing sums taken against different references to a common one multiplies
+                    // them by exact powers of two (lanes, parts of a split row).
+                    const float moved = -(ceilf(m8 * c) + kRefLift);
                     Z *= (double)fast_exp2(moved - neg_mc);  // from the old rounded reference to the new one (see ipt_finish)
                     m = m8;
                     neg_mc = moved;

@@ -1,0 +1,135 @@
+"""Small batches, whose rows are shared by several workgroups, against the one-workgroup kernels (called through the C entry
+points): the Token-DiFR outputs, ranks and admissible counts bit for bit, the Token-IPT-DiFR sums - formed in another order - to
+2e-7 of the CDF (a few times the 1e-8 that either order is off by, and the fp32 rounding of a value below 1).  Around the
+smallest vocabulary that is shared, ragged ends, claims in the first and last part, rejected rows, masked parts, a NaN and a
++inf in a later part, and candidate lists that do not fit."""
+import ctypes as C
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def difr():
+    import paper_2511_02620_amd as m
+    m.load_library()
+    return m
+
+
+def _one_workgroup(difr, logits, T, seeds, sid, pos, cg, ci, delta):
+    """difr_score_both (every output) and difr_score_both_admissible through the C entry points."""
+    from paper_2511_02620_amd import binding as B
+    lib = difr.load_library()
+    r, N, dev = B._rows(logits, None, T, seeds, sid, pos, cg, None)
+    f, i32, u8 = (lambda dt: (lambda: torch.empty(N, dtype=dt, device=dev)))(torch.float32), lambda: torch.empty(
+        N, dtype=torch.int32, device=dev), lambda: torch.empty(N, dtype=torch.uint8, device=dev)
+    g = dict(margin=f(), argmax=i32(), max_score=f(), claimed_score=f(), flags=u8(), logit_rank=i32())
+    i = dict(dist=f(), cdf_lo=f(), cdf_hi=f(), u=f(), ipt_token=i32(), log_mass=f(), flags=u8())
+    p = lambda t: C.c_void_p(t.data_ptr())
+    st = B._stream_ptr(dev)
+    assert lib.difr_score_both(C.byref(r), p(ci), *[p(g[k]) for k in ("margin", "argmax", "max_score", "claimed_score", "flags",
+                                                                     "logit_rank")],
+                               *[p(i[k]) for k in ("dist", "cdf_lo", "cdf_hi", "u", "ipt_token")], 0.01, 1e-30,
+                               p(i["log_mass"]), p(i["flags"]), st) == 0
+    count = difr.admissible_count(logits, T, seeds, sid, pos, g["max_score"], delta)
+    return g, i, count
+
+
+def _same(a, b, what):
+    for k in a:
+        assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), (what, k)
+
+
+def _near(a, b, what):
+    for k in a:
+        x, y = a[k], b[k]
+        if k in ("u", "flags"):
+            assert torch.equal(x & ~9, y & ~9) if k == "flags" else torch.equal(x.view(torch.int32), y.view(torch.int32)), (what, k)
+        elif k in ("dist", "cdf_lo", "cdf_hi"):
+            assert torch.equal(x.isnan(), y.isnan()) and float((x - y).nan_to_num().abs().max()) <= 2e-7, (what, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V,N", [(49152, 3), (49153, 24), (65000, 130), (99991, 7), (151936, 24), (151936, 1)])
+def test_shared_rows_score_as_whole_rows(difr, dtype, V, N):
+    lib = difr.load_library()
+    assert lib.difr_split_workspace_bytes(N, V, 0 if dtype == torch.bfloat16 else 1, 0) > 0
+    g = torch.Generator().manual_seed(V + N)
+    S = min(N, 3)
+    x = torch.randn(N, V, generator=g) - 1.1 * torch.log1p(torch.randperm(V, generator=g).float())
+    if N >= 7:
+        x[1, : V // 2] = -float("inf")            # whole parts without mass
+        x[2, ::2] = -float("inf")
+        x[4, V - 5] = float("inf")
+        x[5] = -float("inf")
+        x[5, V - 1] = 0.5
+    per = 16 // torch.tensor([], dtype=dtype).element_size()
+    buf = torch.zeros(N, -(-V // per) * per, dtype=dtype)
+    buf[:, :V] = x.to(dtype)
+    if N >= 7:                                    # a NaN with its sign bit clear (one with it set counts as -inf)
+        buf.view(torch.int16 if per == 8 else torch.int32)[3, V - 2] = 0x7FC0 if per == 8 else 0x7FC00000
+    x = buf.to(DEV)[:, :V]
+    seeds = torch.randint(-2 ** 63, 2 ** 63 - 1, (S,), generator=g).to(DEV)
+    sid, pos = (torch.arange(N, dtype=torch.int32) % S).to(DEV), torch.arange(N, dtype=torch.int32).to(DEV)
+    if N >= 24:
+        sid[N - 1] = S
+    at = (0.9, seeds, sid, pos)
+    honest = difr.gumbel_score(x, *at)["argmax"].clamp(min=0)
+    cg = torch.where(torch.arange(N, device=DEV) % 2 == 0, honest, torch.randint(0, V, (N,), generator=g, dtype=torch.int32).to(DEV))
+    ci = torch.randint(0, V, (N,), generator=g, dtype=torch.int32).to(DEV)
+    ci[0] = 0
+    if N >= 7:
+        ci[1], ci[2], cg[3] = V - 1, -1, V
+    for delta in (2.5, 12.0):                     # (12: thousands of candidates, more than a part's list holds)
+        print("split", dtype, V, N, delta, flush=True)
+        want_g, want_i, want_c = _one_workgroup(difr, x, *at, cg, ci, delta)
+        ga, ia, ca = difr.score_both_admissible(x, *at, delta, cg, ci)
+        _same(ga, {k: want_g[k] for k in ga}, "admissible")
+        _near(ia, want_i, "admissible")
+        _same(ca, want_c, "admissible")
+    gb, ib = difr.score_both(x, *at, cg, ci, want_rank=True, want_token=True, want_log_mass=True)
+    _same(gb, want_g, "both")
+    _near(ib, want_i, "both")
+    _same({k: ia[k] for k in ia}, {k: ib[k] for k in ia if k != "flags"} | {"flags": ib["flags"] & ~8}, "admissible against both")
+    gs = difr.gumbel_score(x, *at, cg, want_rank=True)
+    _same(gs, gb, "gumbel")
+    si = difr.ipt_score(x, *at, ci, want_token=True, want_log_mass=True, want_rank=True)
+    ranks = difr.gumbel_score(x, *at, ci, want_rank=True)["logit_rank"]
+    clean = torch.arange(N, device=DEV) != (3 if N >= 7 else N)   # (bit patterns count a NaN as above, values do not)
+    assert torch.equal(si.pop("logit_rank")[clean], ranks[clean])
+    _same(si, ib, "ipt")
+    gp, ip = difr.score_both_peaked(x, *at, cg, ci)
+    _same(gp, {k: gb[k] for k in gp}, "peaked")
+    _same({k: ip[k] for k in ip if k != "flags"}, {k: ib[k] for k in ip if k != "flags"}, "peaked")
+    differ = int((ib["ipt_token"] != want_i["ipt_token"]).sum())
+    assert differ <= max(1, N // 20), differ      # near-ties of the CDF, about 1 row in 300 (tests against the oracle: parity.py)
+
+
+def test_what_difr_score_split_refuses(difr):
+    from paper_2511_02620_amd import binding as B
+    lib = difr.load_library()
+    assert lib.difr_split_workspace_bytes(0, 151936, 0, 0) == 0 and lib.difr_split_workspace_bytes(24, 151936, 2, 0) == 0
+    assert lib.difr_split_workspace_bytes(24, 8192, 0, 0) == 0 and lib.difr_split_workspace_bytes(16384, 151936, 0, 0) == 0
+    N, V = 4, 65536
+    x = torch.zeros(N, V, dtype=torch.bfloat16, device=DEV)
+    i = torch.zeros(N, dtype=torch.int32, device=DEV)
+    r, _, dev = B._rows(x, None, 1.0, torch.zeros(1, dtype=torch.int64, device=DEV), i, i, i, None)
+    need = lib.difr_split_workspace_bytes(N, V, 0, 1)
+    buf = torch.zeros(max(need, 4096) + 8, dtype=torch.uint8, device=DEV)
+    p = buf.data_ptr()
+
+    def call(ws=p, n=need, **kw):
+        o = B._Scores(**kw)
+        return lib.difr_score_split(C.byref(r), i.data_ptr(), C.byref(o), ws, n, None)
+    full = dict(margin=p, argmax=p, flags_gumbel=p, dist=p, flags_ipt=p)
+    NULL, SHAPE, ALIGN, ARG = 1, 2, 5, 8
+    assert call() == NULL and call(margin=p) == NULL and call(dist=p) == NULL
+    assert call(n=lib.difr_split_workspace_bytes(N, V, 0, 0) - 1, **full) == SHAPE and call(ws=None, **full) == NULL
+    assert call(ws=p + 4, **full) == ALIGN and call(log_mass=p, sigma=0.0, **full) == ARG
+    assert call(count=p, delta=-1.0, **full) == ARG and call(count=p, delta=1.0, ipt_token=p, **full) == ARG
+    assert call(count=p, delta=1.0, dist=p, flags_ipt=p) == NULL and call(rank_ipt=p, **full) == ARG
+    torch.cuda.synchronize()
+    assert int(buf.sum()) == 0
