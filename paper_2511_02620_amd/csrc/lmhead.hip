@@ -104,9 +104,7 @@ __global__ __launch_bounds__(kBlock) void lmhead_prepare_kernel(LmHeadBatch b, L
         const uint16_t *h = b.hidden + n * b.ldh;
         const uint16_t *w = b.weight + (int64_t)t.tg * b.ldw;
         float dot = 0.0f, mag = 0.0f;
-        for (int64_t c = lane; c < b.d / 8; c += 64) {
-            const uint4 hv = *reinterpret_cast<const uint4 *>(h + 8 * c);
-            const uint4 wv = *reinterpret_cast<const uint4 *>(w + 8 * c);
+        auto add = [&](const uint4 &hv, const uint4 &wv) {
             const uint32_t hw[4] = {hv.x, hv.y, hv.z, hv.w}, ww[4] = {wv.x, wv.y, wv.z, wv.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -117,7 +115,20 @@ __global__ __launch_bounds__(kBlock) void lmhead_prepare_kernel(LmHeadBatch b, L
                 mag = __fmaf_rn(fabsf(h0), fabsf(w0), mag);
                 mag = __fmaf_rn(fabsf(h1), fabsf(w1), mag);
             }
+        };
+        const int64_t nc = b.d / 8;
+        int64_t c = lane;
+        for (; c + 64 * 7 < nc; c += 64 * 8) {  // sixteen loads in flight: a wave has nothing else to hide their latency
+            uint4 hv[8], wv[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                hv[i] = *reinterpret_cast<const uint4 *>(h + 8 * (c + 64 * i));
+                wv[i] = *reinterpret_cast<const uint4 *>(w + 8 * (c + 64 * i));
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) add(hv[i], wv[i]);
         }
+        for (; c < nc; c += 64) add(*reinterpret_cast<const uint4 *>(h + 8 * c), *reinterpret_cast<const uint4 *>(w + 8 * c));
         dot = wave_sum(dot);
         mag = wave_sum(mag);
         x_ref = dot;
@@ -191,7 +202,9 @@ __device__ __forceinline__ void refresh_gates(const Slot &s, BlockCtx &k)
 // reference in the last bits).
 //
 // TOK: `part` follows the mass of the half tile the block belongs to, relative to the slot's reference.
-template <bool RANK, bool TOK>
+//
+// AGPR: the accumulators are kept in the accumulation registers.
+template <bool RANK, bool TOK, bool AGPR>
 __device__ __forceinline__ void score_block(const f32x16 acc, Slot &s, BlockCtx &k, int32_t vlane, int32_t V,
                                             bool ragged, int64_t n, const LmHeadWorkspace &ws, double &part)
 {
@@ -200,7 +213,12 @@ __device__ __forceinline__ void score_block(const f32x16 acc, Slot &s, BlockCtx 
     // register allocator moves whole blocks through scratch memory instead)
     float x[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) asm("v_accvgpr_read_b32 %0, %1" : "=v"(x[r]) : "a"(acc[r]));
+    for (int r = 0; r < 16; ++r) {
+        if constexpr (AGPR)
+            asm("v_accvgpr_read_b32 %0, %1" : "=v"(x[r]) : "a"(acc[r]));
+        else
+            x[r] = acc[r];
+    }
     if (ragged) {  // uniform: the tile runs past the end of the vocabulary
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -547,10 +565,10 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
             refresh_gates(slot[jb], k);
             const int32_t vl = (int32_t)v0 + wv * 128 + 4 * lh;
             double part = 0.0;  // TOK: what this lane's 64 entries of the half tile add to its sum
-            score_block<RANK, TOK>(acc[0][jb], slot[jb], k, vl, V, ragged, tok_row(jb), ws, part);
-            score_block<RANK, TOK>(acc[1][jb], slot[jb], k, vl + 32, V, ragged, tok_row(jb), ws, part);
-            score_block<RANK, TOK>(acc[2][jb], slot[jb], k, vl + 64, V, ragged, tok_row(jb), ws, part);
-            score_block<RANK, TOK>(acc[3][jb], slot[jb], k, vl + 96, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK, true>(acc[0][jb], slot[jb], k, vl, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK, true>(acc[1][jb], slot[jb], k, vl + 32, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK, true>(acc[2][jb], slot[jb], k, vl + 64, V, ragged, tok_row(jb), ws, part);
+            score_block<RANK, TOK, true>(acc[3][jb], slot[jb], k, vl + 96, V, ragged, tok_row(jb), ws, part);
             if (TOK) {
                 // the two lanes that share the token (rows 0-3 and 4-7 mod 8) combined
                 const float ninf = -__builtin_inff();
@@ -625,6 +643,263 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 }
 
 // ---------------------------------------------------------------------------------
+// The same for batches of up to 128 tokens.  What bounds them is reading the LM-head matrix once; the tile is as wide as the
+// batch (T = 64 or 128 token rows), so that the matrix instructions of a slab and its fragment reads take a fraction of the
+// time its share of the memory bandwidth does.  A workgroup's four waves own 32 R vocabulary rows each, all token columns.
+// S LDS stages, so that S - 1 slabs are in flight while one is multiplied, one barrier per slab:
+//   wait for the wave's own copies of slab s (those of the slabs after it may be in flight), barrier: slab s is in LDS whole,
+//   and every wave is done with slab s - 1, whose stage takes slab s + S - 1.
+// T = 64, R = 1, S = 3: 24 KB a stage, two workgroups to a compute unit, one of which works while the other waits or scores.
+// T = 128: one workgroup, R = 2, S = 3 or, for fewer tiles than compute units, R = 1, S = 4.
+// Copies and LDS layout as in the kernel above; logits are summed in the same order, to the same bits.
+// NT: the weights are read past the caches.  A matrix larger than the 256 MB Infinity Cache is never found there again and
+// only displaces the hidden states: 1.24 GB, 64 tokens: 269 us for the call with ordinary loads, 247 with these; a matrix
+// that fits is left to the cache (262 MB: 63 / 67 us, read again and again).
+// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 232 us, 5.4 TB/s (the 256 x 256 kernel: 370).
+// ---------------------------------------------------------------------------------
+template <int T, int R, bool NT, bool RANK, bool TOK>
+__global__ __launch_bounds__(kBlock, T == 64 ? 2 : 1) void lmhead_small_kernel(LmHeadBatch b, LmHeadWorkspace ws, LmHeadPlan plan)
+{
+    constexpr int kRows = 128 * R, TB = T / 32, kStages = T == 128 && R == 1 ? 4 : 3;
+    constexpr int kCopiesW = kRows / 32, kCopiesH = T / 32, kCopies = kCopiesW + kCopiesH;  // per wave and slab, 8 rows each
+    __shared__ __attribute__((aligned(16))) uint16_t lds_w[kStages][kRows * kLmTileK];
+    __shared__ __attribute__((aligned(16))) uint16_t lds_h[kStages][T * kLmTileK];
+    __shared__ uint32_t lds_tok[RANK ? 8 : 7][T];
+    __shared__ float2 lds_half[TOK ? kWaves : 1][T];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, lh = lane >> 5;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int sp = blockIdx.x;
+    const int vt0 = (int)((int64_t)sp * plan.n_tiles / plan.splits), vt1 = (int)((int64_t)(sp + 1) * plan.n_tiles / plan.splits);
+    const int32_t V = (int32_t)b.V;
+    const int nk = (int)(b.d / kLmTileK);
+    const int total = (vt1 - vt0) * nk;  // slabs
+
+    const int crow = tid >> 3;
+    const int cchunk = (tid & 7) ^ ((crow >> 1) & 7);
+    uint32_t hoff[kCopiesH], woff[kCopiesW];
+#pragma unroll
+    for (int p = 0; p < kCopiesH; ++p) {
+        int64_t r = crow + 32 * p;
+        if (r > b.N - 1) r = b.N - 1;  // rows past the end of the batch re-read the last one
+        hoff[p] = (uint32_t)(r * b.ldh + cchunk * 8) * 2u;
+    }
+    const uint32_t wrow_bytes = (uint32_t)b.ldw * 2u;
+    auto set_woff = [&](int vt) {
+        const int64_t tile_v0 = (int64_t)vt * kRows;
+        const int32_t last = (int32_t)((b.V - tile_v0 < kRows ? b.V - tile_v0 : kRows) - 1);  // uniform
+#pragma unroll
+        for (int p = 0; p < kCopiesW; ++p) woff[p] = (uint32_t)min(crow + 32 * p, last) * wrow_bytes + (uint32_t)cchunk * 16u;
+    };
+    set_woff(vt0);
+    int l_vt = vt0, l_kt = 0, l_stage = 0;  // the next slab to fetch and the stage it goes to
+    auto copy_rows = [&](const char *sbase, uint32_t voff, const uint16_t *stage, auto P, auto PAST) {
+        const uint32_t lds_base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)stage;
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+        if constexpr (decltype(PAST)::value)
+            asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0 nt"
+                         :
+                         : "s"(sbase), "v"(voff), "s"(lds_base), "n"(32 * decltype(P)::value * kLmTileK * 2)
+                         : "memory", "m0", "scc");
+        else
+            asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
+                         :
+                         : "s"(sbase), "v"(voff), "s"(lds_base), "n"(32 * decltype(P)::value * kLmTileK * 2)
+                         : "memory", "m0", "scc");
+#pragma clang diagnostic pop
+    };
+    auto fetch_slab = [&]() {
+        const char *wbase = reinterpret_cast<const char *>(b.weight + (int64_t)l_vt * kRows * b.ldw + l_kt * kLmTileK);
+        const char *hbase = reinterpret_cast<const char *>(b.hidden + l_kt * kLmTileK);
+        const uint16_t *sw = &lds_w[l_stage][0] + 8 * wave_u * kLmTileK, *sh = &lds_h[l_stage][0] + 8 * wave_u * kLmTileK;
+        static_for<kCopiesW>([&](auto P) { copy_rows(wbase, woff[decltype(P)::value], sw, P, std::integral_constant<bool, NT>()); });
+        static_for<kCopiesH>([&](auto P) { copy_rows(hbase, hoff[decltype(P)::value], sh, P, std::false_type()); });
+        l_stage = l_stage + 1 == kStages ? 0 : l_stage + 1;
+        if (++l_kt == nk) {
+            l_kt = 0;
+            ++l_vt;
+            if (l_vt < vt1 && (int64_t)(l_vt + 1) * kRows > b.V) set_woff(l_vt);  // the ragged tile, at most once
+        }
+    };
+    auto barrier = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    for (int i = tid; i < T; i += kBlock) {
+        const int64_t n = i < b.N ? i : b.N - 1;
+        const TokInfo t = load_tok(b, n);
+        lds_tok[0][i] = t.key.k0;
+        lds_tok[1][i] = t.key.k1;
+        lds_tok[2][i] = t.pos;
+        lds_tok[3][i] = t.seq;
+        lds_tok[4][i] = __float_as_uint(t.inv_T);
+        lds_tok[5][i] = (uint32_t)t.tg;
+        lds_tok[6][i] = (uint32_t)t.ti;
+        if (RANK) lds_tok[7][i] = __float_as_uint(ws.x_claim_ref[n]);
+    }
+    Slot slot[TB];  // the lane's tokens are l32 + 32 jb
+    auto tok_row = [&](int jb) { return (int64_t)(l32 + 32 * jb < b.N ? l32 + 32 * jb : b.N - 1); };
+    auto tok_is_live = [&](int jb) { return l32 + 32 * jb < b.N; };
+#pragma unroll
+    for (int jb = 0; jb < TB; ++jb) slot[jb] = Slot{-__builtin_inff(), 0x7FFFFFFF, ws.L0[tok_row(jb)], -__builtin_inff(), 0.0, 0.0, 0u};
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    for (int i = 0; i < kStages - 1 && i < total; ++i) fetch_slab();
+    const int sw = (l32 >> 1) & 7;
+    int stage = 0, done = 0;  // stage of the next slab to multiply, slabs multiplied
+    for (int vt = vt0; vt < vt1; ++vt) {
+        const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        f32x16 acc[R][TB];
+#pragma unroll
+        for (int ib = 0; ib < R; ++ib)
+#pragma unroll
+            for (int jb = 0; jb < TB; ++jb) acc[ib][jb] = zero;
+        for (int kt = 0; kt < nk; ++kt) {
+            // (copies of one wave land in order, so with no more than the younger slabs' outstanding this slab has landed;
+            // stores of the epilogue only make the wait stricter.  lgkmcnt: the fragments of slab s - 1 have been read.)
+            if (kStages > 3 && done + 2 < total)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((kStages - 2) * kCopies) : "memory");
+            else if (done + 1 < total)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(kCopies) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            barrier();
+            if (done + kStages - 1 < total) fetch_slab();
+#pragma unroll
+            for (int kk = 0; kk < kLmTileK / 16; ++kk) {
+                const int coff = ((2 * kk + lh) ^ sw) * 8;
+                bf16x8 fa[R], fb[TB];
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    fa[i] = *reinterpret_cast<const bf16x8 *>(&lds_w[stage][(wave * 32 * R + i * 32 + l32) * kLmTileK + coff]);
+#pragma unroll
+                for (int j = 0; j < TB; ++j)
+                    fb[j] = *reinterpret_cast<const bf16x8 *>(&lds_h[stage][(j * 32 + l32) * kLmTileK + coff]);
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+#pragma unroll
+                    for (int j = 0; j < TB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+            }
+            stage = stage + 1 == kStages ? 0 : stage + 1;
+            ++done;
+        }
+
+        // ---- epilogue ----
+        const int32_t v0 = vt * kRows;
+        const bool ragged = (int64_t)v0 + kRows > b.V;
+        // (explicit instantiation per block: the accumulator indices must be compile-time constants)
+        static_for<TB>([&](auto JB) {
+            constexpr int jb = decltype(JB)::value;
+            const int i = jb * 32 + l32;
+            TokInfo t;
+            t.key.k0 = lds_tok[0][i];
+            t.key.k1 = lds_tok[1][i];
+            t.pos = lds_tok[2][i];
+            t.seq = lds_tok[3][i];
+            t.inv_T = __uint_as_float(lds_tok[4][i]);
+            t.tg = (int32_t)lds_tok[5][i];
+            t.ti = (int32_t)lds_tok[6][i];
+            t.ok = t.seq_ok = true;  // not used by the epilogue
+            BlockCtx k{t, t.inv_T * kLog2e, 0.0f, 0.0f, 0u, tok_is_live(jb), RANK ? __uint_as_float(lds_tok[RANK ? 7 : 0][i]) : 0.0f};
+            k.neg_mc = (slot[jb].m > -__builtin_inff()) ? -ref_exp(slot[jb].m, k.c) : 0.0f;
+            refresh_gates(slot[jb], k);
+            double part = 0.0;
+            static_for<R>([&](auto IB) {
+                constexpr int ib = decltype(IB)::value;
+                score_block<RANK, TOK, T == 128>(acc[ib][jb], slot[jb], k, v0 + (wave * R + ib) * 32 + 4 * lh, V, ragged, tok_row(jb), ws, part);
+            });
+            if (TOK) {
+                const float ninf = -__builtin_inff();
+                const float ms = (float)part, mm = slot[jb].m;
+                const float os = __shfl_xor(ms, 32, 64), om = __shfl_xor(mm, 32, 64);
+                const float M = fmaxf(mm, om);
+                const float both = (mm > ninf ? ms * fast_exp2(ref_exp(mm, k.c) - ref_exp(M, k.c)) : 0.0f) +
+                                   (om > ninf ? os * fast_exp2(ref_exp(om, k.c) - ref_exp(M, k.c)) : 0.0f);
+                if (lh == 0) lds_half[wave][i] = make_float2(both, M);
+            }
+        });
+        if (TOK) {
+            // a half tile (128 entries) is the work of 4 / R waves
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            barrier();
+            for (int i = tid; i < T * R; i += kBlock) {
+                const int n = i % T, h = i / T;
+                const float c = __uint_as_float(lds_tok[4][n]) * kLog2e, ninf = -__builtin_inff();
+                float M = ninf, sum = 0.0f;
+#pragma unroll
+                for (int w = 0; w < kWaves / R; ++w) M = fmaxf(M, lds_half[h * (kWaves / R) + w][n].y);
+#pragma unroll
+                for (int w = 0; w < kWaves / R; ++w) {
+                    const float2 p = lds_half[h * (kWaves / R) + w][n];
+                    if (p.y > ninf) sum += p.x * fast_exp2(ref_exp(p.y, c) - ref_exp(M, c));
+                }
+                if (n < b.N) {
+                    ws.half_sum[((int64_t)vt * R + h) * b.N + n] = make_float2(sum, M);
+                    // (the merge reads an even number of half tiles)
+                    if (R == 1 && vt + 1 == plan.n_tiles && (vt & 1) == 0) ws.half_sum[(int64_t)(vt + 1) * b.N + n] = make_float2(0.0f, ninf);
+                }
+            }
+        }
+    }
+
+    // ---- merge the lanes and waves that share a token, in vocabulary-row order of the halves and waves ----
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();  // the tile memory is reused below
+    float *ex_y = reinterpret_cast<float *>(&lds_w[0][0]);  // [kWaves][T] each
+    int32_t *ex_v = reinterpret_cast<int32_t *>(ex_y + kWaves * T);
+    float *ex_m = reinterpret_cast<float *>(ex_v + kWaves * T);
+    double *ex_Z = reinterpret_cast<double *>(ex_m + 2 * kWaves * T);
+    double *ex_P = ex_Z + kWaves * T;
+    uint32_t *ex_a = reinterpret_cast<uint32_t *>(ex_P + kWaves * T);
+    static_assert(kWaves * T * 36 <= (int)sizeof(lds_w), "the exchange fits the tile memory");
+#pragma unroll
+    for (int jb = 0; jb < TB; ++jb) {
+        Slot &s = slot[jb];
+        const int i = jb * 32 + l32;
+        const float c = __uint_as_float(lds_tok[4][i]) * kLog2e;
+        const float oy = __shfl_xor(s.best_y, 32, 64), om = __shfl_xor(s.m, 32, 64);
+        const int32_t ov = __shfl_xor(s.best_v, 32, 64);
+        const double oZ = __shfl_xor(s.Z, 32, 64), oP = __shfl_xor(s.P, 32, 64);
+        if (RANK) s.above += (uint32_t)__shfl_xor((int)s.above, 32, 64);
+        if (lh == 0) {
+            argmax_combine(s.best_y, s.best_v, oy, ov);
+            merge_softmax(s.m, s.Z, s.P, om, oZ, oP, c);
+            ex_y[wave * T + i] = s.best_y;
+            ex_v[wave * T + i] = s.best_v;
+            ex_m[wave * T + i] = s.m;
+            ex_Z[wave * T + i] = s.Z;
+            ex_P[wave * T + i] = s.P;
+            if (RANK) ex_a[wave * T + i] = s.above;
+        }
+    }
+    __syncthreads();
+    if (tid < T && tid < b.N) {
+        const float c = __uint_as_float(lds_tok[4][tid]) * kLog2e;
+        float best_y = ex_y[tid], m = ex_m[tid];
+        int32_t best_v = ex_v[tid];
+        double Z = ex_Z[tid], P = ex_P[tid];
+        uint32_t above = RANK ? ex_a[tid] : 0u;
+        for (int w = 1; w < kWaves; ++w) {
+            argmax_combine(best_y, best_v, ex_y[w * T + tid], ex_v[w * T + tid]);
+            merge_softmax(m, Z, P, ex_m[w * T + tid], ex_Z[w * T + tid], ex_P[w * T + tid], c);
+            if (RANK) above += ex_a[w * T + tid];
+        }
+        const int64_t o = (int64_t)sp * b.N + tid;
+        ws.best_y[o] = best_y;
+        ws.best_v[o] = best_v;
+        ws.m[o] = m;
+        ws.Z[o] = Z;
+        ws.P[o] = P;
+        if (RANK) ws.above[o] = (int32_t)above;
+    }
+}
+
+// ---------------------------------------------------------------------------------
 // Merge the vocabulary ranges of each token and form every output.  A workgroup takes 8 tokens with 32 threads each:
 // thread (t, g) reads the g-th 1/32 of token t's ranges (and, for the sampler's token, of its half tiles), so that
 // neighbouring lanes read neighbouring tokens of the [range][token] arrays and the loads of a token are spread over
@@ -632,11 +907,11 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 // took 174 us of a call with 64 tokens (256 ranges) and 780 us with 4096 tokens and the sampler's token (16 ranges,
 // 1188 half tiles); now 15 and 34 us.
 // ---------------------------------------------------------------------------------
-constexpr int kFinTokens = 8, kFinGroups = kBlock / kFinTokens;
-
+template <int kFinTokens>
 __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, LmHeadWorkspace ws, int splits, int n_vt,
                                                                  GumbelOutputs og, IptOutputs oi)
 {
+    constexpr int kFinGroups = kBlock / kFinTokens;
     __shared__ float lds_y[kWaves][kFinTokens], lds_m[kWaves][kFinTokens];
     __shared__ int32_t lds_v[kWaves][kFinTokens], lds_a[kWaves][kFinTokens];
     __shared__ double lds_Z[kWaves][kFinTokens], lds_P[kWaves][kFinTokens];
@@ -919,19 +1194,46 @@ int launch_lmhead_score(const LmHeadBatch &b, const LmHeadWorkspace &ws, const L
     lmhead_prepare_kernel<<<dim3((unsigned)((b.N + kWaves - 1) / kWaves)), dim3(kBlock), 0, stream>>>(b, ws);
     if (hipGetLastError() != hipSuccess) return 1;
     // the logit rank and the masses behind the sampler's own token are produced in the scoring pass, only when asked for
-    const dim3 grid((unsigned)(plan.n_tb * plan.splits)), block(kBlock);
+    const dim3 block(kBlock);
     const bool rank = og.logit_rank != nullptr, tok = oi.ipt_token != nullptr;
+    auto score = [&](auto RANK, auto TOK) {
+        constexpr bool r = decltype(RANK)::value, t = decltype(TOK)::value;
+        const bool past = b.V * b.ldw * 2 > (int64_t)256 << 20;  // a weight matrix larger than the Infinity Cache
+        const dim3 small_grid((unsigned)plan.splits);
+        if (plan.small == 64 && past)
+            lmhead_small_kernel<64, 1, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        else if (plan.small == 64)
+            lmhead_small_kernel<64, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        else if (plan.small && plan.blocks == 1)  // (few enough entries that the matrix is small for any usual d)
+            lmhead_small_kernel<128, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        else if (plan.small && past)
+            lmhead_small_kernel<128, 2, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        else if (plan.small)
+            lmhead_small_kernel<128, 2, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        else
+            lmhead_score_kernel<r, t><<<dim3((unsigned)(plan.n_tb * plan.splits)), block, 0, stream>>>(b, ws, plan);
+    };
+    const std::true_type yes;
+    const std::false_type no;
     if (rank && tok)
-        lmhead_score_kernel<true, true><<<grid, block, 0, stream>>>(b, ws, plan);
+        score(yes, yes);
     else if (rank)
-        lmhead_score_kernel<true, false><<<grid, block, 0, stream>>>(b, ws, plan);
+        score(yes, no);
     else if (tok)
-        lmhead_score_kernel<false, true><<<grid, block, 0, stream>>>(b, ws, plan);
+        score(no, yes);
     else
-        lmhead_score_kernel<false, false><<<grid, block, 0, stream>>>(b, ws, plan);
+        score(no, no);
     if (hipGetLastError() != hipSuccess) return 1;
-    lmhead_finalize_kernel<<<dim3((unsigned)((b.N + kFinTokens - 1) / kFinTokens)), block, 0, stream>>>(b, ws, plan.splits,
-                                                                                                      plan.n_vt, og, oi);
+    auto finalize = [&](auto TOKENS) {
+        constexpr int per = decltype(TOKENS)::value;
+        lmhead_finalize_kernel<per><<<dim3((unsigned)((b.N + per - 1) / per)), block, 0, stream>>>(b, ws, plan.splits, plan.n_vt, og, oi);
+    };
+    // (two tokens to a workgroup where a token has many ranges: 400 ranges, 64 tokens: 247 / 244 us for the call; the search
+    // for the sampler's token walks a sum per group of threads, of which it is better to have fewer: V = 4000: 45 / 50 us)
+    if (plan.small && plan.splits > 128 && !tok)
+        finalize(std::integral_constant<int, 2>());
+    else
+        finalize(std::integral_constant<int, 8>());
     if (hipGetLastError() != hipSuccess) return 1;
     if (tok) {
         lmhead_ipt_token_kernel<<<dim3((unsigned)b.N), block, 0, stream>>>(b, ws, oi);

@@ -11,6 +11,7 @@ namespace difr {
 constexpr int kLmTileV = 256;  // vocabulary entries per workgroup tile
 constexpr int kLmTileT = 256;  // token rows per workgroup tile
 constexpr int kLmTileK = 64;   // hidden-dimension slab staged through LDS per step
+constexpr int64_t kLmSmallMost = 128;  // most tokens of the small-batch kernel
 
 // Kernel-side image of difr_lmhead.
 struct LmHeadBatch {
@@ -33,7 +34,10 @@ struct LmHeadBatch {
 struct LmHeadPlan {
     int n_tb;    // token blocks of kLmTileT rows
     int n_vt;    // vocabulary tiles of kLmTileV entries
-    int splits;  // vocabulary ranges (1 <= splits <= n_vt)
+    int splits;  // vocabulary ranges
+    int small;   // token rows of the small-batch kernel's tile (64 or 128), 0: the 256 x 256 kernel
+    int blocks;  // small-batch kernel: blocks of 32 vocabulary entries per wave and tile (a tile has 128 entries for each)
+    int n_tiles; // ... and how many such tiles there are
 };
 
 inline LmHeadPlan lmhead_plan(int64_t N, int64_t V)
@@ -41,6 +45,21 @@ inline LmHeadPlan lmhead_plan(int64_t N, int64_t V)
     LmHeadPlan p;
     p.n_tb = (int)((N + kLmTileT - 1) / kLmTileT);
     p.n_vt = (int)((V + kLmTileV - 1) / kLmTileV);
+    p.small = p.blocks = p.n_tiles = 0;
+    // Up to 128 tokens the matrix instructions of the 256 x 256 tile are mostly padding and the LM-head matrix is read at
+    // half the speed of memory (64 tokens, V = 151,936, d = 4096: 375 us for the call, 247 with the small-batch kernel; 128
+    // tokens 398 / 242; 129 to 256 tokens stay: 424).  Up to 64 tokens two workgroups fit a compute unit; beyond, one, with
+    // tiles of 256 entries as long as those give every compute unit one.  Every range has the same number of tiles (but for
+    // the last), so that all workgroups end together.
+    if (N <= kLmSmallMost) {
+        p.small = N <= 64 ? 64 : 128;
+        p.blocks = p.small == 128 && V > 256 * 256 ? 2 : 1;
+        const int rows = 128 * p.blocks, most = p.small == 64 ? 512 : 256;
+        p.n_tiles = (int)((V + rows - 1) / rows);
+        const int each = (p.n_tiles + most - 1) / most;
+        p.splits = each > 0 ? (p.n_tiles + each - 1) / each : 1;
+        return p;
+    }
     // one workgroup per compute unit (256 of them) when the token blocks alone do not fill the chip
     int s = p.n_tb > 0 ? 256 / p.n_tb : 1;
     if (s < 1) s = 1;
