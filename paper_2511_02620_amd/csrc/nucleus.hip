@@ -17,11 +17,12 @@
 //        mass from the top reaches it becomes the bracket: bin1 is monotone in the logit, so its first key is
 //        found by bisection.  (If M lies so far above R that terms could overflow, the pass is repeated with
 //        R = M.)
-//   BC   bf16 rows whose bracket is now at most 16 logit values with many entries each (the usual case when K is
-//        large: near the cut a bf16 value is shared by thousands of tokens) are finished by one counting pass:
+//   BC   bf16 rows whose bracket is now at most 16 logit values (the usual case when K is large: near the cut a bf16
+//        value is shared by thousands of tokens) are finished by one counting pass:
 //        per value of the bracket and per thread the number of entries, and of entries below the claimed token's
 //        index; entries of equal value have equal mass, which is taken per value in fp64.  Two reads in all.
-//        Every other row goes on with B2 and C:
+//        Every other row goes on with B2 and C, with C at once if the first round lets expect few entries in the
+//        bracket (and with B2 after all if they turn out to be many):
 //   B2.. the bracket's key range is divided evenly into at most 16 bins and searched in the same way, until it
 //        is a single key - one logit value - or provably holds at most kNucCap entries (its mass divided by the
 //        weight of its smallest key bounds their number).  Typically one or two passes;
@@ -268,7 +269,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
 #pragma unroll
         for (int k = 0; k < kNucBins; ++k) mass[k * kBlock + tid] = 0.0f;
     };
-    double mass_above = 0.0, target = 0.0;
+    double mass_above = 0.0, Zrow = 0.0, target = 0.0;
     // from the top: the first bin in which the cumulative mass reaches the target (every thread walks the same 16
     // values in the same order); what lies above it is added to mass_above
     auto select_bin = [&]() __attribute__((always_inline)) {
@@ -358,6 +359,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         combine_bins();
         double Z = 0.0;
         for (int k = 0; k < kNucBins; ++k) Z += bin_m[k];
+        Zrow = Z;
         target = (double)top_p * Z;
         const uint32_t sel = (uint32_t)select_bin();
         // the keys of bin `sel`: bin1 is monotone over the keys from -inf to the largest finite one, so the first
@@ -390,8 +392,9 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     bool many_ties = false;
     const uint32_t t32 = valid ? (uint32_t)t : 0u;  // an invalid claim has nothing below it (its outputs are NaN anyway)
 
-    // bf16 rows whose bracket is a handful of logit values with many entries each (the usual case when K is large:
-    // near the cut a bf16 value is shared by thousands of tokens): ONE more pass finishes the row.  Entries of equal
+    // bf16 rows whose bracket is at most 16 logit values, however many entries (the usual case when K is large:
+    // near the cut a bf16 value is shared by thousands of tokens): ONE more pass finishes the row, without the sort that
+    // pass C needs (4096 rows of 8000 with some 1500 entries in the bracket: 285 us sorted, 202 counted).  Entries of equal
     // value have equal mass, so the pass only counts, per value of the bracket and per thread, the entries and those
     // of them below the claimed token's index (16 + 16 bits in one private LDS word), and sums what lies above the
     // bracket as the last pass of the general path does.  The values' masses are then taken in fp64, the value at
@@ -402,7 +405,26 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         const double e_lo = (double)mass_of(value_of_key(klo));
         provably_small = e_lo > 0.0 && e_lo < (double)__builtin_inff() && bracket_mass <= e_lo * (double)(kNucCap - 48);
     }
-    const bool by_counts = DT == 0 && khi > klo && khi - klo < (uint32_t)kNucBins && !provably_small && V <= (int64_t)(1 << 24);
+    const bool by_counts = DT == 0 && khi > klo && khi - klo < (uint32_t)kNucBins && V <= (int64_t)(1 << 24);
+    // A bracket may hold few entries although its mass does not prove it: the end bin at the top takes in everything above
+    // the first round's largest entry, the row's few heaviest tokens among them, and its keys span the octaves around zero,
+    // which the further search passes divide badly (rows whose nucleus is small, top_p = 0.95 at T = 0.7: half of them took
+    // two or three such passes).  The entries of the first round that lie in it say how many to expect; if that is well
+    // below what pass C can gather, pass C is tried at once, and only if its buffer runs over does the search go on
+    // (2048 rows of 128,256 bf16 logits at T = 0.7: 362 -> 306 us; 2048 rows of 65,536 fp32 logits: 321 -> 252).
+    bool try_gather = false;
+    if (!by_counts && !provably_small) {  // uniform
+        const uint32_t span = khi - klo;
+        int32_t seen = 0;
+        if (tid < nvec) {
+            uint32_t kw[4];
+            keys_of(ragged_patched(fetch(tid), (uint32_t)tid * E), kw);
+#pragma unroll
+            for (int j = 0; j < E; ++j) seen += (int32_t)(key_of(kw, j) - klo <= span && (uint32_t)tid * E + j < V32);
+        }
+        seen = block_sum_i32(seen, lds_i);
+        try_gather = (int64_t)seen * ((nvec + kBlock - 1) / kBlock) <= kNucCap / 4;
+    }
     if (by_counts) {  // uniform
         const uint32_t span = khi - klo;
         uint32_t *cnt = reinterpret_cast<uint32_t *>(raw);  // [key - klo][thread]; a thread meets fewer than 2^16 entries
@@ -471,7 +493,11 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             key_cnt[tid] = sm;
         }
         __syncthreads();
-        const int64_t cnt_above = (int64_t)block_sum_i32(n_above, lds_i);
+        // the values' masses, one per thread: an fp64 exponential is 100 instructions and more, and a walk in which every
+        // thread took all of them made the row's fixed cost what a short row spent its time on
+        double *key_mass = &part_m[0][0];
+        if (tid <= (int)span) key_mass[tid] = mass_of_f64(value_of_key(klo + (uint32_t)tid));
+        const int64_t cnt_above = (int64_t)block_sum_i32(n_above, lds_i);  // (its barriers publish the masses)
         // from the top: the first value at which the cumulative mass reaches the target (every thread walks the
         // same values in the same order); the values above it belong to K whole
         double ma = mass_above, below_hi = 0.0, e_cut = 0.0;
@@ -480,7 +506,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int j = (int)span; j >= 0; --j) {
             const int64_t na = key_cnt[2 * j];
             if (na == 0) continue;
-            const double e = mass_of_f64(value_of_key(klo + (uint32_t)j));
+            const double e = key_mass[j];
             jlast = j;
             e_cut = e;
             if (ma + e * (double)na >= target) {
@@ -515,7 +541,12 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // logit value) or provably small enough to sort.  No counts are kept: every entry of the bracket weighs at
     // least as much as the bracket's smallest key would, so mass / that weight bounds the number of entries.
     bool single_value = false;
+    double below_above;   // mass of entries above the bracket with index < t
+    int32_t ties_below;   // many_ties: bracket entries with index < t ...
+    int32_t ties;         // ... and all of them
+    int32_t n_above;      // entries above the bracket
     while (true) {
+    while (!try_gather) {
         if (khi <= klo) {  // (khi < klo cannot happen: the selected bin holds mass)
             khi = klo;
             single_value = true;
@@ -552,10 +583,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     //      bracket and below the claimed token's index ----
     if (tid == 0) s_fill = 0;
     __syncthreads();
-    double below_above = 0.0;  // mass of entries above the bracket with index < t
-    int32_t ties_below = 0;    // many_ties: bracket entries with index < t ...
-    int32_t ties = 0;          // ... and all of them
-    int32_t n_above = 0;       // entries above the bracket
+    below_above = 0.0;
+    ties_below = ties = n_above = 0;
     const uint32_t span_c = khi - klo;
     for_each_vector([&](const u32x4 &q, uint32_t base) {
         uint32_t kw[4];
@@ -582,6 +611,10 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         below_above += (double)below_vec;
     });
     __syncthreads();
+    if (!try_gather || s_fill <= kNucCap) break;  // uniform
+    try_gather = false;  // more than the first round promised: the search goes on
+    __syncthreads();     // (s_fill has been read)
+    }
     const int64_t cnt_above = (int64_t)block_sum_i32(n_above, lds_i);
 
     if (many_ties) {
@@ -600,8 +633,17 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         while (P < n) P <<= 1;
         for (int i = n + tid; i < P; i += kBlock) buf[i] = 0ull;  // below every real composite
         __syncthreads();
-        // bitonic sort, descending: rank order (larger logit first, then the smaller index)
-        for (int k = 2; k <= P; k <<= 1) {
+        // descending: rank order (larger logit first, then the smaller index).  One entry per thread finds its place by
+        // counting the entries above it (two barriers, broadcast reads); more go through a bitonic sort.
+        if (P == kBlock) {
+            const uint64_t mine = buf[tid];
+            int place = 0;
+            for (int i = 0; i < n; ++i) place += (int)(buf[i] > mine);
+            __syncthreads();
+            if (tid < n) buf[place] = mine;
+            __syncthreads();
+        }
+        for (int k = 2; k <= P && P > kBlock; k <<= 1) {
             for (int j = k >> 1; j > 0; j >>= 1) {
                 for (int i = tid; i < P; i += kBlock) {
                     const int l = i ^ j;
@@ -619,7 +661,9 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         }
         // walk the sorted bracket: thread `tid` owns positions [tid * per, tid * per + per)
         const int per = P / kBlock;
+        const double first = tid * per < n ? mass_of_f64(top_key(buf[tid * per])) : 0.0;  // (all there is when per = 1)
         auto term = [&](int q) {  // mass of the thread's q-th position (0 past the end)
+            if (q == 0) return first;
             const int i = tid * per + q;
             return (q < per && i < n) ? mass_of_f64(top_key(buf[i])) : 0.0;
         };
@@ -628,13 +672,17 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int q = 0; q < kNucCap / kBlock; ++q) run += term(q);
         double total;
         const double before = block_inclusive_scan(run, lds_d, total) - run;
+        // The target, with the bracket's share of the total mass in fp64 as well: a bracket that holds the row's heaviest
+        // tokens would otherwise be measured against a total that carries the rounding of their fp32 exponentials (6e-8 of
+        // a mass near 1, a marginal token's worth).
+        const double goal = (double)top_p * (Zrow - bracket_mass + total);
         // the first position at which the cumulative mass reaches the target: in the thread, then over the workgroup
         int32_t my_pos = 0x7FFFFFFF;
         double my_mass = 0.0, acc = before;
 #pragma unroll
         for (int q = 0; q < kNucCap / kBlock; ++q) {
             acc += term(q);
-            if (q < per && tid * per + q < n && my_pos == 0x7FFFFFFF && mass_above + acc >= target) {
+            if (q < per && tid * per + q < n && my_pos == 0x7FFFFFFF && mass_above + acc >= goal) {
                 my_pos = tid * per + q;
                 my_mass = acc;
             }
@@ -804,8 +852,10 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     }
 }
 
+// (six waves per SIMD: 77 registers and no spills, where the compiler's own choice is 81 and five; 16,384 x 151,936: 2257 /
+// 2224 us, 4096 x 8000: 290 / 265; seven and eight spill)
 template <int DT>
-__global__ __launch_bounds__(kBlock) void ipt_nucleus_kernel(RowBatch b, float top_p, IptOutputs o,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void ipt_nucleus_kernel(RowBatch b, float top_p, IptOutputs o,
                                                              int32_t *__restrict__ kept_out, float *__restrict__ tau_out)
 {
     __shared__ __attribute__((aligned(16))) unsigned char raw[kNucRawBytes];

@@ -1,0 +1,38 @@
+"""Nuclei whose cut falls among entries above everything the first round has seen, so that they are gathered at once: one
+entry, as many as one thread each takes and one more (two ways of sorting), and more than the buffer holds (the search then
+goes on).  Against the oracle with the bounds of test_gpu_nucleus.py."""
+import pytest
+import torch
+
+import test_gpu_nucleus as base
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def difr():
+    import paper_2511_02620_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [1, 2, 255, 256, 257, 512, 2048, 2049, 6000])
+def test_heavy_entries_beyond_the_first_round(difr, dtype, n):
+    N, V, S = 6, 20008, 2
+    g = torch.Generator().manual_seed(n)
+    x = -20 - torch.rand(N, V, generator=g)
+    x[:, 100] = -10.0                                  # the first round's largest: a span of bins, one entry in the top one
+    for r in range(N):
+        at = 2048 + torch.randperm(V - 2048, generator=g)[:n]
+        x[r, at] = 4 + 5 * torch.rand(n, generator=g)
+    x[4] = x[4].round()                                # ties
+    x = x.to(dtype).to(DEV)
+    seeds = torch.randint(-2 ** 63, 2 ** 63 - 1, (S,), generator=g).to(DEV)
+    sid, pos = (torch.arange(N, dtype=torch.int32) % S).to(DEV), torch.arange(N, dtype=torch.int32).to(DEV)
+    claims = x.argmax(1).int()
+    claims[1], claims[2] = V - 1, 0
+    for p in (0.5, 0.93):
+        print("nucleus gather", dtype, n, p, flush=True)
+        base._compare(difr, x, V, 0.8, seeds, sid, pos, claims, p)
