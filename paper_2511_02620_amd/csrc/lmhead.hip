@@ -649,18 +649,18 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 // S LDS stages, so that S - 1 slabs are in flight while one is multiplied, one barrier per slab:
 //   wait for the wave's own copies of slab s (those of the slabs after it may be in flight), barrier: slab s is in LDS whole,
 //   and every wave is done with slab s - 1, whose stage takes slab s + S - 1.
-// T = 64, R = 1, S = 3: 24 KB a stage, two workgroups to a compute unit, one of which works while the other waits or scores.
-// T = 128: one workgroup, R = 2, S = 3 or, for fewer tiles than compute units, R = 1, S = 4.
+// R = 2: one workgroup to a compute unit, as many stages as fit; the hidden states that every slab of weights is multiplied
+// with cross from the L2 once for 256 rows.  R = 1, for fewer tiles than compute units: up to 64 tokens two workgroups.
 // Copies and LDS layout as in the kernel above; logits are summed in the same order, to the same bits.
 // NT: the weights are read past the caches.  A matrix larger than the 256 MB Infinity Cache is never found there again and
-// only displaces the hidden states: 1.24 GB, 64 tokens: 269 us for the call with ordinary loads, 247 with these; a matrix
+// only displaces the hidden states: 1.24 GB, 64 tokens: 269 us for the call with ordinary loads, 247 with these (128-entry tiles); a matrix
 // that fits is left to the cache (262 MB: 63 / 67 us, read again and again).
-// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 232 us, 5.4 TB/s (the 256 x 256 kernel: 370).
+// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 190 to 215 us, 5.8 to 6.5 TB/s (the 256 x 256 kernel: 370).
 // ---------------------------------------------------------------------------------
 template <int T, int R, bool NT, bool RANK, bool TOK>
-__global__ __launch_bounds__(kBlock, T == 64 ? 2 : 1) void lmhead_small_kernel(LmHeadBatch b, LmHeadWorkspace ws, LmHeadPlan plan)
+__global__ __launch_bounds__(kBlock, T <= 64 && R == 1 ? 2 : 1) void lmhead_small_kernel(LmHeadBatch b, LmHeadWorkspace ws, LmHeadPlan plan)
 {
-    constexpr int kRows = 128 * R, TB = T / 32, kStages = T == 128 && R == 1 ? 4 : 3;
+    constexpr int kRows = 128 * R, TB = T / 32, kStages = (T == 128 && R == 1) || (T == 32 && R == 2) ? 4 : 3;
     constexpr int kCopiesW = kRows / 32, kCopiesH = T / 32, kCopies = kCopiesW + kCopiesH;  // per wave and slab, 8 rows each
     __shared__ __attribute__((aligned(16))) uint16_t lds_w[kStages][kRows * kLmTileK];
     __shared__ __attribute__((aligned(16))) uint16_t lds_h[kStages][T * kLmTileK];
@@ -1200,16 +1200,21 @@ int launch_lmhead_score(const LmHeadBatch &b, const LmHeadWorkspace &ws, const L
         constexpr bool r = decltype(RANK)::value, t = decltype(TOK)::value;
         const bool past = b.V * b.ldw * 2 > (int64_t)256 << 20;  // a weight matrix larger than the Infinity Cache
         const dim3 small_grid((unsigned)plan.splits);
-        if (plan.small == 64 && past)
-            lmhead_small_kernel<64, 1, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        auto small = [&](auto TOKENS) {
+            constexpr int T = decltype(TOKENS)::value;
+            if (plan.blocks == 1)  // (few enough entries that the matrix is small for any usual d)
+                lmhead_small_kernel<T, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+            else if (past)
+                lmhead_small_kernel<T, 2, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+            else
+                lmhead_small_kernel<T, 2, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+        };
+        if (plan.small == 32)
+            small(std::integral_constant<int, 32>());
         else if (plan.small == 64)
-            lmhead_small_kernel<64, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
-        else if (plan.small && plan.blocks == 1)  // (few enough entries that the matrix is small for any usual d)
-            lmhead_small_kernel<128, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
-        else if (plan.small && past)
-            lmhead_small_kernel<128, 2, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
-        else if (plan.small)
-            lmhead_small_kernel<128, 2, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
+            small(std::integral_constant<int, 64>());
+        else if (plan.small == 128)
+            small(std::integral_constant<int, 128>());
         else
             lmhead_score_kernel<r, t><<<dim3((unsigned)(plan.n_tb * plan.splits)), block, 0, stream>>>(b, ws, plan);
     };

@@ -35,7 +35,7 @@ struct LmHeadPlan {
     int n_tb;    // token blocks of kLmTileT rows
     int n_vt;    // vocabulary tiles of kLmTileV entries
     int splits;  // vocabulary ranges
-    int small;   // token rows of the small-batch kernel's tile (64 or 128), 0: the 256 x 256 kernel
+    int small;   // token rows of the small-batch kernel's tile (32, 64 or 128), 0: the 256 x 256 kernel
     int blocks;  // small-batch kernel: blocks of 32 vocabulary entries per wave and tile (a tile has 128 entries for each)
     int n_tiles; // ... and how many such tiles there are
 };
@@ -47,14 +47,14 @@ inline LmHeadPlan lmhead_plan(int64_t N, int64_t V)
     p.n_vt = (int)((V + kLmTileV - 1) / kLmTileV);
     p.small = p.blocks = p.n_tiles = 0;
     // Up to 128 tokens the matrix instructions of the 256 x 256 tile are mostly padding and the LM-head matrix is read at
-    // half the speed of memory (64 tokens, V = 151,936, d = 4096: 375 us for the call, 247 with the small-batch kernel; 128
-    // tokens 398 / 242; 129 to 256 tokens stay: 424).  Up to 64 tokens two workgroups fit a compute unit; beyond, one, with
-    // tiles of 256 entries as long as those give every compute unit one.  Every range has the same number of tiles (but for
-    // the last), so that all workgroups end together.
+    // half the speed of memory (V = 151,936, d = 4096, whole call: 64 tokens 375 us, 204 with the small-batch kernel; 128
+    // tokens 398 / 240; 129 to 256 tokens stay: 424).  Tiles of 256 entries as long as those give every compute unit one
+    // (64 tokens: 204 us, 128-entry tiles, two workgroups to a compute unit: 245; V = 32,000, d = 2048: 49 / 39).  Every
+    // range has the same number of tiles (but for the last), so that all workgroups end together.
     if (N <= kLmSmallMost) {
-        p.small = N <= 64 ? 64 : 128;
-        p.blocks = p.small == 128 && V > 256 * 256 ? 2 : 1;
-        const int rows = 128 * p.blocks, most = p.small == 64 ? 512 : 256;
+        p.small = N <= 32 ? 32 : (N <= 64 ? 64 : 128);
+        p.blocks = V > 256 * 256 ? 2 : 1;
+        const int rows = 128 * p.blocks, most = p.blocks == 1 && p.small <= 64 ? 512 : 256;
         p.n_tiles = (int)((V + rows - 1) / rows);
         const int each = (p.n_tiles + most - 1) / most;
         p.splits = each > 0 ? (p.n_tiles + each - 1) / each : 1;

@@ -1,5 +1,5 @@
 """difr_lmhead_score at the sizes where its work split changes: token counts around the merge kernel's groups of 8 and the
-token tiles (64, 128 and 256 rows), vocabularies around a vocabulary tile (128 and 256 entries) and with more ranges than the merge has threads per token.  Every
+token tiles (32, 64, 128 and 256 rows), vocabularies around a vocabulary tile (128 and 256 entries) and with more ranges than the merge has threads per token.  Every
 row, every output, against the oracle, with the tolerances of test_gpu_lmhead.py (whose comparison helpers this uses)."""
 import numpy as np
 import pytest
@@ -22,7 +22,7 @@ def difr():
 
 @pytest.mark.parametrize("N,V,d", [(1, 1, 64), (1, 9000, 64), (7, 255, 64), (8, 256, 128), (9, 257, 64), (17, 8500, 128),
                                    (64, 1300, 192), (3, 128, 64), (33, 129, 64), (63, 385, 64), (64, 70000, 64), (65, 256, 128),
-                                   (66, 513, 64), (100, 70000, 64), (128, 1300, 192), (129, 1300, 64)])
+                                   (66, 513, 64), (32, 257, 64), (32, 70000, 64), (2, 66000, 128), (100, 70000, 64), (128, 1300, 192), (129, 1300, 64)])
 def test_every_output_at_split_edges(difr, N, V, d):
     wl = base._case(1, N, V, d, T=0.9)
     Wm = wl.weight(DEV)
