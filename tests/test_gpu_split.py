@@ -108,6 +108,51 @@ def test_shared_rows_score_as_whole_rows(difr, dtype, V, N):
     assert differ <= max(1, N // 20), differ      # near-ties of the CDF, about 1 row in 300 (tests against the oracle: parity.py)
 
 
+def test_capture_and_two_streams(difr):
+    """The workspace is the call's own: replays with new inputs and eager work in between, and two streams at once, give what
+    an eager call gives."""
+    N, V = 24, 65000
+    g = torch.Generator().manual_seed(3)
+    make = lambda: (torch.randn(N, V, generator=g) * 2.5).to(torch.bfloat16).to(DEV)
+    x, inputs = make(), [make() for _ in range(3)]
+    seeds = torch.tensor([5, 6], device=DEV)
+    sid, pos = (torch.arange(N, device=DEV) % 2).int(), torch.arange(N, device=DEV).int()
+    c = torch.randint(0, V, (N,), generator=g, dtype=torch.int32).to(DEV)
+
+    def step(logits):
+        return [t for part in difr.score_both(logits, 0.9, seeds, sid, pos, c, c, want_rank=True, want_token=True)
+                for t in part.values()]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step(x)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = step(x)
+    for other in inputs:
+        x.copy_(other)
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in captured]
+        eager = step(x)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(got, eager))
+    want = [step(i) for i in inputs[:2]]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    got = [[], []]
+    for _ in range(4):
+        for k, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[k].append(step(inputs[k]))
+    torch.cuda.synchronize()
+    for k in range(2):
+        for r in got[k]:
+            assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8)) for a, b in zip(r, want[k]))
+
+
 def test_what_difr_score_split_refuses(difr):
     from paper_2511_02620_amd import binding as B
     lib = difr.load_library()
