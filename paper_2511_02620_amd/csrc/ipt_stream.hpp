@@ -377,7 +377,8 @@ __device__ __forceinline__ bool ipt_row_rejected(const RowInfo &ri, int64_t row,
 // that lie wholly below the claimed token, wholly above it, and are full need no per-entry test:
 // the prefix is simply a snapshot of Z taken between the two groups of rounds.  Only the round
 // that holds the claimed token and the last, partly filled round look at indices.
-constexpr float kRefLift = 16.0f;  // see IptStream::terms()
+constexpr float kRefLift = 16.0f;         // see IptStream::terms()
+constexpr float kRefLeast = -0x1p31f;     // above it m8 * c is rounded by at most 64, and 2^64 does no harm
 
 template <int DT>
 struct IptStream {
@@ -437,7 +438,10 @@ struct IptStream {
                     // terms have to be exact; the many small ones below average their roundings out.
                     // A whole number, so that bringing sums taken against different references to a common one multiplies
                     // them by exact powers of two (lanes, parts of a split row).
-                    const float moved = -(ceilf(m8 * c) + kRefLift);
+                    // And no lower than kRefLeast: a vector of masked entries (the type's lowest value, -1e10) would put it
+                    // where m8 * c is infinite, or rounded by so much that 2^(x c - ref) overflows for m8 itself, and the
+                    // row's sum would be NaN once an unmasked entry moves it.
+                    const float moved = -fmaxf(ceilf(m8 * c) + kRefLift, kRefLeast);
                     Z *= (double)fast_exp2(moved - neg_mc);  // from the old rounded reference to the new one (see ipt_finish)
                     m = m8;
                     neg_mc = moved;
