@@ -190,7 +190,9 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
             const double o = __shfl_up(incl, off, 64);
             if (lane >= off) incl += o;
         }
-        const uint64_t hit = __builtin_amdgcn_ballot_w64(before + incl > target);  // the same in every wave
+        // (lanes without a wave sum, or with an empty one, hold the total in another order of addition: rounding must not
+        // let one of them pass alone.  The same in every wave.)
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(mine > 0.0 && before + incl > target);
         if (hit != 0ull) {
             const int f = __builtin_ctzll(hit);
             if (wave == f % kWaves) {
@@ -205,19 +207,21 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
                     if (lane >= off) in += o;
                 }
                 const uint64_t over = __builtin_amdgcn_ballot_w64(ls > 0.0 && start + in > target);
-                const uint64_t mass = __builtin_amdgcn_ballot_w64(ls > 0.0);
-                // (the two sums of the same terms may round apart: then the last vector with any mass)
-                const int l = over != 0ull ? __builtin_ctzll(over) : (mass != 0ull ? 63 - __builtin_clzll(mass) : 0);
+                const uint64_t mass = __builtin_amdgcn_ballot_w64(ls > 0.0);  // (not empty: the wave's sum was not)
+                // (the two sums of the same terms may round apart: then the last vector with any mass, and its last entry)
+                const int l = over != 0ull ? __builtin_ctzll(over) : 63 - __builtin_clzll(mass);
                 if (lane == l) {
                     double cacc = start + (in - ls);
-                    int32_t found = -1;
+                    int32_t found = -1, last = 0;
 #pragma unroll
                     for (int j = 0; j < E; ++j) {
                         cacc += (double)e[j];
-                        if (found < 0 && cacc > target) found = (int32_t)(base + j);
+                        if (e[j] > 0.0f) {  // (a masked entry, or one past the end of the row, owns no interval)
+                            last = j;
+                            if (found < 0 && cacc > target) found = j;
+                        }
                     }
-                    if (found < 0) found = (int32_t)((base + E - 1 < V) ? base + E - 1 : V - 1);
-                    w.tok = found;
+                    w.tok = (int32_t)base + (found < 0 ? last : found);
                 }
             }
             __syncthreads();
