@@ -18,9 +18,9 @@ namespace difr {
 // With the rank count the body needs 97 registers, one too many for five waves per SIMD; asked for five it fits in 96
 // without spills and runs 5% faster.  The other variants ask for one wave, which is no constraint.
 //
-// TOK: with the honest sampler's Token-IPT-DiFR token (ipt_stream.hpp).
-template <int DT, bool ADM, bool RANK, bool TOK, bool PEAKED = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || TOK ? 5 : 1))) void score_both_kernel(
+// TOK: how the honest sampler's Token-IPT-DiFR token is found (ipt_stream.hpp).
+template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || TOK != kNoToken ? 5 : 1))) void score_both_kernel(
     RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa)
 {
     typedef typename Elem<DT>::type elt_t;
@@ -31,8 +31,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || 
     __shared__ int32_t lds_rank[kWaves];
     __shared__ float lds_f[kWaves];
     __shared__ double lds_d[kWaves];
-    __shared__ double mark_Z[TOK ? kMarks : 1][kBlock];
-    __shared__ float mark_ref[TOK ? kMarks : 1][kBlock];
+    __shared__ double mark_Z[TOK == kTokenMarks ? kMarks : 1][kBlock];
+    __shared__ float mark_ref[TOK == kTokenMarks ? kMarks : 1][kBlock];
     __shared__ WalkScratch walk;
     __shared__ float adm_lists[ADM ? kWaves * kAdmCap : 1];
     __shared__ int32_t adm_fills[kWaves];
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || 
     ipt_finish<DT, TOK>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, marks, &walk);
 }
 
-template <int DT, bool TOK>
+template <int DT, int TOK>
 static void launch_score_both_of(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                                  bool peaked, hipStream_t stream)
 {
@@ -97,16 +97,17 @@ static void launch_score_both_of(const RowBatch &b, const int32_t *claimed_ipt, 
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                       bool peaked, hipStream_t stream)
 {
-    if (b.dtype == 0) {
-        if (oi.ipt_token)
-            launch_score_both_of<0, true>(b, claimed_ipt, og, oi, peaked, stream);
+    auto launch = [&](auto TOK) {
+        constexpr int tok = decltype(TOK)::value;
+        if (b.dtype == 0)
+            launch_score_both_of<0, tok>(b, claimed_ipt, og, oi, peaked, stream);
         else
-            launch_score_both_of<0, false>(b, claimed_ipt, og, oi, peaked, stream);
-    } else {
-        if (oi.ipt_token)
-            launch_score_both_of<1, true>(b, claimed_ipt, og, oi, peaked, stream);
-        else
-            launch_score_both_of<1, false>(b, claimed_ipt, og, oi, peaked, stream);
+            launch_score_both_of<1, tok>(b, claimed_ipt, og, oi, peaked, stream);
+    };
+    switch (token_search(oi.ipt_token, b.V, b.dtype)) {
+        case kNoToken: launch(std::integral_constant<int, kNoToken>()); break;
+        case kTokenWalk: launch(std::integral_constant<int, kTokenWalk>()); break;
+        case kTokenMarks: launch(std::integral_constant<int, kTokenMarks>()); break;
     }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
@@ -117,9 +118,9 @@ int launch_score_both_admissible(const RowBatch &b, const int32_t *claimed_ipt, 
     const dim3 grid((unsigned)b.N), block(kBlock);
     const AdmissibleOutputs oa{delta, count, log2_count};
     if (b.dtype == 0)
-        score_both_kernel<0, true, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        score_both_kernel<0, true, false, kNoToken><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
     else
-        score_both_kernel<1, true, false, false><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        score_both_kernel<1, true, false, kNoToken><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

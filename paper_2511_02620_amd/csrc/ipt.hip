@@ -7,22 +7,24 @@
 //
 // One workgroup per token row, one streaming pass; nothing of size V is stored.  Only when the
 // honest sampler's token is asked for and differs from the claim is the row read a second time.
+#include <type_traits>
+
 #include "difr_device.hpp"
 #include "difr_host.hpp"
 #include "ipt_stream.hpp"
 
 namespace difr {
 
-// Streaming kernel (the streaming state is described in ipt_stream.hpp).  TOK: with the honest sampler's token.
-template <int DT, bool TOK>
+// Streaming kernel (the streaming state is described in ipt_stream.hpp).  TOK: how the honest sampler's token is found.
+template <int DT, int TOK>
 __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutputs o)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
     __shared__ float lds_f[kWaves];
     __shared__ double lds_d[kWaves];
-    __shared__ double mark_Z[TOK ? kMarks : 1][kBlock];
-    __shared__ float mark_ref[TOK ? kMarks : 1][kBlock];
+    __shared__ double mark_Z[TOK == kTokenMarks ? kMarks : 1][kBlock];
+    __shared__ float mark_ref[TOK == kTokenMarks ? kMarks : 1][kBlock];
     __shared__ WalkScratch walk;
     __shared__ int32_t lds_rank[kWaves];
 
@@ -44,17 +46,18 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
         if (r0 >= r1) return;
         u32x4 q_next = load_round(x_row, r0);
         for (int round = r0; round < r1;) {
-            for (const int end = marks.stop(r1); round < end; ++round) {
-                const u32x4 q = q_next;
-                if (round + 1 < r1) q_next = load_round(x_row, round + 1);
-                s.fast_round(q);
-            }
-            marks.at(round, s);
+            const u32x4 q = q_next;
+            if (round + 1 < r1) q_next = load_round(x_row, round + 1);
+            s.fast_round(q);
+            marks.at(++round, s);
         }
     };
     auto careful = [&](int round, bool prefix_open) {
         u32x4 q = u32x4{0u, 0u, 0u, 0u};
-        if (s.has_vector(round)) q = load_vector<DT>(x_row, ((int64_t)round * kBlock + threadIdx.x) * E, V);
+        if (round < full_rounds)  // uniform
+            q = load_round(x_row, round);
+        else if (s.has_vector(round))
+            q = load_vector<DT>(x_row, ((int64_t)round * kBlock + threadIdx.x) * E, V);
         s.careful_round(q, round, prefix_open);
     };
 
@@ -79,16 +82,17 @@ int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_h
 {
     const dim3 grid((unsigned)b.N), block(kBlock);
     const IptOutputs o{dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags, logit_rank};
-    if (b.dtype == 0) {
-        if (ipt_token)
-            ipt_score_kernel<0, true><<<grid, block, 0, stream>>>(b, o);
+    auto launch = [&](auto TOK) {
+        constexpr int tok = decltype(TOK)::value;
+        if (b.dtype == 0)
+            ipt_score_kernel<0, tok><<<grid, block, 0, stream>>>(b, o);
         else
-            ipt_score_kernel<0, false><<<grid, block, 0, stream>>>(b, o);
-    } else {
-        if (ipt_token)
-            ipt_score_kernel<1, true><<<grid, block, 0, stream>>>(b, o);
-        else
-            ipt_score_kernel<1, false><<<grid, block, 0, stream>>>(b, o);
+            ipt_score_kernel<1, tok><<<grid, block, 0, stream>>>(b, o);
+    };
+    switch (token_search(ipt_token, b.V, b.dtype)) {
+        case kNoToken: launch(std::integral_constant<int, kNoToken>()); break;
+        case kTokenWalk: launch(std::integral_constant<int, kTokenWalk>()); break;
+        case kTokenMarks: launch(std::integral_constant<int, kTokenMarks>()); break;
     }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

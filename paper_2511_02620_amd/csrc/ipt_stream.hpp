@@ -98,8 +98,21 @@ __device__ double gaussian_log_mass(double a, double b, double u, double sigma, 
 constexpr int kMarks = 6;
 constexpr int kWalkRounds = 16;  // rounds summed between two barriers of the walk: 16 x 4 wave sums, one per lane
 static_assert(kWalkRounds * kWaves == 64, "the walk scans one wave sum per lane");
+// Full rounds from which a row has marks; a shorter one is walked from its start (ipt_walk_short), which needs fewer steps
+// than bringing the marks to the total.  Calls without claims, walk against marks, us: 2 rounds (16,384 x 4096 bf16) 74 / 113;
+// 15 rounds (4096 x 32,000 bf16) 85 / 88; 24 rounds (4096 x 25,000 fp32) 121 / 112; 31 rounds (4096 x 32,000 fp32) 151 / 127.
+// The kernels are instantiated for either, so that short rows carry neither the marks' LDS nor their code (16,384 x 4096 fp32,
+// both scores with the token, honest claims: 131 us with one kernel for both, 128 apart).
+constexpr int kMarkLeast = 16;
+enum TokenSearch { kNoToken = 0, kTokenWalk = 1, kTokenMarks = 2 };
 
-template <bool TOK>
+inline TokenSearch token_search(const int32_t *ipt_token, int64_t V, int dtype)
+{
+    if (ipt_token == nullptr) return kNoToken;
+    return V / ((dtype == 0 ? 8 : 4) * kBlock) < kMarkLeast ? kTokenWalk : kTokenMarks;
+}
+
+template <int TOK>
 struct IptMarks {
     double (*Z)[kBlock];   // [kMarks][kBlock]
     float (*ref)[kBlock];  // [kMarks][kBlock]
@@ -108,14 +121,12 @@ struct IptMarks {
     __device__ __forceinline__ IptMarks(double (*Z_)[kBlock], float (*ref_)[kBlock], int full_rounds)
         : Z(Z_), ref(ref_), len((full_rounds + kMarks - 1) / kMarks), next(len), n(0)
     {
-        if (len == 0) next = 0x7FFFFFFF;
     }
-    __device__ __forceinline__ int stop(int r_end) const { return TOK ? min(r_end, next) : r_end; }
     // `round` rounds of the row have been summed
     template <class Stream>
     __device__ __forceinline__ void at(int round, const Stream &s)
     {
-        if constexpr (TOK) {
+        if constexpr (TOK == kTokenMarks) {
             if (round == next) {  // (n < kMarks: kMarks * len >= full_rounds, and no full round follows the last mark)
                 Z[n][threadIdx.x] = s.Z;
                 ref[n][threadIdx.x] = s.ref();
@@ -232,6 +243,52 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
     return -1;
 }
 
+// The same for a row of few rounds, from its start: one scan over the workgroup's 256 vectors per round.
+template <int DT>
+__device__ __forceinline__ int32_t ipt_walk_short(const typename Elem<DT>::type *x_row, int64_t V, float c, float neg_Mc,
+                                                  double target, WalkScratch &w)
+{
+    constexpr int E = Elem<DT>::kPerVec;
+    const int tid = threadIdx.x;
+    double before = 0.0;
+    if (tid == 0) w.tok = -1;
+    for (int64_t v0 = 0; v0 < V; v0 += kBlock * E) {
+        const int64_t base = v0 + tid * E;
+        float e[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) e[j] = 0.0f;
+        if (base < V) {
+            float x[E];
+            unpack_vector<DT>(load_vector<DT>(x_row, base, V), x);
+#pragma unroll
+            for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
+        }
+        const double ls = (double)tree_sum<E>(e);
+        double total;
+        const double incl = block_inclusive_scan(ls, w.round_sum, total);
+        if (before + total > target) {  // uniform: the token is inside this round
+            const double excl = before + (incl - ls);
+            if (ls > 0.0 && excl <= target && before + incl > target) {  // one thread
+                double cacc = excl;
+                int32_t found = -1, last = 0;
+#pragma unroll
+                for (int j = 0; j < E; ++j) {
+                    cacc += (double)e[j];
+                    if (e[j] > 0.0f) {
+                        last = j;
+                        if (found < 0 && cacc > target) found = j;
+                    }
+                }
+                w.tok = (int32_t)base + (found < 0 ? last : found);
+            }
+            break;
+        }
+        before += total;
+    }
+    __syncthreads();
+    return w.tok;
+}
+
 // Everything after the streaming pass: combine the partial (reference, sum) pairs, regenerate u,
 // form the interval and the distance, optionally search the honest sampler's token, write outputs.
 struct IptOutputs {
@@ -329,14 +386,15 @@ __device__ __forceinline__ IptTotals ipt_combine(float ref, double Z, double P, 
     return t;
 }
 
-template <int DT, bool TOK>
+template <int DT, int TOK>
 __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
                                            const typename Elem<DT>::type *x_row, float c, float ref, double Z,
                                            double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
                                            double *lds_d, const IptMarks<TOK> &marks, WalkScratch *walk)
 {
     const IptTotals t = ipt_combine(ref, Z, P, refP, lds_f, lds_d);
-    ipt_write<DT, TOK>(b, ri, row, x_row, c, t.M, t.Z, t.P, above, o, [&](double target) {
+    ipt_write<DT, TOK != kNoToken>(b, ri, row, x_row, c, t.M, t.Z, t.P, above, o, [&](double target) {
+        if constexpr (TOK == kTokenWalk) return ipt_walk_short<DT>(x_row, b.V, c, -t.M, target, *walk);
         const int tid = threadIdx.x;
         for (int k = 0; k < marks.n; ++k) {
             double v = marks.Z[k][tid] * (double)fast_exp2(marks.ref[k][tid] - t.M);

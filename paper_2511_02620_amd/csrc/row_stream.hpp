@@ -30,7 +30,7 @@ struct NoIpt {
 
 // Full rounds [r0, r1) of the row (256 complete vectors each), and with them, if `last`, what the row holds beyond its full
 // rounds.  r1 is the number of full rounds then.
-template <int DT, bool TOK, class G, class S>
+template <int DT, int TOK, class G, class S>
 __device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, const typename Elem<DT>::type *x_row, int64_t V,
                                               int r0, int r1, bool last)
 {
@@ -51,6 +51,7 @@ __device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, 
             g.template process<MODE>(q, round, true);
             s.fast_round(q);
             ++round;
+            marks.at(round, s);
             if ((round & 15) == 0) g.pickup();
             return round < r_end && g.gate.mode == MODE;
         };
@@ -66,14 +67,12 @@ __device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, 
     };
     auto run_to = [&](int r_end) {
         while (round < r_end) {
-            const int stop = marks.stop(r_end);
             if (g.gate.mode == 0)
-                run_rounds(std::integral_constant<int, 0>(), stop);
+                run_rounds(std::integral_constant<int, 0>(), r_end);
             else if (g.gate.mode == 1)
-                run_rounds(std::integral_constant<int, 1>(), stop);
+                run_rounds(std::integral_constant<int, 1>(), r_end);
             else
-                run_rounds(std::integral_constant<int, 2>(), stop);
-            marks.at(round, s);
+                run_rounds(std::integral_constant<int, 2>(), r_end);
         }
     };
     // a round in which the IPT stream must look at indices (it holds the claimed token, or it is ragged)

@@ -1,6 +1,6 @@
 """The search for the honest sampler's Token-IPT-DiFR token: marks left in the stream, then a walk from one of them.  Rows
-with no full round, fewer rounds than marks, marks that fall on and beside the end of the full rounds, and more rounds than one
-batch of the walk, with the mass in the first entries, in the last ones and everywhere, with and without a claim that splits the
+with no full round, the rounds below which a row has no marks and the row is walked from its start, marks that fall on and
+beside the end of the full rounds, and more rounds than one batch of the walk, with the mass in the first entries, in the last ones and everywhere, with and without a claim that splits the
 stream; every token against the oracle (a token that differs must own an interval within 1e-6 of u: parity.TIE_REL)."""
 import numpy as np
 import pytest
@@ -22,8 +22,8 @@ def difr():
 
 @pytest.mark.parametrize("dtype,rounds,extra", [
     (dt, r, e) for dt in (torch.bfloat16, torch.float32)
-    for r, e in ((0, 1), (0, 9), (1, -1), (1, 0), (1, 1), (5, 0), (6, 0), (6, 1), (7, -1), (7, 8), (12, 0), (13, 9), (18, 0),
-                 (50, 1021))])
+    for r, e in ((0, 1), (0, 9), (1, -1), (1, 0), (1, 1), (5, 0), (6, 0), (6, 1), (7, -1), (7, 8), (12, 0), (13, 9), (15, 9), (16, -1), (16, 0),
+                 (16, 1), (18, 0), (50, 1021))])
 def test_sampled_token_is_the_oracles(difr, dtype, rounds, extra):
     per = 256 * 16 // torch.tensor([], dtype=dtype).element_size()
     V, N, S = rounds * per + extra, 24, 4
