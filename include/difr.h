@@ -88,8 +88,9 @@ typedef enum { DIFR_BF16 = 0, DIFR_F32 = 1 } difr_dtype;
 #define DIFR_FLAG_NONFINITE 4u     /* a NaN or +inf logit was seen in the row; the     */
                                    /* row's other outputs are unspecified.  -inf is    */
                                    /* a legal "masked" entry: zero probability, never  */
-                                   /* the argmax.  difr_gumbel_score treats a NaN with */
-                                   /* its sign bit set like -inf (masked, not flagged) */
+                                   /* the argmax.  On bf16 rows that start on 16 bytes */
+                                   /* a Token-DiFR score treats a NaN with its sign    */
+                                   /* bit set like -inf (masked, need not be flagged)  */
 #define DIFR_FLAG_SLOW_PATH 8u     /* informational: the row left the streaming fast   */
                                    /* path (re-read of the row)                        */
 

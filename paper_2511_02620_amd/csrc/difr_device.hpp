@@ -39,6 +39,12 @@ struct RowBatch {
     const int32_t *claimed;
 };
 
+// Every row starts on 16 bytes.
+__host__ __device__ inline bool rows_aligned(const RowBatch &b)
+{
+    return (((uint64_t)b.logits | (uint64_t)b.ld * (b.dtype == 0 ? 2u : 4u)) & 15u) == 0;
+}
+
 // ---------------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11).  One round:
 //   (c0,c1,c2,c3) <- (hi(M1 c2)^c1^k0, lo(M1 c2), hi(M0 c0)^c3^k1, lo(M0 c0)),

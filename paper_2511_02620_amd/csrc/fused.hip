@@ -67,6 +67,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || 
     IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
     stream_rounds<DT, TOK>(g, s, marks, x_row, V, 0, full_rounds, true);
+    if (DT == 0 && !ADM && !rows_aligned(b)) g.bad_sum(s.Z);  // (the admissible set is counted on aligned rows only)
     g.finish(row, og, lds_y, lds_i, lds_rank);
     if (ADM) {
         const float M = g.best_y;  // the row maximum, in every thread

@@ -104,9 +104,10 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float 
     }
 }
 
-// Filtered streaming kernel (the filter is described in gumbel_stream.hpp).
-template <int DT, bool RANK>
-__global__ __launch_bounds__(kBlock) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o)
+// Filtered streaming kernel (the filter is described in gumbel_stream.hpp).  NANS: for bf16 rows that do not start on 16
+// bytes; the compiler would take 81 registers, one too many for six waves per SIMD, and is asked for six (no spills).
+template <int DT, bool RANK, bool NANS>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6 : 1))) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_filtered_kernel(RowBatch 
     const elt_t *x_row = reinterpret_cast<const elt_t *>(b.logits) + row * b.ld;
     const int64_t V = b.V;
 
-    GumbelStream<DT, RANK> g(ri, x_row, V, lds_L);
+    GumbelStream<DT, RANK, false, false, false, false, NANS> g(ri, x_row, V, lds_L);
     __syncthreads();
 
     const int64_t nvec = V / E;               // full vectors; the last V % E entries are the tail
@@ -228,17 +229,19 @@ int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t
     const dim3 grid((unsigned)b.N), block(kBlock);
     const GumbelOutputs o{margin, argmax, max_score, claimed_score, flags, logit_rank};
     if (filtered) {
-        if (b.dtype == 0) {
-            if (logit_rank)
-                gumbel_score_filtered_kernel<0, true><<<grid, block, 0, stream>>>(b, o);
+        auto launch = [&](auto RANK) {
+            constexpr bool rank = decltype(RANK)::value;
+            if (b.dtype != 0)
+                gumbel_score_filtered_kernel<1, rank, false><<<grid, block, 0, stream>>>(b, o);
+            else if (rows_aligned(b))
+                gumbel_score_filtered_kernel<0, rank, false><<<grid, block, 0, stream>>>(b, o);
             else
-                gumbel_score_filtered_kernel<0, false><<<grid, block, 0, stream>>>(b, o);
-        } else {
-            if (logit_rank)
-                gumbel_score_filtered_kernel<1, true><<<grid, block, 0, stream>>>(b, o);
-            else
-                gumbel_score_filtered_kernel<1, false><<<grid, block, 0, stream>>>(b, o);
-        }
+                gumbel_score_filtered_kernel<0, rank, true><<<grid, block, 0, stream>>>(b, o);
+        };
+        if (logit_rank)
+            launch(std::true_type());
+        else
+            launch(std::false_type());
     } else if (b.dtype == 0) {
         gumbel_score_kernel<0><<<grid, block, 0, stream>>>(b, margin, argmax, max_score, claimed_score, flags, logit_rank);
     } else {

@@ -177,12 +177,19 @@ __device__ __forceinline__ void gumbel_write(int64_t row, const GumbelOutputs &o
 // concentrated than a Zipf profile (a confident model's) most rounds go that way and the stream runs at the speed
 // of reading them; on flat rows the test never fires and costs a few per cent (the noise generation can no longer
 // start before the vector has arrived), which is why it is a variant the caller asks for.  Same outputs, bit for bit.
+//
+// NANS (bf16): flag every NaN.  A bf16 NaN with its sign bit set counts as -inf in the tests above and is met only where a
+// vector is looked at for another reason (fp32 compares gate every NaN in); rows that do not start on 16 bytes are promised more
+// (every NaN of theirs is flagged), and the largest bit patterns of all vectors tell: four packed maxima per vector, 77 / 79
+// us on 1500 packed rows of 99,991 logits.  Where the softmax sum is formed beside this stream it shows every NaN, and no variant
+// is needed (bad_sum()).
 constexpr int kAdmCap = 1024;  // list entries per wave
 constexpr int kDeferCap = 128; // TOPN streams: queue slots per wave (fewer than 64 waiting + at most 64 new ones)
 
-template <int DT, bool RANK, bool COUNT = false, bool TOPN = false, bool ADM = false, bool PEAKED = false>
+template <int DT, bool RANK, bool COUNT = false, bool TOPN = false, bool ADM = false, bool PEAKED = false, bool NANS = false>
 struct GumbelStream {
     static_assert(!PEAKED || (!COUNT && !TOPN && !ADM), "the early test is kept up to date for the plain argmax stream only");
+    static_assert(!NANS || DT == 0, "fp32 rows flag every NaN as they are");
     typedef typename Elem<DT>::type elt_t;
     static constexpr int E = Elem<DT>::kPerVec;
 
@@ -204,6 +211,7 @@ struct GumbelStream {
     float best_y;
     int32_t best_v;
     uint32_t bad, above;
+    uint32_t pattern_max;  // NANS: largest bit patterns of the even and of the odd entries met, as unsigned
     // COUNT mode
     float count_M, count_delta;
     uint32_t count;
@@ -248,6 +256,7 @@ struct GumbelStream {
         best_y = -__builtin_inff();
         best_v = 0x7FFFFFFF;
         bad = 0;
+        pattern_max = 0u;
         // M0 * (Philox counter word 0) = M0 * (round's first block) + M0 * (lane's block offset): the
         // second term never changes, the first is scalar, and the sum cannot wrap (counter < 2^29).
         lane_prod = (uint64_t)kPhiloxM0 * (uint32_t)(tid * (E / 4));
@@ -490,6 +499,12 @@ struct GumbelStream {
     template <int MODE>
     __device__ __forceinline__ void process(u32x4 q, int round, bool active, TopN *top = nullptr)
     {
+        if (NANS) {  // (a lane without a vector holds zeros)
+            u16x2 m = __builtin_elementwise_max(as_u16x2(q.x), as_u16x2(q.y));
+            m = __builtin_elementwise_max(m, as_u16x2(q.z));
+            m = __builtin_elementwise_max(m, as_u16x2(q.w));
+            pattern_max = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(m, as_u16x2(pattern_max)));
+        }
         if (PEAKED) {
             bool reach;
             if (DT == 0) {
@@ -662,6 +677,9 @@ struct GumbelStream {
                 __builtin_amdgcn_ballot_w64(v < V && Elem<DT>::to_float(x_row[v < V ? v : 0]) > xt));
     }
 
+    // the softmax sum of the entries this thread has streamed (of any reference): not a number if one of them was a NaN
+    __device__ __forceinline__ void bad_sum(double Z) { bad |= (uint32_t)!(Z == Z); }
+
     // block reduction: afterwards best_y / best_v are the row's in every thread, and in thread 0 the result holds
     // whether a NaN or +inf was seen and (RANK) the number of entries above the claim
     struct Reduced {
@@ -672,6 +690,7 @@ struct GumbelStream {
     {
         block_argmax(best_y, best_v, lds_y, lds_i);
         if (RANK && (tid & 63) == 0) lds_rank[wave] = (int32_t)above;
+        if (NANS) bad |= (uint32_t)(max(pattern_max & 0xFFFFu, pattern_max >> 16) > 0xFF80u);
         Reduced r;
         r.any_bad = __syncthreads_or((int)bad);
         r.above = RANK && tid == 0 ? lds_rank[0] + lds_rank[1] + lds_rank[2] + lds_rank[3] : 0;

@@ -38,7 +38,8 @@ struct SplitWorkspace {
 // rows [first, end) of the part's full rounds
 __device__ __forceinline__ int part_begin(int part, int parts, int full_rounds) { return (int)((int64_t)part * full_rounds / parts); }
 
-template <int DT, bool GUM, bool IPT, bool ADM, bool RANK>
+// NANS (Token-DiFR alone): bf16 rows that do not start on 16 bytes (gumbel_stream.hpp).
+template <int DT, bool GUM, bool IPT, bool ADM, bool RANK, bool NANS>
 __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const int32_t *__restrict__ claimed_ipt, bool ipt_rank,
                                                             float delta, SplitWorkspace ws)
 {
@@ -72,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
     double out_Z = 0.0, out_P = 0.0;
     int32_t best_v = 0, above = 0, any_bad = 0, adm_n = 0;
 
-    typedef GumbelStream<DT, RANK, false, false, ADM> G;
+    typedef GumbelStream<DT, RANK, false, false, ADM, false, NANS> G;
     if constexpr (GUM) {
         G g(ri, x_row, V, lds_L);
         __syncthreads();
@@ -111,6 +112,7 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
         if constexpr (IPT) {
             IptStream<DT> s(ri_ipt, x_row, V, false);
             stream_rounds<DT, kNoToken>(g, s, marks, x_row, V, r0, r1, last);
+            if (DT == 0 && !ADM && !rows_aligned(b)) g.bad_sum(s.Z);
             gumbel_done();
             const IptTotals t = ipt_combine(s.ref(), s.Z, s.P, s.refP(), lds_f, lds_d);
             out_M = t.M;
@@ -268,11 +270,11 @@ size_t split_workspace_bytes(int64_t N, int parts, bool admissible)
     return (size_t)N * (size_t)parts * (sizeof(Partial) + (admissible ? kSplitAdmCap * sizeof(float) : 0));
 }
 
-template <int DT, bool GUM, bool IPT, bool ADM, bool RANK>
+template <int DT, bool GUM, bool IPT, bool ADM, bool RANK, bool NANS>
 static int launch_of(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                      const AdmissibleOutputs &oa, const SplitWorkspace &ws, hipStream_t stream)
 {
-    score_part_kernel<DT, GUM, IPT, ADM, RANK><<<dim3((unsigned)(b.N * ws.parts)), dim3(kBlock), 0, stream>>>(
+    score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS><<<dim3((unsigned)(b.N * ws.parts)), dim3(kBlock), 0, stream>>>(
         b, claimed_ipt, oi.logit_rank != nullptr, oa.delta, ws);
     if (hipGetLastError() != hipSuccess) return 1;
     if (IPT && !ADM && oi.ipt_token)
@@ -286,15 +288,20 @@ template <int DT>
 static int launch_for(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                       const AdmissibleOutputs &oa, const SplitWorkspace &ws, hipStream_t stream)
 {
+    auto launch = [&](auto GUM, auto IPT, auto ADM, auto RANK, auto NANS) {
+        return launch_of<DT, decltype(GUM)::value, decltype(IPT)::value, decltype(ADM)::value, decltype(RANK)::value, decltype(NANS)::value>(
+            b, claimed_ipt, og, oi, oa, ws, stream);
+    };
+    const std::true_type yes;
+    const std::false_type no;
     const bool rank = og.logit_rank != nullptr;
-    if (oa.count) return launch_of<DT, true, true, true, false>(b, claimed_ipt, og, oi, oa, ws, stream);
-    if (og.margin && oi.dist)
-        return rank ? launch_of<DT, true, true, false, true>(b, claimed_ipt, og, oi, oa, ws, stream)
-                    : launch_of<DT, true, true, false, false>(b, claimed_ipt, og, oi, oa, ws, stream);
-    if (og.margin)
-        return rank ? launch_of<DT, true, false, false, true>(b, claimed_ipt, og, oi, oa, ws, stream)
-                    : launch_of<DT, true, false, false, false>(b, claimed_ipt, og, oi, oa, ws, stream);
-    return launch_of<DT, false, true, false, false>(b, claimed_ipt, og, oi, oa, ws, stream);
+    if (oa.count) return launch(yes, yes, yes, no, no);
+    if (og.margin && oi.dist) return rank ? launch(yes, yes, no, yes, no) : launch(yes, yes, no, no, no);
+    if constexpr (DT == 0) {
+        if (og.margin && !rows_aligned(b)) return rank ? launch(yes, no, no, yes, yes) : launch(yes, no, no, no, yes);
+    }
+    if (og.margin) return rank ? launch(yes, no, no, yes, no) : launch(yes, no, no, no, no);
+    return launch(no, yes, no, no, no);
 }
 
 int launch_score_split(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
