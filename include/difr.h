@@ -376,7 +376,9 @@ int difr_score_both_admissible(const difr_rows *in, const int32_t *claimed_ipt, 
  *         fp64 interval).
  * workspace  DEVICE scratch of at least difr_lmhead_workspace_bytes(N, V, d, ipt_token != NULL)
  *         bytes, 8-byte aligned, owned by the caller, contents irrelevant before and after the call;
- *         calls that overlap in time need distinct workspaces.  Too small: DIFR_ERR_SHAPE.
+ *         calls that overlap in time need distinct workspaces.  Too small: DIFR_ERR_SHAPE (up to 128
+ *         tokens a little less than that size is taken too, down to 32 bytes per token for each of
+ *         min(256, ceil(V / 256)) ranges, and the vocabulary is then cut into fewer ranges).
  * Three kernels are enqueued on hip_stream (claim bound, GEMM + scoring, merge), four with ipt_token; no sync.
  */
 typedef struct {
@@ -394,7 +396,8 @@ typedef struct {
 } difr_lmhead;
 
 /* Host only, no device needed.  0 for N == 0 or arguments difr_lmhead_score would reject.
- * want_ipt_token != 0: with room for what the ipt_token output needs. */
+ * want_ipt_token != 0: with room for what the ipt_token output needs.  The size for a batch of up to
+ * 256 tokens serves every smaller batch of the same V and outputs too. */
 size_t difr_lmhead_workspace_bytes(int64_t N, int64_t V, int64_t d, int32_t want_ipt_token);
 
 int difr_lmhead_score(const difr_lmhead *in, float *margin, int32_t *argmax, float *max_score, float *claimed_score,

@@ -128,8 +128,7 @@ extern "C" {
 size_t difr_lmhead_workspace_bytes(int64_t N, int64_t V, int64_t d, int32_t want_ipt_token)
 {
     if (N <= 0 || V <= 0 || d <= 0 || N >= (int64_t)1 << 31 || V >= (int64_t)1 << 31) return 0;
-    const difr::LmHeadPlan plan = difr::lmhead_plan(N, V);
-    return difr::lmhead_workspace_bytes(N, plan.splits, plan.n_vt, want_ipt_token != 0);
+    return difr::lmhead_workspace_named(N, V, want_ipt_token != 0);
 }
 
 int difr_lmhead_score(const difr_lmhead *in, float *margin, int32_t *argmax, float *max_score, float *claimed_score,
@@ -143,10 +142,10 @@ int difr_lmhead_score(const difr_lmhead *in, float *margin, int32_t *argmax, flo
     if (log_mass && (!(sigma > 0.0) || !isfinite(sigma) || !(eps >= 0.0) || !isfinite(eps))) return DIFR_ERR_ARGUMENT;
     if (b.N == 0) return DIFR_OK;
     if (!margin || !argmax || !flags_gumbel || !dist || !flags_ipt || !workspace) return DIFR_ERR_NULL;
-    const difr::LmHeadPlan plan = difr::lmhead_plan(b.N, b.V);
+    difr::LmHeadPlan plan = difr::lmhead_plan(b.N, b.V);
     if ((uintptr_t)workspace % 8u) return DIFR_ERR_ALIGN;
     const bool tok = ipt_token != nullptr;
-    if (workspace_bytes < difr::lmhead_workspace_bytes(b.N, plan.splits, plan.n_vt, tok)) return DIFR_ERR_SHAPE;
+    if (!difr::lmhead_fit(plan, b.N, workspace_bytes, tok)) return DIFR_ERR_SHAPE;
     if ((rc = check_device()) != DIFR_OK) return rc;
     const difr::LmHeadWorkspace ws = difr::lmhead_carve(workspace, b.N, plan.splits, plan.n_vt, tok);
     const difr::GumbelOutputs og{margin, argmax, max_score, claimed_score, flags_gumbel, logit_rank};

@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace difr {
 
 constexpr int kLmTileV = 256;  // vocabulary entries per workgroup tile
@@ -92,6 +94,30 @@ inline size_t lmhead_workspace_bytes(int64_t N, int splits, int n_vt = 0, bool w
     size_t bytes = (size_t)N * (size_t)splits * (8 + 8 + 4 + 4 + 4 + 4) + (size_t)N * 16 + 64;
     if (want_token) bytes += (size_t)N * (size_t)n_vt * 16 + (size_t)N * 16;
     return bytes;
+}
+
+// The size the library names for a batch.  A smaller batch may be cut into more ranges (up to 512 instead of 256 up to 64 tokens),
+// so its need can be the larger one; a caller that sizes once for its largest batch gets room for the smaller ones too.
+inline size_t lmhead_workspace_named(int64_t N, int64_t V, bool want_token)
+{
+    size_t most = 0;
+    for (const int64_t n : {N, N < 64 ? N : (int64_t)64, N < kLmSmallMost ? N : kLmSmallMost}) {
+        const LmHeadPlan p = lmhead_plan(n, V);
+        const size_t bytes = lmhead_workspace_bytes(n, p.splits, p.n_vt, want_token);
+        if (bytes > most) most = bytes;
+    }
+    return most;
+}
+
+// A small batch in a smaller workspace is cut into fewer ranges, down to the 256 (or one per 256 entries) that the 256 x 256 kernel
+// would take.  False: not enough for those either.
+inline bool lmhead_fit(LmHeadPlan &p, int64_t N, size_t bytes, bool want_token)
+{
+    if (p.small) {
+        const int least = p.n_vt < 256 ? p.n_vt : 256;
+        while (p.splits > least && bytes < lmhead_workspace_bytes(N, p.splits, p.n_vt, want_token)) --p.splits;
+    }
+    return bytes >= lmhead_workspace_bytes(N, p.splits, p.n_vt, want_token);
 }
 
 inline LmHeadWorkspace lmhead_carve(void *base, int64_t N, int splits, int n_vt = 0, bool want_token = false)
