@@ -203,6 +203,8 @@ int difr_score_both_peaked(const difr_rows *in, const int32_t *claimed_ipt, floa
  * required, no optional output but log2_count, rows aligned to 16 bytes); meaning, layout and optionality as in
  * difr_gumbel_score, difr_ipt_score and difr_score_both_admissible.  The Token-DiFR outputs and the counts equal those
  * calls' bit for bit (and a count is never -1); the Token-IPT-DiFR sums are formed in another order, equal to fp32 rounding.
+ * Rows known to be concentrated are better given to difr_score_both_peaked from some 300 of them on: the noise of shared
+ * rows is regenerated for every vector.
  * in->claimed are the Token-DiFR claims, claimed_ipt the Token-IPT-DiFR ones.  The workspace is 8-byte aligned, needs no
  * initial contents and may be reused once the call's work is done.
  */

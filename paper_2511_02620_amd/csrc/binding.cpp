@@ -284,20 +284,28 @@ PyObject *ipt_score(PyObject *const *a)
                }), o);
 }
 
+// Most peaked rows that are shared.  Shared rows regenerate the noise of all their vectors, the peaked kernel that of few, and is
+// the faster one once the rows by themselves keep most of the chip busy.  Logits falling as -3 ln rank, T = 0.6, peaked kernel /
+// shared rows, us: V = 151,936 256 rows 42.6 / 34.0, 384 rows 46.5 / 45.5, 512 rows 46.9 / 52.7, 740 rows 52 / 69; V = 100,000
+// 256 rows 33.4 / 29.3, 384 rows 35.2 / 36.3; V = 65,000 256 rows 25.5 / 24.5, 310 rows 26.9 / 27.3.
+constexpr int64_t kPeakedShared = 320;
+
 // rows, claimed_ipt, peaked, want_rank, want_token, want_log_mass, sigma, eps
 PyObject *score_both(PyObject *const *a)
 {
     Rows r(a);
     a += kRowArgs;
     const int32_t *ci = (const int32_t *)vec_or_null(a[0], at::kInt, r.N, r.dev);
-    const auto entry = truth(a[1]) ? lib.difr_score_both_peaked : lib.difr_score_both;
+    const bool peaked = truth(a[1]);
+    const auto entry = peaked ? lib.difr_score_both_peaked : lib.difr_score_both;
     const double sigma = number(a[5]), eps = number(a[6]);
     GumbelSide g(r.dev, r.N, truth(a[2]));
     IptSide i(r.dev, r.N, false);
     if (truth(a[3])) i.token = i.out.i32(key::ipt_token, r.N);
     if (truth(a[4])) i.log_mass = i.out.f32(key::log_mass, r.N);
     int rc;
-    if (split(r, ci, both_sides(g, i, sigma, eps), &rc)) return two(rc, g.out, i.out);
+    const bool whole = peaked && !g.rank && r.N > kPeakedShared;  // (with the rank the peaked call is the ordinary one)
+    if (!whole && split(r, ci, both_sides(g, i, sigma, eps), &rc)) return two(rc, g.out, i.out);
     return two(enter(r.dev, [&](void *s) {
                    return entry(&r.in, ci, g.margin, g.argmax, g.max_score, g.claimed_score, g.flags, g.rank, i.dist, i.cdf_lo,
                                 i.cdf_hi, i.u, i.token, sigma, eps, i.log_mass, i.flags, s);

@@ -178,3 +178,32 @@ def test_what_difr_score_split_refuses(difr):
     assert call(count=p, delta=1.0, dist=p, flags_ipt=p) == NULL and call(rank_ipt=p, **full) == ARG
     torch.cuda.synchronize()
     assert int(buf.sum()) == 0
+
+
+@pytest.mark.parametrize("N,shared", [(320, True), (321, False)])
+def test_peaked_rows_are_shared_up_to_a_line(difr, N, shared):
+    """Beyond some rows the peaked kernel is the faster one for them: the call then gives its bits, below the line those of
+    difr_score_both on shared rows."""
+    from paper_2511_02620_amd import binding as B
+    lib, V = difr.load_library(), 151936
+    assert lib.difr_split_workspace_bytes(N, V, 0, 0) > 0
+    g = torch.Generator(device=DEV).manual_seed(N)
+    x = torch.empty(N, V, dtype=torch.bfloat16, device=DEV)
+    x.copy_(-3.0 * torch.log1p(torch.randperm(V, generator=g, device=DEV).float()) + torch.randn(N, V, generator=g, device=DEV))
+    seeds = torch.tensor([5, 6], device=DEV)
+    sid, pos = (torch.arange(N, device=DEV) % 2).int(), torch.arange(N, device=DEV).int()
+    c = torch.randint(0, V, (N,), generator=g, device=DEV, dtype=torch.int32)
+    got = difr.score_both_peaked(x, 0.6, seeds, sid, pos, c, c)
+    whole = {k: torch.empty_like(v) for k, v in (got[0] | {"flags_ipt": got[1]["flags"]} | got[1]).items()}
+    whole["flags_g"] = torch.empty_like(got[0]["flags"])
+    r, _, dev = B._rows(x, None, 0.6, seeds, sid, pos, c, None)
+    p = lambda k: C.c_void_p(whole[k].data_ptr())
+    assert lib.difr_score_both_peaked(C.byref(r), c.data_ptr(), p("margin"), p("argmax"), p("max_score"), p("claimed_score"),
+                                      p("flags_g"), None, p("dist"), p("cdf_lo"), p("cdf_hi"), p("u"), None, 0.01, 1e-30, None,
+                                      p("flags_ipt"), B._stream_ptr(dev)) == 0
+    _same(got[0], {k: whole["flags_g" if k == "flags" else k] for k in got[0]}, "peaked")
+    _near(got[1], {k: whole["flags_ipt" if k == "flags" else k] for k in got[1]}, "peaked")
+    bits = lambda t: t.view(torch.int32)
+    assert torch.equal(bits(got[1]["cdf_lo"]), bits(whole["cdf_lo"])) == (not shared)
+    both = difr.score_both(x, 0.6, seeds, sid, pos, c, c)
+    assert torch.equal(bits(got[1]["cdf_lo"]), bits(both[1]["cdf_lo"])) == shared
