@@ -43,13 +43,13 @@ def _same(a, b, what):
         assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), (what, k)
 
 
-def _near(a, b, what):
+def _near(a, b, what, tol=2e-7):
     for k in a:
         x, y = a[k], b[k]
         if k in ("u", "flags"):
             assert torch.equal(x & ~9, y & ~9) if k == "flags" else torch.equal(x.view(torch.int32), y.view(torch.int32)), (what, k)
         elif k in ("dist", "cdf_lo", "cdf_hi"):
-            assert torch.equal(x.isnan(), y.isnan()) and float((x - y).nan_to_num().abs().max()) <= 2e-7, (what, k)
+            assert torch.equal(x.isnan(), y.isnan()) and float((x - y).nan_to_num().abs().max()) <= tol, (what, k)
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
@@ -202,7 +202,9 @@ def test_peaked_rows_are_shared_up_to_a_line(difr, N, shared):
                                       p("flags_g"), None, p("dist"), p("cdf_lo"), p("cdf_hi"), p("u"), None, 0.01, 1e-30, None,
                                       p("flags_ipt"), B._stream_ptr(dev)) == 0
     _same(got[0], {k: whole["flags_g" if k == "flags" else k] for k in got[0]}, "peaked")
-    _near(got[1], {k: whole["flags_ipt" if k == "flags" else k] for k in got[1]}, "peaked")
+    # (one token carries most of such a row; its exponent lies up to 64 above its thread's reference, where fp32 is good to 1.9e-6
+    # in the exponent and 1.3e-6 in the mass, on either side of the comparison)
+    _near(got[1], {k: whole["flags_ipt" if k == "flags" else k] for k in got[1]}, "peaked", 2.6e-6)
     bits = lambda t: t.view(torch.int32)
     assert torch.equal(bits(got[1]["cdf_lo"]), bits(whole["cdf_lo"])) == (not shared)
     both = difr.score_both(x, 0.6, seeds, sid, pos, c, c)
