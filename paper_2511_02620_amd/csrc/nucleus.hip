@@ -21,7 +21,7 @@
 //        value is shared by thousands of tokens) are finished by one counting pass:
 //        per value of the bracket and per thread the number of entries, and of entries below the claimed token's
 //        index; entries of equal value have equal mass, which is taken per value in fp64.  Two reads in all.
-//        Every other row goes on with B2 and C, with C at once if the first round lets expect few entries in the
+//        Every other row goes on with B2 and C, with C at once if a sample of the row lets expect few entries in the
 //        bracket (and with B2 after all if they turn out to be many):
 //   B2.. the bracket's key range is divided evenly into at most 16 bins and searched in the same way, until it
 //        is a single key - one logit value - or provably holds at most kNucCap entries (its mass divided by the
@@ -409,21 +409,25 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // A bracket may hold few entries although its mass does not prove it: the end bin at the top takes in everything above
     // the first round's largest entry, the row's few heaviest tokens among them, and its keys span the octaves around zero,
     // which the further search passes divide badly (rows whose nucleus is small, top_p = 0.95 at T = 0.7: half of them took
-    // two or three such passes).  The entries of the first round that lie in it say how many to expect; if that is well
-    // below what pass C can gather, pass C is tried at once, and only if its buffer runs over does the search go on
-    // (2048 rows of 128,256 bf16 logits at T = 0.7: 362 -> 306 us; 2048 rows of 65,536 fp32 logits: 321 -> 252).
+    // two or three such passes).  256 vectors spread over the row say how many to expect; if that is well below what pass C can
+    // gather, pass C is tried at once, and only if its buffer runs over does the search go on (2048 rows of 128,256 bf16 logits at
+    // T = 0.7: 368 us without the try, 315 with it; 2048 rows of 65,536 fp32 logits: 321 / 252).  Spread, since the row's beginning
+    // may say nothing about the rest: with the first 256 vectors instead, rows that begin with 2048 very low entries threw a whole
+    // pass away (2048 x 128,256, T = 0.9: 835 us, 694 now, 677 without the try), and 100,000 entries at T = 0.75 took 242 us for
+    // 215; where the first vectors were right they cost 1% less (T = 0.6: 281 / 285).
     bool try_gather = false;
     if (!by_counts && !provably_small) {  // uniform
         const uint32_t span = khi - klo;
         int32_t seen = 0;
+        const int32_t step = max(nvec / kBlock, 1), vec = tid * step;
         if (tid < nvec) {
             uint32_t kw[4];
-            keys_of(ragged_patched(fetch(tid), (uint32_t)tid * E), kw);
+            keys_of(ragged_patched(fetch(vec), (uint32_t)vec * E), kw);
 #pragma unroll
-            for (int j = 0; j < E; ++j) seen += (int32_t)(key_of(kw, j) - klo <= span && (uint32_t)tid * E + j < V32);
+            for (int j = 0; j < E; ++j) seen += (int32_t)(key_of(kw, j) - klo <= span && (uint32_t)vec * E + j < V32);
         }
         seen = block_sum_i32(seen, lds_i);
-        try_gather = (int64_t)seen * ((nvec + kBlock - 1) / kBlock) <= kNucCap / 4;
+        try_gather = (int64_t)seen * step <= kNucCap / 2;
     }
     if (by_counts) {  // uniform
         const uint32_t span = khi - klo;
@@ -612,7 +616,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     });
     __syncthreads();
     if (!try_gather || s_fill <= kNucCap) break;  // uniform
-    try_gather = false;  // more than the first round promised: the search goes on
+    try_gather = false;  // more than the sample promised: the search goes on
     __syncthreads();     // (s_fill has been read)
     }
     const int64_t cnt_above = (int64_t)block_sum_i32(n_above, lds_i);

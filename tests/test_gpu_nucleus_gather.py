@@ -36,3 +36,30 @@ def test_heavy_entries_beyond_the_first_round(difr, dtype, n):
     for p in (0.5, 0.93):
         print("nucleus gather", dtype, n, p, flush=True)
         base._compare(difr, x, V, 0.8, seeds, sid, pos, claims, p)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("n", [2048, 2049, 6000])
+def test_heavy_entries_that_the_sample_misses(difr, dtype, n):
+    """The sample that decides whether a bracket is gathered at once is every step-th vector: heavy entries between its vectors
+    are gathered up to what the buffer holds, and beyond it the search goes on."""
+    N, V, S = 4, 20008, 2
+    per = 16 // torch.tensor([], dtype=dtype).element_size()
+    nvec = -(-V // per)
+    step = nvec // 256
+    g = torch.Generator().manual_seed(n)
+    x = -20 - torch.rand(N, V, generator=g)
+    x[:, 100] = -10.0
+    vec = torch.arange(V) // per
+    free = ((vec % step != 0) & (vec >= 256) & (torch.arange(V) != 100)).nonzero().squeeze(1)
+    for r in range(N):
+        x[r, free[torch.randperm(len(free), generator=g)[:n]]] = 4 + 5 * torch.rand(n, generator=g)
+    x[3] = x[3].round()
+    x = x.to(dtype).to(DEV)
+    seeds = torch.randint(-2 ** 63, 2 ** 63 - 1, (S,), generator=g).to(DEV)
+    sid, pos = (torch.arange(N, dtype=torch.int32) % S).to(DEV), torch.arange(N, dtype=torch.int32).to(DEV)
+    claims = x.argmax(1).int()
+    claims[1], claims[2] = V - 1, 0
+    for p in (0.5, 0.93):
+        print("nucleus gather, unseen", dtype, n, p, flush=True)
+        base._compare(difr, x, V, 0.8, seeds, sid, pos, claims, p)
