@@ -15,12 +15,13 @@
 
 namespace difr {
 
-// With the rank count the body needs 97 registers, one too many for five waves per SIMD; asked for five it fits in 96
-// without spills and runs 5% faster.  The other variants ask for one wave, which is no constraint.
+// With the rank count or the token search the bf16 body needs 97 registers, one too many for five waves per SIMD, and with marks
+// the fp32 one does; asked for five they fit in 96 without vector spills and the rank runs 5% faster.  The other variants ask for
+// one wave, which is no constraint (fp32 with the rank: 89 registers; asked for five it came out with 68 bytes of scratch a lane).
 //
 // TOK: how the honest sampler's Token-IPT-DiFR token is found (ipt_stream.hpp).
 template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RANK || TOK != kNoToken ? 5 : 1))) void score_both_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kTokenMarks || (DT == 0 && (RANK || TOK != kNoToken)) ? 5 : 1))) void score_both_kernel(
     RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa)
 {
     typedef typename Elem<DT>::type elt_t;
