@@ -10,6 +10,7 @@ import torch
 
 import oracle
 import parity
+import whole_rows
 from paper_2511_02620_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -51,7 +52,7 @@ def _check(difr, logits, V, T, seeds, sid, pos, delta, temps=None):
     (torch.bfloat16, 16384, 16384, 0, 6.0),
     (torch.bfloat16, 2051, 2056, 0, 2.0),        # ragged last vector
     (torch.float32, 5003, 5004, 0, 4.0),
-    (torch.bfloat16, 4099, 4099, 1, 2.5),        # unaligned rows: every entry evaluated
+    (torch.bfloat16, 4099, 4099, 1, 2.5),        # unaligned rows
     (torch.bfloat16, 300, 304, 0, 50.0),         # delta beyond every margin: the whole vocabulary
 ])
 def test_admissible_count_every_row(difr, dtype, V, ld, offset, delta):
@@ -117,7 +118,9 @@ def test_admissible_count_rejected_rows(difr):
 
 def _one_pass(difr, logits, V, T, seeds, sid, pos, cg, ci, delta, temps=None):
     """Scores must be those of difr_score_both bit for bit; every determined count must be the two-pass count
-    (same expression, same maximum) and lie inside the oracle's bracket.  Returns (counts, undetermined rows)."""
+    (same expression, same maximum) and lie inside the oracle's bracket.  Small batches of long rows are shared among workgroups, which
+    determines every count; the kernel that takes a row each is then called beside it, and its undetermined rows are the ones
+    returned.  Returns (counts, undetermined rows)."""
     g1, i1, a = difr.score_both_admissible(logits, T, seeds, sid, pos, delta, cg, ci, V=V, temperatures=temps)
     g0, i0 = difr.score_both(logits, T, seeds, sid, pos, cg, ci, V=V, temperatures=temps)
     two = difr.admissible_count(logits, T, seeds, sid, pos, g0["max_score"], delta, V=V, temperatures=temps)
@@ -135,7 +138,13 @@ def _one_pass(difr, logits, V, T, seeds, sid, pos, cg, ci, delta, temps=None):
     assert (c[det] >= o["count_lo"][det]).all() and (c[det] <= o["count_hi"][det]).all()
     l2 = a["log2_count"].cpu().numpy()
     assert np.allclose(l2[det], np.log2(c[det].astype(np.float64)), atol=1e-5) and np.isnan(l2[~det]).all()
-    return c, int((~det).sum())
+    if not whole_rows.is_shared(logits, V):
+        return c, int((~det).sum())
+    assert det.all()
+    gw, iw, aw = whole_rows.score_both_admissible(logits, T, seeds, sid, pos, delta, cg, ci, V=V, temperatures=temps)
+    w = aw["count"].cpu().numpy()
+    assert (w[w >= 0] == c[w >= 0]).all() and all(torch.equal(torch.nan_to_num(gw[k].float(), nan=-7.0), torch.nan_to_num(g0[k].float(), nan=-7.0)) for k in gw)
+    return c, int((w < 0).sum())
 
 
 @pytest.mark.parametrize("dtype,V,ld,delta,claims", [

@@ -12,6 +12,7 @@ import torch
 
 import oracle
 import parity
+import whole_rows
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -131,6 +132,21 @@ def run_case(difr, c, rng):
     bg3, bi3 = difr.score_both_peaked(*a, cg, ci, **kw)
     eq(bg3, g1, "score_both_peaked gumbel side")
     eq(bi3, bi, "score_both_peaked ipt side")
+    if whole_rows.is_shared(c["logits"], V):
+        # few long rows: all of the above went through shared rows; the kernels that take a row each, against one another and them
+        w1 = whole_rows.gumbel_score(*a, cg, want_rank=True, **kw)
+        wi = whole_rows.ipt_score(*a, ci, **kw)
+        eq(w1, g1, "whole rows, gumbel")
+        for peaked in (False, True):
+            bw, bwi = whole_rows.score_both(*a, cg, ci, peaked=peaked, **kw)
+            eq(bw, g1, "whole rows, score_both gumbel side")
+            eq(bwi, wi, "whole rows, score_both ipt side")
+        aw, awi, awc = whole_rows.score_both_admissible(*a, 2.5, cg, ci, **kw)
+        eq(aw, g1, "whole rows, admissible gumbel side")
+        eq(awi, wi, "whole rows, admissible ipt side")
+        det = awc["count"] >= 0
+        if not torch.equal(awc["count"][det], difr.admissible_count(*a, g1["max_score"], 2.5, **kw)["count"][det]):
+            raise AssertionError("whole rows, one-pass admissible count differs from the two-pass count")
     # logit rank against a plain count
     if cg is not None:
         xf = c["logits"][:, :V].float()
