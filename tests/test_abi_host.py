@@ -98,8 +98,7 @@ def test_argument_validation_needs_no_device(lib):
                       (rows(positions=None), NULL), (rows(logits=0x1001), ALIGN), (rows(dtype=1, logits=0x1002), ALIGN)):
         assert g(bad) == want, want
         assert i(bad) == want, want
-        if want != ALIGN:   # unaligned rows are served by the generic kernels
-            assert both(bad) == want, want
+        assert both(bad) == want, want
     assert g(rows(), margin=None) == NULL and g(rows(), argmax=None) == NULL and g(rows(), flags=None) == NULL
     assert i(rows(), dist=None) == NULL and i(rows(), flags=None) == NULL
     for kw in ("margin", "argmax", "fg", "dist", "fi"):

@@ -181,7 +181,7 @@ def test_c2_3b_class_every_row(difr):
 ])
 def test_ragged_shapes_and_unaligned_rows(difr, dtype, V, ld, offset):
     """Vocabulary sizes that are not a multiple of the vector width, padded pitches whose padding
-    holds garbage, and rows that are not 16-byte aligned (generic load path)."""
+    holds garbage, and rows that are not 16-byte aligned."""
     N = 37
     g = torch.Generator(device=DEV).manual_seed(1234 + V)
     store = torch.randn(N * ld + offset + 8, generator=g, device=DEV, dtype=torch.float32).mul_(2.5).to(dtype)
@@ -406,7 +406,7 @@ def test_filtered_kernel_equals_unfiltered_bit_for_bit(difr, case):
     (torch.bfloat16, 300, 304, 0, "mutated"),         # less than one round
     (torch.float32, 4100, 4100, 0, "mutated"),
     (torch.float32, 5003, 5004, 0, "honest"),
-    (torch.bfloat16, 4099, 4099, 1, "mutated"),       # unaligned rows: the two generic kernels
+    (torch.bfloat16, 4099, 4099, 1, "mutated"),       # unaligned rows
 ])
 def test_score_both_equals_the_two_single_calls(difr, dtype, V, ld, offset, case):
     """difr_score_both shares one read of the row between the two estimators; every output must equal

@@ -1,6 +1,7 @@
 """Rows that start at any element: packed rows of an odd vocabulary, at every offset from a 16-byte boundary, must score as
 the same rows do in a padded, aligned buffer - bit for bit, since the same kernels read them -, around one vector, one
-round of 256 vectors and the ragged end, with the packed buffer ending at the last entry of the last row."""
+round of 256 vectors and the ragged end, at lengths at which several workgroups share a row, with the packed buffer ending at the
+last entry of the last row."""
 import numpy as np
 import pytest
 import torch
@@ -23,7 +24,8 @@ def _equal(a, b, what):
 
 
 @pytest.mark.parametrize("dtype,V", [(torch.bfloat16, v) for v in (1, 7, 9, 2047, 2049, 2063, 4099, 20011)] +
-                         [(torch.float32, v) for v in (1, 3, 5, 1023, 1025, 4099)])
+                         [(torch.float32, v) for v in (1, 3, 5, 1023, 1025, 4099)] +
+                         [(dt, v) for dt in (torch.bfloat16, torch.float32) for v in (49153, 99991)])
 def test_packed_rows_score_as_aligned_rows(difr, dtype, V):
     N, S, per = 9, 3, 16 // torch.tensor([], dtype=dtype).element_size()
     g = torch.Generator().manual_seed(V)
