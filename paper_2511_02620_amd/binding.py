@@ -259,7 +259,11 @@ def gumbel_score(logits, temperature, seeds, seq_ids, positions, claimed=None, t
 
 def ipt_score(logits, temperature, seeds, seq_ids, positions, claimed=None, temperatures=None, V=None,
               want_token=False, want_log_mass=False, sigma=0.01, eps=1e-30, want_interval=True, want_rank=False):
-    """difr_ipt_score.  Same inputs as :func:`gumbel_score`.  Returns a dict of device tensors."""
+    """difr_ipt_score.  Same inputs as :func:`gumbel_score`.  Returns a dict of device tensors.
+
+    The rows of a small batch of long rows are shared among workgroups (difr_score_split), which add up a row's softmax sum in
+    another order: dist, cdf_lo, cdf_hi and log_mass of the same row may differ in their last bits between batches of different
+    size, and MATCH and ipt_token where u lies that near to an interval's edge.  The C entry point adds in one order always."""
     out = (_native or _load_native()).ipt_score(logits, V if V is None else int(V), float(temperature), seeds, seq_ids, positions,
                                                 claimed, temperatures, want_token, want_log_mass, float(sigma), float(eps),
                                                 want_interval, want_rank)
@@ -273,7 +277,8 @@ def score_both(logits, temperature, seeds, seq_ids, positions, claimed_gumbel=No
                temperatures=None, V=None, want_rank=False, want_token=False, want_log_mass=False, sigma=0.01, eps=1e-30):
     """difr_score_both: both estimators in one pass.  Returns (gumbel dict, ipt dict) of device tensors;
     want_rank adds logit_rank (of the Token-DiFR claim) to the first, want_token / want_log_mass add ipt_token /
-    log_mass to the second (as in :func:`ipt_score`)."""
+    log_mass to the second (as in :func:`ipt_score`, which
+    also says what depends on the size of the batch: nothing of the first dict, the last bits of the second)."""
     return _score_both("difr_score_both", False, logits, temperature, seeds, seq_ids, positions, claimed_gumbel, claimed_ipt,
                        temperatures, V, want_rank, want_token, want_log_mass, sigma, eps)
 
@@ -281,7 +286,8 @@ def score_both(logits, temperature, seeds, seq_ids, positions, claimed_gumbel=No
 def score_both_peaked(logits, temperature, seeds, seq_ids, positions, claimed_gumbel=None, claimed_ipt=None,
                       temperatures=None, V=None, want_rank=False, want_token=False, want_log_mass=False, sigma=0.01,
                       eps=1e-30):
-    """difr_score_both_peaked: :func:`score_both` for rows known to be concentrated; same arguments, same results."""
+    """difr_score_both_peaked: :func:`score_both` for rows known to be concentrated; same arguments, same results (to the last
+    bits of the second dict: up to 320 rows of a small batch are shared among workgroups, as :func:`score_both` shares them)."""
     return _score_both("difr_score_both_peaked", True, logits, temperature, seeds, seq_ids, positions, claimed_gumbel,
                        claimed_ipt, temperatures, V, want_rank, want_token, want_log_mass, sigma, eps)
 
@@ -306,7 +312,8 @@ def _score_both(entry_name, peaked, logits, temperature, seeds, seq_ids, positio
 def score_both_admissible(logits, temperature, seeds, seq_ids, positions, delta, claimed_gumbel=None, claimed_ipt=None,
                           temperatures=None, V=None):
     """difr_score_both_admissible: both estimators and the admissible-set size in one pass.
-    Returns (gumbel dict, ipt dict, admissible dict with count [-1 = undetermined] and log2_count)."""
+    Returns (gumbel dict, ipt dict, admissible dict with count [-1 = undetermined] and log2_count).  Small batches as in
+    :func:`ipt_score`; their counts are always determined."""
     out = (_native or _load_native()).score_both_admissible(logits, V if V is None else int(V), float(temperature), seeds, seq_ids,
                                                             positions, claimed_gumbel, temperatures, claimed_ipt, float(delta))
     if out.__class__ is not tuple:
@@ -369,6 +376,7 @@ def admissible_count(logits, temperature, seeds, seq_ids, positions, max_score, 
 
 
 def lmhead_workspace_bytes(N, V, d, want_token=False) -> int:
+    """Bytes of workspace for :func:`lmhead_score`; the size for a batch of up to 256 tokens serves every smaller one."""
     return int(load_library().difr_lmhead_workspace_bytes(int(N), int(V), int(d), int(bool(want_token))))
 
 

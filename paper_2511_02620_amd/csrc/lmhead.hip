@@ -644,7 +644,7 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 
 // ---------------------------------------------------------------------------------
 // The same for batches of up to 128 tokens.  What bounds them is reading the LM-head matrix once; the tile is as wide as the
-// batch (T = 64 or 128 token rows), so that the matrix instructions of a slab and its fragment reads take a fraction of the
+// batch (T = 32, 64 or 128 token rows), so that the matrix instructions of a slab and its fragment reads take a fraction of the
 // time its share of the memory bandwidth does.  A workgroup's four waves own 32 R vocabulary rows each, all token columns.
 // S LDS stages, so that S - 1 slabs are in flight while one is multiplied, one barrier per slab:
 //   wait for the wave's own copies of slab s (those of the slabs after it may be in flight), barrier: slab s is in LDS whole,
@@ -654,8 +654,11 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 // Copies and LDS layout as in the kernel above; logits are summed in the same order, to the same bits.
 // NT: the weights are read past the caches.  A matrix larger than the 256 MB Infinity Cache is never found there again and
 // only displaces the hidden states: 1.24 GB, 64 tokens: 269 us for the call with ordinary loads, 247 with these (128-entry tiles); a matrix
-// that fits is left to the cache (262 MB: 63 / 67 us, read again and again).
-// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 190 to 215 us, 5.8 to 6.5 TB/s (the 256 x 256 kernel: 370).
+// that fits is left to the cache (262 MB: 63 / 67 us, read again and again).  R = 1 always reads through the caches: 50,257 x 4096
+// (412 MB), 64 tokens, would take 102 us past them instead of 111, but 33,000 x 4096 (270 MB) 95 instead of 78, the larger part of
+// it being found in the cache.
+// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 190 to 215 us from box to box, 5.8 to 6.5 TB/s (the 256 x 256
+// kernel: 370).
 // ---------------------------------------------------------------------------------
 template <int T, int R, bool NT, bool RANK, bool TOK>
 __global__ __launch_bounds__(kBlock, T <= 64 && R == 1 ? 2 : 1) void lmhead_small_kernel(LmHeadBatch b, LmHeadWorkspace ws, LmHeadPlan plan)
@@ -900,12 +903,12 @@ __global__ __launch_bounds__(kBlock, T <= 64 && R == 1 ? 2 : 1) void lmhead_smal
 }
 
 // ---------------------------------------------------------------------------------
-// Merge the vocabulary ranges of each token and form every output.  A workgroup takes 8 tokens with 32 threads each:
-// thread (t, g) reads the g-th 1/32 of token t's ranges (and, for the sampler's token, of its half tiles), so that
-// neighbouring lanes read neighbouring tokens of the [range][token] arrays and the loads of a token are spread over
-// 32 threads.  What bounds it is the latency of those loads: with one thread per token walking all of them, the merge
-// took 174 us of a call with 64 tokens (256 ranges) and 780 us with 4096 tokens and the sampler's token (16 ranges,
-// 1188 half tiles); now 15 and 34 us.
+// Merge the vocabulary ranges of each token and form every output.  A workgroup takes kFinTokens tokens (8, or 2 where a token has
+// many ranges) with 256 / kFinTokens = G threads each: thread (t, g) reads the g-th 1/G of token t's ranges (and, for the sampler's
+// token, of its half tiles), so that neighbouring lanes read neighbouring tokens of the [range][token] arrays and the loads of a
+// token are spread over G threads.  What bounds it is the latency of those loads: with one thread per token walking all of them,
+// the merge took 174 us of a call with 64 tokens (256 ranges) and 780 us with 4096 tokens and the sampler's token (16 ranges,
+// 1188 half tiles); now 9 (two tokens to a workgroup; 15 with eight) and 34 us.
 // ---------------------------------------------------------------------------------
 template <int kFinTokens>
 __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, LmHeadWorkspace ws, int splits, int n_vt,
@@ -996,7 +999,7 @@ __global__ __launch_bounds__(kBlock) void lmhead_finalize_kernel(LmHeadBatch b, 
 
     // ---- the half tile that holds the sampler's own token: the claim's if it matches, else the first at which the
     // CDF passes u, from the masses the scoring pass left (vocabulary order, each brought to the row's final
-    // reference).  Every thread sums its 1/32 of them, the share in which the CDF passes is found from the 32 sums and
+    // reference).  Every thread sums its share of them, the share in which the CDF passes is found from the sums and
     // its thread walks it; the entry inside the half tile is found by the kernel that follows. ----
     if (oi.ipt_token) {
         const bool search = use && !ipt_bad && !match;
@@ -1202,7 +1205,7 @@ int launch_lmhead_score(const LmHeadBatch &b, const LmHeadWorkspace &ws, const L
         const dim3 small_grid((unsigned)plan.splits);
         auto small = [&](auto TOKENS) {
             constexpr int T = decltype(TOKENS)::value;
-            if (plan.blocks == 1)  // (few enough entries that the matrix is small for any usual d)
+            if (plan.blocks == 1)  // (also where the matrix is larger than the cache; see NT above)
                 lmhead_small_kernel<T, 1, false, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);
             else if (past)
                 lmhead_small_kernel<T, 2, true, r, t><<<small_grid, block, 0, stream>>>(b, ws, plan);

@@ -49,10 +49,14 @@ inline LmHeadPlan lmhead_plan(int64_t N, int64_t V)
     p.n_vt = (int)((V + kLmTileV - 1) / kLmTileV);
     p.small = p.blocks = p.n_tiles = 0;
     // Up to 128 tokens the matrix instructions of the 256 x 256 tile are mostly padding and the LM-head matrix is read at
-    // half the speed of memory (V = 151,936, d = 4096, whole call: 64 tokens 375 us, 204 with the small-batch kernel; 128
-    // tokens 398 / 240; 129 to 256 tokens stay: 424).  Tiles of 256 entries as long as those give every compute unit one
-    // (64 tokens: 204 us, 128-entry tiles, two workgroups to a compute unit: 245; V = 32,000, d = 2048: 49 / 39).  Every
-    // range has the same number of tiles (but for the last), so that all workgroups end together.
+    // half the speed of memory (V = 151,936, d = 4096, whole call: 64 tokens 514 us, 218 with the small-batch kernel; 128
+    // tokens 540 / 259; V = 32,000, d = 2048, 64 tokens: 144 / 38).  Tiles of 256 entries from 65,537 entries on, where there is one
+    // for every compute unit (64 tokens, V = 151,936: 204 us on one box, 128-entry tiles, two workgroups to a compute unit, 245
+    // on the same), shorter ones below (V = 32,000, d = 2048: 39, 49 with the long ones).
+    // Ranges have as many tiles each as the longest must have, even if fewer workgroups than compute units do it: V = 66,000 has 258
+    // tiles, and 129 ranges of two take 133 / 142 / 163 us (16 / 64 / 128 tokens), 256 ranges of one or two 160 / 173 / 204; V =
+    // 131,328 187 / 187 / 252 against 212 / 218 / 267, V = 151,936 209 / 218 / 259 against 222 / 235 / 271; where almost all ranges
+    // are full the two agree (V = 128,256: 181 / 177 / 206 against 178 / 176 / 203; V = 50,257, 128 tokens: 126 / 123).
     if (N <= kLmSmallMost) {
         p.small = N <= 32 ? 32 : (N <= 64 ? 64 : 128);
         p.blocks = V > 256 * 256 ? 2 : 1;

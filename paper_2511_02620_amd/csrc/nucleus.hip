@@ -856,8 +856,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     }
 }
 
-// (six waves per SIMD: 77 registers and no spills, where the compiler's own choice is 81 and five; 16,384 x 151,936: 2257 /
-// 2224 us, 4096 x 8000: 290 / 265; seven and eight spill)
+// (six waves per SIMD: 80 registers (fp32 77) and no vector spills, where the compiler's own choice is 81 and five; 8 bytes of
+// scratch a lane either way; 16,384 x 151,936: 2257 / 2224 us, 4096 x 8000: 290 / 265; seven and eight spill)
 template <int DT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void ipt_nucleus_kernel(RowBatch b, float top_p, IptOutputs o,
                                                              int32_t *__restrict__ kept_out, float *__restrict__ tau_out)

@@ -248,10 +248,11 @@ __global__ __launch_bounds__(kBlock) void score_merge_kernel(RowBatch b, const i
 // Rows are shared while they do not fill the chip: about 1024 workgroups, four to a compute unit, are made of them, each with
 // at least two rounds of 2048 entries, so that its set-up does not outweigh its share.  The lines, on graph replays of both
 // scores (one workgroup per row against shared rows, us):
-//   rows  N <= 10 rounds, and 768: V = 151,936 (74 rounds) N = 512: 60.7 / 54.6, 1024: 93.9 / 91.6, 1536: 124.6 / 128.1;
-//         V = 32,000 (15 rounds) N = 128: 17.9 / 16.1, 256: 18.4 / 19.0;
-//   V     24 rounds and more: V = 65,000, N = 24: 24.1 / 13.4; V = 32,000: 16.9 / 13.2, which the second launch and the
-//         workspace cost the host again; V = 8192: 10.1 / 11.7.
+//   rows  N <= 10 rounds, and 768: V = 151,936 (74 rounds) N = 512: 61.6 / 57.1, 740: 80.7 / 77.6, and with the line lifted 1024:
+//         93.9 / 91.6, 1536: 124.6 / 128.1; V = 65,000 (31 rounds) N = 310: 32.7 / 28.1; V = 50,000 (24 rounds) N = 240: 26.2 / 22.6;
+//         with the line on V lifted, V = 32,000 (15 rounds) N = 128: 17.9 / 16.1, 256: 18.4 / 19.0;
+//   V     24 rounds and more: V = 65,000, N = 24: 24.1 / 13.4; with the line lifted V = 32,000: 16.9 / 13.2, which the second launch
+//         and the workspace cost the host again; V = 8192: 10.1 / 11.7.
 constexpr int64_t kSplitRows = 768, kSplitRowsPerRound = 10, kSplitLeast = 24, kSplitGroups = 1024, kSplitRounds = 2;
 
 int split_parts(int64_t N, int64_t V, int dtype)
