@@ -657,7 +657,7 @@ __global__ __launch_bounds__(kBlock, 1) void lmhead_score_kernel(LmHeadBatch b, 
 // that fits is left to the cache (262 MB: 63 / 67 us, read again and again).  R = 1 always reads through the caches: 50,257 x 4096
 // (412 MB), 64 tokens, would take 102 us past them instead of 111, but 33,000 x 4096 (270 MB) 95 instead of 78, the larger part of
 // it being found in the cache.
-// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 190 to 215 us from box to box, 5.8 to 6.5 TB/s (the 256 x 256
+// 64 tokens, V = 151,936, d = 4096: the scoring kernel alone takes 190 to 215 us, depending on the card, 5.8 to 6.5 TB/s (the 256 x 256
 // kernel: 370).
 // ---------------------------------------------------------------------------------
 template <int T, int R, bool NT, bool RANK, bool TOK>
