@@ -49,8 +49,8 @@ inline LmHeadPlan lmhead_plan(int64_t N, int64_t V)
     p.n_vt = (int)((V + kLmTileV - 1) / kLmTileV);
     p.small = p.blocks = p.n_tiles = 0;
     // Up to 128 tokens the matrix instructions of the 256 x 256 tile are mostly padding and the LM-head matrix is read at
-    // half the speed of memory (V = 151,936, d = 4096, whole call: 64 tokens 514 us, 218 with the small-batch kernel; 128
-    // tokens 540 / 259; V = 32,000, d = 2048, 64 tokens: 144 / 38).  Tiles of 256 entries from 65,537 entries on, where there is one
+    // half the speed of memory (V = 151,936, d = 4096, whole call: 64 tokens 376 us, 207 with the small-batch kernel; 128
+    // tokens 398 / 244; V = 32,000, d = 2048, 64 tokens: 75 / 39).  Tiles of 256 entries from 65,537 entries on, where there is one
     // for every compute unit (64 tokens, V = 151,936: 204 us, and 245 with 128-entry tiles, two workgroups to a compute unit, in the
     // same run), shorter ones below (V = 32,000, d = 2048: 39, 49 with the long ones).
     // Ranges have as many tiles each as the longest must have, even if fewer workgroups than compute units do it: V = 66,000 has 258
