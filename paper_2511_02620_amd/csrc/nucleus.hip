@@ -5,8 +5,27 @@
 // so it is not collected: the kernel finds the CUT, the last (logit, index) pair that still belongs to K,
 // and membership of any token is one comparison against it.
 //
-// One workgroup per row, several passes over the row (it is read from HBM again each time).  Throughout, a
-// token's KEY is the order-preserving integer image of its logit at the storage type's resolution (16 bits for
+// One workgroup per row.  bf16 rows are read ONCE.  A bf16 logit has few values - 2175 of either sign between 2^-10 and 128 -,
+// entries of equal value have equal mass, so the pass only counts: one LDS counter per value, two sets of them, for the entries
+// below the claimed token's index and for the others.  An entry is an address (five packed 16-bit instructions for two entries) and
+// an integer LDS atomic; no exponential is taken in the pass.  Afterwards a thread takes the masses of 17 values, in fp64, one scan over the
+// 256 threads finds the value at which the cumulative mass from the top reaches top_p Z, and that value is treated as a
+// bracket of a single value below: its ties enter K in index order.  Integer counts: any order gives the same bits.
+//   - Entries of -128 and below, masked ones among them, go to 64 words one per lane (max() with the lane's own word, no branch), so
+//     that rows that are mostly masked do not queue up at one counter.  They have no mass if the row's largest logit lies far
+//     enough above; otherwise, and if anything of 128 and more or a NaN has been seen, the row goes to the search below.
+//   - Entries within 2^-10 of zero share a counter; their masses are summed on the side (a quarter of the rounds of rows around
+//     zero have one).  If the cut falls among them, the row goes to the search.
+//   - What it is bound by: LDS atomics at the same address queue up (a wave whose 64 entries are equal takes 64 turns).  32 runs of
+//     eight vectors spread over the row say beforehand how many neighbours are equal; rows with more than one pair in seven go
+//     to the search.  2048 x 128,256, us here / by passes: logits as they are (1 pair in 80) 111 / 383, rounded to 0.5 (one in 10)
+//     276 / 341, to 0.67 (one in 7) 319 / 331, to 1 (one in 5) 409 / 332, constant rows 882 / 232.
+// Reading: 16,384 x 151,936 862 us (5.8 TB/s; 2186 by passes); 2048 x 128,256, T = 0.7: 110 (283); 4096 x 1000: 57 (59); 128 x 151,936:
+// 33 (125).  36 KB of LDS: four workgroups to a compute unit, with the next two rounds requested ahead; rows that go to the search
+// have the registers and LDS of both and take 6 to 9 % longer than by a kernel of their own.
+//
+// The search: several passes over the row (it is read from HBM again each time), for fp32 rows and for those bf16 rows that the
+// counting leaves.  Throughout, a token's KEY is the order-preserving integer image of its logit at the storage type's resolution (16 bits for
 // bf16, formed on the packed patterns), and a bracket is a range of keys [klo, khi].
 //   0    a look at the first 256 vectors: their largest entry R (the exponent reference for every mass
 //        2^((x - R) c): any finite reference serves) and their smallest finite one;
@@ -46,10 +65,22 @@ namespace difr {
 constexpr int kNucBins = 16;    // 4 key bits per pass
 constexpr int kNucCap = 2048;   // entries gathered and sorted at the end
 
-constexpr int kNucRawBytes = kNucBins * kBlock * 4;  // LDS the multi-pass search needs from its caller
-static_assert(kNucRawBytes >= kNucCap * (int)sizeof(uint64_t), "gather buffer must fit the bin memory");
+// The one-read histogram of bf16 rows: one counter per logit value of magnitude above 2^-10 and below 128 (2175 of either sign,
+// kHistMag: the pattern of 2^-10), one for the values in between, 64 below and 64 above them for everything outside.
+constexpr uint32_t kHistMag = 0x3A80u, kHistSide = 2175u, kHistClamp = 2239u;
+constexpr int kHistZero = 2239, kHistWords = 4480, kHistPer = 17;  // word of the values around zero; words; words per thread
+constexpr int kHistTwins = 150;  // of the 1024 pairs looked at
+constexpr int kHistFirst = kHistZero - (int)kHistSide;               // the lowest logit value's word
+static_assert(kHistFirst == 64 && kHistFirst + kHistPer * kBlock == kHistZero + (int)kHistSide + 2, "a thread's words");
+static_assert(kHistMag + kHistSide + 1 == 0x4300u, "128 is the first value above");
 
-// One row by the multi-pass search described above.  `raw`: kNucRawBytes of LDS, 16-byte aligned (mass bins
+// LDS the row search needs from its caller: two histograms (bf16), or the bins, whose memory is also the gather buffer
+template <int DT>
+constexpr int kNucRawBytes = DT == 0 ? 2 * kHistWords * 4 : kNucBins * kBlock * 4;
+static_assert(kNucBins * kBlock * 4 >= kNucCap * (int)sizeof(uint64_t), "gather buffer must fit the bin memory");
+static_assert(kNucRawBytes<0> >= kNucBins * kBlock * 4, "and so must the histograms");
+
+// One row by the multi-pass search described above.  `raw`: kNucRawBytes<DT> of LDS, 16-byte aligned (mass bins
 // [bin][thread] during the search; the gather buffer afterwards).  All 256 threads of the workgroup call it.
 template <int DT>
 __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float top_p, const IptOutputs &o,
@@ -61,6 +92,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     __shared__ double part_m[16][kNucBins];
     __shared__ double bin_m[kNucBins];
     __shared__ float lds_f[kWaves];
+    __shared__ float lds_look[2 * kWaves];
+    __shared__ double lds_h[5][kWaves];
     __shared__ double lds_d[kWaves];
     __shared__ int32_t lds_i[kWaves];
     __shared__ int32_t s_fill;
@@ -179,11 +212,48 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             if (v > ninf) lo_s = fminf(lo_s, v);
         }
     };
-    if (tid < nvec) {
-        look(ragged_patched(fetch(tid), (uint32_t)tid * E));  // (ragged only in a row shorter than one round)
+    // bf16: the first two rounds are requested here already, ahead of what decides how they are used
+    const int32_t rounds = (int32_t)((V / E) / kBlock);  // rounds of 256 complete vectors
+    u32x4 qa = u32x4{0u, 0u, 0u, 0u}, qb = qa;
+    int32_t twins = 0;  // bf16: neighbouring entries of equal value among those looked at
+    if constexpr (DT == 0) {
+        // 32 runs of eight vectors spread over the row, which say how the rest looks
+        u32x4 q = u32x4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
+        const int32_t vec = nvec >= kBlock ? (tid >> 3) * (nvec / 32) + (tid & 7) : tid;
+        if (vec < nvec) q = fetch(vec);
+        if (rounds > 0) qa = load_round(x_row, 0);
+        if (rounds > 1) qb = load_round(x_row, 1);
+        u32x4 *z = reinterpret_cast<u32x4 *>(raw);  // the histograms start at zero
+        for (int i = tid; i < 2 * kHistWords / 4; i += kBlock) z[i] = u32x4{0u, 0u, 0u, 0u};
+        q = ragged_patched(q, (uint32_t)vec * E);
+        if (vec < nvec) look(q);
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) twins += (int32_t)(((w[i] ^ (w[i] >> 16)) & 0xFFFFu) == 0u && (w[i] & 0x7FFFu) < kHistMag + kHistSide + 1);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            R = fmaxf(R, __shfl_xor(R, off, 64));
+            lo_s = fminf(lo_s, __shfl_xor(lo_s, off, 64));
+            twins += __shfl_xor(twins, off, 64);
+        }
+        if ((tid & 63) == 0) {
+            lds_look[tid >> 6] = R;
+            lds_look[kWaves + (tid >> 6)] = lo_s;
+            lds_i[tid >> 6] = twins;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            R = fmaxf(R, lds_look[k]);
+            lo_s = fminf(lo_s, lds_look[kWaves + k]);
+        }
+        twins = lds_i[0] + lds_i[1] + lds_i[2] + lds_i[3];
+    } else {
+        if (tid < nvec) look(ragged_patched(fetch(tid), (uint32_t)tid * E));  // (ragged only in a row shorter than one round)
+        R = block_max(R, lds_f);
     }
-    R = block_max(R, lds_f);
-    if (!(R > ninf && R < __builtin_inff())) {  // uniform
+    const bool looked = R > ninf && R < __builtin_inff();
+    if (!looked) {  // uniform
         R = ninf;
         lo_s = __builtin_inff();
         for_each_vector([&](const u32x4 &q, uint32_t) { look(q); });
@@ -193,7 +263,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             return;
         }
     }
-    lo_s = -block_max(-lo_s, lds_f);  // finite and <= R, since R is
+    if (DT != 0 || !looked) lo_s = -block_max(-lo_s, lds_f);  // finite and <= R, since R is
     // A mass is 2^((x - R) c64), c64 = log2(e) / T.  The difference x - R comes first: for the entries that carry the
     // mass it is small and exact, so what the fp32 exponent loses is in proportion to it (an exponent formed as
     // x c - R c would carry the rounding of two products of the size of R c, 1e-5 and more when |R| / T is in the
@@ -212,6 +282,24 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     };
     // (the same real number in fp64: for the few masses of the last step)
     auto mass_of_f64 = [&](float x) __attribute__((always_inline)) { return exp2(((double)x - (double)R) * c64); };
+
+    // The same to 1e-11 in a fifth of the instructions: 2^f, |f| <= 1/2, by its Taylor series up to (f ln 2)^9.  For the masses of
+    // the counted values, each of which stands for thousands of entries, so that an error of it does not average out.
+    auto mass_of_value = [&](float x) __attribute__((always_inline)) {
+        const double y = fmin(fmax(((double)x - (double)R) * c64, -2000.0), 1100.0);  // (2^y: 0 and inf out there)
+        const double whole = rint(y), f = (y - whole) * 0.69314718055994530942;
+        double e = 1.0 / 362880.0;
+        e = fma(e, f, 1.0 / 40320.0);
+        e = fma(e, f, 1.0 / 5040.0);
+        e = fma(e, f, 1.0 / 720.0);
+        e = fma(e, f, 1.0 / 120.0);
+        e = fma(e, f, 1.0 / 24.0);
+        e = fma(e, f, 1.0 / 6.0);
+        e = fma(e, f, 0.5);
+        e = fma(e, f, 1.0);
+        e = fma(e, f, 1.0);
+        return ldexp(e, (int)whole);
+    };
 
     // ---- passes B: search for the bracket [klo, khi] of keys that holds the cut ----
     // Keys are the order-preserving images of the logits at the storage type's resolution (16 bits for bf16).
@@ -270,6 +358,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int k = 0; k < kNucBins; ++k) mass[k * kBlock + tid] = 0.0f;
     };
     double mass_above = 0.0, Zrow = 0.0, target = 0.0;
+    uint32_t klo = 0u, khi = 0u;
     // from the top: the first bin in which the cumulative mass reaches the target (every thread walks the same 16
     // values in the same order); what lies above it is added to mass_above
     auto select_bin = [&]() __attribute__((always_inline)) {
@@ -284,11 +373,214 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         return sel;
     };
 
+    double Zk = 0.0, below = 0.0;  // mass of K; mass of the members of K below the claimed token's index
+    int64_t kept = 0;
+    float tau_val = nan;
+    uint64_t cut = 0ull;   // sorted path: the last member of K in rank order
+    int64_t n_tie = 0;     // tie path: how many of the ties belong to K
+    int32_t tb = 0;        //           and how many ties lie below the claimed token's index
+    bool many_ties = false;
+    const uint32_t t32 = valid ? (uint32_t)t : 0u;  // an invalid claim has nothing below it (its outputs are NaN anyway)
+
+    // bf16 rows: one read (see the top of this file), unless what has been looked at says that the row is not one for it - its masses reach beyond the
+    // histograms' values, or so many entries share a value that a wave's counting would be one entry after the other.
+    bool found = false;
+    bool try_counts = false;
+    if constexpr (DT == 0)
+        try_counts = R < 128.0f && (lo_s > -128.0f || (-127.5f - R) * c < -126.0f) && twins <= kHistTwins;
+    if (DT == 0 && try_counts) {  // uniform
+        typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+        typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
+        uint32_t *hist = reinterpret_cast<uint32_t *>(raw);  // [kHistWords] entries below the claim's index, [kHistWords] the others
+        const uint32_t lane4 = (uint32_t)(tid & 63) * 0x00040004u;
+        u16x2_t mag_max = {0, 0};              // of all entries: above 0x7F80 there was a NaN
+        double zero_mass = 0.0, zero_low = 0.0;  // masses of the entries around zero, and of those below the claim's index
+        // byte offsets of the counters of two entries
+        auto words_of = [&](uint32_t w, uint32_t zero_at, uint32_t least, u16x2_t &v_min) __attribute__((always_inline)) {
+            const u16x2_t m = __builtin_bit_cast(u16x2_t, w & 0x7FFF7FFFu);
+            mag_max = __builtin_elementwise_max(mag_max, m);
+            const u16x2_t first = {(uint16_t)kHistMag, (uint16_t)kHistMag}, most = {(uint16_t)kHistClamp, (uint16_t)kHistClamp};
+            const u16x2_t v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(m, first), most);
+            v_min = __builtin_elementwise_min(v_min, v);
+            const uint32_t sg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2_t, w) >> 15);
+            const u16x2_t step = __builtin_bit_cast(u16x2_t, (sg & 0xFFF8FFF8u) | 0x00040004u);  // +4 or -4
+            const u16x2_t at = v * step + __builtin_bit_cast(u16x2_t, zero_at);
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(at, __builtin_bit_cast(u16x2_t, least)));
+        };
+        auto count_at = [&](uint32_t byte) __attribute__((always_inline)) {
+            __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(raw + byte), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        auto add_vector = [&](const u32x4 &q, uint32_t base) __attribute__((always_inline)) {
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+            const bool all_below = base + E <= t32;
+            const uint32_t other = all_below ? 0u : (uint32_t)(kHistWords * 4) * 0x00010001u;
+            const uint32_t zero_at = (uint32_t)(kHistZero * 4) * 0x00010001u + other, least = lane4 + other;
+            u16x2_t v_min = {0xFFFF, 0xFFFF};
+            uint32_t at[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) at[i] = words_of(w[i], zero_at, least, v_min);
+            if (!all_below && base < t32) {  // the one vector that holds the claim: the entries below it move to the first histogram
+#pragma unroll
+                for (int j = 0; j < E; ++j)
+                    if (base + j < t32) at[j >> 1] -= (uint32_t)(kHistWords * 4) << ((j & 1) * 16);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                count_at(at[i] & 0xFFFFu);
+                count_at(at[i] >> 16);
+            }
+            if (min(v_min.x, v_min.y) == 0) {  // entries around zero share a counter: their masses are summed here
+                float e[E];
+#pragma unroll
+                for (int j = 0; j < E; ++j) {
+                    const float x = value_of(q, j), m = mass_of(x);
+                    e[j] = fabsf(x) <= 0x1p-10f ? m : 0.0f;
+                }
+                zero_mass += (double)tree_sum<E>(e);
+                if (base < t32) {
+#pragma unroll
+                    for (int j = 0; j < E; ++j) e[j] = base + j < t32 ? e[j] : 0.0f;
+                    zero_low += (double)tree_sum<E>(e);
+                }
+            }
+        };
+        {
+            int32_t r = 0;
+            for (; r + 1 < rounds; r += 2) {
+                const u32x4 a = qa, bq = qb;
+                if (r + 2 < rounds) qa = load_round(x_row, r + 2);
+                if (r + 3 < rounds) qb = load_round(x_row, r + 3);
+                add_vector(a, (uint32_t)(r * kBlock + tid) * E);
+                add_vector(bq, (uint32_t)((r + 1) * kBlock + tid) * E);
+            }
+            if (r < rounds) add_vector(qa, (uint32_t)(r * kBlock + tid) * E);
+            const int32_t vec = rounds * kBlock + tid;
+            if (vec < nvec) add_vector(ragged_patched(fetch(vec), (uint32_t)vec * E), (uint32_t)vec * E);
+        }
+        const int lane = tid & 63, wave = tid >> 6;
+        if (max(mag_max.x, mag_max.y) > 0x7F80u) count_at((uint32_t)(kHistWords - 2) * 4u);  // a NaN: counted with what is too large
+        if (__builtin_amdgcn_ballot_w64(zero_mass != 0.0) != 0ull) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                zero_mass += __shfl_xor(zero_mass, off, 64);
+                zero_low += __shfl_xor(zero_low, off, 64);
+            }
+        }
+        if (lane == 0) {
+            lds_h[0][wave] = zero_mass;
+            lds_h[1][wave] = zero_low;
+        }
+        __syncthreads();
+        // what the histograms cannot hold (a NaN, +inf, 128 and more) goes to the search below
+        const bool any_odd = __builtin_amdgcn_ballot_w64((hist[kHistWords - 65 + lane] | hist[2 * kHistWords - 65 + lane]) != 0u) != 0ull;
+        const bool any_low = __builtin_amdgcn_ballot_w64((hist[lane] | hist[kHistWords + lane]) != 0u) != 0ull;  // -128 and less, or masked
+        zero_mass = lds_h[0][0] + lds_h[0][1] + lds_h[0][2] + lds_h[0][3];
+        zero_low = lds_h[1][0] + lds_h[1][1] + lds_h[1][2] + lds_h[1][3];
+        // a thread's words: their mass, the part of it below the claim's index, their entries
+        auto value_at = [&](int word) __attribute__((always_inline)) {
+            const int v = word - kHistZero;
+            return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : (kHistMag + v) << 16);
+        };
+        const int word0 = kHistFirst + tid * kHistPer;
+        double sum = 0.0, sum_low = 0.0;
+        int32_t n = 0;
+        float top = ninf;
+        for (int i = 0; i < kHistPer; ++i) {
+            const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
+            if (na + nb == 0u) continue;
+            const bool zero = word0 + i == kHistZero;
+            const float x = zero ? 0.0f : value_at(word0 + i);
+            const double e = mass_of_value(x);
+            sum += zero ? zero_mass : e * (double)(na + nb);
+            sum_low += zero ? zero_low : e * (double)na;
+            n += (int32_t)(na + nb);
+            top = x;
+        }
+        double upto = sum;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const double o = __shfl_up(upto, off, 64);
+            if (lane >= off) upto += o;
+        }
+        const float M_wave = wave_max(top);
+        if (lane == 63) {
+            lds_h[2][wave] = upto;
+            lds_f[wave] = M_wave;
+        }
+        __syncthreads();
+        const float M = fmaxf(fmaxf(lds_f[0], lds_f[1]), fmaxf(lds_f[2], lds_f[3]));
+        double total = 0.0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            if (k == wave) upto += total;
+            total += lds_h[2][k];
+        }
+        const double goal = (double)top_p * total;
+        const double above = total - upto;
+        // the highest thread in whose words the cumulative mass from the top reaches the goal
+        const uint64_t reached = __builtin_amdgcn_ballot_w64(above + sum >= goal && sum > 0.0);
+        if (lane == 0) lds_i[wave] = reached != 0ull ? wave * 64 + 63 - __builtin_clzll(reached) : -1;
+        __syncthreads();
+        const int ct = max(max(lds_i[0], lds_i[1]), max(lds_i[2], lds_i[3]));
+        if (tid == ct) {
+            int at = 0;
+            double low_above = 0.0, e_above = above;
+            int32_t n_above = 0;
+            for (int i = kHistPer - 1; i >= 0; --i) {
+                const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
+                if (na + nb == 0u) continue;
+                const bool zero = word0 + i == kHistZero;
+                const double e = mass_of_value(zero ? 0.0f : value_at(word0 + i));
+                const double em = zero ? zero_mass : e * (double)(na + nb);
+                at = word0 + i;
+                if (e_above + em >= goal || n_above + (int32_t)(na + nb) == n) break;  // (the last of the thread's entries)
+                e_above += em;
+                low_above += zero ? zero_low : e * (double)na;
+                n_above += (int32_t)(na + nb);
+            }
+            s_fill = at;
+            s_mass_in = e_above;
+            sum_low = low_above;
+            n = n_above;
+        }
+        __syncthreads();
+        // (masses of values below the histograms' are zero if the largest logit lies far enough above them)
+        found = !any_odd && ct >= 0 && M > ninf && (M - R) * c <= 96.0f && (!any_low || (-127.5f - M) * c < -126.0f) && s_fill != kHistZero;
+        if (found) {  // uniform
+            const int at = s_fill;
+            tau_val = value_at(at);
+            klo = khi = key_of_value(tau_val);
+            tb = (int32_t)hist[at];
+            const int64_t bracket = (int64_t)hist[at] + (int64_t)hist[kHistWords + at];
+            mass_above = s_mass_in;
+            const double e_cut = mass_of_value(tau_val);
+            n_tie = e_cut > 0.0 ? (int64_t)ceil((goal - mass_above) / e_cut) : bracket;
+            n_tie = n_tie < 1 ? 1 : (n_tie > bracket ? bracket : n_tie);
+            many_ties = true;
+            double low_sum = tid >= ct ? sum_low : 0.0;
+            int32_t n_sum = tid >= ct ? n : 0;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                low_sum += __shfl_xor(low_sum, off, 64);
+                n_sum += __shfl_xor(n_sum, off, 64);
+            }
+            if (lane == 0) {
+                lds_h[3][wave] = low_sum;
+                lds_h[4][wave] = (double)n_sum;
+            }
+            __syncthreads();
+            below = lds_h[3][0] + lds_h[3][1] + lds_h[3][2] + lds_h[3][3] + e_cut * (double)((int64_t)tb < n_tie ? (int64_t)tb : n_tie);
+            Zk = mass_above + e_cut * (double)n_tie;
+            kept = (int64_t)(lds_h[4][0] + lds_h[4][1] + lds_h[4][2] + lds_h[4][3]) + n_tie;
+        }
+        __syncthreads();
+    }
+
+    if (!found) {  // uniform: the search by passes
     // First pass: every entry counts (the total mass Z fixes the target), and the 16 bins divide the span of
     // LOGIT VALUES seen in the first round evenly - the mass is spread over logit values, not over key bits, which
     // spend most of their range on exponents near zero.  bin1 is monotone in the logit, so each bin is a range of
     // keys; values outside the span seen in the first round fall into the end bins.
-    uint32_t klo, khi;
     double bracket_mass;  // mass of the entries with keys in [klo, khi]
     while (true) {
         float sc = (R > lo_s) ? 16.0f / (R - lo_s) : 0.0f;
@@ -383,14 +675,6 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         __syncthreads();            // the bins are cleared or reused next
         break;
     }
-    double Zk = 0.0, below = 0.0;  // mass of K; mass of the members of K below the claimed token's index
-    int64_t kept = 0;
-    float tau_val = nan;
-    uint64_t cut = 0ull;   // sorted path: the last member of K in rank order
-    int64_t n_tie = 0;     // tie path: how many of the ties belong to K
-    int32_t tb = 0;        //           and how many ties lie below the claimed token's index
-    bool many_ties = false;
-    const uint32_t t32 = valid ? (uint32_t)t : 0u;  // an invalid claim has nothing below it (its outputs are NaN anyway)
 
     // bf16 rows whose bracket is at most 16 logit values, however many entries (the usual case when K is large:
     // near the cut a bf16 value is shared by thousands of tokens): ONE more pass finishes the row, without the sort that
@@ -726,6 +1010,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         tau_val = n > 0 ? top_key(cut) : nan;
     }
     }  // (the general path)
+    }  // (the search by passes)
     const uint32_t span_c = khi - klo;  // for the sampler's token below
 
     if (tid == 0) {
@@ -753,7 +1038,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         } else {
             in_K = top_composite(xt, (int32_t)t) >= cut;
         }
-        const double own = in_K ? (double)mass_of(xt) : 0.0;
+        const double own = !in_K ? 0.0 : found ? mass_of_value(xt) : (double)mass_of(xt);
         ad = below / Zk;
         bd = ad + own / Zk;
         a = (float)ad;
@@ -856,13 +1141,13 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     }
 }
 
-// (six waves per SIMD: 80 registers (fp32 77) and no vector spills, where the compiler's own choice is 81 and five; 8 bytes of
-// scratch a lane either way; 16,384 x 151,936: 2257 / 2224 us, 4096 x 8000: 290 / 265; seven and eight spill)
+// (bf16: four workgroups to a compute unit is what the histograms' LDS allows.  fp32, six waves per SIMD: 77 registers, no vector
+// spills; seven and eight spill)
 template <int DT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void ipt_nucleus_kernel(RowBatch b, float top_p, IptOutputs o,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(DT == 0 ? 4 : 6))) void ipt_nucleus_kernel(RowBatch b, float top_p, IptOutputs o,
                                                              int32_t *__restrict__ kept_out, float *__restrict__ tau_out)
 {
-    __shared__ __attribute__((aligned(16))) unsigned char raw[kNucRawBytes];
+    __shared__ __attribute__((aligned(16))) unsigned char raw[kNucRawBytes<DT>];
     nucleus_row_multipass<DT>(b, top_p, o, kept_out, tau_out, raw);
 }
 

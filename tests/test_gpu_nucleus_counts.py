@@ -1,0 +1,80 @@
+"""bf16 nuclei that one read with a counter per logit value decides, and rows that it leaves to the search: values at the edges of
+the counted range (2^-10, 127.5, 128, -128), entries around zero, masked entries, a cut on a shared counter, rows of few values,
+rows shorter than a round and with ragged ends.  Against the oracle with the bounds of test_gpu_nucleus.py."""
+import pytest
+import torch
+
+import test_gpu_nucleus as base
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def difr():
+    import paper_2511_02620_amd as m
+    m.load_library()
+    return m
+
+
+def _rows(kind, N, V, g):
+    x = torch.randn(N, V, generator=g) * 2
+    edge = torch.randperm(V, generator=g)
+    if kind == "shifted":
+        x -= 11
+    elif kind == "edges":  # the lowest and highest counted values and their neighbours, either sign
+        e = torch.tensor([2.0 ** -10, -2.0 ** -10, 2.0 ** -10 * (1 + 2.0 ** -7), -2.0 ** -10 * (1 + 2.0 ** -7), -127.5, -127.0])
+        x[:, edge[:min(V, 600)]] = e[torch.arange(min(V, 600)) % 6]
+    elif kind == "large":  # rows 0 and 1 hold a value of 127.5 and 128, the others neither
+        x += 100
+        x[0, edge[0]], x[1, edge[0]] = 127.5, 128.0
+    elif kind == "low":    # entries of -128 and less, with mass and without
+        x -= 130
+        x[::2, edge[0]] = 5.0
+    elif kind == "zeros":  # hundreds of zeros and values around them: the cut may lie among them
+        x = x * 2.0 ** -9
+        x[:, edge[:V // 3]] = 0.0
+    elif kind == "masked":
+        x[:, edge[V // 20 + 1:]] = -float("inf")
+        x[1, edge[V // 20 + 1:]] = -3.3895314e38
+        x[2] = -float("inf")
+        x[2, edge[0]] = -3.0
+    elif kind == "few":    # rows of few values
+        x = x.round()
+        x[1] = 1.5
+        x[2] = 0.0
+    return x.bfloat16()
+
+
+@pytest.mark.parametrize("V", [1, 7, 8, 1000, 2047, 2048, 2056, 4099, 20004])
+@pytest.mark.parametrize("kind", ["plain", "shifted", "edges", "large", "low", "zeros", "masked", "few"])
+def test_counted_rows(difr, kind, V):
+    N, S = 6, 2
+    g = torch.Generator().manual_seed(V)
+    x = torch.empty(N, -(-V // 8) * 8, dtype=torch.bfloat16)
+    x[:, V:] = float("nan")                        # never read into a result
+    x[:, :V] = _rows(kind, N, V, g)
+    x = x.to(DEV)[:, :V]
+    seeds = torch.randint(-2 ** 63, 2 ** 63 - 1, (S,), generator=g).to(DEV)
+    sid, pos = (torch.arange(N, dtype=torch.int32) % S).to(DEV), torch.arange(N, dtype=torch.int32).to(DEV)
+    claims = x.float().nan_to_num(-1e30).argmax(1).int()
+    claims[1], claims[2], claims[3] = V - 1, 0, V // 2
+    for p, T in ((0.93, 0.8), (0.5, 1.3)):
+        print("nucleus counts", kind, V, p, flush=True)
+        base._compare(difr, x, V, T, seeds, sid, pos, claims, p)
+
+
+@pytest.mark.parametrize("V", [1, 8, 2056, 20004])
+def test_counted_rows_without_a_distribution(difr, V):
+    """A NaN of either sign and +inf: nothing is kept and the row is flagged, with the entry at the row's start, middle and end."""
+    bits = [0x7FC0, -1, 0x7F80]
+    N = 3 * len(bits)
+    x = torch.zeros(N, -(-V // 8) * 8, dtype=torch.bfloat16)
+    x[:, :V] = _rows("plain", N, V, torch.Generator().manual_seed(V))
+    for r in range(N):
+        x.view(torch.int16)[r, (0, V // 2, V - 1)[r // 3]] = bits[r % 3]
+    x = x.to(DEV)[:, :V]
+    row = torch.arange(N, dtype=torch.int32).to(DEV)
+    print("nucleus counts, undefined", V, flush=True)
+    out = difr.ipt_score_filtered(x, 0.8, torch.tensor([5]).to(DEV), row * 0, row, row * 0, top_k=0, top_p=0.9, V=V)
+    assert (out["flags"] == 4).all() and (out["kept"] == 0).all() and out["dist"].isnan().all()
