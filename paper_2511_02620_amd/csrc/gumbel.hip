@@ -139,8 +139,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6
             g.template process<MODE>(q, round, true);
             ++round;
             if ((round & 15) == 0) g.pickup();
-            return round < n_main && g.gate.mode == MODE;
+            return round < n_main && (DT != 0 || g.gate.mode == MODE);
         };
+        if constexpr (DT != 0) {  // two vectors in flight (see row_stream.hpp)
+            u32x4 qa = load_round(x_row, round), qb = qa, qc = qa;
+            if (round + 1 < n_main) qb = load_round(x_row, round + 1);
+            while (true) {
+                if (round + 2 < n_main) qc = load_round(x_row, round + 2);
+                if (!body(qa)) break;
+                if (round + 2 < n_main) qa = load_round(x_row, round + 2);
+                if (!body(qb)) break;
+                if (round + 2 < n_main) qb = load_round(x_row, round + 2);
+                if (!body(qc)) break;
+            }
+            return;
+        }
         // one vector is kept in flight; two copies of the body, so that the vector being loaded and the one
         // being used swap roles instead of being copied from register to register every round
         u32x4 qa = load_round(x_row, round), qb = qa;
@@ -152,7 +165,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6
         }
     };
     while (round < n_main) {
-        if (g.gate.mode == 0)
+        if (DT != 0 || g.gate.mode == 0)
             run_rounds(std::integral_constant<int, 0>());
         else if (g.gate.mode == 1)
             run_rounds(std::integral_constant<int, 1>());

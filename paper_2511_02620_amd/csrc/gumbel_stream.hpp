@@ -486,12 +486,12 @@ struct GumbelStream {
         if (MODE == 1) return (int16_t)hi >= 0 ? f_hi : -0.0f;         // all negative: bounded by zero
         return (int16_t)hi >= 0 ? f_hi : f_lo;
     }
+    // The largest of the four logits, or a NaN if there is one: two instructions, after which one compare against a gate stands for
+    // four (2048 x 128,256: 196 us with four compares per gate, 189 so, 180 with two vectors in flight as well).
     __device__ __forceinline__ static float vector_upper_bound_f32(u32x4 q)
     {
-        const float x0 = __uint_as_float(q.x), x1 = __uint_as_float(q.y), x2 = __uint_as_float(q.z), x3 = __uint_as_float(q.w);
-        float xub = fmaxf(fmaxf(x0, x1), fmaxf(x2, x3));
-        if (!(x0 + x1 + x2 + x3 == x0 + x1 + x2 + x3)) xub = __builtin_inff();  // a NaN among them (or both infinities)
-        return xub;
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(__uint_as_float(q.x), __uint_as_float(q.y)),
+                                             __builtin_elementwise_maximum(__uint_as_float(q.z), __uint_as_float(q.w)));
     }
 
     // One 16-byte vector per lane; `round` is the vector round (vector index = round * 256 + tid).
@@ -520,8 +520,7 @@ struct GumbelStream {
                     reach = (uint16_t)(m.x < m.y ? m.x : m.y) <= (uint16_t)cap16_max;
                 }
             } else {
-                reach = !(__uint_as_float(q.x) < xcap_max) || !(__uint_as_float(q.y) < xcap_max) ||
-                        !(__uint_as_float(q.z) < xcap_max) || !(__uint_as_float(q.w) < xcap_max);
+                reach = !(vector_upper_bound_f32(q) < xcap_max);
             }
             if (__builtin_amdgcn_ballot_w64(active && reach) == 0ull) {
                 if (RANK) count_above(q, active);
@@ -578,6 +577,7 @@ struct GumbelStream {
         const uint64_t cnmask = __builtin_amdgcn_ballot_w64(active && rmax >= kGateLo);
         uint64_t bmask, cxmask;
         uint16_t lo = 0, hi = 0;  // bf16: extreme bit patterns of the vector (see below)
+        float xmax = 0.0f;        // fp32: its largest logit
         if (DT == 0) {
             if (MODE != 1) {  // smallest bit pattern as unsigned: the largest logit if it is <= 0 ...
                 u16x2 m = __builtin_elementwise_min(as_u16x2(q.x), as_u16x2(q.y));
@@ -596,12 +596,9 @@ struct GumbelStream {
             bmask = __builtin_amdgcn_ballot_w64(active && b_hit);
             cxmask = __builtin_amdgcn_ballot_w64(active && c_hit);
         } else {  // fp32 logits: plain compares (a NaN counts as gated in)
-            const float x0 = __uint_as_float(q.x), x1 = __uint_as_float(q.y), x2 = __uint_as_float(q.z),
-                        x3 = __uint_as_float(q.w);
-            bmask = __builtin_amdgcn_ballot_w64(active && (!(x0 < gate.xcap_hi) || !(x1 < gate.xcap_hi) ||
-                                                           !(x2 < gate.xcap_hi) || !(x3 < gate.xcap_hi)));
-            cxmask = __builtin_amdgcn_ballot_w64(active && (!(x0 < gate.xcap_lo) || !(x1 < gate.xcap_lo) ||
-                                                            !(x2 < gate.xcap_lo) || !(x3 < gate.xcap_lo)));
+            xmax = vector_upper_bound_f32(q);
+            bmask = __builtin_amdgcn_ballot_w64(active && !(xmax < gate.xcap_hi));
+            cxmask = __builtin_amdgcn_ballot_w64(active && !(xmax < gate.xcap_lo));
         }
         const uint64_t hitmask = amask | bmask | (cnmask & cxmask);
         if (RANK) count_above(q, active);
@@ -614,7 +611,7 @@ struct GumbelStream {
                 // fail for each of their entries.  x_max from the extreme bit patterns: the largest signed
                 // pattern if it is a positive number (a NaN with its sign clear stays a NaN and passes), else the
                 // smallest unsigned pattern if all are negative, else something that passes.
-                const float xub = DT == 0 ? vector_upper_bound<MODE>(lo, hi) : vector_upper_bound_f32(q);
+                const float xub = DT == 0 ? vector_upper_bound<MODE>(lo, hi) : xmax;
                 if (!(__fmaf_rn(xub, inv_T, gumbel_upper_bound(rmax)) < gate.Lgate)) {
                     // Entries that could matter are those with moderate noise or a moderate logit; each of
                     // them is then tested against its own noise bound before anything exact is computed.
