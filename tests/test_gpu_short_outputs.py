@@ -1,0 +1,56 @@
+"""Outputs of up to 1 KB share an allocation: around that length of either element size every output is what the call through the C
+entry leaves in buffers of its own, none overlaps another, writing to one leaves the others, and each lives as long as it is held."""
+import pytest
+import torch
+
+import whole_rows
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def difr():
+    import paper_2511_02620_amd as m
+    m.load_library()
+    return m
+
+
+@pytest.mark.parametrize("N", [0, 1, 63, 64, 65, 255, 256, 257, 1024, 1025])
+@pytest.mark.parametrize("inference", [False, True])
+def test_outputs_around_the_shared_length(difr, N, inference):
+    g = torch.Generator().manual_seed(N)
+    V = 640
+    x = torch.randn(N, V, generator=g).to(DEV)
+    row = torch.arange(N, dtype=torch.int32).to(DEV)
+    seeds = torch.tensor([11], device=DEV)
+    c = torch.randint(0, V, (N,), generator=g, dtype=torch.int32).to(DEV)
+    at = (0.9, seeds, row * 0, row)
+    print("short outputs", N, inference, flush=True)
+    want = whole_rows.score_both(x, *at, c, c, want_rank=True, want_token=True, want_log_mass=True) if N else None
+    with torch.inference_mode(inference):
+        got = difr.score_both(x, *at, c, c, want_rank=True, want_token=True, want_log_mass=True)
+        cls = difr.classify(got[0]["margin"], got[0]["logit_rank"], 0.05, 8, V) if N else {}
+        pooled = difr.seq_reduce(got[0]["margin"], got[0]["flags"], torch.tensor([0, N], device=DEV), 0.05) if N else {}
+    outs = [t for d in (*got, cls, pooled) for t in d.values()]
+    spans = sorted((t.data_ptr(), t.data_ptr() + t.numel() * t.element_size()) for t in outs if t.numel())
+    assert all(a[1] <= b[0] for a, b in zip(spans, spans[1:])) and all(a % 16 == 0 for a, _ in spans)
+    for t in outs:
+        assert t.is_contiguous() and t.is_leaf and not t.requires_grad and t.is_inference() == inference and t._base is None
+    if not N:
+        assert all(t.shape[0] == 0 for d in got for t in d.values())
+        return
+    for mine, ref in zip(got, want):
+        assert set(mine) == set(ref)
+        for k in ref:
+            assert mine[k].dtype == ref[k].dtype and torch.equal(mine[k].view(torch.uint8), ref[k].view(torch.uint8)), k
+    if not inference:
+        got[0]["margin"].fill_(7.0)
+        side = torch.cuda.Stream()
+        got[0]["flags"].record_stream(side)
+        assert torch.equal(got[0]["argmax"], want[0]["argmax"]) and torch.equal(got[0]["flags"], want[0]["flags"])
+    keep, ref = got[1]["dist"], want[1]["dist"]
+    del got, cls, pooled, outs
+    for _ in range(8):                               # new outputs do not land where one that is held lives
+        difr.score_both(x, 1.3, seeds, row * 0, row, None, None)
+    assert torch.equal(keep.view(torch.uint8), ref.view(torch.uint8))
