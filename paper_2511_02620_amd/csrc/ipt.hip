@@ -23,7 +23,8 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
     constexpr int E = Elem<DT>::kPerVec;
     __shared__ float lds_f[kWaves];
     __shared__ double lds_d[kWaves];
-    __shared__ WaveMarkSums mark_sums;
+    __shared__ double mark_Z[TOK == kTokenMarks ? kMarks : 1][kBlock];
+    __shared__ float mark_ref[TOK == kTokenMarks ? kMarks : 1][kBlock];
     __shared__ WalkScratch walk;
     __shared__ int32_t lds_rank[kWaves];
 
@@ -39,7 +40,7 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
     const int full_rounds = (int)((V / E) / kBlock);                 // rounds of 256 complete vectors
     const int n_rounds = (int)((nvec_total + kBlock - 1) / kBlock);  // full_rounds or full_rounds + 1
     const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;
-    WaveMarks<TOK> marks(mark_sums, full_rounds);
+    IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
     auto stream = [&](int r0, int r1) {  // full rounds [r0, r1) with one vector kept in flight
         if (r0 >= r1) return;

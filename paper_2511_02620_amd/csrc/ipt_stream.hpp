@@ -95,14 +95,7 @@ __device__ double gaussian_log_mass(double a, double b, double u, double sigma, 
 // 2048 rows of 151,936 bf16 logits without claims take 227 us; with the marks, and up to 16 rounds (four loads in flight)
 // between two barriers, it takes 136.  Six marks: 19 KB of LDS, eight workgroups to a compute unit; four (longer stretches)
 // 142 us, eight (six workgroups) 139.
-//
-// Where Token-IPT-DiFR is scored alone the stream waits for memory, and each wave adds its mark up at once (six exchanges of Z and of
-// the reference, still no barrier): a mark is 12 bytes per wave instead of 12 per thread, so there can be one every kWaveMarkRounds
-// rounds, and the search reads four rounds instead of 13: two loads one after the other.  2048 x 151,936 bf16 without claims 136 us ->
-// 122; 4096 x 33,000 89 -> 67; 2048 x 128,256 fp32 224 -> 202; 8192 x 128,256 bf16 with claims 355 -> 342.  The pair's stream has no
-// instructions to spare: with a mark every 12 rounds 16,384 x 151,936 takes 1276 us for 1257, with one every 19 1251 for 1228.
 constexpr int kMarks = 6;
-constexpr int kWaveMarks = 32, kWaveMarkRounds = 4;
 constexpr int kWalkRounds = 16;  // rounds summed between two barriers of the walk: 16 x 4 wave sums, one per lane
 static_assert(kWalkRounds * kWaves == 64, "the walk scans one wave sum per lane");
 // Full rounds from which a row has marks; a shorter one is walked from its start (ipt_walk_short), which needs fewer steps
@@ -118,13 +111,6 @@ inline TokenSearch token_search(const int32_t *ipt_token, int64_t V, int dtype)
     if (ipt_token == nullptr) return kNoToken;
     return V / ((dtype == 0 ? 8 : 4) * kBlock) < kMarkLeast ? kTokenWalk : kTokenMarks;
 }
-
-// LDS of the search (of one workgroup).
-struct WalkScratch {
-    double mark_sum[kMarks][kWaves];
-    double round_sum[kWalkRounds * kWaves];
-    int32_t tok;
-};
 
 template <int TOK>
 struct IptMarks {
@@ -149,87 +135,22 @@ struct IptMarks {
             }
         }
     }
-    // All threads: rounds up to the last mark at which the CDF has not passed `target`, and the mass of those rounds.
-    __device__ __forceinline__ int locate(float M, double target, WalkScratch &w, double &before) const
-    {
-        const int tid = (int)threadIdx.x;
-        for (int k = 0; k < n; ++k) {
-            double v = Z[k][tid] * (double)fast_exp2(ref[k][tid] - M);
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-            if ((tid & 63) == 0) w.mark_sum[k][tid >> 6] = v;
-        }
-        __syncthreads();
-        before = 0.0;
-        int r0 = 0;
-        for (int k = 0; k < n; ++k) {
-            const double v = w.mark_sum[k][0] + w.mark_sum[k][1] + w.mark_sum[k][2] + w.mark_sum[k][3];
-            if (v > target) break;
-            before = v;
-            r0 = (k + 1) * len;
-        }
-        return r0;
-    }
 };
 
-// The same with a sum per wave and mark.
-struct WaveMarkSums {
-    double Z[kWaveMarks][kWaves];
-    float ref[kWaveMarks][kWaves];
-};
-template <int TOK>
-struct WaveMarks {
-    WaveMarkSums &m;
-    int len, next, n;
-
-    __device__ __forceinline__ WaveMarks(WaveMarkSums &m_, int full_rounds)
-        : m(m_), len(max(kWaveMarkRounds, (full_rounds + kWaveMarks - 1) / kWaveMarks)), next(len), n(0)
-    {
-    }
-    template <class Stream>
-    __device__ __forceinline__ void at(int round, const Stream &s)
-    {
-        if constexpr (TOK == kTokenMarks) {
-            if (round == next) {  // (n < kWaveMarks: kWaveMarks * len >= full_rounds)
-                // a lane without a reference has met masked entries only and holds 0 (or a NaN: then nothing is searched)
-                const float ref = s.ref(), M = wave_max(ref);
-                double v = ref > -__builtin_inff() ? s.Z * (double)fast_exp2(ref - M) : 0.0;
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                if ((threadIdx.x & 63) == 0) {
-                    m.Z[n][threadIdx.x >> 6] = v;
-                    m.ref[n][threadIdx.x >> 6] = M;
-                }
-                ++n;
-                next += len;
-            }
-        }
-    }
-    __device__ __forceinline__ int locate(float M, double target, WalkScratch &, double &before) const
-    {
-        __syncthreads();  // (the marks of all waves)
-        const int lane = (int)threadIdx.x & 63;  // one mark per lane, in every wave
-        double v = 0.0;
-        if (lane < n) {
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w)
-                if (m.ref[lane][w] > -__builtin_inff()) v += m.Z[lane][w] * (double)fast_exp2(m.ref[lane][w] - M);
-        }
-        const uint64_t passed = __builtin_amdgcn_ballot_w64(lane < n && v > target);
-        const int k = passed != 0ull ? __builtin_ctzll(passed) : n;
-        before = __shfl(v, k > 0 ? k - 1 : 0, 64);
-        if (k == 0) before = 0.0;
-        return k * len;
-    }
+// LDS of the search (of one workgroup).
+struct WalkScratch {
+    double mark_sum[kMarks][kWaves];
+    double round_sum[kWalkRounds * kWaves];
+    int32_t tok;
 };
 
 // All 256 threads: the token at which the CDF of the entries of rounds r0, r0 + 1, ... passes `target`; `before` is the mass of
-// the rounds below r0, terms are 2^(x c + neg_Mc); the next `first` rounds are expected to hold it.  -1 if it is not passed before the end of the row.  The wave sums of up to
+// the rounds below r0, terms are 2^(x c + neg_Mc).  -1 if it is not passed before the end of the row.  The wave sums of up to
 // kWalkRounds rounds are formed between two barriers, one scan over them finds the 512 entries that hold the token, and their
 // wave finds it.
 template <int DT>
 __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row, int64_t V, float c, float neg_Mc, int r0,
-                                            double before, double target, WalkScratch &w, int first = kWalkRounds)
+                                            double before, double target, WalkScratch &w)
 {
     constexpr int E = Elem<DT>::kPerVec;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -245,9 +166,8 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
         for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
         return (double)tree_sum<E>(e);
     };
-    for (int nr; r0 < n_rounds; r0 += nr) {
-        nr = min(min(first, kWalkRounds), n_rounds - r0);
-        first = kWalkRounds;
+    for (; r0 < n_rounds; r0 += kWalkRounds) {
+        const int nr = min(kWalkRounds, n_rounds - r0);
         __syncthreads();  // (the scan of the batch before has been read; w.tok is set)
         for (int k0 = 0; k0 < nr; k0 += 4) {
             u32x4 q[4];
@@ -466,18 +386,33 @@ __device__ __forceinline__ IptTotals ipt_combine(float ref, double Z, double P, 
     return t;
 }
 
-template <int DT, int TOK, class Marks>
+template <int DT, int TOK>
 __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri, int64_t row,
                                            const typename Elem<DT>::type *x_row, float c, float ref, double Z,
                                            double P, float refP, int32_t above, const IptOutputs &o, float *lds_f,
-                                           double *lds_d, const Marks &marks, WalkScratch *walk)
+                                           double *lds_d, const IptMarks<TOK> &marks, WalkScratch *walk)
 {
     const IptTotals t = ipt_combine(ref, Z, P, refP, lds_f, lds_d);
     ipt_write<DT, TOK != kNoToken>(b, ri, row, x_row, c, t.M, t.Z, t.P, above, o, [&](double target) {
         if constexpr (TOK == kTokenWalk) return ipt_walk_short<DT>(x_row, b.V, c, -t.M, target, *walk);
-        double before;
-        const int r0 = marks.locate(t.M, target, *walk, before);
-        return ipt_walk<DT>(x_row, b.V, c, -t.M, r0, before, target, *walk, marks.len);
+        const int tid = threadIdx.x;
+        for (int k = 0; k < marks.n; ++k) {
+            double v = marks.Z[k][tid] * (double)fast_exp2(marks.ref[k][tid] - t.M);
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+            if ((tid & 63) == 0) walk->mark_sum[k][tid >> 6] = v;
+        }
+        __syncthreads();
+        // the last mark at which the CDF has not passed u yet
+        double before = 0.0;
+        int r0 = 0;
+        for (int k = 0; k < marks.n; ++k) {
+            const double v = walk->mark_sum[k][0] + walk->mark_sum[k][1] + walk->mark_sum[k][2] + walk->mark_sum[k][3];
+            if (v > target) break;
+            before = v;
+            r0 = (k + 1) * marks.len;
+        }
+        return ipt_walk<DT>(x_row, b.V, c, -t.M, r0, before, target, *walk);
     });
 }
 
