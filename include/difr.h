@@ -240,10 +240,10 @@ int difr_score_split(const difr_rows *in, const int32_t *claimed_ipt, const difr
  * 1 <= top_k <= 256; top_p > 0; rows 16-byte aligned (DIFR_ERR_ALIGN).  Outputs as difr_ipt_score (all
  * optional ones may be NULL) plus kept [N] int32 or NULL = |K|.  One pass over the logits.
  * top_k = 0 with top_p < 1 is the bare nucleus filter: the prefix is taken over the WHOLE vocabulary and may hold
- * tens of thousands of tokens.  The library then searches for the last (logit, index) pair inside K with a search
- * over the logit keys weighted by probability mass: three to five passes over the row instead of one.  The
- * marginal tokens of such a nucleus have probabilities around 1e-6, the accuracy of the fp32 exponentials the mass
- * is summed from, so kept[n] may differ from an evaluation in double by those few tokens; a, b and d keep the 1e-4
+ * tens of thousands of tokens.  bf16 rows are then read once and counted by logit value; fp32 rows, and bf16 rows that hold
+ * logits of 128 and more or very few different ones, are searched over the logit keys weighted by probability mass, in two to
+ * five passes.  The marginal tokens of such a nucleus have probabilities around 1e-6, the accuracy of the fp32 exponentials the
+ * search sums the mass from, so kept[n] may differ from an evaluation in double by those few tokens; a, b and d keep the 1e-4
  * contract.  The sampler's own token, when asked for and not the claim, costs one more (early-exit) pass.
  * top_k = 0 with top_p >= 1 is refused (DIFR_ERR_ARGUMENT: no filter at all, call difr_ipt_score).
  */
