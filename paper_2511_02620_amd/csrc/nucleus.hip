@@ -79,6 +79,7 @@ template <int DT>
 constexpr int kNucRawBytes = DT == 0 ? 2 * kHistWords * 4 : kNucBins * kBlock * 4;
 static_assert(kNucBins * kBlock * 4 >= kNucCap * (int)sizeof(uint64_t), "gather buffer must fit the bin memory");
 static_assert(kNucRawBytes<0> >= kNucBins * kBlock * 4, "and so must the histograms");
+static_assert(kNucRawBytes<0> >= (kHistPer * kBlock + 1) * (int)sizeof(double), "a mass per value for the token search");
 
 // One row by the multi-pass search described above.  `raw`: kNucRawBytes<DT> of LDS, 16-byte aligned (mass bins
 // [bin][thread] during the search; the gather buffer afterwards).  All 256 threads of the workgroup call it.
@@ -386,27 +387,35 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // histograms' values, or so many entries share a value that a wave's counting would be one entry after the other.
     bool found = false;
     bool try_counts = false;
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
+    // byte offsets of the counters of two entries: `zero_at` that of the values around zero, `least` that of the lowest ones
+    auto words_of = [&](uint32_t w, uint32_t zero_at, uint32_t least, u16x2_t &v_min) __attribute__((always_inline)) {
+        const u16x2_t m = __builtin_bit_cast(u16x2_t, w & 0x7FFF7FFFu);
+        const u16x2_t first = {(uint16_t)kHistMag, (uint16_t)kHistMag}, most = {(uint16_t)kHistClamp, (uint16_t)kHistClamp};
+        const u16x2_t v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(m, first), most);
+        v_min = __builtin_elementwise_min(v_min, v);
+        const uint32_t sg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2_t, w) >> 15);
+        const u16x2_t step = __builtin_bit_cast(u16x2_t, (sg & 0xFFF8FFF8u) | 0x00040004u);  // +4 or -4
+        const u16x2_t at = v * step + __builtin_bit_cast(u16x2_t, zero_at);
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(at, __builtin_bit_cast(u16x2_t, least)));
+    };
+    auto value_at = [&](int word) __attribute__((always_inline)) {  // the logit value of a counter
+        const int v = word - kHistZero;
+        return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : (kHistMag + v) << 16);
+    };
+    // entries around zero share a counter, so each has its own mass, here and in all that is compared with sums of it
+    auto around_zero = [&](float x) __attribute__((always_inline)) { return fabsf(x) <= 0x1p-10f; };
+    const int word0 = kHistFirst + tid * kHistPer;  // the thread's values
+    int cut_word = 0, top_word = 0;                 // found: the counters of the cut's value and of the row's largest logit
+    double e_cut = 0.0;                             //        and the mass of the cut's value
     if constexpr (DT == 0)
         try_counts = R < 128.0f && (lo_s > -128.0f || (-127.5f - R) * c < -126.0f) && twins <= kHistTwins;
     if (DT == 0 && try_counts) {  // uniform
-        typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-        typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
         uint32_t *hist = reinterpret_cast<uint32_t *>(raw);  // [kHistWords] entries below the claim's index, [kHistWords] the others
         const uint32_t lane4 = (uint32_t)(tid & 63) * 0x00040004u;
         u16x2_t mag_max = {0, 0};              // of all entries: above 0x7F80 there was a NaN
         double zero_mass = 0.0, zero_low = 0.0;  // masses of the entries around zero, and of those below the claim's index
-        // byte offsets of the counters of two entries
-        auto words_of = [&](uint32_t w, uint32_t zero_at, uint32_t least, u16x2_t &v_min) __attribute__((always_inline)) {
-            const u16x2_t m = __builtin_bit_cast(u16x2_t, w & 0x7FFF7FFFu);
-            mag_max = __builtin_elementwise_max(mag_max, m);
-            const u16x2_t first = {(uint16_t)kHistMag, (uint16_t)kHistMag}, most = {(uint16_t)kHistClamp, (uint16_t)kHistClamp};
-            const u16x2_t v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(m, first), most);
-            v_min = __builtin_elementwise_min(v_min, v);
-            const uint32_t sg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2_t, w) >> 15);
-            const u16x2_t step = __builtin_bit_cast(u16x2_t, (sg & 0xFFF8FFF8u) | 0x00040004u);  // +4 or -4
-            const u16x2_t at = v * step + __builtin_bit_cast(u16x2_t, zero_at);
-            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(at, __builtin_bit_cast(u16x2_t, least)));
-        };
         auto count_at = [&](uint32_t byte) __attribute__((always_inline)) {
             __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(raw + byte), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
@@ -418,7 +427,10 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             u16x2_t v_min = {0xFFFF, 0xFFFF};
             uint32_t at[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) at[i] = words_of(w[i], zero_at, least, v_min);
+            for (int i = 0; i < 4; ++i) {
+                mag_max = __builtin_elementwise_max(mag_max, __builtin_bit_cast(u16x2_t, w[i] & 0x7FFF7FFFu));
+                at[i] = words_of(w[i], zero_at, least, v_min);
+            }
             if (!all_below && base < t32) {  // the one vector that holds the claim: the entries below it move to the first histogram
 #pragma unroll
                 for (int j = 0; j < E; ++j)
@@ -430,17 +442,12 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 count_at(at[i] >> 16);
             }
             if (min(v_min.x, v_min.y) == 0) {  // entries around zero share a counter: their masses are summed here
-                float e[E];
 #pragma unroll
                 for (int j = 0; j < E; ++j) {
-                    const float x = value_of(q, j), m = mass_of(x);
-                    e[j] = fabsf(x) <= 0x1p-10f ? m : 0.0f;
-                }
-                zero_mass += (double)tree_sum<E>(e);
-                if (base < t32) {
-#pragma unroll
-                    for (int j = 0; j < E; ++j) e[j] = base + j < t32 ? e[j] : 0.0f;
-                    zero_low += (double)tree_sum<E>(e);
+                    const float x = value_of(q, j);
+                    const double e = around_zero(x) ? (double)mass_of(x) : 0.0;
+                    zero_mass += e;
+                    if (base + j < t32) zero_low += e;
                 }
             }
         };
@@ -477,11 +484,6 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         zero_mass = lds_h[0][0] + lds_h[0][1] + lds_h[0][2] + lds_h[0][3];
         zero_low = lds_h[1][0] + lds_h[1][1] + lds_h[1][2] + lds_h[1][3];
         // a thread's words: their mass, the part of it below the claim's index, their entries
-        auto value_at = [&](int word) __attribute__((always_inline)) {
-            const int v = word - kHistZero;
-            return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : (kHistMag + v) << 16);
-        };
-        const int word0 = kHistFirst + tid * kHistPer;
         double sum = 0.0, sum_low = 0.0;
         int32_t n = 0;
         float top = ninf;
@@ -548,12 +550,14 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         found = !any_odd && ct >= 0 && M > ninf && (M - R) * c <= 96.0f && (!any_low || (-127.5f - M) * c < -126.0f) && s_fill != kHistZero;
         if (found) {  // uniform
             const int at = s_fill;
+            cut_word = at;
+            top_word = M > 0.0f ? kHistZero + max((int)(__float_as_uint(M) >> 16) - (int)kHistMag, 0) : kHistZero;
             tau_val = value_at(at);
             klo = khi = key_of_value(tau_val);
             tb = (int32_t)hist[at];
             const int64_t bracket = (int64_t)hist[at] + (int64_t)hist[kHistWords + at];
             mass_above = s_mass_in;
-            const double e_cut = mass_of_value(tau_val);
+            e_cut = mass_of_value(tau_val);
             n_tie = e_cut > 0.0 ? (int64_t)ceil((goal - mass_above) / e_cut) : bracket;
             n_tie = n_tie < 1 ? 1 : (n_tie > bracket ? bracket : n_tie);
             many_ties = true;
@@ -788,7 +792,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         const int64_t cnt_above = (int64_t)block_sum_i32(n_above, lds_i);  // (its barriers publish the masses)
         // from the top: the first value at which the cumulative mass reaches the target (every thread walks the
         // same values in the same order); the values above it belong to K whole
-        double ma = mass_above, below_hi = 0.0, e_cut = 0.0;
+        double ma = mass_above, below_hi = 0.0;
         int64_t cnt_hi = 0;
         int jcut = -1, jlast = -1;
         for (int j = (int)span; j >= 0; --j) {
@@ -1038,7 +1042,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         } else {
             in_K = top_composite(xt, (int32_t)t) >= cut;
         }
-        const double own = !in_K ? 0.0 : found ? mass_of_value(xt) : (double)mass_of(xt);
+        const double own = !in_K ? 0.0 : found && !around_zero(xt) ? mass_of_value(xt) : (double)mass_of(xt);
         ad = below / Zk;
         bd = ad + own / Zk;
         a = (float)ad;
@@ -1054,7 +1058,11 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // ---- the sampler's own token, when asked for and the claim is not it: one more pass, in vocabulary order, over
     //      the masses of the members of K until their running sum exceeds u Z_K.  A token above the bracket is a
     //      member, one inside it is if it ranks no lower than the cut (sorted bracket) or is among the first n_tie
-    //      of the ties in index order; the pass ends with the step that holds the token. ----
+    //      of the ties in index order; the pass ends with the step that holds the token.
+    //      A counted row is walked in the masses that its interval is made of, the fp64 masses of the values above the cut, in the
+    //      memory of the counters.  In fp32 exponentials, whose error is the same for all the entries of a value, one drawn token in
+    //      1400 to 4000 did not match when it was scored (4096 rows of 128,256 entries, 60,000 to 120,000 kept).  Price, us, fp32 /
+    //      fp64: 2048 x 128,256 with 124 kept 329 / 336, with 27,000 kept 366 / 372; 4096 x 1000 62 / 72. ----
     int32_t tok = match ? (int32_t)t : -1;
     if (o.ipt_token != nullptr && ok && !match) {  // uniform
         f |= kFlagSlowPath;
@@ -1063,6 +1071,11 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         int64_t ties_before = 0;   // many_ties: bracket entries in those steps
         int32_t last_member = -1;  // the thread's last member so far (rounding can leave the goal just out of reach)
         if (tid == 0) s_fill = -1;
+        double *mass_at = reinterpret_cast<double *>(raw);  // counted rows: [0] for the cut's value and all below, then the values above it
+        const bool zeros_in = cut_word < kHistZero;
+        if (DT == 0 && found) {
+            for (int i = tid; i <= top_word - cut_word; i += kBlock) mass_at[i] = i > 0 ? mass_of_value(value_at(cut_word + i)) : 0.0;
+        }
         __syncthreads();
         for (int32_t vec0 = 0; vec0 < nvec; vec0 += kBlock) {
             const int32_t vec = vec0 + tid;
@@ -1085,7 +1098,39 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 tie_rank = ties_before + (int64_t)(incl - (double)my_ties);
                 ties_before += (int64_t)tie_total;
             }
+            double ls = 0.0;
+            double ed[E];  // counted rows
             float e[E];
+            if (DT == 0 && found) {  // uniform
+                if (vec < nvec) {
+                    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+                    u16x2_t v_min = {0xFFFF, 0xFFFF};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t at = words_of(w[i], (uint32_t)(kHistZero * 4) * 0x00010001u, (uint32_t)(cut_word * 4) * 0x00010001u, v_min);
+                        ed[2 * i] = mass_at[(at & 0xFFFFu) / 4 - cut_word];
+                        ed[2 * i + 1] = mass_at[(at >> 16) / 4 - cut_word];
+                    }
+                    if (zeros_in && min(v_min.x, v_min.y) == 0) {
+#pragma unroll
+                        for (int j = 0; j < E; ++j)
+                            if (around_zero(value_of(q, j))) ed[j] = (double)mass_of(value_of(q, j));
+                    }
+                    if (my_ties > 0) {
+#pragma unroll
+                        for (int j = 0; j < E; ++j)
+                            if (key_of(kw, j) == klo && tie_rank++ < n_tie) ed[j] = e_cut;
+                    }
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        ls += ed[j];
+                        if (ed[j] > 0.0) last_member = (int32_t)(base + j);
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < E; ++j) ed[j] = 0.0;
+                }
+            } else {
 #pragma unroll
             for (int j = 0; j < E; ++j) {
                 e[j] = 0.0f;
@@ -1099,20 +1144,22 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                     last_member = (int32_t)(base + j);
                 }
             }
-            const double ls = (double)tree_sum<E>(e);
+            ls = (double)tree_sum<E>(e);
+            }
             double total;
             const double incl = block_inclusive_scan(ls, lds_d, total);
             if (before + total > goal) {  // uniform: the token is inside this step
                 const double excl = before + (incl - ls);
                 if (excl <= goal && before + incl > goal) {  // exactly one thread
                     double cacc = excl;
-                    int32_t found = -1;
+                    int32_t here = -1;
 #pragma unroll
                     for (int j = 0; j < E; ++j) {
-                        cacc += (double)e[j];
-                        if (found < 0 && e[j] > 0.0f && cacc > goal) found = (int32_t)(base + j);
+                        const double ej = DT == 0 && found ? ed[j] : (double)e[j];
+                        cacc += ej;
+                        if (here < 0 && ej > 0.0 && cacc > goal) here = (int32_t)(base + j);
                     }
-                    s_fill = found >= 0 ? found : last_member;  // (found < 0: rounding between the two sums)
+                    s_fill = here >= 0 ? here : last_member;  // (here < 0: rounding between the two sums)
                 }
                 break;
             }

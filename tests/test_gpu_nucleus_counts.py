@@ -78,3 +78,28 @@ def test_counted_rows_without_a_distribution(difr, V):
     print("nucleus counts, undefined", V, flush=True)
     out = difr.ipt_score_filtered(x, 0.8, torch.tensor([5]).to(DEV), row * 0, row, row * 0, top_k=0, top_p=0.9, V=V)
     assert (out["flags"] == 4).all() and (out["kept"] == 0).all() and out["dist"].isnan().all()
+
+
+@pytest.mark.parametrize("temps,scale", [((1.3, 1.5, 4.0, 5.0), 2.0), ((1.3,), 0.02)])
+def test_counted_rows_round_trip(difr, temps, scale):
+    """A drawn token, scored as a claim, matches with distance 0 and is the token again, over rows whose nuclei hold about 100,000 tokens
+    (at a scale of 0.02 with thousands of entries around zero), and a claim is the token exactly where MATCH says so."""
+    N, V, p = 4096, 128256, 0.97
+    g = torch.Generator(device=DEV).manual_seed(1)
+    x = torch.empty(N, V, dtype=torch.bfloat16, device=DEV)
+    for r in range(0, N, 512):
+        x[r:r + 512] = (torch.randn(512, V, generator=g, device=DEV) * scale).bfloat16()
+    row = torch.arange(N, dtype=torch.int32, device=DEV)
+    for T in temps:
+        at = (x, T, torch.tensor([5], device=DEV), row * 0, row)
+        print("nucleus counts, round trip", T, scale, flush=True)
+        drawn = difr.ipt_score_filtered(*at, None, top_k=0, top_p=p, want_token=True)
+        tok = drawn["ipt_token"]
+        back = difr.ipt_score_filtered(*at, tok, top_k=0, top_p=p, want_token=True)
+        missed = int(((back["flags"] & 1) == 0).sum()), int((back["dist"] != 0).sum()), int((back["ipt_token"] != tok).sum())
+        print("not matched, at a distance, another token:", missed, "mean kept", float(back["kept"].float().mean()), flush=True)
+        assert missed == (0, 0, 0)
+        other = torch.where(row % 2 == 0, tok + 1, tok - 1).clamp(0, V - 1)  # a neighbour shares an end of the interval
+        near = difr.ipt_score_filtered(*at, other, top_k=0, top_p=p, want_token=True)
+        assert torch.equal(near["ipt_token"], tok)
+        assert torch.equal((near["flags"] & 1) != 0, other == tok)

@@ -54,3 +54,26 @@ def test_outputs_around_the_shared_length(difr, N, inference):
     for _ in range(8):                               # new outputs do not land where one that is held lives
         difr.score_both(x, 1.3, seeds, row * 0, row, None, None)
     assert torch.equal(keep.view(torch.uint8), ref.view(torch.uint8))
+
+
+@pytest.mark.parametrize("N", [1, 64, 256])
+def test_an_output_that_grows_leaves_the_others(difr, N):
+    """In-place growth, and an operation that resizes its out argument, end in memory of the tensor's own; an output that is kept or
+    saved holds its own bytes."""
+    V = 512
+    x = torch.randn(N, V, generator=torch.Generator().manual_seed(N)).to(DEV)
+    row = torch.arange(N, dtype=torch.int32, device=DEV)
+    c = (row * 7) % V
+    print("short outputs, growing", N, flush=True)
+    got = difr.score_both(x, 0.9, torch.tensor([11], device=DEV), row * 0, row, c, c, want_rank=True, want_log_mass=True)
+    outs = [(i, k, t) for i, d in enumerate(got) for k, t in d.items()]
+    for _, k, t in outs:
+        assert t.untyped_storage().nbytes() == t.numel() * t.element_size() and t.storage_offset() == 0, k
+    before = {(i, k): t.clone() for i, k, t in outs}
+    grown = got[0]["margin"].resize_(4 * N)
+    grown.fill_(7.0)
+    torch.add(torch.ones(2 * N, device=DEV), 1.0, out=got[1]["cdf_lo"].resize_(0))
+    for i, k, t in outs:
+        if (i, k) not in ((0, "margin"), (1, "cdf_lo")):
+            assert torch.equal(t.view(torch.uint8), before[i, k].view(torch.uint8)), k
+    assert bool((grown == 7.0).all()) and bool((got[1]["cdf_lo"] == 2.0).all())
