@@ -57,7 +57,7 @@ def _build_native() -> None:
               os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
         cmd += ["-isystem", d]
     cmd += [os.path.join(CSRC, "binding.cpp"), "-o", tmp, "-L" + os.path.join(home, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu",
-            "-ltorch_python"]
+            "-ltorch_hip", "-ltorch_python"]
     proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if proc.returncode:
         raise RuntimeError("the host compiler failed for binding.cpp:\n%s" % proc.stdout)

@@ -13,7 +13,9 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
 #include <c10/core/DeviceGuard.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -133,37 +135,23 @@ struct Rows {
 };
 constexpr int kRowArgs = 8;
 
-// One dictionary of output tensors.  Short ones share an allocation: a call on few tokens has up to twelve of them, 0.8 us each,
-// while the allocator hands out no less than 512 bytes at a time (64 tokens, both scores and pooling, host time: 26 us with an
-// allocation each, 16 with this).  Each is a tensor of its own on a common storage, at a multiple of 256 bytes, so that streams
-// recorded on one hold for all, and one that is kept keeps 8 KB.
+// One dictionary of output tensors, each in memory of its own, so that a caller may grow, save, keep or record any of them.  A call on
+// few tokens has up to twelve: they come from torch's allocator without the way through its dispatcher (64 tokens, both scores and
+// pooling, host time: 30 us by at::empty, 23 so; views of one allocation took 17, but one that was grown in place lay over the next).
 struct Outputs {
-    static constexpr int64_t kShort = 1024, kShared = 8192;  // bytes: longest output that shares, and what is allocated for them
     THPObjectPtr dict;
     c10::Device dev;
-    at::Tensor shared;
-    int64_t used = kShared;
-    explicit Outputs(c10::Device d) : dict(PyDict_New()), dev(d)
+    const bool direct;  // nobody watches allocations, and nobody wants them filled
+    explicit Outputs(c10::Device d)
+        : dict(PyDict_New()), dev(d),
+          direct(!c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::globalContext().deterministicAlgorithms())
     {
         if (!dict) throw python_error();
     }
     at::Tensor make(at::ScalarType type, at::IntArrayRef shape)
     {
-        const int64_t item = (int64_t)c10::elementSize(type);
-        int64_t bytes = item;
-        for (const int64_t n : shape) bytes = n >= 0 && n <= kShort ? std::min(bytes * n, kShort + 1) : kShort + 1;
-        if (bytes > kShort || bytes == 0) return at::empty(shape, at::TensorOptions().dtype(type).device(dev));
-        if (used + bytes > kShared) {
-            shared = at::empty({kShared}, at::TensorOptions().dtype(at::kByte).device(dev));
-            shared.data_ptr();  // (raises for a tensor without memory)
-            used = 0;
-        }
-        at::Tensor t = at::detail::make_tensor<c10::TensorImpl>(c10::Storage(shared.storage()), c10::DispatchKeySet(c10::DispatchKey::CUDA),
-                                                                c10::scalarTypeToTypeMeta(type));
-        t.unsafeGetTensorImpl()->set_storage_offset(used / item);
-        t.unsafeGetTensorImpl()->set_sizes_contiguous(shape);
-        used = (used + bytes + 255) / 256 * 256;
-        return t;
+        if (!direct) return at::empty(shape, at::TensorOptions().dtype(type).device(dev));
+        return at::Tensor(at::detail::empty_cuda(shape, type, dev, std::nullopt));
     }
     void *add(PyObject *name, at::ScalarType type, at::IntArrayRef shape)
     {

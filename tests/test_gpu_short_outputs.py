@@ -1,5 +1,6 @@
-"""Outputs of up to 1 KB share an allocation: around that length of either element size every output is what the call through the C
-entry leaves in buffers of its own, none overlaps another, writing to one leaves the others, and each lives as long as it is held."""
+"""Outputs have memory of their own, which the binding takes from torch's allocator: at short and longer lengths of either element size
+every output is what the call through the C entry leaves in buffers of the caller's, none overlaps another, writing to one or growing
+it leaves the others, and each lives as long as it is held."""
 import pytest
 import torch
 
@@ -18,7 +19,7 @@ def difr():
 
 @pytest.mark.parametrize("N", [0, 1, 63, 64, 65, 255, 256, 257, 1024, 1025])
 @pytest.mark.parametrize("inference", [False, True])
-def test_outputs_around_the_shared_length(difr, N, inference):
+def test_outputs_of_short_and_longer_calls(difr, N, inference):
     g = torch.Generator().manual_seed(N)
     V = 640
     x = torch.randn(N, V, generator=g).to(DEV)
@@ -77,3 +78,31 @@ def test_an_output_that_grows_leaves_the_others(difr, N):
         if (i, k) not in ((0, "margin"), (1, "cdf_lo")):
             assert torch.equal(t.view(torch.uint8), before[i, k].view(torch.uint8)), k
     assert bool((grown == 7.0).all()) and bool((got[1]["cdf_lo"] == 2.0).all())
+
+
+def test_outputs_under_a_dispatch_mode_and_filled(difr):
+    """A mode that watches allocations sees those of the outputs, and with deterministic algorithms the results are the same."""
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        n = 0
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            self.n += "empty" in str(func)
+            return func(*args, **(kwargs or {}))
+
+    x = torch.randn(8, 512, generator=torch.Generator().manual_seed(2)).to(DEV)
+    row = torch.arange(8, dtype=torch.int32, device=DEV)
+    at = (x, 0.9, torch.tensor([11], device=DEV), row * 0, row, row)
+    print("short outputs, watched", flush=True)
+    want = difr.gumbel_score(*at)
+    with Seen() as seen:
+        got = difr.gumbel_score(*at)
+    assert seen.n >= len(got)
+    torch.use_deterministic_algorithms(True)
+    try:
+        filled = difr.gumbel_score(*at)
+    finally:
+        torch.use_deterministic_algorithms(False)
+    for k in want:
+        assert torch.equal(got[k].view(torch.uint8), want[k].view(torch.uint8)) and torch.equal(filled[k].view(torch.uint8), want[k].view(torch.uint8)), k
