@@ -64,6 +64,29 @@ def test_counted_rows(difr, kind, V):
         base._compare(difr, x, V, T, seeds, sid, pos, claims, p)
 
 
+@pytest.mark.parametrize("V", [1, 7, 9, 2047, 2051, 20004, 20008])
+def test_low_and_masked_entries_at_high_temperatures(difr, V):
+    """Where entries of -128 have mass: rows with -inf only, with one finite entry of -128 and less among them, and with a claim there."""
+    N = 6
+    g = torch.Generator().manual_seed(V)
+    x = torch.empty(N, -(-V // 8) * 8, dtype=torch.bfloat16)
+    x[:, V:] = float("nan")
+    v = torch.randn(N, V, generator=g) * 2
+    low = torch.randperm(V, generator=g)[:max(0, V // 3 - 1)]
+    v[1:, low] = -float("inf")
+    for r, value in ((2, -128.0), (3, -191.0), (4, -200.0), (5, -3.3895314e38)):
+        v[r, low[-1:]] = value
+    x[:, :V] = v.bfloat16()
+    x = x.to(DEV)[:, :V]
+    row = torch.arange(N, dtype=torch.int32, device=DEV)
+    claims = v.argmax(1).int()
+    if len(low):
+        claims[3:5] = int(low[-1])
+    for T in (1.2, 2.0, 40.0):
+        print("nucleus counts, low entries", V, T, flush=True)
+        base._compare(difr, x, V, T, torch.tensor([5], device=DEV), row * 0, row, claims.to(DEV), 0.97)
+
+
 @pytest.mark.parametrize("V", [1, 8, 2056, 20004])
 def test_counted_rows_without_a_distribution(difr, V):
     """A NaN of either sign and +inf: nothing is kept and the row is flagged, with the entry at the row's start, middle and end."""
