@@ -406,8 +406,16 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         const int v = word - kHistZero;
         return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : (kHistMag + v) << 16);
     };
-    // entries around zero share a counter, so each has its own mass, here and in all that is compared with sums of it
+    // Entries around zero share a counter: their masses are summed vector by vector, and in the same way wherever that sum is met again
+    // (entry by entry in fp64, the masses of rows around zero took 3 % of the pass over 16,384 x 151,936).
     auto around_zero = [&](float x) __attribute__((always_inline)) { return fabsf(x) <= 0x1p-10f; };
+    auto zero_masses = [&](const u32x4 &q, float (&e)[E]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const float x = value_of(q, j), m = mass_of(x);
+            e[j] = around_zero(x) ? m : 0.0f;
+        }
+    };
     const int word0 = kHistFirst + tid * kHistPer;  // the thread's values
     int cut_word = 0, top_word = 0;                 // found: the counters of the cut's value and of the row's largest logit
     double e_cut = 0.0;                             //        and the mass of the cut's value
@@ -444,12 +452,13 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 count_at(at[i] >> 16);
             }
             if (min(v_min.x, v_min.y) == 0) {  // entries around zero share a counter: their masses are summed here
+                float e[E];
+                zero_masses(q, e);
+                zero_mass += (double)tree_sum<E>(e);
+                if (base < t32) {
 #pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const float x = value_of(q, j);
-                    const double e = around_zero(x) ? (double)mass_of(x) : 0.0;
-                    zero_mass += e;
-                    if (base + j < t32) zero_low += e;
+                    for (int j = 0; j < E; ++j) e[j] = base + j < t32 ? e[j] : 0.0f;
+                    zero_low += (double)tree_sum<E>(e);
                 }
             }
         };
@@ -1127,9 +1136,13 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                         ed[2 * i + 1] = mass_at[(at >> 16) / 4 - cut_word];
                     }
                     if (zeros_in && min(v_min.x, v_min.y) == 0) {
+                        zero_masses(q, e);
+                        ls = (double)tree_sum<E>(e);  // their sum as the interval has it, less what is added below
 #pragma unroll
-                        for (int j = 0; j < E; ++j)
-                            if (around_zero(value_of(q, j))) ed[j] = (double)mass_of(value_of(q, j));
+                        for (int j = 0; j < E; ++j) {
+                            if (around_zero(value_of(q, j))) ed[j] = (double)e[j];
+                            ls -= (double)e[j];
+                        }
                     }
                     if (my_ties > 0) {
 #pragma unroll
