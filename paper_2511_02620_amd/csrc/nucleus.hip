@@ -17,7 +17,8 @@
 //     or a NaN has been seen, the row goes to the search below.  (2048 x 128,256, one entry in 20 masked, T = 1.6: 191 us, 357 by
 //     passes.  Telling them apart in the pass, two packed instructions for two entries, took 16,384 x 151,936 from 856 to 899.)
 //   - Entries within 2^-10 of zero share a counter; their masses are summed on the side (a quarter of the rounds of rows around
-//     zero have one).  If the cut falls among them, the row goes to the search.
+//     zero have one).  If they are all zero, that counter is a value's like the others; if not and the cut falls among them, the
+//     row goes to the search.
 //   - What it is bound by: LDS atomics at the same address queue up (a wave whose 64 entries are equal takes 64 turns).  32 runs of
 //     eight vectors spread over the row say beforehand how many neighbours are equal; rows with more than one pair in seven go
 //     to the search.  2048 x 128,256, us here / by passes: logits as they are (1 pair in 80) 111 / 383, rounded to 0.5 (one in 10)
@@ -404,7 +405,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     };
     auto value_at = [&](int word) __attribute__((always_inline)) {  // the logit value of a counter
         const int v = word - kHistZero;
-        return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : (kHistMag + v) << 16);
+        return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : v > 0 ? (kHistMag + v) << 16 : 0u);
     };
     // Entries around zero share a counter: their masses are summed vector by vector, and in the same way wherever that sum is met again
     // (entry by entry in fp64, the masses of rows around zero took 3 % of the pass over 16,384 x 151,936).
@@ -417,6 +418,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         }
     };
     const int word0 = kHistFirst + tid * kHistPer;  // the thread's values
+    bool zero_mixed = false;                        // entries around zero that are not zero: the counter there is not one of a value
     int cut_word = 0, top_word = 0;                 // found: the counters of the cut's value and of the row's largest logit
     double e_cut = 0.0;                             //        and the mass of the cut's value
     if constexpr (DT == 0)
@@ -425,6 +427,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         uint32_t *hist = reinterpret_cast<uint32_t *>(raw);  // [kHistWords] entries below the claim's index, [kHistWords] the others
         const uint32_t lane4 = (uint32_t)(tid & 63) * 0x00040004u;
         u16x2_t mag_max = {0, 0};              // of all entries: above 0x7F80 there was a NaN
+        u16x2_t near_min = {0xFFFF, 0xFFFF};   // of the magnitude less one, of entries around zero
         double zero_mass = 0.0, zero_low = 0.0;  // masses of the entries around zero, and of those below the claim's index
         auto count_at = [&](uint32_t byte) __attribute__((always_inline)) {
             __hip_atomic_fetch_add(reinterpret_cast<uint32_t *>(raw + byte), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -452,6 +455,11 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 count_at(at[i] >> 16);
             }
             if (min(v_min.x, v_min.y) == 0) {  // entries around zero share a counter: their masses are summed here
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const u16x2_t m = __builtin_bit_cast(u16x2_t, w[i] & 0x7FFF7FFFu), one = {1, 1};
+                    near_min = __builtin_elementwise_min(near_min, m - one);
+                }
                 float e[E];
                 zero_masses(q, e);
                 zero_mass += (double)tree_sum<E>(e);
@@ -477,6 +485,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         }
         const int lane = tid & 63, wave = tid >> 6;
         if (max(mag_max.x, mag_max.y) > 0x7F80u) count_at((uint32_t)(kHistWords - 2) * 4u);  // a NaN: counted with what is too large
+        if (min(near_min.x, near_min.y) < kHistMag) count_at((uint32_t)(kHistWords - 1) * 4u);  // (a word no value has)
         if (__builtin_amdgcn_ballot_w64(zero_mass != 0.0) != 0ull) {
 #pragma unroll
             for (int off = 32; off >= 1; off >>= 1) {
@@ -494,6 +503,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         // -128 and less, or masked; what a ragged last vector has past the row's end is in one word, its thread's, and not meant
         const uint32_t past = lane == ((nvec - 1) & 63) ? (uint32_t)nvec * E - V32 : 0u;
         const bool any_low = __builtin_amdgcn_ballot_w64((hist[lane] | (hist[kHistWords + lane] - past)) != 0u) != 0ull;
+        zero_mixed = hist[kHistWords - 1] != 0u;
         zero_mass = lds_h[0][0] + lds_h[0][1] + lds_h[0][2] + lds_h[0][3];
         zero_low = lds_h[1][0] + lds_h[1][1] + lds_h[1][2] + lds_h[1][3];
         // a thread's words: their mass, the part of it below the claim's index, their entries
@@ -503,8 +513,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int i = 0; i < kHistPer; ++i) {
             const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
             if (na + nb == 0u) continue;
-            const bool zero = word0 + i == kHistZero;
-            const float x = zero ? 0.0f : value_at(word0 + i);
+            const bool zero = zero_mixed && word0 + i == kHistZero;
+            const float x = value_at(word0 + i);
             const double e = mass_of_value(x);
             sum += zero ? zero_mass : e * (double)(na + nb);
             sum_low += zero ? zero_low : e * (double)na;
@@ -544,8 +554,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             for (int i = kHistPer - 1; i >= 0; --i) {
                 const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
                 if (na + nb == 0u) continue;
-                const bool zero = word0 + i == kHistZero;
-                const double e = mass_of_value(zero ? 0.0f : value_at(word0 + i));
+                const bool zero = zero_mixed && word0 + i == kHistZero;
+                const double e = mass_of_value(value_at(word0 + i));
                 const double em = zero ? zero_mass : e * (double)(na + nb);
                 at = word0 + i;
                 if (e_above + em >= goal || n_above + (int32_t)(na + nb) == n) break;  // (the last of the thread's entries)
@@ -559,7 +569,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             n = n_above;
         }
         __syncthreads();
-        found = !any_odd && ct >= 0 && M > ninf && (M - R) * c <= 96.0f && s_fill != kHistZero;
+        found = !any_odd && ct >= 0 && M > ninf && (M - R) * c <= 96.0f && !(zero_mixed && s_fill == kHistZero);
         // masses of values below the histograms' are zero if the largest logit lies far enough above them; if not, the row is read once
         // more to see whether they are all -inf (finite magnitudes of 128 and more, subtracted from the last one, are below 0x3C80)
         if (found && any_low && !((-127.5f - M) * c < -126.0f)) {  // uniform
@@ -1066,7 +1076,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         } else {
             in_K = top_composite(xt, (int32_t)t) >= cut;
         }
-        const double own = !in_K ? 0.0 : found && !around_zero(xt) ? mass_of_value(xt) : (double)mass_of(xt);
+        const double own = !in_K ? 0.0 : found && !(zero_mixed && around_zero(xt)) ? mass_of_value(xt) : (double)mass_of(xt);
         ad = below / Zk;
         bd = ad + own / Zk;
         a = (float)ad;
@@ -1096,7 +1106,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         int32_t last_member = -1;  // the thread's last member so far (rounding can leave the goal just out of reach)
         if (tid == 0) s_fill = -1;
         double *mass_at = reinterpret_cast<double *>(raw);  // counted rows: [0] for the cut's value and all below, then the values above it
-        const bool zeros_in = cut_word < kHistZero;
+        const bool zeros_in = zero_mixed && cut_word < kHistZero;
         if (DT == 0 && found) {
             for (int i = tid; i <= top_word - cut_word; i += kBlock) mass_at[i] = i > 0 ? mass_of_value(value_at(cut_word + i)) : 0.0;
         }

@@ -56,3 +56,10 @@ def test_a_mask_does_not_send_rows_to_the_search(difr, T):
     m[:, 5::20] = -float("inf")
     print("nucleus routes, masked", T, flush=True)
     assert _ratio(difr, m, x, T) < 2.5
+
+
+def test_a_cut_at_zero_does_not_send_rows_of_few_values_to_the_search(difr):
+    """Rows of multiples of 1/2 around zero, the cut at zero, against the same rows a step of 1 higher."""
+    x = (_rows(50256, 0.0, 4).float() * 2).round() / 2
+    print("nucleus routes, cut at zero", flush=True)
+    assert _ratio(difr, x.bfloat16(), (x + 1).bfloat16(), 1.0, 0.933) < 1.4
