@@ -20,9 +20,13 @@
 //     zero have one).  If they are all zero, that counter is a value's like the others; if not and the cut falls among them, the
 //     row goes to the search.
 //   - What it is bound by: LDS atomics at the same address queue up (a wave whose 64 entries are equal takes 64 turns).  32 runs of
-//     eight vectors spread over the row say beforehand how many neighbours are equal; rows with more than one pair in seven go
-//     to the search.  2048 x 128,256, us here / by passes: logits as they are (1 pair in 80) 111 / 383, rounded to 0.5 (one in 10)
-//     276 / 341, to 0.67 (one in 7) 319 / 331, to 1 (one in 5) 409 / 332, constant rows 882 / 232.
+//     eight vectors spread over the row say beforehand how many of the entries that a wave counts at once - the same place of
+//     vectors one and four lanes apart - share a counter.  Up to 12 % of these pairs, plus 4500 / V (the search's fixed costs weigh
+//     more in short rows) and never beyond 60 %, the row is counted, otherwise it is searched; rows of fewer than 256 vectors are
+//     counted.  us counted / searched, at T = 0.7, top_p = 0.95 (the search depends on them), rows rounded to steps: 128,256 entries
+//     with 8 % of the pairs 236 / 298, 10 % 272 / 307, 20 % 409 / 312, 39 % 619 / 356; 50,256: 14 % 106 / 171, 20 % 171 / 161, 37 % 250 / 205;
+//     16,000: 29 % 136 / 191, 49 % 170 / 290; 8000: 56 % 118 / 218; 4000, constant rows: 95 / 65; 1000: 51 % 93 / 142.  One value in 30,
+//     40 and 50 % of the places (10, 17 and 25 % of the pairs) of 128,256: 282 / 351, 365 / 351, 451 / 332.  (2048 to 8192 rows.)
 // Reading: 16,384 x 151,936 862 us (5.8 TB/s; 2186 by passes); 2048 x 128,256, T = 0.7: 110 (283); 4096 x 1000: 57 (59); 128 x 151,936:
 // 33 (125).  36 KB of LDS: four workgroups to a compute unit, with the next two rounds requested ahead; rows that go to the search
 // have the registers and LDS of both and take 6 to 9 % longer than by a kernel of their own.
@@ -72,7 +76,8 @@ constexpr int kNucCap = 2048;   // entries gathered and sorted at the end
 // kHistMag: the pattern of 2^-10), one for the values in between, 64 below and 64 above them for everything outside.
 constexpr uint32_t kHistMag = 0x3A80u, kHistSide = 2175u, kHistClamp = 2239u;
 constexpr int kHistZero = 2239, kHistWords = 4480, kHistPer = 17;  // word of the values around zero; words; words per thread
-constexpr int kHistTwins = 150;  // of the 1024 pairs looked at
+constexpr int kHistPairs = 8;  // pairs a thread looks at
+constexpr float kHistTwinShare = 0.12f, kHistTwinShort = 4500.0f, kHistTwinMost = 0.6f;  // rows are counted up to this share of equal pairs
 constexpr int kHistFirst = kHistZero - (int)kHistSide;               // the lowest logit value's word
 static_assert(kHistFirst == 64 && kHistFirst + kHistPer * kBlock == kHistZero + (int)kHistSide + 2, "a thread's words");
 static_assert(kHistMag + kHistSide + 1 == 0x4300u, "128 is the first value above");
@@ -216,10 +221,23 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             if (v > ninf) lo_s = fminf(lo_s, v);
         }
     };
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
+    // byte offsets of the counters of two entries: `zero_at` that of the values around zero, `least` that of the lowest ones
+    auto words_of = [&](uint32_t w, uint32_t zero_at, uint32_t least, u16x2_t &v_min) __attribute__((always_inline)) {
+        const u16x2_t m = __builtin_bit_cast(u16x2_t, w & 0x7FFF7FFFu);
+        const u16x2_t first = {(uint16_t)kHistMag, (uint16_t)kHistMag}, most = {(uint16_t)kHistClamp, (uint16_t)kHistClamp};
+        const u16x2_t v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(m, first), most);
+        v_min = __builtin_elementwise_min(v_min, v);
+        const uint32_t sg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2_t, w) >> 15);
+        const u16x2_t step = __builtin_bit_cast(u16x2_t, (sg & 0xFFF8FFF8u) | 0x00040004u);  // +4 or -4
+        const u16x2_t at = v * step + __builtin_bit_cast(u16x2_t, zero_at);
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(at, __builtin_bit_cast(u16x2_t, least)));
+    };
     // bf16: the first two rounds are requested here already, ahead of what decides how they are used
     const int32_t rounds = (int32_t)((V / E) / kBlock);  // rounds of 256 complete vectors
     u32x4 qa = u32x4{0u, 0u, 0u, 0u}, qb = qa;
-    int32_t twins = 0;  // bf16: neighbouring entries of equal value among those looked at
+    int32_t twins = 0;  // bf16: pairs of entries looked at that a wave would count at once and that share a counter
     if constexpr (DT == 0) {
         // 32 runs of eight vectors spread over the row, which say how the rest looks
         u32x4 q = u32x4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
@@ -231,9 +249,22 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         for (int i = tid; i < 2 * kHistWords / 4; i += kBlock) z[i] = u32x4{0u, 0u, 0u, 0u};
         q = ragged_patched(q, (uint32_t)vec * E);
         if (vec < nvec) look(q);
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        if (nvec >= kBlock) {  // uniform; shorter rows are counted whatever they hold
+            const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+            u16x2_t v_min = {0xFFFF, 0xFFFF}, differ = {0, 0};  // of a lane's 8 pairs, those on different counters
 #pragma unroll
-        for (int i = 0; i < 4; ++i) twins += (int32_t)(((w[i] ^ (w[i] >> 16)) & 0xFFFFu) == 0u && (w[i] & 0x7FFFu) < kHistMag + kHistSide + 1);
+            for (int i = 0; i < 4; i += 2) {
+                const uint32_t at = words_of(w[i], (uint32_t)(kHistZero * 4) * 0x00010001u, (uint32_t)(tid & 63) * 0x00040004u, v_min);
+                const u16x2_t first = {(uint16_t)(kHistFirst * 4), (uint16_t)(kHistFirst * 4)}, one = {1, 1};
+                const uint32_t low = __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(first, __builtin_bit_cast(u16x2_t, at)));
+                auto compare = [&](int other) __attribute__((always_inline)) {  // (low entries do not count as equal)
+                    differ += __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, (at ^ (uint32_t)other) | low), one);
+                };
+                compare(__builtin_amdgcn_mov_dpp((int)at, 0xB1, 0xF, 0xF, true));  // lane ^ 1
+                compare(__builtin_amdgcn_ds_swizzle((int)at, 0x101F));             // lane ^ 4
+            }
+            twins = kHistPairs - (int32_t)differ.x - (int32_t)differ.y;
+        }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             R = fmaxf(R, __shfl_xor(R, off, 64));
@@ -390,19 +421,6 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     // histograms' values, or so many entries share a value that a wave's counting would be one entry after the other.
     bool found = false;
     bool try_counts = false;
-    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
-    typedef int16_t i16x2_t __attribute__((ext_vector_type(2)));
-    // byte offsets of the counters of two entries: `zero_at` that of the values around zero, `least` that of the lowest ones
-    auto words_of = [&](uint32_t w, uint32_t zero_at, uint32_t least, u16x2_t &v_min) __attribute__((always_inline)) {
-        const u16x2_t m = __builtin_bit_cast(u16x2_t, w & 0x7FFF7FFFu);
-        const u16x2_t first = {(uint16_t)kHistMag, (uint16_t)kHistMag}, most = {(uint16_t)kHistClamp, (uint16_t)kHistClamp};
-        const u16x2_t v = __builtin_elementwise_min(__builtin_elementwise_sub_sat(m, first), most);
-        v_min = __builtin_elementwise_min(v_min, v);
-        const uint32_t sg = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2_t, w) >> 15);
-        const u16x2_t step = __builtin_bit_cast(u16x2_t, (sg & 0xFFF8FFF8u) | 0x00040004u);  // +4 or -4
-        const u16x2_t at = v * step + __builtin_bit_cast(u16x2_t, zero_at);
-        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(at, __builtin_bit_cast(u16x2_t, least)));
-    };
     auto value_at = [&](int word) __attribute__((always_inline)) {  // the logit value of a counter
         const int v = word - kHistZero;
         return __uint_as_float(v < 0 ? (0x8000u + kHistMag - v) << 16 : v > 0 ? (kHistMag + v) << 16 : 0u);
@@ -422,7 +440,8 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     int cut_word = 0, top_word = 0;                 // found: the counters of the cut's value and of the row's largest logit
     double e_cut = 0.0;                             //        and the mass of the cut's value
     if constexpr (DT == 0)
-        try_counts = R < 128.0f && (lo_s > -128.0f || (-127.5f - R) * c < -126.0f) && twins <= kHistTwins;
+        try_counts = R < 128.0f && (lo_s > -128.0f || (-127.5f - R) * c < -126.0f) &&
+                     (float)twins <= fminf(kHistTwinShare + kHistTwinShort / (float)V32, kHistTwinMost) * (float)(kHistPairs * kBlock);
     if (DT == 0 && try_counts) {  // uniform
         uint32_t *hist = reinterpret_cast<uint32_t *>(raw);  // [kHistWords] entries below the claim's index, [kHistWords] the others
         const uint32_t lane4 = (uint32_t)(tid & 63) * 0x00040004u;

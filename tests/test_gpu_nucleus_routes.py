@@ -58,6 +58,25 @@ def test_a_mask_does_not_send_rows_to_the_search(difr, T):
     assert _ratio(difr, m, x, T) < 2.5
 
 
+# (counted, these rows take 2.7, 2.9 and 5.7 times as long as constant ones, which are searched; searched 1.0, 1.8 and 2.9 times)
+@pytest.mark.parametrize("kind,bound", [("two in turn", 1.7), ("period 8", 2.3), ("around zero", 4.0)])
+def test_rows_whose_waves_would_queue_at_a_counter_are_searched(difr, kind, bound):
+    """Entries that a wave counts at once - eight apart in the row - and that share a counter: a constant row shows it in any pair, these
+    in the same place of neighbouring vectors, or on the counter of the values around zero, only."""
+    V = 50256
+    x = _rows(V, 0.0, 3)
+    m = x.clone()
+    if kind == "two in turn":
+        m[:, ::2], m[:, 1::2] = 1.5, 0.5
+    elif kind == "period 8":
+        m = x[:, :8].repeat(1, V // 8).contiguous()
+    else:
+        m[:, torch.rand(V, device=DEV) < 0.9] *= 1e-5
+    const = torch.full_like(x, 1.5)
+    print("nucleus routes, queues", kind, flush=True)
+    assert _ratio(difr, m, const, 0.7) < bound
+
+
 def test_a_cut_at_zero_does_not_send_rows_of_few_values_to_the_search(difr):
     """Rows of multiples of 1/2 around zero, the cut at zero, against the same rows a step of 1 higher."""
     x = (_rows(50256, 0.0, 4).float() * 2).round() / 2
