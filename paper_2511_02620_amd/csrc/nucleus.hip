@@ -125,6 +125,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
                 if (o.cdf_lo) o.cdf_lo[row] = nan;
                 if (o.cdf_hi) o.cdf_hi[row] = nan;
                 if (o.u) o.u[row] = nan;
+                if (o.ipt_token) o.ipt_token[row] = -1;
                 if (o.log_mass) o.log_mass[row] = nan;
                 o.flags[row] = (uint8_t)flag;
             }
