@@ -147,11 +147,12 @@ def test_nucleus_every_row(difr, dtype, V, p, kind):
 @pytest.mark.parametrize("layout", ["ascending", "descending", "head_masked", "constant", "two_values",
                                     "tiny_head_span", "far_below_head", "huge_tail"])
 def test_nucleus_first_round_unlike_the_row(difr, dtype, layout):
-    """The search lays its first bins over the values met in the first 2048 (bf16) or 1024 (fp32) entries and takes
-    its exponent reference from them; rows whose beginning says nothing about the rest - or something misleading -
+    """The search of fp32 rows lays its first bins over the values met in the first 1024 entries and takes its exponent
+    reference from them; rows whose beginning says nothing about the rest - or something misleading -
     must come out the same: sorted either way, a masked beginning, one or two distinct values, a beginning whose
     values span next to nothing, a maximum so far above the beginning that the pass has to start again, and a
-    beginning of outliers far above a flat rest."""
+    beginning of outliers far above a flat rest.  (bf16 rows are looked at all over and mostly counted:
+    test_gpu_nucleus_looks.py has what misleads that look.)"""
     N, V = 24, 9000
     g = torch.Generator().manual_seed(77 + len(layout) + (dtype == torch.float32))
     x = torch.randn(N, V, generator=g) * 2.0

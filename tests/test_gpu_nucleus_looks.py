@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import nucleus_look
+import test_gpu_nucleus as base
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -23,6 +24,70 @@ def _seen(V):
     seen = torch.zeros(-(-V // 8) * 8, dtype=torch.bool)
     seen.view(-1, 8)[nucleus_look.looked_at(V)] = True
     return seen[:V]
+
+
+# kind: whether the rows are counted first (and then searched, unless "masked"), and the temperature
+KINDS = {
+    "masked": (True, 0.9),           # nothing usable is looked at: a pass of its own finds the reference
+    "one value": (False, 0.9),       # a look of one value, no span for the bins
+    "two values": (False, 0.9),      # a span of one step
+    "far below, equal": (False, 0.9),  # the reference lies 120 below: the first pass starts again
+    "far below": (True, 0.9),        # the same after counting
+    "far above": (True, 0.9),        # outliers above a flat rest: counted
+    "far above, equal": (False, 0.9),  # searched, with one bin that holds nearly all
+    "spike": (True, 0.9),            # one entry of 130 and more that is not looked at
+    "low": (True, 1.7),              # entries of -128 and below, not looked at, that carry mass
+    "around zero": (True, 0.9),      # the cut among different values that share a counter
+}
+
+
+@pytest.mark.parametrize("V", [9000, 9003])
+@pytest.mark.parametrize("kind", list(KINDS))
+def test_looked_at_entries_unlike_the_row(difr, kind, V):
+    N = 24
+    counted, T = KINDS[kind]
+    g = torch.Generator().manual_seed(len(kind) + V)
+    seen = _seen(V)
+    other = (~seen).nonzero().squeeze(1)
+    x = torch.randn(N, V, generator=g) * 2.0
+    noise = torch.randn(N, int(seen.sum()), generator=g)
+    if kind == "masked":
+        x[:, seen] = -float("inf")
+    elif kind == "one value":
+        x[:, seen] = 1.0
+    elif kind == "two values":
+        x[:, seen] = 1.0
+        x[:, 7] = 1.0 + 2.0 ** -7
+    elif kind == "far below, equal":
+        x[:, seen] = -120.0
+        x[:, 7] = -119.0
+    elif kind == "far below":
+        x[:, seen] = -110 + 3 * noise
+    elif kind.startswith("far above"):
+        x = x * 0.05 - 30.0
+        x[:, seen] = 5.0 + (0.0 if "equal" in kind else 1.0) * noise
+    elif kind == "spike":
+        x[:, other[77]] = 130.0
+        x[1::2, other[901]] = 131.0
+    elif kind == "low":
+        x = x * 8.0 - 95.0
+        x[x < -127] = -127.0
+        x[:, other[5:1500:3]] = -128.0 - 10 * torch.rand(N, len(other[5:1500:3]), generator=g)
+    else:
+        x = x.abs() * -1.0
+        x[:, other[torch.randperm(len(other), generator=g)[:1500]]] = 2.0 ** -11 * torch.randn(N, 1500, generator=g)
+    x = x.bfloat16()
+    assert (nucleus_look.counted_first(x, V, T) == counted).all()
+    logits = torch.full((N, -(-V // 8) * 8), float("nan"), dtype=torch.bfloat16, device=DEV)
+    logits[:, :V] = x.to(DEV)
+    row = torch.arange(N, dtype=torch.int32, device=DEV)
+    claims = x.float().argmax(1).int()
+    claims[1::2] = torch.randint(0, V, (N // 2,), generator=g, dtype=torch.int32)
+    for p in (0.05, 0.3, 0.9, 0.99):
+        print("nucleus looks", kind, V, p, flush=True)
+        st, out = base._compare(difr, logits, V, T, torch.tensor([3], device=DEV), row * 0, row, claims.to(DEV), p)
+        base.say("nucleus looks", kind, V, p, st)
+        assert not (out["flags"] & 4).any()
 
 
 @pytest.mark.parametrize("V", [2048, 9003])
