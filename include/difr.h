@@ -240,9 +240,11 @@ int difr_score_split(const difr_rows *in, const int32_t *claimed_ipt, const difr
  * 1 <= top_k <= 256; top_p > 0; rows 16-byte aligned (DIFR_ERR_ALIGN).  Outputs as difr_ipt_score (all
  * optional ones may be NULL) plus kept [N] int32 or NULL = |K|.  One pass over the logits.
  * top_k = 0 with top_p < 1 is the bare nucleus filter: the prefix is taken over the WHOLE vocabulary and may hold
- * tens of thousands of tokens.  bf16 rows are then read once and counted by logit value; fp32 rows, and bf16 rows that hold
- * logits of 128 and more or very few different ones, are searched over the logit keys weighted by probability mass, in two to
- * five passes.  The marginal tokens of such a nucleus have probabilities around 1e-6, the accuracy of the fp32 exponentials the
+ * tens of thousands of tokens.  bf16 rows are then read once and counted by logit value; fp32 rows, and bf16 rows of very few
+ * different logits, are searched over the logit keys weighted by probability mass, in two to five passes.  bf16 rows with a logit of
+ * 128 and more, with finite ones of -128 and less that carry mass, or with the end of the nucleus among different logits within 2^-10
+ * of zero are searched too, after the counting if that has to find it out (one pass more, and another where masked logits have to
+ * be told from finite ones).  The marginal tokens of such a nucleus have probabilities around 1e-6, the accuracy of the fp32 exponentials the
  * search sums the mass from, so kept[n] may differ from an evaluation in double by those few tokens; a, b and d keep the 1e-4
  * contract.  The sampler's own token, when asked for and not the claim, costs one more (early-exit) pass.
  * top_k = 0 with top_p >= 1 is refused (DIFR_ERR_ARGUMENT: no filter at all, call difr_ipt_score).

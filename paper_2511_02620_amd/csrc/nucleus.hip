@@ -8,7 +8,7 @@
 // One workgroup per row.  bf16 rows are read ONCE.  A bf16 logit has few values - 2175 of either sign between 2^-10 and 128 -,
 // entries of equal value have equal mass, so the pass only counts: one LDS counter per value, two sets of them, for the entries
 // below the claimed token's index and for the others.  An entry is an address (five packed 16-bit instructions for two entries) and
-// an integer LDS atomic; no exponential is taken in the pass.  Afterwards a thread takes the masses of 17 values, in fp64, one scan over the
+// an integer LDS atomic; the pass takes no exponential but for entries around zero.  Afterwards a thread takes the masses of 17 values, in fp64, one scan over the
 // 256 threads finds the value at which the cumulative mass from the top reaches top_p Z, and that value is treated as a
 // bracket of a single value below: its ties enter K in index order.  Integer counts: any order gives the same bits.
 //   - Entries of -128 and below, masked ones among them, go to 64 words one per lane (max() with the lane's own word, no branch), so
@@ -27,15 +27,17 @@
 //     with 8 % of the pairs 236 / 298, 10 % 272 / 307, 20 % 409 / 312, 39 % 619 / 356; 50,256: 14 % 106 / 171, 20 % 171 / 161, 37 % 250 / 205;
 //     16,000: 29 % 136 / 191, 49 % 170 / 290; 8000: 56 % 118 / 218; 4000, constant rows: 95 / 65; 1000: 51 % 93 / 142.  One value in 30,
 //     40 and 50 % of the places (10, 17 and 25 % of the pairs) of 128,256: 282 / 351, 365 / 351, 451 / 332.  (2048 to 8192 rows.)
-// Reading: 16,384 x 151,936 862 us (5.8 TB/s; 2186 by passes); 2048 x 128,256, T = 0.7: 110 (283); 4096 x 1000: 57 (59); 128 x 151,936:
-// 33 (125).  36 KB of LDS: four workgroups to a compute unit, with the next two rounds requested ahead; rows that go to the search
-// have the registers and LDS of both and take 6 to 9 % longer than by a kernel of their own.
+// Reading: 16,384 x 151,936 852 us (5.8 TB/s; 2040 by passes); 2048 x 128,256, T = 0.7: 112 (268); 4096 x 1000: 52 (55); 128 x 151,936:
+// 33 (125).  36 KB of LDS: four workgroups to a compute unit, with the next two rounds requested ahead.  Rows that go to the search have
+// the registers and LDS of both.  us of the kernel of their own / here, 2048 x 128,256: constant rows 239 / 253, rounded to 1 274 / 311,
+// period 16 338 / 386; 4096 x 8000, had they been searched: 91 / 120.  Rows that turn out not to be for the counters only when they
+// have been counted pay for both: one entry of 130 that is not looked at 225 / 414, the cut among values around zero 797 / 967.
 //
 // The search: several passes over the row (it is read from HBM again each time), for fp32 rows and for those bf16 rows that the
 // counting leaves.  Throughout, a token's KEY is the order-preserving integer image of its logit at the storage type's resolution (16 bits for
 // bf16, formed on the packed patterns), and a bracket is a range of keys [klo, khi].
-//   0    a look at the first 256 vectors: their largest entry R (the exponent reference for every mass
-//        2^((x - R) c): any finite reference serves) and their smallest finite one;
+//   0    a look at 256 vectors (fp32: the first ones, bf16: the runs above): their largest entry R (the exponent reference
+//        for every mass 2^((x - R) c): any finite reference serves) and their smallest finite one;
 //   B1   every thread adds the mass of its entries to 16 private LDS bins (no atomics, no conflicts) that divide
 //        the span of LOGIT VALUES seen in step 0 evenly, values outside falling into the end bins; the same pass
 //        finds the smallest and largest key of the row (NaN / +inf check, the maximum M).  The bins are combined
@@ -208,11 +210,11 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         return __uint_as_float(w[j]);
     };
 
-    // ---- a look at the first 256 vectors: their largest entry R and their smallest finite one.  R is the exponent
+    // ---- a look at 256 vectors (bf16: spread over the row): their largest entry R and their smallest finite one.  R is the exponent
     //      reference: any finite reference serves (fp32 terms keep their relative precision at every scale, the sums
     //      are fp64); the row maximum M itself comes out of the first search pass, and that pass is repeated with
     //      R = M in the rare case that M lies so far above R that terms could overflow.  The two together tell the
-    //      first search pass where to put its bins.  A first round without a usable value takes a pass of its own. ----
+    //      first search pass where to put its bins.  A look without a usable value takes a pass of its own. ----
     float R = ninf, lo_s = __builtin_inff();
     auto look = [&](const u32x4 &q) __attribute__((always_inline)) {
 #pragma unroll
@@ -636,9 +638,9 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
 
     if (!found) {  // uniform: the search by passes
     // First pass: every entry counts (the total mass Z fixes the target), and the 16 bins divide the span of
-    // LOGIT VALUES seen in the first round evenly - the mass is spread over logit values, not over key bits, which
+    // LOGIT VALUES seen in the look evenly - the mass is spread over logit values, not over key bits, which
     // spend most of their range on exponents near zero.  bin1 is monotone in the logit, so each bin is a range of
-    // keys; values outside the span seen in the first round fall into the end bins.
+    // keys; values outside the span that was seen fall into the end bins.
     double bracket_mass;  // mass of the entries with keys in [klo, khi]
     while (true) {
         float sc = (R > lo_s) ? 16.0f / (R - lo_s) : 0.0f;
@@ -749,7 +751,7 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
     }
     const bool by_counts = DT == 0 && khi > klo && khi - klo < (uint32_t)kNucBins && V <= (int64_t)(1 << 24);
     // A bracket may hold few entries although its mass does not prove it: the end bin at the top takes in everything above
-    // the first round's largest entry, the row's few heaviest tokens among them, and its keys span the octaves around zero,
+    // the largest entry looked at, the row's few heaviest tokens among them, and its keys span the octaves around zero,
     // which the further search passes divide badly (rows whose nucleus is small, top_p = 0.95 at T = 0.7: half of them took
     // two or three such passes).  256 vectors spread over the row say how many to expect; if that is well below what pass C can
     // gather, pass C is tried at once, and only if its buffer runs over does the search go on (2048 rows of 128,256 bf16 logits at

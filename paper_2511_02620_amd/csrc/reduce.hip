@@ -5,7 +5,7 @@
 // One workgroup per sequence.  Each thread accumulates a strided share in fp64, then a
 // fixed binary tree over the 64 lanes of a wave and the four waves: no atomics, so the result is reproducible.
 // What bounds it is latency, a launch's and that of two dependent loads (64 tokens in 4 sequences: 3.0 us with a tree over 256 slots
-// of LDS, eight barriers, 2.2 with exchanges inside the waves and one; behind a long kernel, with cold caches, 4.4 either way).
+// of LDS, nine barriers, 2.2 with exchanges inside the waves and one; behind a long kernel, with cold caches, 4.4 either way).
 #include <math.h>
 
 #include "difr_device.hpp"
