@@ -13,7 +13,7 @@
 // bracket of a single value below: its ties enter K in index order.  Integer counts: any order gives the same bits.
 //   - Entries of -128 and below, masked ones among them, go to 64 words one per lane (max() with the lane's own word, no branch), so
 //     that rows that are mostly masked do not queue up at one counter.  They have no mass if the row's largest logit lies far
-//     enough above; otherwise a second read tells whether they are all masked.  If they are not, and if anything of 128 and more
+//     enough above; otherwise a second read tells whether they are all masked.  If they are not, or if anything of 128 and more
 //     or a NaN has been seen, the row goes to the search below.  (2048 x 128,256, one entry in 20 masked, T = 1.6: 191 us, 357 by
 //     passes.  Telling them apart in the pass, two packed instructions for two entries, took 16,384 x 151,936 from 856 to 899.)
 //   - Entries within 2^-10 of zero share a counter; their masses are summed on the side (a quarter of the rounds of rows around
