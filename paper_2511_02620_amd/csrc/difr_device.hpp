@@ -296,6 +296,57 @@ __device__ __forceinline__ void block_argmax(float &y, int32_t &i, float *lds_y,
     for (int w = 1; w < kWaves; ++w) argmax_combine(y, i, lds_y[w], lds_i[w]);
 }
 
+// Wave priority along a row, for kernels that are bound by instruction issue and give a row one workgroup.
+//
+// A SIMD issues from its oldest wave first, so of the rows that share a compute unit one runs ahead, and a launch ends with one row
+// to a compute unit: a single wave per SIMD, which its own dependent instructions keep from more than half of the issue slots
+// (timeline of 1024 x 128,256, both scores: the four rows of a compute unit end 42, 49, 62 and 77 us after the launch, and the
+// last of them would have needed 16 us of issue slots for what it does in the 15 us alone and the 60 before).  The rows that end
+// the launch - the last `resident` of the grid, as many as the device holds at once - therefore take their priority from what they
+// have left: two thirds or more of the row 2, one third 1, less 0, so that they end together.  The rows before them stay at 3:
+// their places are what the last rows wait for.  Both scores, bf16, V = 128,256, us without / with: 769 rows 77 / 70, 1024 76 / 68,
+// 1280 88 / 78, 1500 104 / 95, 2048 132 / 122, 4096 247 / 241, 8192 485 / 480.  Four levels with the earlier rows at the highest
+// of them: 1280 rows with the admissible set 84 against 87, 1500 115 against 110; 1536 instead of the 1280 rows that fit: 1500
+// rows 105, 768 instead of them 96.
+#ifndef PCHK
+#define PCHK 7
+#endif
+//
+// (`first_last`, the row from which on they are the last, comes from the host: the grid's size would be one more dependent load,
+// 1.5% of 8000 rows of 9000 logits.  Setting the priority before the row's scalars and its claim are loaded, so that a new row does
+// not wait for those that stream: 8000 x 9000 with the token 84 -> 117 us, not done.)
+struct RowPace {
+    int third, next, level;
+    // `rounds`: of the row.  All waves; the row runs at its first priority from here.
+    __device__ __forceinline__ RowPace(int first_last, int rounds) : third((rounds + 2) / 3), next(-1), level(2)
+    {
+        if ((int)blockIdx.x >= first_last) {
+            next = third;
+            __builtin_amdgcn_s_setprio(2);
+        } else {
+            __builtin_amdgcn_s_setprio(3);
+        }
+    }
+    // `round` rounds of the row are behind this wave (called for each of them)
+    __device__ __forceinline__ void at(int round)
+    {
+        if (round == next) {
+            next += third;
+            if (--level == 1)
+                __builtin_amdgcn_s_setprio(1);
+            else
+                __builtin_amdgcn_s_setprio(0);
+        }
+    }
+    // what follows the stream is a few dependent steps
+    __device__ __forceinline__ void done() { __builtin_amdgcn_s_setprio(3); }
+};
+struct NoPace {
+    __device__ __forceinline__ NoPace(int = 0, int = 0) {}
+    __device__ __forceinline__ void at(int) {}
+    __device__ __forceinline__ void done() {}
+};
+
 // Per-row scalars every kernel needs.  `ok` is false for a sequence id outside [0,S)
 // or a temperature that is not a positive finite number.
 struct RowInfo {

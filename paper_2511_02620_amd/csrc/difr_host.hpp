@@ -10,6 +10,23 @@
 
 namespace difr {
 
+// Workgroups of `Kernel` that the device holds at once (RowPace); 0 if the runtime does not say.  A figure of the kernel's code
+// and of the GPU the process runs on, found once.
+template <auto Kernel>
+int resident_rows()
+{
+    static const int n = [] {
+        int dev = 0, cus = 0, per_cu = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), kBlock, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return 0;
+        }
+        return cus * per_cu;
+    }();
+    return n;
+}
+
 // filtered = false forces the unfiltered kernel (every entry evaluated exactly).
 int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t *argmax,
                         float *max_score, float *claimed_score, uint8_t *flags, int32_t *logit_rank,

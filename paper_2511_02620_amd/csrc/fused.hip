@@ -22,7 +22,7 @@ namespace difr {
 // TOK: how the honest sampler's Token-IPT-DiFR token is found (ipt_stream.hpp).
 template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kTokenMarks || (DT == 0 && (RANK || TOK != kNoToken)) ? 5 : 1))) void score_both_kernel(
-    RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa)
+    RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa, int first_last)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -67,7 +67,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
     const int full_rounds = (int)((V / E) / kBlock);  // rounds of 256 complete vectors
     IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
-    stream_rounds<DT, TOK>(g, s, marks, x_row, V, 0, full_rounds, true);
+    RowPace pace(first_last, full_rounds);
+    stream_rounds<DT, TOK>(g, s, marks, pace, x_row, V, 0, full_rounds, true);
+    pace.done();
     if (DT == 0 && !ADM && !rows_aligned(b)) g.bad_sum(s.Z);  // (the admissible set is counted on aligned rows only)
     g.finish(row, og, lds_y, lds_i, lds_rank);
     if (ADM) {
@@ -82,18 +84,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
     ipt_finish<DT, TOK>(b, ri_ipt, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), 0, oi, lds_f, lds_d, marks, &walk);
 }
 
+template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
+static void launch_score_both_kernel(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
+                                     const AdmissibleOutputs &oa, hipStream_t stream)
+{
+    score_both_kernel<DT, ADM, RANK, TOK, PEAKED><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(
+        b, claimed_ipt, og, oi, oa, (int)b.N - resident_rows<score_both_kernel<DT, ADM, RANK, TOK, PEAKED>>());
+}
+
 template <int DT, int TOK>
 static void launch_score_both_of(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                                  bool peaked, hipStream_t stream)
 {
-    const dim3 grid((unsigned)b.N), block(kBlock);
     const AdmissibleOutputs none{0.0f, nullptr, nullptr};
     if (og.logit_rank)  // counted in the same stream, only when asked for; every round is then looked at: no early test
-        score_both_kernel<DT, false, true, TOK><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+        launch_score_both_kernel<DT, false, true, TOK>(b, claimed_ipt, og, oi, none, stream);
     else if (peaked)
-        score_both_kernel<DT, false, false, TOK, true><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+        launch_score_both_kernel<DT, false, false, TOK, true>(b, claimed_ipt, og, oi, none, stream);
     else
-        score_both_kernel<DT, false, false, TOK><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, none);
+        launch_score_both_kernel<DT, false, false, TOK>(b, claimed_ipt, og, oi, none, stream);
 }
 
 int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
@@ -117,12 +126,11 @@ int launch_score_both(const RowBatch &b, const int32_t *claimed_ipt, const Gumbe
 int launch_score_both_admissible(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og,
                                  const IptOutputs &oi, float delta, int32_t *count, float *log2_count, hipStream_t stream)
 {
-    const dim3 grid((unsigned)b.N), block(kBlock);
     const AdmissibleOutputs oa{delta, count, log2_count};
     if (b.dtype == 0)
-        score_both_kernel<0, true, false, kNoToken><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        launch_score_both_kernel<0, true, false, kNoToken>(b, claimed_ipt, og, oi, oa, stream);
     else
-        score_both_kernel<1, true, false, kNoToken><<<grid, block, 0, stream>>>(b, claimed_ipt, og, oi, oa);
+        launch_score_both_kernel<1, true, false, kNoToken>(b, claimed_ipt, og, oi, oa, stream);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

@@ -30,8 +30,8 @@ struct NoIpt {
 
 // Full rounds [r0, r1) of the row (256 complete vectors each), and with them, if `last`, what the row holds beyond its full
 // rounds.  r1 is the number of full rounds then.
-template <int DT, int TOK, class G, class S>
-__device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, const typename Elem<DT>::type *x_row, int64_t V,
+template <int DT, int TOK, class G, class S, class Pace>
+__device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, Pace &pace, const typename Elem<DT>::type *x_row, int64_t V,
                                               int r0, int r1, bool last)
 {
     constexpr int E = Elem<DT>::kPerVec;
@@ -53,6 +53,7 @@ __device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, 
             ++round;
             marks.at(round, s);
             if ((round & 15) == 0) g.pickup();
+            pace.at(round);
             return round < r_end && (DT != 0 || g.gate.mode == MODE);
         };
         if constexpr (DT != 0) {
@@ -103,6 +104,7 @@ __device__ __forceinline__ void stream_rounds(G &g, S &s, IptMarks<TOK> &marks, 
         careful(round_t, true);
         round = round_t + 1;
         marks.at(round, s);
+        pace.at(round);
         run_to(r1);
         if (ragged) careful(r1, false);
     } else {

@@ -68,6 +68,7 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
     const int r0 = part_begin(part, ws.parts, full_rounds), r1 = part_begin(part + 1, ws.parts, full_rounds);
     const bool last = part == ws.parts - 1;
     IptMarks<kNoToken> marks(nullptr, nullptr, 0);
+    NoPace pace;
     // (single variables: as one struct the compiler moves it through memory)
     float out_M = 0.0f, best_y = 0.0f;
     double out_Z = 0.0, out_P = 0.0;
@@ -111,7 +112,7 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
         };
         if constexpr (IPT) {
             IptStream<DT> s(ri_ipt, x_row, V, false);
-            stream_rounds<DT, kNoToken>(g, s, marks, x_row, V, r0, r1, last);
+            stream_rounds<DT, kNoToken>(g, s, marks, pace, x_row, V, r0, r1, last);
             if (DT == 0 && !ADM && !rows_aligned(b)) g.bad_sum(s.Z);
             gumbel_done();
             const IptTotals t = ipt_combine(s.ref(), s.Z, s.P, s.refP(), lds_f, lds_d);
@@ -120,13 +121,13 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
             out_P = t.P;
         } else {
             NoIpt s;
-            stream_rounds<DT, kNoToken>(g, s, marks, x_row, V, r0, r1, last);
+            stream_rounds<DT, kNoToken>(g, s, marks, pace, x_row, V, r0, r1, last);
             gumbel_done();
         }
     } else {
         NoGumbel g;
         IptStream<DT> s(ri_ipt, x_row, V, ipt_rank);
-        stream_rounds<DT, kNoToken>(g, s, marks, x_row, V, r0, r1, last);
+        stream_rounds<DT, kNoToken>(g, s, marks, pace, x_row, V, r0, r1, last);
         above = s.total_above(lds_rank);
         const IptTotals t = ipt_combine(s.ref(), s.Z, s.P, s.refP(), lds_f, lds_d);
         out_M = t.M;
