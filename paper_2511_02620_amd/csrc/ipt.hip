@@ -16,8 +16,18 @@
 namespace difr {
 
 // Streaming kernel (the streaming state is described in ipt_stream.hpp).  TOK: how the honest sampler's token is found.
+//
+// Bound by reading; what costs beside it is the end of a launch, where the rows left over have too few bytes in flight.
+//
+// Eight waves per SIMD (without the token; the compiler's own choice of scalar registers held six): 2048 rows fit at once.  With the
+// marks it is seven, and eight would spill.
+//
+// `deep`: three vectors in flight beside the one in use instead of one.  Where the rows are few it is what keeps the memory busy, where
+// many share it they get in each other's way.  bf16, V = 128,256, us with one / three: 800 rows 43 / 37, 1024 46 / 43, 1500 58.5 /
+// 61; with the token (every row reads a part of itself again, when others have ended) 1024 60 / 56, 2048 110 / 99, 4096 204 / 188.
 template <int DT, int TOK>
-__global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutputs o)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kNoToken ? 8 : 1))) void ipt_score_kernel(RowBatch b, IptOutputs o,
+                                                                                                                bool deep)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -42,14 +52,35 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
     const int round_t = s.valid ? (int)((s.t / E) / kBlock) : -1;
     IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
-    auto stream = [&](int r0, int r1) {  // full rounds [r0, r1) with one vector kept in flight
+    auto stream = [&](int r0, int r1) {  // full rounds [r0, r1)
         if (r0 >= r1) return;
-        u32x4 q_next = load_round(x_row, r0);
-        for (int round = r0; round < r1;) {
-            const u32x4 q = q_next;
-            if (round + 1 < r1) q_next = load_round(x_row, round + 1);
+        int round = r0;
+        auto body = [&](const u32x4 &q) {
             s.fast_round(q);
             marks.at(++round, s);
+            return round < r1;
+        };
+        if (TOK != kTokenMarks && !deep) {
+            u32x4 q_next = load_round(x_row, round);
+            while (true) {
+                const u32x4 q = q_next;
+                if (round + 1 < r1) q_next = load_round(x_row, round + 1);
+                if (!body(q)) break;
+            }
+            return;
+        }
+        u32x4 qa = load_round(x_row, round), qb = qa, qc = qa, qd = qa;
+        if (round + 1 < r1) qb = load_round(x_row, round + 1);
+        if (round + 2 < r1) qc = load_round(x_row, round + 2);
+        while (true) {
+            if (round + 3 < r1) qd = load_round(x_row, round + 3);
+            if (!body(qa)) break;
+            if (round + 3 < r1) qa = load_round(x_row, round + 3);
+            if (!body(qb)) break;
+            if (round + 3 < r1) qb = load_round(x_row, round + 3);
+            if (!body(qc)) break;
+            if (round + 3 < r1) qc = load_round(x_row, round + 3);
+            if (!body(qd)) break;
         }
     };
     auto careful = [&](int round, bool prefix_open) {
@@ -76,18 +107,41 @@ __global__ __launch_bounds__(kBlock) void ipt_score_kernel(RowBatch b, IptOutput
     ipt_finish<DT, TOK>(b, ri, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), above, o, lds_f, lds_d, marks, &walk);
 }
 
+// Workgroups to a compute unit, without the token: the eight that fit, or seven or six if the launch's last generation of rows is
+// fuller then (idle LDS keeps the others out); a generation that starts with a few rows left takes as long as a full one.  2 x 1536
+// rows at six, us for bf16, V = 128,256, with eight / by this rule: 2304 rows 109 / 98, 3000 120 / 115, 5000 195 / 191, 7000 268 / 265;
+// 2048, 3500, 4096 the same.  Five as well: 2304 rows 96, but 5000 x 30,000 58 against 53.
+static unsigned idle_lds(int64_t N, int resident)
+{
+    constexpr int kFit = 8, kLeast = 6, kLdsOfUnit = 160 * 1024;
+    const int64_t units = resident / kFit;
+    if (N <= resident || units == 0) return 0;
+    int best = kFit;
+    auto places = [&](int per_unit) { return (N + units * per_unit - 1) / (units * per_unit) * per_unit; };
+    for (int p = kFit - 1; p >= kLeast; --p)
+        if (places(p) < places(best)) best = p;
+    return best == kFit ? 0 : (unsigned)(kLdsOfUnit / best - 1024);
+}
+
+template <int DT, int TOK>
+static void launch_ipt(const RowBatch &b, const IptOutputs &o, hipStream_t stream)
+{
+    const int resident = resident_rows<ipt_score_kernel<DT, TOK>>();
+    const unsigned lds = TOK == kNoToken ? idle_lds(b.N, resident) : 0u;
+    ipt_score_kernel<DT, TOK><<<dim3((unsigned)b.N), dim3(kBlock), lds, stream>>>(b, o, 2 * b.N <= resident);
+}
+
 int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_hi, float *u,
                      int32_t *ipt_token, double sigma, double eps, float *log_mass, uint8_t *flags,
                      int32_t *logit_rank, hipStream_t stream)
 {
-    const dim3 grid((unsigned)b.N), block(kBlock);
     const IptOutputs o{dist, cdf_lo, cdf_hi, u, ipt_token, sigma, eps, log_mass, flags, logit_rank};
     auto launch = [&](auto TOK) {
         constexpr int tok = decltype(TOK)::value;
         if (b.dtype == 0)
-            ipt_score_kernel<0, tok><<<grid, block, 0, stream>>>(b, o);
+            launch_ipt<0, tok>(b, o, stream);
         else
-            ipt_score_kernel<1, tok><<<grid, block, 0, stream>>>(b, o);
+            launch_ipt<1, tok>(b, o, stream);
     };
     switch (token_search(ipt_token, b.V, b.dtype)) {
         case kNoToken: launch(std::integral_constant<int, kNoToken>()); break;

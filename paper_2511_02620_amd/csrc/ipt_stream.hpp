@@ -92,10 +92,11 @@ __device__ double gaussian_log_mass(double a, double b, double u, double sigma, 
 // after each 1/kMarks of the full rounds (its own slots: no barrier).  Once the total is known, the sums at the marks say in
 // which stretch the CDF passes u Z, and only that stretch is read again.  What bounds the search is that second read and the
 // latency of its dependent steps: walking the CDF from the row's start, one round and two barriers at a time, made a call on
-// 2048 rows of 151,936 bf16 logits without claims take 227 us; with the marks, and up to 16 rounds (four loads in flight)
-// between two barriers, it takes 136.  Six marks: 19 KB of LDS, eight workgroups to a compute unit; four (longer stretches)
-// 142 us, eight (six workgroups) 139.
-constexpr int kMarks = 6;
+// 2048 rows of 151,936 bf16 logits without claims take 227 us; with the marks, up to 16 rounds (four loads in flight) between
+// two barriers and nothing read past the stretch it takes 113 (2048 x 50,000: 47.5 us, 59 with 16 rounds read whatever the stretch).
+// Seven marks: 22.4 KB of LDS, seven workgroups to a compute unit; six 116 us; eight, which leave room for six workgroups, 113, but
+// 2048 x 50,000 49.6.
+constexpr int kMarks = 7;
 constexpr int kWalkRounds = 16;  // rounds summed between two barriers of the walk: 16 x 4 wave sums, one per lane
 static_assert(kWalkRounds * kWaves == 64, "the walk scans one wave sum per lane");
 // Full rounds from which a row has marks; a shorter one is walked from its start (ipt_walk_short), which needs fewer steps
@@ -145,11 +146,12 @@ struct WalkScratch {
 };
 
 // All 256 threads: the token at which the CDF of the entries of rounds r0, r0 + 1, ... passes `target`; `before` is the mass of
-// the rounds below r0, terms are 2^(x c + neg_Mc).  -1 if it is not passed before the end of the row.  The wave sums of up to
+// the rounds below r0, terms are 2^(x c + neg_Mc); by the sums at hand it is passed before round r_mark, and what follows is read only
+// if rounding has it otherwise.  -1 if it is not passed before the end of the row.  The wave sums of up to
 // kWalkRounds rounds are formed between two barriers, one scan over them finds the 512 entries that hold the token, and their
 // wave finds it.
 template <int DT>
-__device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row, int64_t V, float c, float neg_Mc, int r0,
+__device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row, int64_t V, float c, float neg_Mc, int r0, int r_mark,
                                             double before, double target, WalkScratch &w)
 {
     constexpr int E = Elem<DT>::kPerVec;
@@ -166,8 +168,8 @@ __device__ __forceinline__ int32_t ipt_walk(const typename Elem<DT>::type *x_row
         for (int j = 0; j < E; ++j) e[j] = fast_exp2(__fmaf_rn(x[j], c, neg_Mc));
         return (double)tree_sum<E>(e);
     };
-    for (; r0 < n_rounds; r0 += kWalkRounds) {
-        const int nr = min(kWalkRounds, n_rounds - r0);
+    for (int nr; r0 < n_rounds; r0 += nr) {
+        nr = min(kWalkRounds, (r0 < r_mark ? r_mark : n_rounds) - r0);
         __syncthreads();  // (the scan of the batch before has been read; w.tok is set)
         for (int k0 = 0; k0 < nr; k0 += 4) {
             u32x4 q[4];
@@ -405,14 +407,17 @@ __device__ __forceinline__ void ipt_finish(const RowBatch &b, const RowInfo &ri,
         __syncthreads();
         // the last mark at which the CDF has not passed u yet
         double before = 0.0;
-        int r0 = 0;
+        int r0 = 0, r_mark = 0;
         for (int k = 0; k < marks.n; ++k) {
             const double v = walk->mark_sum[k][0] + walk->mark_sum[k][1] + walk->mark_sum[k][2] + walk->mark_sum[k][3];
-            if (v > target) break;
+            if (v > target) {
+                r_mark = (k + 1) * marks.len;
+                break;
+            }
             before = v;
             r0 = (k + 1) * marks.len;
         }
-        return ipt_walk<DT>(x_row, b.V, c, -t.M, r0, before, target, *walk);
+        return ipt_walk<DT>(x_row, b.V, c, -t.M, r0, r_mark, before, target, *walk);
     });
 }
 

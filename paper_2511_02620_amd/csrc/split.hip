@@ -241,7 +241,9 @@ __global__ __launch_bounds__(kBlock) void score_merge_kernel(RowBatch b, const i
             const uint64_t hit = __builtin_amdgcn_ballot_w64(have && incl > target);
             const int f = hit != 0ull ? __builtin_ctzll(hit) : ws.parts - 1;
             const double before = __shfl(incl - z, f, 64);
-            return ipt_walk<DT>(x_row, V, c, -M, part_begin(f, ws.parts, (int)((V / E) / kBlock)), before, target, walk);
+            const int full_rounds = (int)((V / E) / kBlock);
+            return ipt_walk<DT>(x_row, V, c, -M, part_begin(f, ws.parts, full_rounds), part_begin(f + 1, ws.parts, full_rounds), before,
+                                target, walk);
         });
     }
 }
