@@ -26,7 +26,7 @@ namespace difr {
 // eight words; B and C use packed 16-bit min / max of the raw bf16 bit patterns (for a
 // cap <= 0, "x >= cap" is "bits <= bits(cap)" as unsigned 16-bit; for a cap > 0 it is
 // "bits >= bits(cap)" as signed 16-bit).  Entries of a vector that trips a test get a
-// per-entry bound g_v <= (151 - bits(float(q_v)) 2^-23) ln 2, q_v = (~r_v) >> 8  (from
+// per-entry bound g_v <= (159 - bits(float(q_v)) 2^-23) ln 2, q_v = ~r_v without its low 9 bits  (from
 // -ln(-ln(1-w)) <= -ln w and log2(1+m) >= m), and only those whose bound still reaches L
 // are evaluated exactly, with the same arithmetic as the unfiltered kernel.  Every noise
 // word is still generated; the outputs are identical to the unfiltered kernel's, bit for
@@ -50,9 +50,10 @@ __device__ __forceinline__ i16x2 as_i16x2(uint32_t w) { return __builtin_bit_cas
 // float conversions is below 1e-5 and is covered by the caller's slack.
 __device__ __forceinline__ float gumbel_upper_bound(uint32_t r)
 {
-    const float f = (float)((~r) >> 8);
+    // ((~r) >> 9 times 2^9: at most w 2^32, in one bitwise instruction)
+    const float f = (float)(~r & 0xFFFFFE00u);
     const float bits = (float)__float_as_int(f);
-    return __fmaf_rn(bits, -kLn2 * 0x1p-23f, 151.0f * kLn2);
+    return __fmaf_rn(bits, -kLn2 * 0x1p-23f, 159.0f * kLn2);
 }
 
 // bf16 bit pattern of a logit cap, rounded so that the 16-bit test never misses an entry:
@@ -347,6 +348,32 @@ struct GumbelStream {
         }
     }
 
+    // TOPN mode: key of one of the vector's best scores for TopN::publish_prime(): the exact score of the entry with the largest bound
+    // (0: there is none; the claimed token is left out).
+    __device__ __forceinline__ uint32_t prime_key(u32x4 q, int round, bool active) const
+    {
+        const uint64_t p0 = (uint64_t)kPhiloxM0 * (uint32_t)(round * kBlock * (E / 4)) + lane_prod;
+        uint32_t r[E];
+        philox4x32_10_from_product(p0, ri.pos, ri.seq, kStreamGumbel, ri.key, r);
+        if (E == 8) philox4x32_10_from_product(p0 + kPhiloxM0, ri.pos, ri.seq, kStreamGumbel, ri.key, r + (E - 4));
+        float x[E];
+        unpack_vector<DT>(q, x);
+        const int32_t v0 = (round * kBlock + tid) * E;
+        float best = -__builtin_inff(), xb = 0.0f;
+        uint32_t rb = 0u;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const float bound = __fmaf_rn(x[j], inv_T, gumbel_upper_bound(r[j]));
+            if (bound > best && v0 + j != t) {
+                best = bound;
+                xb = x[j];
+                rb = r[j];
+            }
+        }
+        const float y = perturbed_score(xb, inv_T, rb);
+        return active && best > -__builtin_inff() && y == y ? float_order_bits(y + 0.0f) : 0u;
+    }
+
     // TOPN mode: scores go to the selection handed to process() / tail() (by pointer argument, never stored:
     // the selection must stay in registers); the bound is its threshold (call retarget() whenever that
     // moves).  Same synchronisation rules as arm_count().
@@ -562,12 +589,12 @@ struct GumbelStream {
             } else {
                 xub = vector_upper_bound_f32(q);
             }
-            const uint64_t hitmask =
-                __builtin_amdgcn_ballot_w64(active && !(__fmaf_rn(xub, inv_T, gumbel_upper_bound(rmax)) < gate.Lgate));
+            const bool hit = active && !(__fmaf_rn(xub, inv_T, gumbel_upper_bound(rmax)) < gate.Lgate);
+            const uint64_t hitmask = __builtin_amdgcn_ballot_w64(hit);
             if (hitmask != 0ull) {
                 const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(hitmask >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)hitmask, 0u));
-                if ((hitmask >> (tid & 63)) & 1ull) defer_q[defer_n + (int)before] = round * kBlock + tid;
+                if (hit) defer_q[defer_n + (int)before] = round * kBlock + tid;
                 defer_n += (int)__builtin_popcountll(hitmask);
             }
             return;

@@ -64,11 +64,21 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
         const int64_t vec = (int64_t)round * kBlock + tid;
         lx.push_vector(q, vec * E, vec < nvec && (only_wave < 0 || (tid >> 6) == only_wave));
     };
-    // priming run of the first round (topn.hpp): a threshold before anything is pushed
+    // a threshold before anything is pushed (topn.hpp), from the first round and others spread over the row
     if (n_rounds > 0) {
-        lx.top.begin_prime();
-        do_round(fetch(0), 0);
-        if (lx.top.end_prime(scratch)) lx.retarget();
+        const u32x4 q = fetch(0);
+        uint32_t *slots = reinterpret_cast<uint32_t *>(scratch.hist);
+        lx.top.publish_prime(lx.prime_key(q, tid < nvec, n_main), slots);
+        __syncthreads();
+        const uint64_t theta = lx.top.read_prime(slots);
+        if (theta != 0ull) {
+            lx.top.theta = theta;
+        } else {  // (masked rows, coarse logits, fewer entries than wanted)
+            lx.top.begin_prime();
+            do_round(q, 0);
+            lx.top.end_prime(scratch);
+        }
+        lx.retarget();
     }
     // Epochs without barriers, as in the likelihood kernel: vectors that hold a candidate wait in the wave's queue until
     // 64 of them make the look at their entries worth the wave's while; one barrier per epoch combines "a push found
@@ -76,9 +86,10 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
     int round = 0, epoch = 0;
     bool ran_full = false;
     while (round < n_rounds) {
-        // epochs of 1, 1, 2, 4 rounds, then 8 at a time: the threshold moves only between epochs, and while little
-        // of the row has been seen it moves a lot (each doubling of what has been seen brings about top_k pushes)
-        const int len = round < 2 ? 1 : (round < 4 ? 2 : (round < 8 ? 4 : kTopEpoch));
+        // Epochs of 8 rounds; a large selection begins with 2 and 6 (each doubling of what has been seen brings about top_k pushes, and
+        // the threshold moves only between epochs: 2048 x 128,256 with k = 200: 182 us, with 8 at once 350, the buffer having run full).
+        // k = 50, us with 1, 1, 2, 4 and then 8 / with 8: 4096 x 128,256 204 / 201, 4096 x 9000 58.3 / 53.4.
+        const int len = CAP == kTopCapSmall ? kTopEpoch : (round < 2 ? 2 : (round < 8 ? 6 : kTopEpoch));
         const int r_end = round < n_main ? min(n_main, round + len) : n_rounds;
         if (round >= n_main) {
             do_round(fetch(round), round);
@@ -103,7 +114,7 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
             if (mine) atomicOr(word, mine);
             if (tid == 0) epoch_flags[(epoch + 1) % 3] = 0u;
             __syncthreads();
-            const uint32_t all = *word;
+            const uint32_t all = (uint32_t)__builtin_amdgcn_readfirstlane((int)*word);  // (so that what it decides is scalar code)
             ++epoch;
             if (all & 1u) {
                 ran_full = true;

@@ -45,7 +45,7 @@ struct FilteredIptSide {
 
 template <int DT, int CAP, bool BOTH>
 __device__ __forceinline__ void likelihood_row(const RowBatch &b, const LikelihoodParams &p, const LikelihoodOutputs &o,
-                                               const FilteredIptSide &ipt)
+                                               const FilteredIptSide &ipt, int first_last)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -59,6 +59,7 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
     __shared__ double lds_d[kWaves];
     __shared__ double sA[kTopMaxN], sB[kTopMaxN];
     __shared__ int32_t s_bad, s_tok;
+    __shared__ double s_gt;
     __shared__ double s_e[BOTH ? kTopMaxN : 1];     // the IPT side's kept set in ascending vocabulary index
     __shared__ int32_t s_idx[BOTH ? kTopMaxN : 1];
 
@@ -132,17 +133,19 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         g.drain(&top_y);
         if (p.top_k > 0) lx.push_vector(q, vec * E, active);
     };
+    u32x4 q_next = u32x4{0u, 0u, 0u, 0u};
+    RowPace pace(first_last, n_main);
     // full rounds [r0, r1) with the loop body instantiated for the gate's mode (it can only change at a
     // compaction, i.e. between epochs): one copy of the Philox + gate code per mode instead of one per
     // mode and unrolled round, which did not fit the instruction cache.  Vectors that trip a test wait in the
     // two per-wave queues, across epochs, until 64 of them make a look at them worth the wave's while.
     auto run_rounds = [&](auto mode_tag, int r0, int r1) __attribute__((always_inline)) {
         constexpr int MODE = decltype(mode_tag)::value;
-        u32x4 q_next = load_round(x_row, r0);
 #pragma nounroll
         for (int r = r0; r < r1; ++r) {
             const u32x4 q = q_next;
-            if (r + 1 < r1) q_next = load_round(x_row, r + 1);  // keep one vector in flight
+            if (r + 1 < n_main) q_next = load_round(x_row, r + 1);  // one vector in flight, across epochs
+            pace.at(r + 1);
             g.template process<MODE>(q, r, true, &top_y);
             if (g.defer_n >= 64) g.drain(&top_y);
             if (p.top_k > 0) {
@@ -151,23 +154,36 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
             }
         }
     };
-    // priming run of the first round (topn.hpp): thresholds for both selections before anything is pushed
+    // thresholds for both selections before anything is pushed (topn.hpp), from the first round
     if (n_rounds > 0) {
-        top_y.begin_prime();
-        top_x.begin_prime();
-        do_round(0);
-        if (top_y.end_prime(scratch)) g.retarget(top_y);
-        if (top_x.end_prime(scratch)) lx.retarget();
+        if (tid < nvec) q_next = load_round(x_row, 0);
+        uint32_t *slots_y = reinterpret_cast<uint32_t *>(scratch.hist), *slots_x = reinterpret_cast<uint32_t *>(scratch.tmp);
+        top_y.publish_prime(top_y.n > 0 ? g.prime_key(q_next, 0, tid < nvec) : 0u, slots_y);
+        top_x.publish_prime(p.top_k > 0 ? lx.prime_key(q_next, tid < nvec, n_main) : 0u, slots_x);
+        __syncthreads();
+        const uint64_t theta_y = top_y.read_prime(slots_y), theta_x = top_x.read_prime(slots_x);
+        if (theta_y != 0ull && theta_x != 0ull) {
+            top_y.theta = theta_y;
+            top_x.theta = theta_x;
+        } else {  // (masked rows, coarse logits, fewer entries than wanted)
+            top_y.begin_prime();
+            top_x.begin_prime();
+            do_round(0);
+            top_y.end_prime(scratch);
+            top_x.end_prime(scratch);
+        }
+        g.retarget(top_y);
+        lx.retarget();
     }
     // Epochs: the first round alone, then up to kLikEpoch rounds at a time without a barrier; the partly filled round is
     // an epoch of its own.  A push that finds a buffer full (data in ascending order, for instance) ends this mode.
     int round = 0, epoch = 0;
     bool ran_full = false;
     while (round < n_rounds) {
-        // (the first epochs are 1, 1, 2 and 4 rounds long: the thresholds move only between epochs, and while little of
-        // the row has been seen they move a lot - a threshold that is one doubling of the data behind lets twice as
-        // many vectors through the tests)
-        const int len = round < 2 ? 1 : (round < 4 ? 2 : (round < 8 ? 4 : kLikEpoch));
+        // (the first epochs are 2 and 6 rounds long: the thresholds move only between epochs, and while little of the row has been
+        // seen they move a lot.  4096 x 9000, k = 50, s = 16: 142.4 us, with 1, 1, 2 and 4 rounds 145.5; 2048 x 128,256 with k = 200
+        // and s = 64 561 / 580.)
+        const int len = round < 2 ? 2 : (round < 8 ? 6 : kLikEpoch);
         const int r_end = round < n_main ? min(n_main, round + len) : n_rounds;
         if (round >= n_main)
             do_round(round);
@@ -190,7 +206,7 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
             if (mine) atomicOr(word, mine);
             if (tid == 0) epoch_flags[(epoch + 1) % 3] = 0u;
             __syncthreads();
-            const uint32_t all = *word;
+            const uint32_t all = (uint32_t)__builtin_amdgcn_readfirstlane((int)*word);  // (so that what it decides is scalar code)
             ++epoch;
             if (all & 1u) {
                 ran_full = true;
@@ -205,6 +221,7 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         }
         round = r_end;
     }
+    pace.done();
     if (ran_full) {
         // Careful mode: the row again from its start, one wave and one round at a time with a compaction check after
         // each step.  A step starts with fewer than kTopTrigger entries in a buffer and adds at most 8 per lane of one
@@ -247,19 +264,26 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         __syncthreads();
     }
     if (p.tau_in) tau = (double)p.tau_in[row];  // found beforehand by the nucleus kernel (NaN if it could not: pi becomes NaN)
-    double xt = 0.0, gt = 0.0;
-    if (valid) {
-        xt = (double)Elem<DT>::to_float(x_row[t]);
-        gt = gumbel_f64(ri, t);
+    const double xt = valid ? (double)Elem<DT>::to_float(x_row[t]) : 0.0;
+    if (valid && tid <= ns) {  // (the claimed token's noise by the thread after the members of S: ns <= s < kBlock or below)
+        const int32_t i = tid < ns ? top_index(buf_y[tid]) : t;
+        const double gi = gumbel_f64(ri, i);
+        if (tid < ns) {
+            const double xi = (double)Elem<DT>::to_float(x_row[i]);
+            sA[tid] = gi;
+            sB[tid] = xi;
+            if (o.active) o.active[row * p.s + tid] = i;
+        } else {
+            s_gt = gi;
+        }
     }
+    if (o.active && tid >= ns && tid < p.s) o.active[row * p.s + tid] = -1;
+    if (ns == kBlock && tid == 0) s_gt = gumbel_f64(ri, t);  // (no thread is left after 256 members)
+    __syncthreads();
     if (tid < ns) {
-        const int32_t i = top_index(buf_y[tid]);
-        const double xi = (double)Elem<DT>::to_float(x_row[i]);
-        sA[tid] = xt - xi + (double)ri.T * (gt - gumbel_f64(ri, i));
+        const double xi = sB[tid];
+        sA[tid] = xt - xi + (double)ri.T * (s_gt - sA[tid]);
         sB[tid] = tau - xi;
-        if (o.active) o.active[row * p.s + tid] = i;
-    } else if (o.active && tid < p.s) {
-        o.active[row * p.s + tid] = -1;
     }
     if (o.active)
         for (int j = kBlock + tid; j < p.s; j += kBlock) o.active[row * p.s + j] = -1;  // (s <= 256: never runs)
@@ -301,14 +325,14 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
 template <int DT, bool BOTH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void likelihood_small_kernel(RowBatch b, LikelihoodParams p,
                                                                                                          LikelihoodOutputs o,
-                                                                                                         FilteredIptSide ipt)
+                                                                                                         FilteredIptSide ipt, int first_last)
 {
-    likelihood_row<DT, kTopCapSmall, BOTH>(b, p, o, ipt);
+    likelihood_row<DT, kTopCapSmall, BOTH>(b, p, o, ipt, first_last);
 }
 template <int DT, bool BOTH>
-__global__ __launch_bounds__(kBlock) void likelihood_big_kernel(RowBatch b, LikelihoodParams p, LikelihoodOutputs o, FilteredIptSide ipt)
+__global__ __launch_bounds__(kBlock) void likelihood_big_kernel(RowBatch b, LikelihoodParams p, LikelihoodOutputs o, FilteredIptSide ipt, int first_last)
 {
-    likelihood_row<DT, kTopCapBig, BOTH>(b, p, o, ipt);
+    likelihood_row<DT, kTopCapBig, BOTH>(b, p, o, ipt, first_last);
 }
 
 template <bool BOTH>
@@ -319,14 +343,14 @@ static int launch_likelihood_any(const RowBatch &b, const LikelihoodParams &p, c
     const bool small = p.s <= kTopSmallN && p.top_k <= kTopSmallN;
     if (b.dtype == 0) {
         if (small)
-            likelihood_small_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt);
+            likelihood_small_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<0, BOTH>>());
         else
-            likelihood_big_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt);
+            likelihood_big_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_big_kernel<0, BOTH>>());
     } else {
         if (small)
-            likelihood_small_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt);
+            likelihood_small_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<1, BOTH>>());
         else
-            likelihood_big_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt);
+            likelihood_big_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_big_kernel<1, BOTH>>());
     }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

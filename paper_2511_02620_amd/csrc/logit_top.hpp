@@ -124,6 +124,28 @@ struct LogitTop {
         }
     }
 
+    // Key for TopN::publish_prime() of the largest logit in this thread's vectors of the first round (given) and of up to three more
+    // rounds spread over the row (NaNs apart; 0: there is none): the k-th largest of four rounds lies four times nearer to the row's than
+    // that of one, and rows that rise towards their end do not fill the buffer.
+    __device__ __forceinline__ uint32_t prime_key(u32x4 q, bool active, int n_main) const
+    {
+        const int step = n_main >> 2;
+        u32x4 more[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) more[i] = step > 0 ? load_round(defer_row, (i + 1) * step) : q;
+        auto largest = [](u32x4 v, float m) {
+            float x[E];
+            unpack_vector<DT>(v, x);
+#pragma unroll
+            for (int j = 0; j < E; ++j) m = fmaxf(m, x[j]);
+            return m;
+        };
+        float m = largest(q, __builtin_nanf(""));
+#pragma unroll
+        for (int i = 0; i < 3; ++i) m = largest(more[i], m);
+        return active && m == m ? float_order_bits(m + 0.0f) : 0u;
+    }
+
     // One 16-byte vector (entries v0 .. v0 + E - 1).  bf16: packed 16-bit min / max on the raw bit patterns, as
     // in the Gumbel gates; a NaN with the sign bit clear passes the test and is flagged, one with the sign bit
     // set counts as -inf.
@@ -209,23 +231,20 @@ __device__ __forceinline__ int filter_prefix_length(const uint64_t *buf, int nk,
     double *e = reinterpret_cast<double *>(s.tmp);
     if (tid < nk) e[tid] = exp(((double)top_key(buf[tid]) - (double)top_key(buf[0])) / T);
     __syncthreads();
+    // (the cumulative mass against top_p Z: the same cut as the cumulative probability against top_p, except within a rounding of
+    // the boundary.  The one thread that everybody waits for leaves its partial sums; where they reach top_p Z all threads see.)
     if (tid == 0) {
         double Z = 0.0;
-        for (int r = 0; r < nk; ++r) Z += e[r];
-        // (the cumulative mass against top_p Z: the same cut as the cumulative probability against top_p, except
-        // within a rounding of the boundary, and no division per entry on the one thread everybody waits for)
-        const double target = (double)top_p * Z;
-        double cum = 0.0;
-        int kept = nk;
+#pragma unroll 8
         for (int r = 0; r < nk; ++r) {
-            cum += e[r];
-            if (cum >= target) {
-                kept = r + 1;
-                break;
-            }
+            Z += e[r];
+            e[r] = Z;
         }
-        s.kept = kept;
+        s.kept = nk;
     }
+    __syncthreads();
+    const double target = (double)top_p * e[nk - 1];
+    if (tid < nk && e[tid] >= target && (tid == 0 || !(e[tid - 1] >= target))) s.kept = tid + 1;
     __syncthreads();
     const int kept = s.kept;
     __syncthreads();

@@ -3,12 +3,15 @@
 // Candidates are pushed into an LDS buffer as 64-bit composites (order-preserving image of the float
 // key in the high word, complemented index in the low word: a larger composite is a larger key or,
 // for equal keys - -0 and +0 are equal -, a smaller index, so all composites of a row are distinct).  Only composites above the
-// current threshold are pushed.  A compaction finds a lower bound of the n-th largest composite with a
-// radix select over the buffer, makes it the new threshold and keeps the entries at or above it.  In the
-// stream the select stops after the top 16 bits of the key (2 passes of 8 bits: the n-th largest key at
-// bf16 resolution, a handful of entries too many survive) unless more than kTopKeep entries share them;
-// all 8 passes, down to the exact n-th composite, run at the end of the row.  Nothing that belongs to the
-// final top n is ever dropped: the threshold is a lower bound of the n-th largest of what has been seen.
+// current threshold are pushed.  A compaction finds a lower bound of the n-th largest composite, makes it the
+// new threshold and keeps the entries at or above it.  In the stream a buffer of up to 256 entries is searched bit by bit
+// for the top 20 bits of the n-th key, by every wave for itself (nth_key); a handful of entries too many survive.  Fuller buffers
+// go by radix passes, which stop after the top 16 bits unless more than kTopKeep entries share them.  Where many entries
+// share the bits, and at the end of the row, the n-th composite is found exactly, by counting ranks or with all 8 radix passes.
+// Nothing that belongs to the final top n is ever dropped: the threshold is a lower bound of the n-th largest of what has been seen.
+// (4096 x 128,256, k = 50 and s = 16, T = 1: 500 us with rank counts, radix passes and a priming run over every entry of the first
+// round; 420 with bits, with priming by a key per thread - of four rounds for the logits -, with what the compactions decide in
+// scalar registers, and with priorities by what is left of the row.)
 //
 // Capacity.  The caller works in epochs of a few stream rounds without any barrier.  A push that finds the
 // buffer full raises `over` instead of storing its entry, and the caller then starts the row again in a careful
@@ -23,7 +26,7 @@
 
 namespace difr {
 
-constexpr int kTopEpoch = 8;       // stream rounds per epoch (measured: 4 and 16 are both slower)
+constexpr int kTopEpoch = 8;       // stream rounds per epoch of the filtered Token-IPT-DiFR kernel (measured: 4 and 16 are both slower)
 constexpr int kTopFresh = 16;      // a compaction is due after max(n, kTopFresh) pushes (measured: 8 to 64 within 1%)
 constexpr int kTopTrigger = 512;   // a compaction is due at the latest when this many slots are used
 constexpr int kTopCapSmall = kTopTrigger + 64 * 8;   // slots per buffer: the trigger plus one round of one wave
@@ -31,8 +34,8 @@ constexpr int kTopCapBig = kTopTrigger + 256 * 8;    // ... of the whole workgro
 constexpr int kTopSmallN = 64;     // largest n served with the small buffer
 constexpr int kTopMaxN = 256;      // largest n supported
 constexpr int kTopKeep = 256;      // a coarse compaction may leave up to this many entries
-constexpr int kTopRankMax = 96;    // a coarse compaction of more entries than this goes by radix passes: counting ranks
-                                   // costs every thread two instructions per entry, two 8-bit passes about 150 in all
+constexpr int kTopBits = 20;       // key bits at which a coarse compaction or the priming separates (nth_key)
+constexpr int kTopTies = 8;        // more entries than this that share the n-th key's bits: what follows is exact
 
 // float -> uint32 such that a < b  <=>  image(a) < image(b)  (-0 < +0; NaNs must be kept out by the caller)
 __device__ __forceinline__ uint32_t float_order_bits(float f)
@@ -52,6 +55,13 @@ __device__ __forceinline__ uint64_t top_composite(float key, int32_t index)
 __device__ __forceinline__ float top_key(uint64_t c) { return float_from_order_bits((uint32_t)(c >> 32)); }
 __device__ __forceinline__ int32_t top_index(uint64_t c) { return (int32_t)(0xFFFFFFFFu - (uint32_t)c); }
 
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint64_t uniform64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    return (uint64_t)hi << 32 | lo;
+}
+
 // LDS scratch shared by the selections of one workgroup (they never run at the same time).
 struct TopScratch {
     int32_t hist[256];
@@ -60,6 +70,31 @@ struct TopScratch {
     uint64_t sel64;
     uint64_t tmp[kTopKeep];
 };
+
+// Key bits of the n-th largest of the entries whose top kTopBits key bits the lanes of this wave hold, PER to a lane (0: none), or
+// 0 if there are fewer; `at_or_above`: how many have these bits or larger ones.  A search bit by bit, counting with ballots: every
+// wave finds it by itself from the same values, without a barrier, in kTopBits * PER compares.
+template <int PER>
+__device__ __forceinline__ uint32_t nth_key(const uint32_t (&k)[PER], int n, int &at_or_above)
+{
+    uint32_t prefix = 0;
+    auto count = [&](uint32_t least) {
+        int c = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) c += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(k[i] >= least));
+        return c;
+    };
+    at_or_above = 0x7FFFFFFF;
+    for (uint32_t bit = 1u << (kTopBits - 1); bit != 0u; bit >>= 1) {
+        const int c = count(prefix | bit);
+        if (c >= n) {
+            prefix |= bit;
+            at_or_above = c;
+            if (c == n) break;  // (the bits found separate exactly n)
+        }
+    }
+    return prefix;
+}
 
 struct TopN {
     uint64_t *buf;   // `cap` slots in LDS
@@ -135,6 +170,36 @@ struct TopN {
         return moved;
     }
 
+    // The same from one key per thread (float_order_bits of a real entry's key; 0: none) with one barrier instead of a compaction
+    // and without running the round's entries through push(): publish_prime(), a __syncthreads(), read_prime().  `slots`: kBlock words.
+    // read_prime() returns the threshold, or 0 if there are too few keys, if the n-th is a masked entry's, or if so many share its bits
+    // (coarse logits) that the entries' indices have to decide: then the priming run above finds one.  The next barrier after it
+    // frees the slots.
+    __device__ __forceinline__ int prime_group() const { return n <= 32 ? 4 : (n <= 100 ? 2 : 1); }
+    __device__ __forceinline__ void publish_prime(uint32_t key, uint32_t *slots) const
+    {
+        const int group = prime_group();
+        if (group >= 2) key = max(key, (uint32_t)__shfl_xor((int)key, 1, 64));
+        if (group >= 4) key = max(key, (uint32_t)__shfl_xor((int)key, 2, 64));
+        if (((int)threadIdx.x & (group - 1)) == 0) slots[(int)threadIdx.x / group] = key >> (32 - kTopBits);
+    }
+    template <int PER>
+    __device__ __forceinline__ uint64_t read_prime_of(const uint32_t *slots) const
+    {
+        uint32_t k[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) k[i] = slots[((int)threadIdx.x & 63) + 64 * i];
+        int at_or_above;
+        const uint32_t p = nth_key<PER>(k, n, at_or_above);
+        return p <= 0x007FFFFFu >> (32 - kTopBits) || at_or_above > n + kTopTies ? 0ull : (uint64_t)p << (64 - kTopBits);
+    }
+    __device__ __forceinline__ uint64_t read_prime(const uint32_t *slots) const
+    {
+        if (n <= 0) return ~0ull;
+        const int group = prime_group();
+        return group == 4 ? read_prime_of<1>(slots) : (group == 2 ? read_prime_of<2>(slots) : read_prime_of<4>(slots));
+    }
+
     __device__ __forceinline__ void push(uint64_t c)
     {
         if (priming) {
@@ -151,6 +216,40 @@ struct TopN {
         }
     }
 
+    // A coarse compaction of up to 64 * PER entries: every wave holds all of them and finds the threshold by itself; two barriers.  Returns
+    // false, and has changed nothing, if too many entries share the threshold's bits.
+    template <int PER>
+    __device__ __forceinline__ bool compact_by_bits(int cnt)
+    {
+        const int lane = (int)threadIdx.x & 63;
+        uint64_t c[PER];
+        uint32_t k[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            c[i] = lane + 64 * i < cnt ? buf[lane + 64 * i] : 0ull;
+            k[i] = (uint32_t)(c[i] >> (64 - kTopBits));
+        }
+        int kept;
+        const uint32_t p = nth_key<PER>(k, n, kept);
+        if (kept > n + kTopTies) return false;
+        __syncthreads();
+        if (threadIdx.x < 64) {
+            int at = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const uint64_t m = __builtin_amdgcn_ballot_w64(k[i] >= p);
+                if (k[i] >= p)
+                    buf[at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = c[i];
+                at += (int)__builtin_popcountll(m);
+            }
+            if (lane == 0) *count = kept;
+        }
+        theta = (uint64_t)p << (64 - kTopBits);
+        trigger = min(kTopTrigger, kept + (n > kTopFresh ? n : kTopFresh));
+        __syncthreads();
+        return true;
+    }
+
     // All 256 threads, after a barrier that follows the pushes.  If the buffer holds more than n entries,
     // raise the threshold to a lower bound of the n-th largest composite and keep only the entries at or
     // above it: exactly the n largest (coarse = false), or at most kTopKeep of them chosen at the
@@ -159,7 +258,7 @@ struct TopN {
     __device__ __forceinline__ bool compact(TopScratch &s, bool coarse = false)
     {
         const int tid = threadIdx.x;
-        const int cnt = min(*count, cap);
+        const int cnt = __builtin_amdgcn_readfirstlane(min(*count, cap));
         full = false;
         if (n <= 0) {  // nothing wanted: an impossible threshold
             __syncthreads();
@@ -173,7 +272,12 @@ struct TopN {
             __syncthreads();
             return false;
         }
-        const bool by_rank = !coarse || cnt <= kTopRankMax;
+        if (coarse && cnt <= 2 * 64) {
+            if (compact_by_bits<2>(cnt)) return true;
+        } else if (coarse && cnt <= 4 * 64) {
+            if (compact_by_bits<4>(cnt)) return true;
+        }
+        const bool by_rank = !coarse || cnt <= kBlock;
         if (by_rank && cnt <= kBlock) {
             // Few entries: every entry finds its rank by counting the entries above it (broadcast reads), the n
             // best move to the front in rank order and the n-th of them is the new, exact threshold.  Three
@@ -185,7 +289,7 @@ struct TopN {
             __syncthreads();
             if (tid < cnt && r < n) buf[r] = mine;
             if (tid == 0) *count = n;
-            theta = s.sel64;
+            theta = uniform64(s.sel64);
             trigger = min(kTopTrigger, n + (n > kTopFresh ? n : kTopFresh));
             __syncthreads();
             return true;
@@ -205,7 +309,7 @@ struct TopN {
             if (r0 < n) buf[r0] = mine0;
             if (tid + kBlock < cnt && r1 < n) buf[r1] = mine1;
             if (tid == 0) *count = n;
-            theta = s.sel64;
+            theta = uniform64(s.sel64);
             trigger = min(kTopTrigger, n + (n > kTopFresh ? n : kTopFresh));
             __syncthreads();
             return true;
@@ -242,10 +346,10 @@ struct TopN {
                 s.kept = (n - need) + v;
             }
             __syncthreads();
-            prefix |= (uint64_t)s.sel_bin << shift;
+            prefix |= (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(s.sel_bin) << shift;
             mask |= 255ull << shift;
-            need = s.sel_need;
-            at_or_above = s.kept;
+            need = __builtin_amdgcn_readfirstlane(s.sel_need);
+            at_or_above = __builtin_amdgcn_readfirstlane(s.kept);
             __syncthreads();
         }
         // gather the survivors (at_or_above <= kTopKeep of them) and move them to the front
@@ -274,7 +378,9 @@ struct TopN {
     {
         const int tid = threadIdx.x;
         __syncthreads();
+        const int cnt = __builtin_amdgcn_readfirstlane(min(*count, cap));
         compact(s, false);
+        if (cnt > n && cnt <= 2 * kBlock) return n;  // (the n best were put in rank order)
         const int m = min(min(*count, cap), n);
         if (tid < m) {
             const uint64_t mine = buf[tid];
