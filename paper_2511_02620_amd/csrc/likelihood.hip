@@ -175,15 +175,18 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         g.retarget(top_y);
         lx.retarget();
     }
-    // Epochs: the first round alone, then up to kLikEpoch rounds at a time without a barrier; the partly filled round is
+    const bool large = CAP != kTopCapSmall && max(p.s, p.top_k) > 128;
+    // Epochs: a few rounds, then up to kLikEpoch rounds at a time without a barrier; the partly filled round is
     // an epoch of its own.  A push that finds a buffer full (data in ascending order, for instance) ends this mode.
     int round = 0, epoch = 0;
     bool ran_full = false;
     while (round < n_rounds) {
         // (the first epochs are 2 and 6 rounds long: the thresholds move only between epochs, and while little of the row has been
-        // seen they move a lot.  4096 x 9000, k = 50, s = 16: 142.4 us, with 1, 1, 2 and 4 rounds 145.5; 2048 x 128,256 with k = 200
-        // and s = 64 561 / 580.)
-        const int len = round < 2 ? 2 : (round < 8 ? 6 : kLikEpoch);
+        // seen they move a lot.  4096 x 9000, k = 50, s = 16: 142.4 us, with 1, 1, 2 and 4 rounds 145.5.  Selections of more than 128
+        // begin with these, and 8: half of the first round may lie above their first threshold, and a buffer that runs full costs
+        // the row a second, slow pass.)
+        const int len = large ? (round < 2 ? 1 : (round < 16 ? (round < 4 ? 2 : (round < 8 ? 4 : 8)) : kLikEpoch))
+                              : (round < 2 ? 2 : (round < 8 ? 6 : kLikEpoch));
         const int r_end = round < n_main ? min(n_main, round + len) : n_rounds;
         if (round >= n_main)
             do_round(round);
@@ -321,7 +324,9 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
 }
 
 // Small selections (s and top_k up to kTopSmallN): 24 KB of LDS per workgroup, and the register budget of five
-// waves per SIMD (the few spills that costs are worth the fifth workgroup: measured).  Large ones: big buffers.
+// waves per SIMD (the few spills that costs are worth the fifth workgroup: measured).  Larger ones: 40 KB, four workgroups (with
+// kTopCapBig slots two: 2048 x 128,256, us with these / with 1536 slots: k = 65, s = 16 364 / 229, k = 200, s = 64 557 / 355), and only
+// active sets of more than 128 the big buffers: for one row in 250 the first round alone would fill 1536 slots (s = 256).
 template <int DT, bool BOTH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void likelihood_small_kernel(RowBatch b, LikelihoodParams p,
                                                                                                          LikelihoodOutputs o,
@@ -329,29 +334,36 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
 {
     likelihood_row<DT, kTopCapSmall, BOTH>(b, p, o, ipt, first_last);
 }
-template <int DT, bool BOTH>
-__global__ __launch_bounds__(kBlock) void likelihood_big_kernel(RowBatch b, LikelihoodParams p, LikelihoodOutputs o, FilteredIptSide ipt, int first_last)
+template <int DT, int CAP, bool BOTH>
+__global__ __launch_bounds__(kBlock) void likelihood_large_kernel(RowBatch b, LikelihoodParams p, LikelihoodOutputs o, FilteredIptSide ipt,
+                                                                  int first_last)
 {
-    likelihood_row<DT, kTopCapBig, BOTH>(b, p, o, ipt, first_last);
+    likelihood_row<DT, CAP, BOTH>(b, p, o, ipt, first_last);
+}
+
+template <int DT, bool BOTH>
+static void launch_likelihood_of(const RowBatch &b, const LikelihoodParams &p, const LikelihoodOutputs &o, const FilteredIptSide &ipt,
+                                 hipStream_t stream)
+{
+    const dim3 grid((unsigned)b.N), block(kBlock);
+    if (p.s <= kTopSmallN && p.top_k <= kTopSmallN)
+        likelihood_small_kernel<DT, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<DT, BOTH>>());
+    else if (p.s <= 128)
+        likelihood_large_kernel<DT, kTopCapMid, BOTH>
+            <<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_large_kernel<DT, kTopCapMid, BOTH>>());
+    else
+        likelihood_large_kernel<DT, kTopCapBig, BOTH>
+            <<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_large_kernel<DT, kTopCapBig, BOTH>>());
 }
 
 template <bool BOTH>
 static int launch_likelihood_any(const RowBatch &b, const LikelihoodParams &p, const LikelihoodOutputs &o,
                                  const FilteredIptSide &ipt, hipStream_t stream)
 {
-    const dim3 grid((unsigned)b.N), block(kBlock);
-    const bool small = p.s <= kTopSmallN && p.top_k <= kTopSmallN;
-    if (b.dtype == 0) {
-        if (small)
-            likelihood_small_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<0, BOTH>>());
-        else
-            likelihood_big_kernel<0, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_big_kernel<0, BOTH>>());
-    } else {
-        if (small)
-            likelihood_small_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<1, BOTH>>());
-        else
-            likelihood_big_kernel<1, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_big_kernel<1, BOTH>>());
-    }
+    if (b.dtype == 0)
+        launch_likelihood_of<0, BOTH>(b, p, o, ipt, stream);
+    else
+        launch_likelihood_of<1, BOTH>(b, p, o, ipt, stream);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 

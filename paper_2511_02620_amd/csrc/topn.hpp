@@ -19,7 +19,7 @@
 // fewer than kTopTrigger entries and adds at most 8 per thread of one wave, so in that mode kTopCapSmall =
 // kTopTrigger + 64 * 8 slots always suffice, whatever the order of the data.  Small buffers are what lets five
 // workgroups share a compute unit; selections of more than kTopSmallN entries push so much in an ordinary epoch
-// that they get kTopCapBig slots instead (the kernels are instantiated for both).
+// that they get kTopCapMid or kTopCapBig slots instead (the kernels are instantiated for both).
 #pragma once
 
 #include "difr_device.hpp"
@@ -30,7 +30,8 @@ constexpr int kTopEpoch = 8;       // stream rounds per epoch of the filtered To
 constexpr int kTopFresh = 16;      // a compaction is due after max(n, kTopFresh) pushes (measured: 8 to 64 within 1%)
 constexpr int kTopTrigger = 512;   // a compaction is due at the latest when this many slots are used
 constexpr int kTopCapSmall = kTopTrigger + 64 * 8;   // slots per buffer: the trigger plus one round of one wave
-constexpr int kTopCapBig = kTopTrigger + 256 * 8;    // ... of the whole workgroup
+constexpr int kTopCapMid = kTopTrigger + 128 * 8;    // ... for the larger selections of the likelihood kernel, which has two buffers
+constexpr int kTopCapBig = kTopTrigger + 256 * 8;    // ... plus one round of the whole workgroup
 constexpr int kTopSmallN = 64;     // largest n served with the small buffer
 constexpr int kTopMaxN = 256;      // largest n supported
 constexpr int kTopKeep = 256;      // a coarse compaction may leave up to this many entries
@@ -73,8 +74,9 @@ struct TopScratch {
 
 // Key bits of the n-th largest of the entries whose top kTopBits key bits the lanes of this wave hold, PER to a lane (0: none), or
 // 0 if there are fewer; `at_or_above`: how many have these bits or larger ones.  A search bit by bit, counting with ballots: every
-// wave finds it by itself from the same values, without a barrier, in kTopBits * PER compares.
-template <int PER>
+// wave finds it by itself from the same values, without a barrier, in kTopBits * PER compares.  Without TIGHT the bits may be those of
+// a smaller key that still lies above the next entry's (and any key at all if there are only n entries).
+template <int PER, bool TIGHT = false>
 __device__ __forceinline__ uint32_t nth_key(const uint32_t (&k)[PER], int n, int &at_or_above)
 {
     uint32_t prefix = 0;
@@ -90,7 +92,7 @@ __device__ __forceinline__ uint32_t nth_key(const uint32_t (&k)[PER], int n, int
         if (c >= n) {
             prefix |= bit;
             at_or_above = c;
-            if (c == n) break;  // (the bits found separate exactly n)
+            if (!TIGHT && c == n) break;  // (the bits found separate exactly n from the others)
         }
     }
     return prefix;
@@ -190,7 +192,7 @@ struct TopN {
 #pragma unroll
         for (int i = 0; i < PER; ++i) k[i] = slots[((int)threadIdx.x & 63) + 64 * i];
         int at_or_above;
-        const uint32_t p = nth_key<PER>(k, n, at_or_above);
+        const uint32_t p = nth_key<PER, true>(k, n, at_or_above);
         return p <= 0x007FFFFFu >> (32 - kTopBits) || at_or_above > n + kTopTies ? 0ull : (uint64_t)p << (64 - kTopBits);
     }
     __device__ __forceinline__ uint64_t read_prime(const uint32_t *slots) const
