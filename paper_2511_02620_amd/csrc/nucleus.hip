@@ -528,19 +528,27 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
         zero_mixed = hist[kHistWords - 1] != 0u;
         zero_mass = lds_h[0][0] + lds_h[0][1] + lds_h[0][2] + lds_h[0][3];
         zero_low = lds_h[1][0] + lds_h[1][1] + lds_h[1][2] + lds_h[1][3];
-        // a thread's words: their mass, the part of it below the claim's index, their entries
+        // a thread's words: their mass, the part of it below the claim's index, their entries.  All of them are read at once and
+        // kept for the thread that holds the cut (128 x 128,256: 27.2 us, 28.6 with a word read when its turn comes; 8192: 370 / 373.
+        // The masses kept as well and formed without branches: 26.3, but 8192 rows 434, the wave skips words that none of its lanes has).
         double sum = 0.0, sum_low = 0.0;
         int32_t n = 0;
         float top = ninf;
+        uint32_t na[kHistPer], nb[kHistPer];
+#pragma unroll
         for (int i = 0; i < kHistPer; ++i) {
-            const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
-            if (na + nb == 0u) continue;
+            na[i] = hist[word0 + i];
+            nb[i] = hist[kHistWords + word0 + i];
+        }
+#pragma unroll
+        for (int i = 0; i < kHistPer; ++i) {
+            if (na[i] + nb[i] == 0u) continue;
             const bool zero = zero_mixed && word0 + i == kHistZero;
             const float x = value_at(word0 + i);
             const double e = mass_of_value(x);
-            sum += zero ? zero_mass : e * (double)(na + nb);
-            sum_low += zero ? zero_low : e * (double)na;
-            n += (int32_t)(na + nb);
+            sum += zero ? zero_mass : e * (double)(na[i] + nb[i]);
+            sum_low += zero ? zero_low : e * (double)na[i];
+            n += (int32_t)(na[i] + nb[i]);
             top = x;
         }
         double upto = sum;
@@ -573,17 +581,20 @@ __device__ __forceinline__ void nucleus_row_multipass(const RowBatch &b, float t
             int at = 0;
             double low_above = 0.0, e_above = above;
             int32_t n_above = 0;
+            bool done = false;
+#pragma unroll
             for (int i = kHistPer - 1; i >= 0; --i) {
-                const uint32_t na = hist[word0 + i], nb = hist[kHistWords + word0 + i];
-                if (na + nb == 0u) continue;
+                const int32_t c_i = (int32_t)(na[i] + nb[i]);
+                if (done || c_i == 0) continue;
                 const bool zero = zero_mixed && word0 + i == kHistZero;
-                const double e = mass_of_value(value_at(word0 + i));
-                const double em = zero ? zero_mass : e * (double)(na + nb);
+                const double e = mass_of_value(value_at(word0 + i)), em = zero ? zero_mass : e * (double)c_i;
                 at = word0 + i;
-                if (e_above + em >= goal || n_above + (int32_t)(na + nb) == n) break;  // (the last of the thread's entries)
-                e_above += em;
-                low_above += zero ? zero_low : e * (double)na;
-                n_above += (int32_t)(na + nb);
+                done = e_above + em >= goal || n_above + c_i == n;  // (the last of the thread's entries)
+                if (!done) {
+                    e_above += em;
+                    low_above += zero ? zero_low : e * (double)na[i];
+                    n_above += c_i;
+                }
             }
             s_fill = at;
             s_mass_in = e_above;
