@@ -105,9 +105,10 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float 
 }
 
 // Filtered streaming kernel (the filter is described in gumbel_stream.hpp).  NANS: for bf16 rows that do not start on 16
-// bytes; the compiler would take 81 registers, one too many for six waves per SIMD, and is asked for six (no spills).
+// bytes; the compiler would take 81 registers, one too many for six waves per SIMD, and is asked for six (no spills).  fp32: 60 vector
+// registers, but scalar ones for seven waves; asked for eight, 2048 rows fit at once: 2048 x 128,256 173 -> 160 us, with the rank 169 -> 161.
 template <int DT, bool RANK, bool NANS>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6 : 1))) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o, int first_last)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6 : (DT != 0 ? 8 : 1)))) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o, int first_last)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
