@@ -317,11 +317,11 @@ __device__ __forceinline__ void block_argmax(float &y, int32_t &i, float *lds_y,
 // not wait for those that stream: 8000 x 9000 with the token 84 -> 117 us, not done.)
 struct RowPace {
     int third, next, level;
-    // `rounds`: of the row.  All waves; the row runs at its first priority from here.
-    __device__ __forceinline__ RowPace(int first_last, int rounds) : third((rounds + 2) / 3), next(-1), level(2)
+    // `rounds`: of the row, or of the part of it that begins with round `begin`.  All waves; it runs at its first priority from here.
+    __device__ __forceinline__ RowPace(int first_last, int rounds, int begin = 0) : third((rounds + 2) / 3), next(-1), level(2)
     {
         if ((int)blockIdx.x >= first_last) {
-            next = third;
+            next = begin + third;
             __builtin_amdgcn_s_setprio(2);
         } else {
             __builtin_amdgcn_s_setprio(3);
@@ -342,7 +342,7 @@ struct RowPace {
     __device__ __forceinline__ void done() { __builtin_amdgcn_s_setprio(3); }
 };
 struct NoPace {
-    __device__ __forceinline__ NoPace(int = 0, int = 0) {}
+    __device__ __forceinline__ NoPace(int = 0, int = 0, int = 0) {}
     __device__ __forceinline__ void at(int) {}
     __device__ __forceinline__ void done() {}
 };
