@@ -348,26 +348,32 @@ struct GumbelStream {
         }
     }
 
-    // TOPN mode: key of one of the vector's best scores for TopN::publish_prime(): the exact score of the entry with the largest bound
-    // (0: there is none; the claimed token is left out).
-    __device__ __forceinline__ uint32_t prime_key(u32x4 q, int round, bool active) const
+    // TOPN mode: key of one of the best scores of this thread's vectors of rounds 0, step, 2 step, ... for TopN::publish_prime(): the exact
+    // score of the entry with the largest bound (0: there is none; the claimed token is left out).  step = 0: round 0 alone.
+    template <int NV>
+    __device__ __forceinline__ uint32_t prime_key(const u32x4 (&q)[NV], int step, bool active) const
     {
-        const uint64_t p0 = (uint64_t)kPhiloxM0 * (uint32_t)(round * kBlock * (E / 4)) + lane_prod;
-        uint32_t r[E];
-        philox4x32_10_from_product(p0, ri.pos, ri.seq, kStreamGumbel, ri.key, r);
-        if (E == 8) philox4x32_10_from_product(p0 + kPhiloxM0, ri.pos, ri.seq, kStreamGumbel, ri.key, r + (E - 4));
-        float x[E];
-        unpack_vector<DT>(q, x);
-        const int32_t v0 = (round * kBlock + tid) * E;
         float best = -__builtin_inff(), xb = 0.0f;
         uint32_t rb = 0u;
 #pragma unroll
-        for (int j = 0; j < E; ++j) {
-            const float bound = __fmaf_rn(x[j], inv_T, gumbel_upper_bound(r[j]));
-            if (bound > best && v0 + j != t) {
-                best = bound;
-                xb = x[j];
-                rb = r[j];
+        for (int i = 0; i < NV; ++i) {
+            if (i > 0 && step == 0) break;
+            const int round = i * step;
+            const uint64_t p0 = (uint64_t)kPhiloxM0 * (uint32_t)(round * kBlock * (E / 4)) + lane_prod;
+            uint32_t r[E];
+            philox4x32_10_from_product(p0, ri.pos, ri.seq, kStreamGumbel, ri.key, r);
+            if (E == 8) philox4x32_10_from_product(p0 + kPhiloxM0, ri.pos, ri.seq, kStreamGumbel, ri.key, r + (E - 4));
+            float x[E];
+            unpack_vector<DT>(q[i], x);
+            const int32_t v0 = (round * kBlock + tid) * E;
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const float bound = __fmaf_rn(x[j], inv_T, gumbel_upper_bound(r[j]));
+                if (bound > best && v0 + j != t) {
+                    best = bound;
+                    xb = x[j];
+                    rb = r[j];
+                }
             }
         }
         const float y = perturbed_score(xb, inv_T, rb);

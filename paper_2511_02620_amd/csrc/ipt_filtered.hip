@@ -64,18 +64,19 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
         const int64_t vec = (int64_t)round * kBlock + tid;
         lx.push_vector(q, vec * E, vec < nvec && (only_wave < 0 || (tid >> 6) == only_wave));
     };
-    // a threshold before anything is pushed (topn.hpp), from the first round and others spread over the row
+    // a threshold before anything is pushed (topn.hpp)
     if (n_rounds > 0) {
-        const u32x4 q = fetch(0);
+        u32x4 q[kPrimeRounds];
+        load_prime_rounds(x_row, tid < nvec, n_main, q);
         uint32_t *slots = reinterpret_cast<uint32_t *>(scratch.hist);
-        lx.top.publish_prime(lx.prime_key(q, tid < nvec, n_main), slots);
+        lx.top.publish_prime(lx.prime_key(q, tid < nvec), slots);
         __syncthreads();
         const uint64_t theta = lx.top.read_prime(slots);
         if (theta != 0ull) {
             lx.top.theta = theta;
         } else {  // (masked rows, coarse logits, fewer entries than wanted)
             lx.top.begin_prime();
-            do_round(q, 0);
+            do_round(q[0], 0);
             lx.top.end_prime(scratch);
         }
         lx.retarget();

@@ -17,10 +17,6 @@
 
 namespace difr {
 
-// stream rounds per epoch once the thresholds have settled (vectors that trip a test only queue up, so a threshold that
-// is an epoch old costs little; measured: 16, 24 and 32 alike, 8 slower by 4%)
-constexpr int kLikEpoch = 16;
-
 __device__ __forceinline__ double gumbel_f64(const RowInfo &ri, int32_t v)
 {
     uint32_t r[4];
@@ -154,40 +150,37 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
             }
         }
     };
-    // thresholds for both selections before anything is pushed (topn.hpp), from the first round
+    // thresholds for both selections before anything is pushed (topn.hpp)
+    int round = 0, epoch = 0;
     if (n_rounds > 0) {
-        if (tid < nvec) q_next = load_round(x_row, 0);
+        u32x4 q[kPrimeRounds];
+        const int step = load_prime_rounds(x_row, tid < nvec, n_main, q);
+        q_next = q[0];
         uint32_t *slots_y = reinterpret_cast<uint32_t *>(scratch.hist), *slots_x = reinterpret_cast<uint32_t *>(scratch.tmp);
-        top_y.publish_prime(top_y.n > 0 ? g.prime_key(q_next, 0, tid < nvec) : 0u, slots_y);
-        top_x.publish_prime(p.top_k > 0 ? lx.prime_key(q_next, tid < nvec, n_main) : 0u, slots_x);
+        top_y.publish_prime(top_y.n > 0 ? g.prime_key(q, step, tid < nvec) : 0u, slots_y);
+        top_x.publish_prime(p.top_k > 0 ? lx.prime_key(q, tid < nvec) : 0u, slots_x);
         __syncthreads();
         const uint64_t theta_y = top_y.read_prime(slots_y), theta_x = top_x.read_prime(slots_x);
         if (theta_y != 0ull && theta_x != 0ull) {
             top_y.theta = theta_y;
             top_x.theta = theta_x;
+            g.retarget(top_y);
+            lx.retarget();
         } else {  // (masked rows, coarse logits, fewer entries than wanted)
             top_y.begin_prime();
             top_x.begin_prime();
             do_round(0);
             top_y.end_prime(scratch);
             top_x.end_prime(scratch);
+            g.retarget(top_y);
+            lx.retarget();
         }
-        g.retarget(top_y);
-        lx.retarget();
     }
-    const bool large = CAP != kTopCapSmall && max(p.s, p.top_k) > 128;
     // Epochs: a few rounds, then up to kLikEpoch rounds at a time without a barrier; the partly filled round is
     // an epoch of its own.  A push that finds a buffer full (data in ascending order, for instance) ends this mode.
-    int round = 0, epoch = 0;
     bool ran_full = false;
     while (round < n_rounds) {
-        // (the first epochs are 2 and 6 rounds long: the thresholds move only between epochs, and while little of the row has been
-        // seen they move a lot.  4096 x 9000, k = 50, s = 16: 142.4 us, with 1, 1, 2 and 4 rounds 145.5.  Selections of more than 128
-        // begin with these, and 8: half of the first round may lie above their first threshold, and a buffer that runs full costs
-        // the row a second, slow pass.)
-        const int len = large ? (round < 2 ? 1 : (round < 16 ? (round < 4 ? 2 : (round < 8 ? 4 : 8)) : kLikEpoch))
-                              : (round < 2 ? 2 : (round < 8 ? 6 : kLikEpoch));
-        const int r_end = round < n_main ? min(n_main, round + len) : n_rounds;
+        const int r_end = round < n_main ? min(n_main, round + selection_epoch(round, likelihood_first_epoch(CAP), kLikEpoch)) : n_rounds;
         if (round >= n_main)
             do_round(round);
         else if (g.gate.mode == 0)

@@ -9,6 +9,19 @@
 
 namespace difr {
 
+// The vectors that the first thresholds are formed from: those of the first round and of three more spread over the row (the same one
+// again if it has fewer than four full rounds).  The n-th largest of four rounds lies four times nearer to the row's than that of one, and
+// rows that rise towards their end, or begin with masked entries, do not fill the buffers.  Returns the distance of the rounds, or 0.
+constexpr int kPrimeRounds = 4;
+__device__ __forceinline__ int load_prime_rounds(const void *x_row, bool active, int n_main, u32x4 (&q)[kPrimeRounds])
+{
+    const int step = n_main / kPrimeRounds;
+    q[0] = active ? load_round(x_row, 0) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 1; i < kPrimeRounds; ++i) q[i] = step > 0 ? load_round(x_row, i * step) : q[0];
+    return step;
+}
+
 template <int DT>
 struct LogitTop {
     static constexpr int E = Elem<DT>::kPerVec;
@@ -124,25 +137,18 @@ struct LogitTop {
         }
     }
 
-    // Key for TopN::publish_prime() of the largest logit in this thread's vectors of the first round (given) and of up to three more
-    // rounds spread over the row (NaNs apart; 0: there is none): the k-th largest of four rounds lies four times nearer to the row's than
-    // that of one, and rows that rise towards their end do not fill the buffer.
-    __device__ __forceinline__ uint32_t prime_key(u32x4 q, bool active, int n_main) const
+    // Key for TopN::publish_prime() of the largest logit in this thread's vectors q (NaNs apart; 0: there is none).
+    template <int NV>
+    __device__ __forceinline__ uint32_t prime_key(const u32x4 (&q)[NV], bool active) const
     {
-        const int step = n_main >> 2;
-        u32x4 more[3];
+        float m = __builtin_nanf("");
 #pragma unroll
-        for (int i = 0; i < 3; ++i) more[i] = step > 0 ? load_round(defer_row, (i + 1) * step) : q;
-        auto largest = [](u32x4 v, float m) {
+        for (int i = 0; i < NV; ++i) {
             float x[E];
-            unpack_vector<DT>(v, x);
+            unpack_vector<DT>(q[i], x);
 #pragma unroll
             for (int j = 0; j < E; ++j) m = fmaxf(m, x[j]);
-            return m;
-        };
-        float m = largest(q, __builtin_nanf(""));
-#pragma unroll
-        for (int i = 0; i < 3; ++i) m = largest(more[i], m);
+        }
         return active && m == m ? float_order_bits(m + 0.0f) : 0u;
     }
 

@@ -1,0 +1,30 @@
+// How many slots a selection's buffer has, and how many stream rounds it goes without a barrier (topn.hpp).  Plain host code as well:
+// the test of the schedule runs it on rows that rise along the vocabulary.
+#pragma once
+
+namespace difr {
+
+constexpr int kTopTrigger = 512;                     // a compaction is due at the latest when this many slots are used
+constexpr int kTopCapSmall = kTopTrigger + 64 * 8;   // slots per buffer: the trigger plus one round of one wave
+constexpr int kTopCapMid = kTopTrigger + 128 * 8;    // ... for the larger selections of the likelihood kernel, which has two buffers
+constexpr int kTopCapBig = kTopTrigger + 256 * 8;    // ... plus one round of the whole workgroup
+constexpr int kTopEpoch = 8;   // stream rounds per epoch of the filtered Token-IPT-DiFR kernel (measured: 4 and 16 are both slower)
+constexpr int kLikEpoch = 16;  // ... and of the likelihood kernel: vectors that trip a test only queue up there, so a threshold that is an
+                               // epoch old costs little (measured: 16, 24 and 32 alike, 8 slower by 4%)
+
+// The epoch that begins with round `round`.  The threshold moves only between epochs, and while little of the row has been seen it
+// moves a lot: after the first, no epoch is longer than what lies behind it.  (One longer than that tests rows that rise along the
+// vocabulary against a threshold from far below them, and a buffer that runs full costs the row a second, slow pass: 1024 rows of 8
+// rounds whose logits rise by 0.5 a round, s = 64, k = 50: 200 us with epochs of 2 and 6 rounds and first thresholds of y from the first
+// round alone; 59 so.)
+constexpr int selection_epoch(int round, int first, int full)
+{
+    const int len = round > first ? round : first;
+    return len < full ? len : full;
+}
+
+// Rounds in the first epoch.  Likelihood kernel, us with one / two rounds for the small buffers: 4096 x 9000, k = 50, s = 16 127.5 /
+// 125.7, s = 64 160.9 / 158.6.  The larger selections take one: their first thresholds let up to a sixth of a round through.
+constexpr int likelihood_first_epoch(int cap) { return cap == kTopCapSmall ? 2 : 1; }
+
+}  // namespace difr

@@ -10,8 +10,8 @@
 // share the bits, and at the end of the row, the n-th composite is found exactly, by counting ranks or with all 8 radix passes.
 // Nothing that belongs to the final top n is ever dropped: the threshold is a lower bound of the n-th largest of what has been seen.
 // (4096 x 128,256, k = 50 and s = 16, T = 1: 500 us with rank counts, radix passes and a priming run over every entry of the first
-// round; 420 with bits, with priming by a key per thread - of four rounds for the logits -, with what the compactions decide in
-// scalar registers, and with priorities by what is left of the row.)
+// round; 420 with bits, with priming by a key per thread, with what the compactions decide in scalar registers, and with priorities
+// by what is left of the row.)
 //
 // Capacity.  The caller works in epochs of a few stream rounds without any barrier.  A push that finds the
 // buffer full raises `over` instead of storing its entry, and the caller then starts the row again in a careful
@@ -19,19 +19,15 @@
 // fewer than kTopTrigger entries and adds at most 8 per thread of one wave, so in that mode kTopCapSmall =
 // kTopTrigger + 64 * 8 slots always suffice, whatever the order of the data.  Small buffers are what lets five
 // workgroups share a compute unit; selections of more than kTopSmallN entries push so much in an ordinary epoch
-// that they get kTopCapMid or kTopCapBig slots instead (the kernels are instantiated for both).
+// that they get kTopCapMid or kTopCapBig slots instead (the kernels are instantiated for each).
 #pragma once
 
 #include "difr_device.hpp"
+#include "selection_epochs.hpp"
 
 namespace difr {
 
-constexpr int kTopEpoch = 8;       // stream rounds per epoch of the filtered Token-IPT-DiFR kernel (measured: 4 and 16 are both slower)
 constexpr int kTopFresh = 16;      // a compaction is due after max(n, kTopFresh) pushes (measured: 8 to 64 within 1%)
-constexpr int kTopTrigger = 512;   // a compaction is due at the latest when this many slots are used
-constexpr int kTopCapSmall = kTopTrigger + 64 * 8;   // slots per buffer: the trigger plus one round of one wave
-constexpr int kTopCapMid = kTopTrigger + 128 * 8;    // ... for the larger selections of the likelihood kernel, which has two buffers
-constexpr int kTopCapBig = kTopTrigger + 256 * 8;    // ... plus one round of the whole workgroup
 constexpr int kTopSmallN = 64;     // largest n served with the small buffer
 constexpr int kTopMaxN = 256;      // largest n supported
 constexpr int kTopKeep = 256;      // a coarse compaction may leave up to this many entries
