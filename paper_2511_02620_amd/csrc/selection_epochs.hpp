@@ -26,5 +26,9 @@ constexpr int selection_epoch(int round, int first, int full)
 // Rounds in the first epoch.  Likelihood kernel, us with one / two rounds for the small buffers: 4096 x 9000, k = 50, s = 16 127.5 /
 // 125.7, s = 64 160.9 / 158.6.  The larger selections take one: their first thresholds let up to a sixth of a round through.
 constexpr int likelihood_first_epoch(int cap) { return cap == kTopCapSmall ? 2 : 1; }
+// Filtered Token-IPT-DiFR kernel (`primed`: its threshold is from rounds spread over the row, and not from the first alone), k = 50, us
+// with 2 / 4 / 8 rounds: 4096 x 9000 54.9 / 53.0 / 52.4, 2048 x 16,424 40.4 / 38.9 / 37.8; with eight, rows whose rounds 1 to 7 lie 3
+// above the others run full.
+constexpr int filtered_first_epoch(int cap, int n, bool primed) { return cap == kTopCapSmall ? 4 : (primed && n <= 128 ? 2 : 1); }
 
 }  // namespace difr

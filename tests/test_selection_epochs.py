@@ -14,6 +14,7 @@ SOURCE = """
 using namespace difr;
 extern "C" int epoch(int round, int first, int full) { return selection_epoch(round, first, full); }
 extern "C" int lik_first(int cap) { return likelihood_first_epoch(cap); }
+extern "C" int filt_first(int cap, int n, int primed) { return filtered_first_epoch(cap, n, primed != 0); }
 extern "C" int size(int which) { return which == 0 ? kTopCapSmall : which == 1 ? kTopCapMid : which == 2 ? kTopCapBig : which == 3 ? kLikEpoch : kTopEpoch; }
 """
 PER, THREADS = 2048, 256  # entries of a round, bf16
@@ -68,9 +69,10 @@ def test_rising_rows(plan, rounds, n, rise):
 
 @pytest.mark.parametrize("n", [16, 50, 100, 256])
 def test_band_of_early_rounds(plan, n):
-    lik = plan.size(0 if n <= 64 else (1 if n <= 128 else 2))
+    lik, filt = plan.size(0 if n <= 64 else (1 if n <= 128 else 2)), plan.size(0 if n <= 64 else 2)
     for v in _rows(60, 6, band=(1, 8), height=3.0):
         assert not _runs_full(plan, v, n, lik, plan.lik_first(lik), plan.size(3))
+        assert not _runs_full(plan, v, n, filt, plan.filt_first(filt, n, 1), plan.size(4))
 
 
 def test_schedule_is_plain(plan):
