@@ -174,6 +174,18 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
             top_x.end_prime(scratch);
             g.retarget(top_y);
             lx.retarget();
+            if constexpr (CAP == kTopCapMid) {
+                // Equal entries (masked ones) lie above such a threshold up to an index, 8 n of them: where the buffer may not hold
+                // these, the round goes by waves, as in the careful mode below.
+                if (8 * max(top_y.n, top_x.n) > CAP) {
+                    for (int w = 0; w < kWaves; ++w) {
+                        do_round(0, w);
+                        settle();
+                    }
+                    round = 1;
+                    if (n_main > 1) q_next = load_round(x_row, 1);
+                }
+            }
         }
     }
     // Epochs: a few rounds, then up to kLikEpoch rounds at a time without a barrier; the partly filled round is

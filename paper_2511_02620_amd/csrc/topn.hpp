@@ -142,8 +142,9 @@ struct TopN {
         priming = false;
         // (a small selection does not need all 256 candidates: the best of every 4 or 2 neighbouring lanes are real
         // entries too, and the n-th largest of 64 or 128 of them costs a fraction of the rank count over 256 to find -
-        // it lies a few ranks lower, which lets a few more entries of the first round through)
-        const int group = n <= 32 ? 4 : (n <= 100 ? 2 : 1);
+        // it lies a few ranks lower, which lets a few more entries of the first round through.  Of equal - masked - entries, of which
+        // the n-th candidate is the one with index 8 n group at most, 896 do for n = 28 and 56, with room for some others in 1024 slots.)
+        const int group = n <= 28 ? 4 : (n <= 56 ? 2 : 1);
         if (group >= 2) {
             const uint64_t o = __shfl_xor(prime_best, 1, 64);
             if (o > prime_best) prime_best = o;
@@ -170,9 +171,10 @@ struct TopN {
 
     // The same from one key per thread (float_order_bits of a real entry's key; 0: none) with one barrier instead of a compaction
     // and without running the round's entries through push(): publish_prime(), a __syncthreads(), read_prime().  `slots`: kBlock words.
-    // read_prime() returns the threshold, or 0 if there are too few keys, if the n-th is a masked entry's, or if so many share its bits
-    // (coarse logits) that the entries' indices have to decide: then the priming run above finds one.  The next barrier after it
-    // frees the slots.
+    // read_prime() returns the threshold, or 0 if there are too few keys, if the n-th is a masked entry's, or if so many keys share its
+    // bits (coarse logits; 256 bf16 keys around -10 share them by dozens) that it would let half as many entries again through, or - where
+    // all keys are at or above it, which says nothing - if more than kTopTies do: then the priming run above finds one.  The next barrier
+    // after it frees the slots.
     __device__ __forceinline__ int prime_group() const { return n <= 32 ? 4 : (n <= 100 ? 2 : 1); }
     __device__ __forceinline__ void publish_prime(uint32_t key, uint32_t *slots) const
     {
@@ -187,9 +189,12 @@ struct TopN {
         uint32_t k[PER];
 #pragma unroll
         for (int i = 0; i < PER; ++i) k[i] = slots[((int)threadIdx.x & 63) + 64 * i];
-        int at_or_above;
+        int at_or_above, equal = 0;
         const uint32_t p = nth_key<PER, true>(k, n, at_or_above);
-        return p <= 0x007FFFFFu >> (32 - kTopBits) || at_or_above > n + kTopTies ? 0ull : (uint64_t)p << (64 - kTopBits);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) equal += (int)__builtin_popcountll(__builtin_amdgcn_ballot_w64(k[i] == p));
+        const bool coarse = at_or_above > n + max(kTopTies, n / 2) || (at_or_above == 64 * PER && equal > kTopTies);
+        return p <= 0x007FFFFFu >> (32 - kTopBits) || coarse ? 0ull : (uint64_t)p << (64 - kTopBits);
     }
     __device__ __forceinline__ uint64_t read_prime(const uint32_t *slots) const
     {
