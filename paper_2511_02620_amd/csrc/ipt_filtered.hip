@@ -69,10 +69,13 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
     if (n_rounds > 0) {
         u32x4 q[kPrimeRounds];
         load_prime_rounds(x_row, tid < nvec, n_main, q);
-        uint32_t *slots = reinterpret_cast<uint32_t *>(scratch.hist);
-        lx.top.publish_prime(lx.prime_key(q, tid < nvec), slots);
-        __syncthreads();
-        const uint64_t theta = lx.top.read_prime(slots);
+        uint64_t theta = 0ull;
+        if (lx.top.can_prime((int)min(nvec, (int64_t)kBlock))) {
+            uint32_t *slots = reinterpret_cast<uint32_t *>(scratch.hist);
+            lx.top.publish_prime(lx.prime_key(q, tid < nvec), slots);
+            __syncthreads();
+            theta = lx.top.read_prime(slots);
+        }
         primed = theta != 0ull;
         if (primed) {
             lx.top.theta = theta;

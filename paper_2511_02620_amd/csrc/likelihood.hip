@@ -156,11 +156,16 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         u32x4 q[kPrimeRounds];
         const int step = load_prime_rounds(x_row, tid < nvec, n_main, q);
         q_next = q[0];
-        uint32_t *slots_y = reinterpret_cast<uint32_t *>(scratch.hist), *slots_x = reinterpret_cast<uint32_t *>(scratch.tmp);
-        top_y.publish_prime(top_y.n > 0 ? g.prime_key(q, step, tid < nvec) : 0u, slots_y);
-        top_x.publish_prime(p.top_k > 0 ? lx.prime_key(q, tid < nvec) : 0u, slots_x);
-        __syncthreads();
-        const uint64_t theta_y = top_y.read_prime(slots_y), theta_x = top_x.read_prime(slots_x);
+        const int lanes = (int)min(nvec, (int64_t)kBlock);
+        uint64_t theta_y = 0ull, theta_x = 0ull;
+        if (top_y.can_prime(lanes) && top_x.can_prime(lanes)) {
+            uint32_t *slots_y = reinterpret_cast<uint32_t *>(scratch.hist), *slots_x = reinterpret_cast<uint32_t *>(scratch.tmp);
+            top_y.publish_prime(top_y.n > 0 ? g.prime_key(q, step, tid < nvec) : 0u, slots_y);
+            top_x.publish_prime(p.top_k > 0 ? lx.prime_key(q, tid < nvec) : 0u, slots_x);
+            __syncthreads();
+            theta_y = top_y.read_prime(slots_y);
+            theta_x = top_x.read_prime(slots_x);
+        }
         if (theta_y != 0ull && theta_x != 0ull) {
             top_y.theta = theta_y;
             top_x.theta = theta_x;

@@ -176,6 +176,8 @@ struct TopN {
     // all keys are at or above it, which says nothing - if more than kTopTies do: then the priming run above finds one.  The next barrier
     // after it frees the slots.
     __device__ __forceinline__ int prime_group() const { return n <= 32 ? 4 : (n <= 100 ? 2 : 1); }
+    // whether `lanes` keys can be enough (uniform)
+    __device__ __forceinline__ bool can_prime(int lanes) const { return n * prime_group() <= lanes; }
     __device__ __forceinline__ void publish_prime(uint32_t key, uint32_t *slots) const
     {
         const int group = prime_group();
