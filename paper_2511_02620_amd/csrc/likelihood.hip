@@ -179,10 +179,10 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
             top_x.end_prime(scratch);
             g.retarget(top_y);
             lx.retarget();
-            if constexpr (CAP == kTopCapMid) {
+            if constexpr (CAP == kTopCapMid && E * kBlock > CAP) {
                 // Equal entries (masked ones) lie above such a threshold up to an index, 8 n of them: where the buffer may not hold
                 // these, the round goes by waves, as in the careful mode below.
-                if (8 * max(top_y.n, top_x.n) > CAP) {
+                if (E * min(lanes, max(top_y.n, top_x.n)) > CAP) {
                     for (int w = 0; w < kWaves; ++w) {
                         do_round(0, w);
                         settle();
