@@ -338,7 +338,8 @@ struct RowPace {
                 __builtin_amdgcn_s_setprio(0);
         }
     }
-    // what follows the stream is a few dependent steps
+    // what follows the stream is a few dependent steps (not where it is more: the likelihood kernel keeps its priority for the careful
+    // pass and the estimate; 2048 x 30,000, s = 16, k = 50, us so / raised for them: bf16 100.3 / 101.9, fp32 113.7 / 115.5)
     __device__ __forceinline__ void done() { __builtin_amdgcn_s_setprio(3); }
 };
 struct NoPace {

@@ -234,7 +234,6 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
         }
         round = r_end;
     }
-    pace.done();
     if (ran_full) {
         // Careful mode: the row again from its start, one wave and one round at a time with a compaction check after
         // each step.  A step starts with fewer than kTopTrigger entries in a buffer and adds at most 8 per lane of one

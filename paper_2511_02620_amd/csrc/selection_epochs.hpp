@@ -13,14 +13,14 @@ constexpr int kLikEpoch = 16;  // ... and of the likelihood kernel: vectors that
                                // epoch old costs little (measured: 16, 24 and 32 alike, 8 slower by 4%)
 
 // The epoch that begins with round `round`.  The threshold moves only between epochs, and while little of the row has been seen it
-// moves a lot: after the first, no epoch is longer than what lies behind it.  (One longer than that tests rows that rise along the
+// moves a lot: after the first, and up to round eight, none is longer than what lies behind it.  (One longer than that tests rows that rise along the
 // vocabulary against a threshold from far below them, and a buffer that runs full costs the row a second, slow pass: 1024 rows of 8
 // rounds whose logits rise by 0.5 a round, s = 64, k = 50: 200 us with epochs of 2 and 6 rounds and first thresholds of y from the first
 // round alone; 59 so.)
 constexpr int selection_epoch(int round, int first, int full)
 {
     const int len = round > first ? round : first;
-    return len < full ? len : full;
+    return len < 8 ? len : full;
 }
 
 // Rounds in the first epoch.  Likelihood kernel, us with one / two rounds for the small buffers: 4096 x 9000, k = 50, s = 16 127.5 /
