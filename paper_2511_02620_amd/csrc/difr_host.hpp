@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "difr_device.hpp"
+#include "launch_rules.hpp"
 
 namespace difr {
 

@@ -356,13 +356,13 @@ static void launch_likelihood_of(const RowBatch &b, const LikelihoodParams &p, c
 {
     const dim3 grid((unsigned)b.N), block(kBlock);
     if (p.s <= kTopSmallN && p.top_k <= kTopSmallN)
-        likelihood_small_kernel<DT, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_small_kernel<DT, BOTH>>());
+        likelihood_small_kernel<DT, BOTH><<<grid, block, 0, stream>>>(b, p, o, ipt, pace_from(b.N, resident_rows<likelihood_small_kernel<DT, BOTH>>()));
     else if (p.s <= 128)
         likelihood_large_kernel<DT, kTopCapMid, BOTH>
-            <<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_large_kernel<DT, kTopCapMid, BOTH>>());
+            <<<grid, block, 0, stream>>>(b, p, o, ipt, pace_from(b.N, resident_rows<likelihood_large_kernel<DT, kTopCapMid, BOTH>>()));
     else
         likelihood_large_kernel<DT, kTopCapBig, BOTH>
-            <<<grid, block, 0, stream>>>(b, p, o, ipt, (int)b.N - resident_rows<likelihood_large_kernel<DT, kTopCapBig, BOTH>>());
+            <<<grid, block, 0, stream>>>(b, p, o, ipt, pace_from(b.N, resident_rows<likelihood_large_kernel<DT, kTopCapBig, BOTH>>()));
 }
 
 template <bool BOTH>

@@ -41,7 +41,7 @@ __device__ __forceinline__ int part_begin(int part, int parts, int full_rounds) 
 // NANS (Token-DiFR alone): bf16 rows that do not start on 16 bytes (gumbel_stream.hpp).
 template <int DT, bool GUM, bool IPT, bool ADM, bool RANK, bool NANS>
 __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const int32_t *__restrict__ claimed_ipt, bool ipt_rank,
-                                                            float delta, SplitWorkspace ws)
+                                                            float delta, SplitWorkspace ws, int first_last)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -68,9 +68,11 @@ __global__ __launch_bounds__(kBlock) void score_part_kernel(RowBatch b, const in
     const int r0 = part_begin(part, ws.parts, full_rounds), r1 = part_begin(part + 1, ws.parts, full_rounds);
     const bool last = part == ws.parts - 1;
     IptMarks<kNoToken> marks(nullptr, nullptr, 0);
-    // All parts of a batch are resident at once, and they should end together (RowPace).  bf16, V = 128,256, both scores, us with one
-    // priority / so: 128 rows 22.5 / 20.9, 256 30.7 / 28.3, 400 41 / 36.7, 512 47.1 / 42.5; with the admissible set 512 rows 52 / 46.
-    typename std::conditional<GUM && (IPT || DT == 0), RowPace, NoPace>::type pace(0, r1 - r0, r0);
+    // The parts that end the launch should end together (RowPace): all of them where they fit at once, and the last that do where they
+    // do not (both scores in bf16: five to a compute unit, four with the rank).  bf16, both scores, us with one priority / so / with every
+    // part taken for one of the last: 128 x 128,256 27.0 / 24.2 / 24.3, 400 49.2 / 42.7 / 42.5, with the rank 58.6 / 57.8 / 60.5;
+    // 641 x 151,936 80.1 / 69.4 / 81.0, 740 83.0 / 74.5 / 83.0, with the admissible set 109.3 / 101.9 / 109.1.
+    typename std::conditional<GUM && (IPT || DT == 0), RowPace, NoPace>::type pace(first_last, r1 - r0, r0);
     // (single variables: as one struct the compiler moves it through memory)
     float out_M = 0.0f, best_y = 0.0f;
     double out_Z = 0.0, out_P = 0.0;
@@ -283,7 +285,8 @@ static int launch_of(const RowBatch &b, const int32_t *claimed_ipt, const Gumbel
                      const AdmissibleOutputs &oa, const SplitWorkspace &ws, hipStream_t stream)
 {
     score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS><<<dim3((unsigned)(b.N * ws.parts)), dim3(kBlock), 0, stream>>>(
-        b, claimed_ipt, oi.logit_rank != nullptr, oa.delta, ws);
+        b, claimed_ipt, oi.logit_rank != nullptr, oa.delta, ws,
+        pace_from(b.N * ws.parts, resident_rows<score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS>>()));
     if (hipGetLastError() != hipSuccess) return 1;
     if (IPT && !ADM && oi.ipt_token)
         score_merge_kernel<DT, GUM, IPT, false, IPT && !ADM><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, claimed_ipt, og, oi, oa, ws);
