@@ -89,7 +89,7 @@ static void launch_score_both_kernel(const RowBatch &b, const int32_t *claimed_i
                                      const AdmissibleOutputs &oa, hipStream_t stream)
 {
     score_both_kernel<DT, ADM, RANK, TOK, PEAKED><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(
-        b, claimed_ipt, og, oi, oa, pace_from(b.N, resident_rows<score_both_kernel<DT, ADM, RANK, TOK, PEAKED>>()));
+        b, claimed_ipt, og, oi, oa, pace_from(b.N, resident_rows<score_both_kernel<DT, ADM, RANK, TOK, PEAKED>>(), b.V));
 }
 
 template <int DT, int TOK>

@@ -245,7 +245,7 @@ template <int DT, bool RANK, bool NANS>
 static void launch_filtered(const RowBatch &b, const GumbelOutputs &o, hipStream_t stream)
 {
     gumbel_score_filtered_kernel<DT, RANK, NANS>
-        <<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, o, pace_from(b.N, resident_rows<gumbel_score_filtered_kernel<DT, RANK, NANS>>()));
+        <<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, o, pace_from(b.N, resident_rows<gumbel_score_filtered_kernel<DT, RANK, NANS>>(), b.V));
 }
 
 int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t *argmax,

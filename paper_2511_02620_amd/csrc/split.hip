@@ -286,7 +286,7 @@ static int launch_of(const RowBatch &b, const int32_t *claimed_ipt, const Gumbel
 {
     score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS><<<dim3((unsigned)(b.N * ws.parts)), dim3(kBlock), 0, stream>>>(
         b, claimed_ipt, oi.logit_rank != nullptr, oa.delta, ws,
-        pace_from(b.N * ws.parts, resident_rows<score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS>>()));
+        pace_from(b.N * ws.parts, resident_rows<score_part_kernel<DT, GUM, IPT, ADM, RANK, NANS>>(), b.V / ws.parts));
     if (hipGetLastError() != hipSuccess) return 1;
     if (IPT && !ADM && oi.ipt_token)
         score_merge_kernel<DT, GUM, IPT, false, IPT && !ADM><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, claimed_ipt, og, oi, oa, ws);
