@@ -11,21 +11,34 @@
 
 namespace difr {
 
-// Workgroups of `Kernel` that the device holds at once (RowPace); 0 if the runtime does not say.  A figure of the kernel's code
-// and of the GPU the process runs on, found once.
+// Workgroups of `Kernel` that the device holds at once: compute units, and workgroups to each of them; 0 and 0 if the runtime does not
+// say.  Figures of the kernel's code and of the GPU the process runs on, found once.
+//
+// The runtime counts vector registers and LDS as they are, but not the 16 scalar registers a wave that the trap handler has: a unit holds
+// eight workgroups of up to 80 scalar registers, seven of up to 96 and six of more (measured with kernels that count themselves), where
+// it says eight up to 96 and seven beyond.  The kernels whose figure is used here are bound by vector registers or LDS, or have
+// 80 scalar registers or fewer.
+struct Residence {
+    int units, per_unit;
+};
+template <auto Kernel>
+Residence residence()
+{
+    static const Residence r = [] {
+        int dev = 0, units = 0, per_unit = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&units, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_unit, reinterpret_cast<const void *>(Kernel), kBlock, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            return Residence{0, 0};
+        }
+        return Residence{units, per_unit};
+    }();
+    return r;
+}
 template <auto Kernel>
 int resident_rows()
 {
-    static const int n = [] {
-        int dev = 0, cus = 0, per_cu = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(Kernel), kBlock, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            return 0;
-        }
-        return cus * per_cu;
-    }();
-    return n;
+    return residence<Kernel>().units * residence<Kernel>().per_unit;
 }
 
 // filtered = false forces the unfiltered kernel (every entry evaluated exactly).

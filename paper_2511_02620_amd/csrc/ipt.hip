@@ -107,28 +107,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
     ipt_finish<DT, TOK>(b, ri, row, x_row, s.c, s.ref(), s.Z, s.P, s.refP(), above, o, lds_f, lds_d, marks, &walk);
 }
 
-// Workgroups to a compute unit, without the token: the eight that fit, or seven or six if the launch's last generation of rows is
-// fuller then (idle LDS keeps the others out); a generation that starts with a few rows left takes as long as a full one.  2 x 1536
-// rows at six, us for bf16, V = 128,256, with eight / by this rule: 2304 rows 109 / 98, 3000 120 / 115, 5000 195 / 191, 7000 268 / 265;
-// 2048, 3500, 4096 the same.  Five as well: 2304 rows 96, but 5000 x 30,000 58 against 53.
-static unsigned idle_lds(int64_t N, int resident)
-{
-    constexpr int kFit = 8, kLeast = 6, kLdsOfUnit = 160 * 1024;
-    const int64_t units = resident / kFit;
-    if (N <= resident || units == 0) return 0;
-    int best = kFit;
-    auto places = [&](int per_unit) { return (N + units * per_unit - 1) / (units * per_unit) * per_unit; };
-    for (int p = kFit - 1; p >= kLeast; --p)
-        if (places(p) < places(best)) best = p;
-    return best == kFit ? 0 : (unsigned)(kLdsOfUnit / best - 1024);
-}
-
 template <int DT, int TOK>
 static void launch_ipt(const RowBatch &b, const IptOutputs &o, hipStream_t stream)
 {
-    const int resident = resident_rows<ipt_score_kernel<DT, TOK>>();
-    const unsigned lds = TOK == kNoToken ? idle_lds(b.N, resident) : 0u;
-    ipt_score_kernel<DT, TOK><<<dim3((unsigned)b.N), dim3(kBlock), lds, stream>>>(b, o, 2 * b.N <= resident);
+    const Residence r = residence<ipt_score_kernel<DT, TOK>>();
+    const unsigned lds = TOK == kNoToken ? ipt_idle_lds(b.N, r.units, r.per_unit, b.V / (Elem<DT>::kPerVec * kBlock)) : 0u;
+    ipt_score_kernel<DT, TOK><<<dim3((unsigned)b.N), dim3(kBlock), lds, stream>>>(b, o, 2 * b.N <= r.units * r.per_unit);
 }
 
 int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_hi, float *u,

@@ -21,4 +21,28 @@ constexpr int pace_from(int64_t groups, int resident, int64_t entries)
     return before > 0 && 12 * before <= resident && entries < kPaceEntries ? (int)groups : (int)before;
 }
 
+// Token-IPT-DiFR without the token: idle LDS per workgroup that keeps a compute unit at seven or six of the eight that fit, if the launch's
+// last generation of rows is fuller then; a generation that starts with a few rows left takes as long as a full one.  (Five as well: 2304 x
+// 128,256 96 us for 98, but 5000 x 30,000 58 for 53.)  Rows of fewer than eight rounds are set-up and latency in good part, and eight are better
+// whatever the last generation is like; up to 24 rounds they are where there are more than two and a half generations.  us with eight /
+// seven / six: bf16 2304 x 128,256 109 / 103 / 98, 4500 185 / 176 / 171, 2304 x 30,000 (14 rounds) 29.9 / 28.9 / 28.1, 9000 x 30,000 92.2 / 94.6 /
+// 94.8, 4500 x 16,000 (7) 30.3 / 31.0 / 31.5, 9000 x 9000 38.9 / 41.3 / 44.4, 9000 x 1000 21.6 / 22.4 / 23.8; fp32 2304 x 30,000 53.9 / 51.7 / 49.3,
+// 2304 x 16,000 (15) 30.7 / 30.0 / 29.4, 2304 x 9000 (8) 19.2 / 18.8 / 19.0, 9000 x 9000 58.7 / 60.2 / 61.9.
+constexpr unsigned ipt_idle_lds(int64_t N, int units, int per_unit, int64_t rounds)
+{
+    constexpr int kFit = 8, kLeast = 6, kLdsOfUnit = 160 * 1024;  // (gfx950; the figures are for eight)
+    const int64_t fit = (int64_t)units * kFit;
+    if (per_unit != kFit || N <= fit || rounds < 8 || (rounds < 24 && 2 * N > 5 * fit)) return 0;
+    int best = kFit;
+    int64_t best_places = 0;
+    for (int p = kFit; p >= kLeast; --p) {
+        const int64_t at_once = (int64_t)units * p, places = (N + at_once - 1) / at_once * p;
+        if (p == kFit || places < best_places) {
+            best = p;
+            best_places = places;
+        }
+    }
+    return best == kFit ? 0u : (unsigned)(kLdsOfUnit / best - 1024);
+}
+
 }  // namespace difr

@@ -9,6 +9,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "launch_rules.hpp"
 extern "C" int pace(int64_t groups, int resident, int64_t entries) { return difr::pace_from(groups, resident, entries); }
+extern "C" unsigned idle(int64_t N, int units, int per_unit, int64_t rounds) { return difr::ipt_idle_lds(N, units, per_unit, rounds); }
 """
 
 
@@ -19,6 +20,7 @@ def rules(tmp_path_factory):
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = C.CDLL(str(d / "r.so"))
     lib.pace.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.idle.argtypes, lib.idle.restype = [C.c_int64, C.c_int, C.c_int, C.c_int64], C.c_uint
     return lib
 
 
@@ -32,3 +34,17 @@ def test_pace(rules, entries):
         for groups in (resident + resident // 12 + 1, 3 * resident, 1 << 30):
             assert rules.pace(groups, resident, entries) == groups - resident
     assert rules.pace(1000, 0, entries) == 1000                   # not known: none is one of the last
+
+
+@pytest.mark.parametrize("N", [1, 2048, 2049, 2304, 3000, 3072, 3500, 4096, 4500, 5000, 9000, 16384])
+def test_workgroups_to_a_unit(rules, N):
+    places = {p: -(-N // (256 * p)) * p for p in (8, 7, 6)}
+    for rounds in (0, 4, 7, 8, 23, 24, 74):
+        lds = rules.idle(N, 256, 8, rounds)
+        if N <= 2048 or rounds < 8 or (rounds < 24 and N > 5120):
+            assert lds == 0
+            continue
+        best = min(places, key=lambda p: (places[p], -p))
+        assert lds == (0 if best == 8 else 163840 // best - 1024)
+        assert lds == 0 or (163840 // (lds + 64) >= best and 163840 // (lds + 64) < best + 1)  # that many fit, and no more
+    assert rules.idle(N, 256, 7, 74) == 0 and rules.idle(N, 0, 0, 74) == 0                       # not eight, or not known
