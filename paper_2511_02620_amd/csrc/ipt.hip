@@ -19,15 +19,13 @@ namespace difr {
 //
 // Bound by reading; what costs beside it is the end of a launch, where the rows left over have too few bytes in flight.
 //
-// Eight waves per SIMD (without the token; the compiler's own choice of scalar registers held six): 2048 rows fit at once.  With the
-// marks it is seven, and eight would spill.
+// Eight waves per SIMD (without the token; the compiler's own choice, 102 scalar registers, held six): 2048 rows fit at once.  With the
+// marks it is six, by 100 scalar registers; the LDS of seven marks leaves room for seven.
 //
-// `deep`: three vectors in flight beside the one in use instead of one.  Where the rows are few it is what keeps the memory busy, where
-// many share it they get in each other's way.  bf16, V = 128,256, us with one / three: 800 rows 43 / 37, 1024 46 / 43, 1500 58.5 /
-// 61; with the token (every row reads a part of itself again, when others have ended) 1024 60 / 56, 2048 110 / 99, 4096 204 / 188.
-template <int DT, int TOK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kNoToken ? 8 : 1))) void ipt_score_kernel(RowBatch b, IptOutputs o,
-                                                                                                                bool deep)
+// DEEP: three vectors in flight beside the one in use instead of one (ipt_deep); always with the marks: every row reads a part of itself
+// again, when others have ended.  bf16, V = 128,256, us with one / three: 1024 rows 60 / 56, 2048 110 / 99, 4096 204 / 188.
+template <int DT, int TOK, bool DEEP>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kNoToken ? 8 : 1))) void ipt_score_kernel(RowBatch b, IptOutputs o)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -60,27 +58,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
             marks.at(++round, s);
             return round < r1;
         };
-        if (TOK != kTokenMarks && !deep) {
+        if constexpr (!DEEP) {
             u32x4 q_next = load_round(x_row, round);
             while (true) {
                 const u32x4 q = q_next;
                 if (round + 1 < r1) q_next = load_round(x_row, round + 1);
                 if (!body(q)) break;
             }
-            return;
-        }
-        u32x4 qa = load_round(x_row, round), qb = qa, qc = qa, qd = qa;
-        if (round + 1 < r1) qb = load_round(x_row, round + 1);
-        if (round + 2 < r1) qc = load_round(x_row, round + 2);
-        while (true) {
-            if (round + 3 < r1) qd = load_round(x_row, round + 3);
-            if (!body(qa)) break;
-            if (round + 3 < r1) qa = load_round(x_row, round + 3);
-            if (!body(qb)) break;
-            if (round + 3 < r1) qb = load_round(x_row, round + 3);
-            if (!body(qc)) break;
-            if (round + 3 < r1) qc = load_round(x_row, round + 3);
-            if (!body(qd)) break;
+        } else {
+            u32x4 qa = load_round(x_row, round), qb = qa, qc = qa, qd = qa;
+            if (round + 1 < r1) qb = load_round(x_row, round + 1);
+            if (round + 2 < r1) qc = load_round(x_row, round + 2);
+            while (true) {
+                if (round + 3 < r1) qd = load_round(x_row, round + 3);
+                if (!body(qa)) break;
+                if (round + 3 < r1) qa = load_round(x_row, round + 3);
+                if (!body(qb)) break;
+                if (round + 3 < r1) qb = load_round(x_row, round + 3);
+                if (!body(qc)) break;
+                if (round + 3 < r1) qc = load_round(x_row, round + 3);
+                if (!body(qd)) break;
+            }
         }
     };
     auto careful = [&](int round, bool prefix_open) {
@@ -110,9 +108,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
 template <int DT, int TOK>
 static void launch_ipt(const RowBatch &b, const IptOutputs &o, hipStream_t stream)
 {
-    const Residence r = residence<ipt_score_kernel<DT, TOK>>();
-    const unsigned lds = TOK == kNoToken ? ipt_idle_lds(b.N, r.units, r.per_unit, b.V / (Elem<DT>::kPerVec * kBlock)) : 0u;
-    ipt_score_kernel<DT, TOK><<<dim3((unsigned)b.N), dim3(kBlock), lds, stream>>>(b, o, 2 * b.N <= r.units * r.per_unit);
+    const dim3 grid((unsigned)b.N), block(kBlock);
+    const int64_t rounds = b.V / (Elem<DT>::kPerVec * kBlock);
+    if constexpr (TOK == kTokenMarks) {
+        ipt_score_kernel<DT, TOK, true><<<grid, block, 0, stream>>>(b, o);
+    } else {
+        // (workgroups that fit: eight to a unit without the token; with it, where rows are walked from their start, six)
+        const Residence r = residence<ipt_score_kernel<DT, kNoToken, false>>();
+        if (ipt_deep(b.N, r.units * r.per_unit, rounds))
+            ipt_score_kernel<DT, TOK, true><<<grid, block, 0, stream>>>(b, o);
+        else
+            ipt_score_kernel<DT, TOK, false>
+                <<<grid, block, TOK == kNoToken ? ipt_idle_lds(b.N, r.units, r.per_unit, rounds) : 0u, stream>>>(b, o);
+    }
 }
 
 int launch_ipt_score(const RowBatch &b, float *dist, float *cdf_lo, float *cdf_hi, float *u,

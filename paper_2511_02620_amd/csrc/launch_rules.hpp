@@ -21,6 +21,12 @@ constexpr int pace_from(int64_t groups, int resident, int64_t entries)
     return before > 0 && 12 * before <= resident && entries < kPaceEntries ? (int)groups : (int)before;
 }
 
+// Token-IPT-DiFR: whether a wave has three vectors in flight beside the one in use, and not one.  Where the rows are few it is what keeps the
+// memory busy, where many share it they get in each other's way; a row of a few rounds ends before it pays.  us with one / three, every call
+// on rows of its own (700 MB in all): bf16 64 x 9000 (4 rounds) 6.78 / 6.89, 64 x 16,000 (7) 8.05 / 7.61, 300 x 30,000 (14) 12.3 / 10.5, 700 x
+// 128,256 44.3 / 36.8; fp32 64 x 4000 (3) 5.74 / 5.92, 64 x 9000 (8) 8.05 / 7.27.  By rows, 128,256 bf16: 1024 45.6 / 42.7, 1500 58.5 / 61.
+constexpr bool ipt_deep(int64_t N, int resident, int64_t rounds) { return 2 * N <= resident && rounds >= 6; }
+
 // Token-IPT-DiFR without the token: idle LDS per workgroup that keeps a compute unit at seven or six of the eight that fit, if the launch's
 // last generation of rows is fuller then; a generation that starts with a few rows left takes as long as a full one.  (Five as well: 2304 x
 // 128,256 96 us for 98, but 5000 x 30,000 58 for 53.)  Rows of fewer than eight rounds are set-up and latency in good part, and eight are better

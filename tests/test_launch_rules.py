@@ -9,6 +9,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 SOURCE = """
 #include "launch_rules.hpp"
 extern "C" int pace(int64_t groups, int resident, int64_t entries) { return difr::pace_from(groups, resident, entries); }
+extern "C" int deep(int64_t N, int resident, int64_t rounds) { return difr::ipt_deep(N, resident, rounds); }
 extern "C" unsigned idle(int64_t N, int units, int per_unit, int64_t rounds) { return difr::ipt_idle_lds(N, units, per_unit, rounds); }
 """
 
@@ -19,7 +20,7 @@ def rules(tmp_path_factory):
     (d / "r.cpp").write_text(SOURCE)
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = C.CDLL(str(d / "r.so"))
-    lib.pace.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.pace.argtypes = lib.deep.argtypes = [C.c_int64, C.c_int, C.c_int64]
     lib.idle.argtypes, lib.idle.restype = [C.c_int64, C.c_int, C.c_int, C.c_int64], C.c_uint
     return lib
 
@@ -34,6 +35,11 @@ def test_pace(rules, entries):
         for groups in (resident + resident // 12 + 1, 3 * resident, 1 << 30):
             assert rules.pace(groups, resident, entries) == groups - resident
     assert rules.pace(1000, 0, entries) == 1000                   # not known: none is one of the last
+
+
+def test_vectors_in_flight(rules):
+    for N, rounds, deep in [(1, 5, 0), (1, 6, 1), (1024, 74, 1), (1025, 74, 0), (16384, 3, 0)]:
+        assert rules.deep(N, 2048, rounds) == deep
 
 
 @pytest.mark.parametrize("N", [1, 2048, 2049, 2304, 3000, 3072, 3500, 4096, 4500, 5000, 9000, 16384])
