@@ -105,10 +105,11 @@ __global__ __launch_bounds__(kBlock) void gumbel_score_kernel(RowBatch b, float 
 }
 
 // Filtered streaming kernel (the filter is described in gumbel_stream.hpp).  NANS: for bf16 rows that do not start on 16
-// bytes; the compiler would take 81 registers, one too many for six waves per SIMD, and is asked for six (no spills).  fp32: 60 vector
-// registers, but scalar ones for seven waves; asked for eight, 2048 rows fit at once: 2048 x 128,256 173 -> 160 us, with the rank 169 -> 161.
-template <int DT, bool RANK, bool NANS>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(NANS ? 6 : (DT != 0 ? 8 : 1)))) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o, int first_last)
+// bytes; the compiler would take 81 registers, one too many for six waves per SIMD, and is asked for six (no spills).  WAVES: asked for where
+// it is more than the compiler's own choice; fp32 has 60 vector registers, but scalar ones that hold it at seven waves, with the rank
+// at six (gumbel_f32_waves).
+template <int DT, bool RANK, bool NANS, int WAVES>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(WAVES))) void gumbel_score_filtered_kernel(RowBatch b, GumbelOutputs o, int first_last)
 {
     typedef typename Elem<DT>::type elt_t;
     constexpr int E = Elem<DT>::kPerVec;
@@ -241,11 +242,11 @@ __global__ __launch_bounds__(kBlock) void debug_gumbel_map_kernel(const uint32_t
 }
 
 // bf16, V = 128,256, us with one priority / with RowPace: 1280 rows 68.5 / 62, 1500 79.5 / 72.5, 2048 103 / 95, with the rank 118 / 111.
-template <int DT, bool RANK, bool NANS>
+template <int DT, bool RANK, bool NANS, int WAVES>
 static void launch_filtered(const RowBatch &b, const GumbelOutputs &o, hipStream_t stream)
 {
-    gumbel_score_filtered_kernel<DT, RANK, NANS>
-        <<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, o, pace_from(b.N, resident_rows<gumbel_score_filtered_kernel<DT, RANK, NANS>>(), b.V));
+    gumbel_score_filtered_kernel<DT, RANK, NANS, WAVES>
+        <<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, o, pace_from(b.N, resident_rows<gumbel_score_filtered_kernel<DT, RANK, NANS, WAVES>>(), b.V));
 }
 
 int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t *argmax,
@@ -257,12 +258,16 @@ int launch_gumbel_score(const RowBatch &b, bool filtered, float *margin, int32_t
     if (filtered) {
         auto launch = [&](auto RANK) {
             constexpr bool rank = decltype(RANK)::value;
-            if (b.dtype != 0)
-                launch_filtered<1, rank, false>(b, o, stream);
-            else if (rows_aligned(b))
-                launch_filtered<0, rank, false>(b, o, stream);
-            else
-                launch_filtered<0, rank, true>(b, o, stream);
+            if (b.dtype != 0) {
+                if (gumbel_f32_waves(b.N, residence<gumbel_score_filtered_kernel<1, rank, false, 8>>().units, rank, b.V) == 8)
+                    launch_filtered<1, rank, false, 8>(b, o, stream);
+                else
+                    launch_filtered<1, rank, false, 1>(b, o, stream);
+            } else if (rows_aligned(b)) {
+                launch_filtered<0, rank, false, 1>(b, o, stream);
+            } else {
+                launch_filtered<0, rank, true, 6>(b, o, stream);
+            }
         };
         if (logit_rank)
             launch(std::true_type());

@@ -21,6 +21,19 @@ constexpr int pace_from(int64_t groups, int resident, int64_t entries)
     return before > 0 && 12 * before <= resident && entries < kPaceEntries ? (int)groups : (int)before;
 }
 
+// Token-DiFR alone, fp32: waves per SIMD, 8 or the compiler's choice (1), which holds seven, with the rank six.  Eight cost scalar registers
+// (104 spilled to vector lanes with the rank, 7 without) and are worth it where the rows fit at once with them only, where there are many rows that
+// are not long, and where a row is its set-up alone.  us with the compiler's choice / eight: 1200 x 30,000 with the rank 30.8 / 33.1,
+// 1600 x 128,256 134.5 / 135.7, with the rank 155.0 / 138.9, 1600 x 2048 with the rank 11.5 / 11.9, 2048 x 128,256 176 / 161 and 174 / 162, 2048 x 9000
+// 22.1 / 20.9, 2304 x 128,256 189 / 195 and 191 / 199, 2304 x 9000 with the rank 25.6 / 26.7, 4500 x 128,256 349 / 353, 16,000 x 4000 with
+// the rank 92.6 / 90.6, 10,516 x 30,000 207.6 / 202.4, 10,516 x 78,058 508 / 516, 10,516 x 1000 37.7 / 34.6, 2304 x 1600 14.3 / 14.8.
+constexpr int gumbel_f32_waves(int64_t N, int units, bool rank, int64_t V)
+{
+    const int64_t fit = (int64_t)units * 8;
+    const bool fit_only_so = N > (int64_t)units * (rank ? 6 : 7) && N <= fit && (!rank || V >= 8192);
+    return fit_only_so || (2 * N > 5 * fit && V < 65536) || V < 1024 ? 8 : 1;
+}
+
 // Token-IPT-DiFR: whether a wave has three vectors in flight beside the one in use, and not one.  Where the rows are few it is what keeps the
 // memory busy, where many share it they get in each other's way; a row of a few rounds ends before it pays.  us with one / three, every call
 // on rows of its own (700 MB in all): bf16 64 x 9000 (4 rounds) 6.78 / 6.89, 64 x 16,000 (7) 8.05 / 7.61, 300 x 30,000 (14) 12.3 / 10.5, 700 x

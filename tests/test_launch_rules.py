@@ -10,6 +10,7 @@ SOURCE = """
 #include "launch_rules.hpp"
 extern "C" int pace(int64_t groups, int resident, int64_t entries) { return difr::pace_from(groups, resident, entries); }
 extern "C" int deep(int64_t N, int resident, int64_t rounds) { return difr::ipt_deep(N, resident, rounds); }
+extern "C" int f32_waves(int64_t N, int units, int rank, int64_t V) { return difr::gumbel_f32_waves(N, units, rank != 0, V); }
 extern "C" unsigned idle(int64_t N, int units, int per_unit, int64_t rounds) { return difr::ipt_idle_lds(N, units, per_unit, rounds); }
 """
 
@@ -21,6 +22,7 @@ def rules(tmp_path_factory):
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = C.CDLL(str(d / "r.so"))
     lib.pace.argtypes = lib.deep.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.f32_waves.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64]
     lib.idle.argtypes, lib.idle.restype = [C.c_int64, C.c_int, C.c_int, C.c_int64], C.c_uint
     return lib
 
@@ -54,3 +56,12 @@ def test_workgroups_to_a_unit(rules, N):
         assert lds == (0 if best == 8 else 163840 // best - 1024)
         assert lds == 0 or (163840 // (lds + 64) >= best and 163840 // (lds + 64) < best + 1)  # that many fit, and no more
     assert rules.idle(N, 256, 7, 74) == 0 and rules.idle(N, 0, 0, 74) == 0                       # not eight, or not known
+
+
+def test_waves_of_the_fp32_stream(rules):
+    for rank, fits in ((0, 1792), (1, 1536)):
+        for N, waves in ((1, 1), (fits, 1), (fits + 1, 8), (2048, 8), (2049, 1), (5120, 1), (16384, 1)):
+            assert rules.f32_waves(N, 256, rank, 128256) == waves
+            assert rules.f32_waves(N, 256, rank, 1023) == 8
+        assert rules.f32_waves(2048, 256, rank, 8191) == (1 if rank else 8)
+        assert [rules.f32_waves(N, 256, rank, V) for N, V in ((5120, 30000), (5121, 30000), (5121, 65536))] == [1, 8, 1]
