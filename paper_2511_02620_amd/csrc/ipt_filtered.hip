@@ -90,13 +90,10 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
     // 64 of them make the look at their entries worth the wave's while; one barrier per epoch combines "a push found
     // the buffer full" and the compaction trigger.
     int round = 0, epoch = 0;
-    const int first = filtered_first_epoch(CAP, top_k, primed);
+    const int first = filtered_first_epoch(CAP, top_k, primed, 8 / E);
     bool ran_full = false;
     while (round < n_rounds) {
-        // Epochs of 8 rounds; a large selection begins with 2 and 6 (each doubling of what has been seen brings about top_k pushes, and
-        // the threshold moves only between epochs: 2048 x 128,256 with k = 200: 182 us, with 8 at once 350, the buffer having run full).
-        // k = 50, us with 1, 1, 2, 4 and then 8 / with 8: 4096 x 128,256 204 / 201, 4096 x 9000 58.3 / 53.4.
-        const int r_end = round < n_main ? min(n_main, round + selection_epoch(round, first, kTopEpoch)) : n_rounds;
+        const int r_end = round < n_main ? min(n_main, round + selection_epoch(round, first, kTopEpoch, kTopEpoch)) : n_rounds;
         if (round >= n_main) {
             do_round(fetch(round), round);
         } else {
@@ -113,7 +110,7 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
                 }
             }
         }
-        if (r_end == n_rounds || (CAP != kTopCapSmall && round == 0)) lx.drain();  // the row's last epoch: nothing may be left waiting
+        if (r_end == n_rounds) lx.drain();  // the row's last epoch: nothing may be left waiting
         {
             const uint32_t mine = (uint32_t)lx.top.over | ((uint32_t)lx.top.full << 1);
             uint32_t *word = &epoch_flags[epoch % 3];  // (three words in turn, see the likelihood kernel)

@@ -197,7 +197,7 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
     // an epoch of its own.  A push that finds a buffer full (data in ascending order, for instance) ends this mode.
     bool ran_full = false;
     while (round < n_rounds) {
-        const int r_end = round < n_main ? min(n_main, round + selection_epoch(round, likelihood_first_epoch(CAP), kLikEpoch)) : n_rounds;
+        const int r_end = round < n_main ? min(n_main, round + selection_epoch(round, likelihood_first_epoch(CAP, 8 / E), likelihood_settled(CAP, 8 / E), kLikEpoch)) : n_rounds;
         if (round >= n_main)
             do_round(round);
         else if (g.gate.mode == 0)
@@ -332,10 +332,12 @@ __device__ __forceinline__ void likelihood_row(const RowBatch &b, const Likeliho
     }
 }
 
-// Small selections (s and top_k up to kTopSmallN): 24 KB of LDS per workgroup, and the register budget of five
-// waves per SIMD (the few spills that costs are worth the fifth workgroup: measured).  Larger ones: 40 KB, four workgroups (with
-// kTopCapBig slots two: 2048 x 128,256, us with these / with 1536 slots: k = 65, s = 16 364 / 229, k = 200, s = 64 557 / 355), and only
-// active sets of more than 128 the big buffers: for one row in 250 the first round alone would fill 1536 slots (s = 256).
+// Small selections (s and top_k up to kTopSmallN): 28,032 bytes of LDS per workgroup, 31,104 with the Token-IPT-DiFR side, and the register
+// budget of five waves per SIMD (the few spills that costs, 32 bytes of scratch a lane in bf16 and 12 in fp32, are worth the fifth workgroup:
+// measured).  Larger ones: 36,224 or 39,296 bytes, four workgroups (with kTopCapBig slots three or, with that side, two: 2048 x 128,256, us with
+// these / with 1536 slots: k = 65, s = 16 364 / 229, k = 200, s = 64 557 / 355; the price is that rows which rise by more than these buffers take
+// run full earlier: 4096 x 32,000 rising by 0.3 a round, s = 16, k = 200, 923 / 1274), and only active sets of more than 128 the big
+// buffers: for one row in 250 the first round alone would fill 1536 slots (s = 256).
 template <int DT, bool BOTH>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void likelihood_small_kernel(RowBatch b, LikelihoodParams p,
                                                                                                          LikelihoodOutputs o,

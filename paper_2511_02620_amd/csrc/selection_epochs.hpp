@@ -13,22 +13,30 @@ constexpr int kLikEpoch = 16;  // ... and of the likelihood kernel: vectors that
                                // epoch old costs little (measured: 16, 24 and 32 alike, 8 slower by 4%)
 
 // The epoch that begins with round `round`.  The threshold moves only between epochs, and while little of the row has been seen it
-// moves a lot: after the first, and up to round eight, none is longer than what lies behind it.  (One longer than that tests rows that rise along the
-// vocabulary against a threshold from far below them, and a buffer that runs full costs the row a second, slow pass: 1024 rows of 8
+// moves a lot: after the first, and up to round `settled`, none is longer than what lies behind it.  (One longer than that tests rows that
+// rise along the vocabulary against a threshold from far below them, and a buffer that runs full costs the row a second, slow pass: 1024 rows of 8
 // rounds whose logits rise by 0.5 a round, s = 64, k = 50: 200 us with epochs of 2 and 6 rounds and first thresholds of y from the first
 // round alone; 59 so.)
-constexpr int selection_epoch(int round, int first, int full)
+constexpr int selection_epoch(int round, int first, int settled, int full)
 {
     const int len = round > first ? round : first;
-    return len < 8 ? len : full;
+    return len < settled && len < full ? len : full;
 }
 
-// Rounds in the first epoch.  Likelihood kernel, us with one / two rounds for the small buffers: 4096 x 9000, k = 50, s = 16 127.5 /
-// 125.7, s = 64 160.9 / 158.6.  The larger selections take one: their first thresholds let up to a sixth of a round through.
-constexpr int likelihood_first_epoch(int cap) { return cap == kTopCapSmall ? 2 : 1; }
-// Filtered Token-IPT-DiFR kernel (`primed`: its threshold is from rounds spread over the row, and not from the first alone), k = 50, us
+// Rounds in the first epoch, and `settled`; `wide` is 1 for bf16 and 2 for fp32, whose rounds have half as many entries.
+//
+// Likelihood kernel, us with one / two rounds for the small buffers: 4096 x 9000, k = 50, s = 16 127.5 / 125.7, s = 64 160.9 / 158.6.  The larger
+// selections take one, since their first thresholds let up to a sixth of a round through, and are not settled before round 16: with k = 200 a
+// few rows in a thousand fill 1536 slots in rounds 8 to 23.
+constexpr int likelihood_first_epoch(int cap, int wide) { return (cap == kTopCapSmall ? 2 : 1) * wide; }
+constexpr int likelihood_settled(int cap, int wide) { return (cap == kTopCapSmall ? 8 : 16) * wide; }
+// Filtered Token-IPT-DiFR kernel (`primed`: its threshold is from rounds spread over the row, and not from the first alone), k = 50, bf16, us
 // with 2 / 4 / 8 rounds: 4096 x 9000 54.9 / 53.0 / 52.4, 2048 x 16,424 40.4 / 38.9 / 37.8; with eight, rows whose rounds 1 to 7 lie 3
-// above the others run full.
-constexpr int filtered_first_epoch(int cap, int n, bool primed) { return cap == kTopCapSmall ? 4 : (primed && n <= 128 ? 2 : 1); }
+// above the others run full, for k of more than 32.  More than 64 logits: one round always fits their buffer, two do after such a threshold for
+// up to 128.
+constexpr int filtered_first_epoch(int cap, int n, bool primed, int wide)
+{
+    return cap == kTopCapSmall ? (n <= 32 ? 8 : 2 + 2 * wide) : (primed && n <= 128 ? 2 : 1);
+}
 
 }  // namespace difr
