@@ -16,8 +16,8 @@ namespace difr {
 //
 // The runtime counts vector registers and LDS as they are, but not the 16 scalar registers a wave that the trap handler has: a unit holds
 // eight workgroups of up to 80 scalar registers, seven of up to 96 and six of more (measured with kernels that count themselves), where
-// it says eight up to 96 and seven beyond.  The kernels whose figure is used here are bound by vector registers or LDS, or have
-// 80 scalar registers or fewer.
+// it says eight up to 96 and seven beyond.  The kernels whose figure is used here are bound by vector registers or LDS or have
+// 80 scalar registers or fewer (shared fp32 rows apart, of which there are never more parts than six workgroups to a unit).
 struct Residence {
     int units, per_unit;
 };

@@ -17,7 +17,10 @@ namespace difr {
 
 // With the rank count or the token search the bf16 body needs 97 registers, one too many for five waves per SIMD, and with marks
 // the fp32 one does; asked for five they fit in 96 without vector spills and the rank runs 5% faster.  The other variants ask for
-// one wave, which is no constraint (fp32 with the rank: 89 registers; asked for five it came out with 68 bytes of scratch a lane).
+// one wave, which is no constraint (fp32 with the rank: 89 registers; asked for five it came out with 68 bytes of scratch a lane).  The
+// peaked bf16 one, 97 registers and four waves, has such 68 bytes since it shares the issue slots by RowPace, for scalars that find no
+// vector lane; without either it is slower, us: 1024 x 128,256 flat 73.9 / 81.6, concentrated 52.4 / 53.9, 4096 x 9000 concentrated 48.8 /
+// 50.0.  fp32 is alike on concentrated rows (2048 x 128,256 166.1 / 164.6) and faster so on flat ones (174.8 / 183.8).
 //
 // TOK: how the honest sampler's Token-IPT-DiFR token is found (ipt_stream.hpp).
 template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>

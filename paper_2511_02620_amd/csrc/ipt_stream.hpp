@@ -94,8 +94,8 @@ __device__ double gaussian_log_mass(double a, double b, double u, double sigma, 
 // latency of its dependent steps: walking the CDF from the row's start, one round and two barriers at a time, made a call on
 // 2048 rows of 151,936 bf16 logits without claims take 227 us; with the marks, up to 16 rounds (four loads in flight) between
 // two barriers and nothing read past the stretch it takes 113 (2048 x 50,000: 47.5 us, 59 with 16 rounds read whatever the stretch).
-// Seven marks: 22.4 KB of LDS, seven workgroups to a compute unit; six 116 us; eight, which leave room for six workgroups, 113, but
-// 2048 x 50,000 49.6.
+// Seven marks: 22.4 KB of LDS; six marks 116 us; eight 113, but 2048 x 50,000 49.6.  (The kernels' scalar registers hold them at six workgroups
+// to a compute unit with any of these.)
 constexpr int kMarks = 7;
 constexpr int kWalkRounds = 16;  // rounds summed between two barriers of the walk: 16 x 4 wave sums, one per lane
 static_assert(kWalkRounds * kWaves == 64, "the walk scans one wave sum per lane");

@@ -257,9 +257,9 @@ struct TopN {
 
     // All 256 threads, after a barrier that follows the pushes.  If the buffer holds more than n entries,
     // raise the threshold to a lower bound of the n-th largest composite and keep only the entries at or
-    // above it: exactly the n largest (coarse = false), or at most kTopKeep of them chosen at the
-    // resolution of the top 16 key bits (coarse = true).  Returns true if the threshold moved.  Ends with
-    // a __syncthreads().
+    // above it: exactly the n largest (coarse = false), or a few more (coarse = true): up to 256 entries are cut at the
+    // resolution of the top kTopBits key bits, n + kTopTies of them at most staying, more at that of the top 16, at most kTopKeep
+    // staying; where more share the bits the cut is exact.  Returns true if the threshold moved.  Ends with a __syncthreads().
     __device__ __forceinline__ bool compact(TopScratch &s, bool coarse = false)
     {
         const int tid = threadIdx.x;
