@@ -23,7 +23,9 @@ namespace difr {
 // 50.0.  fp32 is alike on concentrated rows (2048 x 128,256 166.1 / 164.6) and faster so on flat ones (174.8 / 183.8).
 //
 // TOK: how the honest sampler's Token-IPT-DiFR token is found (ipt_stream.hpp).
-template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
+//
+// PACED: whether the rows share the issue slots by RowPace (pace_needed); the variants without it hold the same outputs.
+template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED, bool PACED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == kTokenMarks || (DT == 0 && (RANK || TOK != kNoToken)) ? 5 : 1))) void score_both_kernel(
     RowBatch b, const int32_t *__restrict__ claimed_ipt, GumbelOutputs og, IptOutputs oi, AdmissibleOutputs oa, int first_last)
 {
@@ -70,7 +72,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TOK == k
     const int full_rounds = (int)((V / E) / kBlock);  // rounds of 256 complete vectors
     IptMarks<TOK> marks(mark_Z, mark_ref, full_rounds);
 
-    RowPace pace(first_last, full_rounds);
+    typename std::conditional<PACED, RowPace, NoPace>::type pace(first_last, full_rounds);
     stream_rounds<DT, TOK>(g, s, marks, pace, x_row, V, 0, full_rounds, true);
     pace.done();
     if (DT == 0 && !ADM && !rows_aligned(b)) g.bad_sum(s.Z);  // (the admissible set is counted on aligned rows only)
@@ -91,8 +93,15 @@ template <int DT, bool ADM, bool RANK, int TOK, bool PEAKED = false>
 static void launch_score_both_kernel(const RowBatch &b, const int32_t *claimed_ipt, const GumbelOutputs &og, const IptOutputs &oi,
                                      const AdmissibleOutputs &oa, hipStream_t stream)
 {
-    score_both_kernel<DT, ADM, RANK, TOK, PEAKED><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(
-        b, claimed_ipt, og, oi, oa, pace_from(b.N, resident_rows<score_both_kernel<DT, ADM, RANK, TOK, PEAKED>>(), b.V));
+    const Residence r = residence<score_both_kernel<DT, ADM, RANK, TOK, PEAKED, true>>();
+    if constexpr (!PEAKED) {  // (which is for some 300 rows and more)
+        if (!pace_needed(b.N, r.units)) {
+            score_both_kernel<DT, ADM, RANK, TOK, false, false><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(b, claimed_ipt, og, oi, oa, 0);
+            return;
+        }
+    }
+    score_both_kernel<DT, ADM, RANK, TOK, PEAKED, true><<<dim3((unsigned)b.N), dim3(kBlock), 0, stream>>>(
+        b, claimed_ipt, og, oi, oa, pace_from(b.N, r.units * r.per_unit, b.V));
 }
 
 template <int DT, int TOK>

@@ -21,6 +21,11 @@ constexpr int pace_from(int64_t groups, int resident, int64_t entries)
     return before > 0 && 12 * before <= resident && entries < kPaceEntries ? (int)groups : (int)before;
 }
 
+// Whether rows of both scores run by RowPace at all: not where a compute unit has one row at most, for which looking after the priority costs 3 to
+// 4%.  us with / without, graph replays: bf16 64 x 30,000 19.8 / 19.6 (with the rank 22.3 / 21.7), 14 x 10,000 12.8 / 12.5, 64 x 2064 9.6 / 9.2, 300 x
+// 30,000 21.6 / 22.1; fp32 64 x 30,000 20.1 / 19.6, 64 x 10,000 13.1 / 12.7, with the admissible set 17.8 / 17.2, 300 x 30,000 23.1 / 23.3.
+constexpr bool pace_needed(int64_t N, int units) { return N > units; }
+
 // Token-DiFR alone, fp32: waves per SIMD, 8 or the compiler's choice (1), which holds seven, with the rank six.  Eight cost scalar registers
 // (104 spilled to vector lanes with the rank, 7 without) and are worth it where the rows fit at once with them only, where there are many rows that
 // are not long, and where a row is its set-up alone.  us with the compiler's choice / eight: 1200 x 30,000 with the rank 30.8 / 33.1,

@@ -10,6 +10,7 @@ SOURCE = """
 #include "launch_rules.hpp"
 extern "C" int pace(int64_t groups, int resident, int64_t entries) { return difr::pace_from(groups, resident, entries); }
 extern "C" int deep(int64_t N, int resident, int64_t rounds) { return difr::ipt_deep(N, resident, rounds); }
+extern "C" int needed(int64_t N, int units) { return difr::pace_needed(N, units); }
 extern "C" int f32_waves(int64_t N, int units, int rank, int64_t V) { return difr::gumbel_f32_waves(N, units, rank != 0, V); }
 extern "C" unsigned idle(int64_t N, int units, int per_unit, int64_t rounds) { return difr::ipt_idle_lds(N, units, per_unit, rounds); }
 """
@@ -22,6 +23,7 @@ def rules(tmp_path_factory):
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "r.cpp"), "-o", str(d / "r.so")], check=True)
     lib = C.CDLL(str(d / "r.so"))
     lib.pace.argtypes = lib.deep.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.needed.argtypes = [C.c_int64, C.c_int]
     lib.f32_waves.argtypes = [C.c_int64, C.c_int, C.c_int, C.c_int64]
     lib.idle.argtypes, lib.idle.restype = [C.c_int64, C.c_int, C.c_int, C.c_int64], C.c_uint
     return lib
@@ -37,6 +39,7 @@ def test_pace(rules, entries):
         for groups in (resident + resident // 12 + 1, 3 * resident, 1 << 30):
             assert rules.pace(groups, resident, entries) == groups - resident
     assert rules.pace(1000, 0, entries) == 1000                   # not known: none is one of the last
+    assert [rules.needed(N, 256) for N in (1, 256, 257, 16384)] == [0, 0, 1, 1]
 
 
 def test_vectors_in_flight(rules):
