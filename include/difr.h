@@ -171,6 +171,8 @@ int difr_ipt_score(const difr_rows *in, float *dist, float *cdf_lo, float *cdf_h
  * [Sec. 7.1].  ipt_token, sigma, eps and log_mass are difr_ipt_score's (the sampler's own token costs its second,
  * early-exit pass on the rows whose claim does not match; log_mass is the paper's Token-IPT-DiFR score).  [Sec. 6.2 and Sec. 6.3 together: a verifier that does not know which sampler the server
  * ran, or that feeds both scores to one classifier.]
+ * The kernels of this call, of difr_gumbel_score on bf16 rows and of the calls with the filter policy run their waves at raised priority: kernels on
+ * other streams that share the device with them get their turn later (some 10% for short calls of the other scores).
  */
 int difr_score_both(const difr_rows *in, const int32_t *claimed_ipt, float *margin, int32_t *argmax, float *max_score,
                     float *claimed_score, uint8_t *flags_gumbel, int32_t *logit_rank, float *dist, float *cdf_lo,
