@@ -70,7 +70,8 @@ __global__ __launch_bounds__(kBlock) void ipt_filtered_kernel(RowBatch b, int to
         u32x4 q[kPrimeRounds];
         load_prime_rounds(x_row, tid < nvec, n_main, q);
         uint64_t theta = 0ull;
-        if (lx.top.can_prime((int)min(nvec, (int64_t)kBlock))) {
+        // (fp32: 2048 x 32,000 with k = 20 67.3 us with a look at the number of keys, 63.5 without, which only rows of less than a round pay for)
+        if (DT != 0 || lx.top.can_prime((int)min(nvec, (int64_t)kBlock))) {
             uint32_t *slots = reinterpret_cast<uint32_t *>(scratch.hist);
             lx.top.publish_prime(lx.prime_key(q, tid < nvec), slots);
             __syncthreads();
@@ -163,12 +164,12 @@ int launch_ipt_filtered(const RowBatch &b, int top_k, float top_p, const IptOutp
         if (small)
             ipt_filtered_kernel<0, kTopCapSmall><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
         else
-            ipt_filtered_kernel<0, kTopCapBig><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
+            ipt_filtered_kernel<0, kTopCapOne><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
     } else {
         if (small)
             ipt_filtered_kernel<1, kTopCapSmall><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
         else
-            ipt_filtered_kernel<1, kTopCapBig><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
+            ipt_filtered_kernel<1, kTopCapOne><<<grid, block, 0, stream>>>(b, top_k, top_p, o, kept);
     }
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }

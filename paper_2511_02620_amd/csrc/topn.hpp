@@ -19,7 +19,7 @@
 // fewer than kTopTrigger entries and adds at most 8 per thread of one wave, so in that mode kTopCapSmall =
 // kTopTrigger + 64 * 8 slots always suffice, whatever the order of the data.  Small buffers are what lets five
 // workgroups share a compute unit; selections of more than kTopSmallN entries push so much in an ordinary epoch
-// that they get kTopCapMid or kTopCapBig slots instead (the kernels are instantiated for each).
+// that they get kTopCapMid, kTopCapBig or kTopCapOne slots instead (the kernels are instantiated for each).
 #pragma once
 
 #include "difr_device.hpp"

@@ -16,10 +16,10 @@ extern "C" int epoch(int round, int first, int settled, int full) { return selec
 extern "C" int lik_first(int cap, int wide) { return likelihood_first_epoch(cap, wide); }
 extern "C" int lik_settled(int cap, int wide) { return likelihood_settled(cap, wide); }
 extern "C" int filt_first(int cap, int n, int primed, int wide) { return filtered_first_epoch(cap, n, primed != 0, wide); }
-extern "C" int size(int which) { return which == 0 ? kTopCapSmall : which == 1 ? kTopCapMid : which == 2 ? kTopCapBig : which == 3 ? kLikEpoch : kTopEpoch; }
+extern "C" int size(int which) { return which == 0 ? kTopCapSmall : which == 1 ? kTopCapMid : which == 2 ? kTopCapBig : which == 3 ? kLikEpoch : which == 4 ? kTopEpoch : kTopCapOne; }
 """
 THREADS = 256
-SMALL, MID, BIG, LIK, FILT = range(5)
+SMALL, MID, BIG, LIK, FILT, ONE = range(6)
 
 
 @pytest.fixture(scope="module")
@@ -67,7 +67,7 @@ def _likelihood(plan, v, n, wide):
 
 
 def _filtered(plan, v, n, wide):
-    cap = plan.size(SMALL if n <= 64 else BIG)
+    cap = plan.size(SMALL if n <= 64 else ONE)
     return _most(plan, v, n, wide, plan.filt_first(cap, n, 1, wide), plan.size(FILT), plan.size(FILT)) / cap
 
 
@@ -93,6 +93,22 @@ def test_band_of_early_rounds(plan, n, wide):
     for v in _rows(60 * 2048, 6, band=3.0):
         assert _likelihood(plan, v, n, wide) <= 1
         assert _filtered(plan, v, n, wide) <= 1
+
+
+@pytest.mark.parametrize("wide", [1, 2])
+@pytest.mark.parametrize("n", [65, 128, 200, 256])
+def test_larger_filtered_selections(plan, n, wide):
+    for row in (dict(rise=0.3), dict(band=3.0)):
+        for v in _rows(8 * 2048, 6, **row):
+            assert _filtered(plan, v, n, wide) <= 1
+
+
+@pytest.mark.parametrize("n", [200, 256])
+def test_second_round_of_a_band_and_what_waits(plan, n):
+    # the filtered kernel: all of the first round's entries above the threshold may wait for the second round, all of which passes
+    for v in _rows(16 * 2048, 150):
+        best = np.max([v[r * 2048:(r + 1) * 2048].reshape(THREADS, -1).max(1) for r in (0, 4, 8, 12)], axis=0)
+        assert np.count_nonzero(v[:2048] > np.sort(best)[-n]) + 2048 <= plan.size(ONE)
 
 
 def test_schedule_is_plain(plan):
